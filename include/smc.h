@@ -26,8 +26,10 @@
  *          from site (c, j) to its +mu neighbour.
  *          SMC_J_FP32: float [d][2][N/2], the coupling of that bond.
  *   workspace  at least smc_workspace_bytes(p) bytes, 256-byte aligned:
- *          reduction partials, an observable slot and, for the fused schedule,
- *          the second spin buffer.
+ *          reduction partials, an observable slot, for the fused schedule the
+ *          second spin buffer and, for plain sweeps of Ising spins with
+ *          uniform or +-1 couplings, two copies at one bit per site (and the
+ *          bonds' signs) that calls of several sweeps may work on.
  * Random numbers.  Philox4x32-10 (Salmon et al., SC'11), key = seed, counter
  *   = (block, sweep t, replica, colour | purpose << 1); the same (seed,
  *   replica) gives the same chain whatever the launch geometry or schedule.
@@ -69,7 +71,8 @@ enum smc_flags {
   SMC_FLAG_COUPLINGS_KEEP = 8,   /* do not generate J at init; use the caller's values */
   SMC_FLAG_HEATBATH = 32,        /* Ising, uniform or +-1 J: heat-bath rule (Sec. 2): new spin
                                     +1 iff u32 < ceil(2^32 / (1 + exp(-2 beta h))) with the
-                                    Metropolis draws; plain sweeps run the one-site kernel */
+                                    Metropolis draws; a plain half-sweep by itself runs the
+                                    one-site kernel */
   SMC_FLAG_PACKED = 16           /* Ising spins (and +-1 couplings) at one bit per site
                                     (Sec. 2, multi-spin coding): the int8 planes' site
                                     order, site j in bit j & 31 of 32-bit word j >> 5,
@@ -231,7 +234,9 @@ int smc_set_samples(smc_lattice* h, int64_t samples);
 int smc_autotune(smc_lattice* h, double beta, void* scratch, size_t scratch_bytes,
                  uint32_t* rows_out);
 
-/* Name of the kernel the handle's sweeps launch -- Ising: "ising_packed"
+/* Name of the kernel the handle's half-sweeps launch (a call of several plain
+ * Ising sweeps may run many half-sweeps in one launch instead, with the same
+ * result) -- Ising: "ising_packed"
  * (one bit per site), "ising_fused", "ising_stream", "ising_chunk",
  * "ising_site", and for the tiled schedule "ising_tiles" (int8 tiles) or
  * "ising_tiles_packed" (tiles at one bit per site in LDS, Metropolis or heat

@@ -32,6 +32,14 @@ hipError_t launch_ising_half_sweep(const IsingLaunch& a, int8_t* spins, uint32_t
 // Chunk kernel requires L % 32 == 0 (plane rows are whole 16-byte chunks).
 bool ising_chunk_supported(const Geom& g, int J_kind);
 
+// Half-sweeps of one lattice held in LDS: ceil(Wp / own) workgroups, at most
+// two words of a colour per lane.
+hipError_t launch_resident(const ResidentLaunch& a, bool heatbath, uint32_t threads,
+                           hipStream_t st);
+// Bond signs (int8 or packed +-1 couplings) as words aligned with the sites.
+hipError_t launch_bond_words(const Geom& g, bool bytes, const void* J, uint32_t* out,
+                             hipStream_t st);
+
 uint32_t cont_default_sites_per_lane(int n);
 bool cont_sites_per_lane_ok(int n, uint32_t V);
 bool cont_stream_supported(const Geom& g, uint32_t V, uint32_t H);

@@ -40,6 +40,33 @@ struct IsingLaunch {
   FastDiv divL;      // edge length
 };
 
+// Several half-sweeps of one Ising lattice with its words in LDS (resident.hip).
+struct ResidentLaunch {
+  Geom g;
+  RngKey key;
+  uint32_t th[7];      // threshold byte T >> 24 of each class with a mask
+  uint32_t frac[7];    // T & 0xFFFFFF (2^24: accepts on every draw)
+  uint32_t invert;     // ~0: count satisfied bonds (Metropolis with J0 < 0)
+  uint32_t Wp;         // 32-site words of a colour plane
+  uint32_t t0;         // sweep counter of step 0 of the call
+  uint32_t step0;      // first half-sweep of this launch (of the call); its parity is the colour
+  uint32_t steps;      // half-sweeps of this launch
+  uint32_t own;        // words of a colour a workgroup owns
+  uint32_t rho;        // words of halo a half-sweep uses up (0: the whole lattice is local)
+  uint32_t halo;       // rho * steps
+  uint32_t chunk;      // half-sweeps whose masks are formed together
+  uint32_t mask_words; // capacity of a class's masks
+  uint32_t list_words; // capacity of a wave's tie list
+  uint32_t src_bytes, dst_bytes;  // 1: int8 planes, 0: words
+  const void* src;
+  void* dst;
+  const uint32_t* bonds;  // bond-sign words (+-1 couplings) or null
+  void* parts;         // reduction partials of the final state (several workgroups), or null
+  void* obs;           // its record (one workgroup), or null
+  double J0;
+  int64_t sweep;
+};
+
 struct ContLaunch {
   Geom g;
   int n;             // 2 or 3

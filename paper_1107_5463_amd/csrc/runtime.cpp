@@ -41,6 +41,20 @@ hipError_t smc::allow_dynamic_lds(const void* fn, size_t bytes) {
   return e;
 }
 
+// How the half-sweeps of a call of plain Ising sweeps are run.  Every way gives
+// the same chain.
+enum SweepWay {
+  kWayHalf = 0,      // one launch a half-sweep on the caller's buffer
+  kWayResident       // several half-sweeps a launch (resident.hip)
+};
+
+struct SweepPlan {
+  SweepWay way;
+  uint32_t launches;                        // resident: how many,
+  uint32_t own, rho, threads, chunk;        // and their shape
+  double us;                                // estimated time of the call
+};
+
 struct smc_lattice {
   smc_params p;
   Geom g;
@@ -66,6 +80,13 @@ struct smc_lattice {
   uint32_t cont_rows;        // continuous streaming band height (SMC_CONT_ROWS overrides)
   uint32_t cont_spl;         // continuous streaming sites per lane (SMC_CONT_SPL overrides)
   FastDiv divQc;             // continuous streaming lanes per plane row
+  bool multi_ok;             // multi-sweep calls may leave the half-sweep kernels (plan_sweeps)
+  uint32_t forced_steps, forced_own, forced_list;  // SMC_RESIDENT=steps,own[,list] (tests)
+  uint32_t* work[2];         // two packed copies of the spins (multi-sweep calls)
+  int64_t plan_sweeps;       // the call the plan below is for (0: none yet)
+  bool plan_measured;
+  SweepPlan plan;
+  uint32_t* work_bonds;      // bond-sign words (+-1 couplings)
   // workspace carve-up
   void* obs_slot;      // smc_obs (64 B)
   uint32_t* counter;   // validation counter
@@ -433,6 +454,212 @@ int fused_sweeps(smc_lattice* h, double beta, int64_t n, void* dev_obs) {
   return SMC_OK;
 }
 
+// ---------------------------------------------------------------------------
+// Multi-sweep calls of plain Ising sweeps (uniform or +-1 couplings).
+// ---------------------------------------------------------------------------
+// Whether calls of parameters p may take those ways, and so need the
+// workspace for them: packed lattices beyond 2^20 words a colour (2D
+// L = 8192) fill the chip with one half-sweep and stay with it.
+bool multi_params(const smc_params* p) {
+  return p->n == 1 && p->J_kind != SMC_J_FP32 && p->tile == 0 &&
+         !(p->flags & (SMC_FLAG_GENERIC_KERNEL | SMC_FLAG_SCHEDULE_FUSED)) &&
+         !(is_packed(p) && n_sites(p) / 64 > (1 << 20));
+}
+
+uint32_t plane_words(const Geom& g) { return (uint32_t)((g.Nh + 31) / 32); }
+
+size_t multi_bytes(const smc_params* p) {
+  if (!multi_params(p)) return 0;
+  const size_t plane = 4 * (size_t)plane_words(make_geom(p));
+  return 2 * round_up(2 * plane, kAlign) +
+         (p->J_kind == SMC_J_PM ? round_up(4 * (size_t)p->d * plane, kAlign) : 0);
+}
+
+// Times in us, measured on the device.  A launch occupies the stream for
+// kLaunch at least.  A launch of the resident kernel takes kStage (start,
+// staging, stores), kChunk for the ties of a chunk, kRoundWave a round of the
+// draws and wave of a SIMD (kRoundMin: a wave alone), kStep a half-sweep and
+// kWordStep a word's step in the workgroup.
+constexpr double kLaunch = 3.5, kFinish = 3.0, kStage = 4.5, kChunk = 0.5, kStep = 0.25, kWordStep = 0.4e-3,
+                 kRoundMin = 1.2, kRoundWave = 0.42;
+constexpr uint32_t kCUs = 256;
+
+// The resident kernel with `launches` launches of at most `steps` half-sweeps
+// and `own` words a workgroup; false if it does not fit.
+bool resident_shape(const smc_lattice* h, uint32_t S, uint32_t launches, uint32_t own, bool whole,
+                    SweepPlan& o) {
+  const Geom& g = h->g;
+  const bool hb = (h->p.flags & SMC_FLAG_HEATBATH) != 0;
+  const uint32_t Wp = plane_words(g), tail = Wp * 32u - (uint32_t)g.Nh;
+  const uint32_t steps = (S + launches - 1) / launches;
+  const uint32_t reach = (uint32_t)(g.d == 2 ? g.R : g.L * g.R) + tail;
+  const uint64_t rho = whole ? 0 : (reach + 31u) / 32u;
+  const uint64_t Wl = own + 2 * rho * steps;
+  if (Wl > 2048 || (!whole && (own < 8 || Wl > 2 * (uint64_t)Wp))) return false;
+  const uint32_t nc = hb ? 2 * g.d + 1 : g.d;
+  // masks and tie list of a chunk: at most 96 KiB of LDS
+  const uint32_t room = 96u * 1024u / (4u * (nc + 1u));  // a list entry a word is ample
+  const uint32_t chunk = std::min<uint32_t>({steps, 128u, std::max<uint32_t>(1u, room / (uint32_t)Wl)});
+  if ((uint64_t)chunk * Wl > room) return false;
+  // workgroup size: the draws of a chunk are rounds of `waves` waves, four
+  // SIMDs wide; a round takes a wave's own latency at least
+  const uint64_t M = (uint64_t)chunk * (Wl - 2 * rho) - rho * chunk * (chunk - 1);
+  const uint32_t need = (uint32_t)((Wl + 127) / 128);  // waves for two words a lane
+  double draw = 1e30;
+  for (uint32_t w = std::max(1u, need); w <= 16; ++w) {
+    const double rounds = (double)((M + 64 * w - 1) / (64 * w));
+    const double us = rounds * std::max(kRoundMin, kRoundWave * ((w + 3) / 4)) * (1.0 + 0.2 * (nc - 2));
+    if (us < 0.98 * draw) {
+      draw = us;
+      o.threads = 64 * w;
+    }
+  }
+  draw *= (double)((steps + chunk - 1) / chunk);
+  double step = 0;
+  for (uint32_t k = 0; k < steps; ++k)
+    step += kStep + (double)(Wl - 2 * rho * (k + 1)) * kWordStep;
+  const uint32_t groups = (Wp + own - 1) / own;
+  const double chunks = (steps + chunk - 1) / chunk;
+  const double one = kStage + (h->p.J_kind == SMC_J_PM ? 0.5 : 0.0) + draw + step + kChunk * chunks;
+  const uint32_t rounds = (groups + kCUs - 1) / kCUs;
+  o.way = kWayResident;
+  o.launches = launches;
+  o.own = own;
+  o.rho = (uint32_t)rho;
+  o.chunk = chunk;
+  o.us = launches * (rounds == 1 ? one : 0.9 * one * rounds);
+  return true;
+}
+
+// Time of one half-sweep launch on the caller's buffer, or on a packed copy
+// (measured, 2D L = 32 .. 16384 and 3D L = 40 .. 256).
+double half_us(const smc_lattice* h, bool packed) {
+  const double n = (double)h->g.Nh;
+  if (packed) return std::max(4.0, 2.9 + n / (h->g.d == 2 ? 4.75e6 : 3.8e6));
+  IsingLaunch a;
+  std::memset(&a, 0, sizeof(a));
+  a.g = h->g;
+  a.J_kind = h->p.J_kind;
+  a.variant = h->ising_variant;
+  a.rows_per_band = h->rows_per_band;
+  a.heatbath = (h->p.flags & SMC_FLAG_HEATBATH) ? 1 : 0;
+  switch (ising_variant_used(a)) {
+    case kVariantStream: return std::max(5.2, 2.5 + n / 2.1e6);
+    case kVariantChunk: return std::max(4.1, 3.5 + n / 1.2e6);
+    default: return 3.8 + n / 0.21e6;
+  }
+}
+
+SweepPlan plan_sweeps(const smc_lattice* h, int64_t n_sweeps, bool measured) {
+  SweepPlan best;
+  std::memset(&best, 0, sizeof(best));
+  best.way = kWayHalf;
+  // a long call runs as several of at most 64 sweeps, planned alike
+  const uint32_t S = 2u * (uint32_t)std::min<int64_t>(n_sweeps, 64);
+  const bool pm = h->p.J_kind == SMC_J_PM, packed = is_packed(&h->p);
+  const bool hb = (h->p.flags & SMC_FLAG_HEATBATH) != 0;
+  const double N = 2.0 * (double)h->g.Nh;
+  const double finish = measured ? kFinish : 0.0;
+  best.us = S * half_us(h, packed) + finish;
+  if (!h->multi_ok) return best;
+  if (h->forced_steps) {
+    SweepPlan o;
+    const bool whole = h->forced_own >= plane_words(h->g);
+    const uint32_t launches = whole ? 1u : std::max(2u, (S + h->forced_steps - 1) / h->forced_steps);
+    if (resident_shape(h, S, launches, std::min(h->forced_own, plane_words(h->g)), whole, o)) {
+      if (whole) o.chunk = std::min(o.chunk, h->forced_steps);
+      return o;
+    }
+    return best;
+  }
+  const uint32_t Wp = plane_words(h->g);
+  const double bonds = pm ? std::max(kLaunch, N / 1e6) : 0.0;
+  SweepPlan o;
+  if (Wp <= 2048 && resident_shape(h, S, 1, Wp, true, o) && (o.us += bonds) < best.us) best = o;
+  for (uint32_t launches = 2; launches <= S; launches = launches < 8 ? launches + 1 : launches * 5 / 4) {
+    for (uint32_t own = 16; own <= 2048; own = own * 3 / 2) {
+      if (!resident_shape(h, S, launches, own, false, o)) continue;
+      o.us += bonds + finish;
+      if (o.us < best.us) best = o;
+    }
+  }
+  return best;
+}
+
+int resident_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs,
+                    const SweepPlan& plan) {
+  const IsingLaunch ia = ising_args(h, beta);
+  const bool hb = ia.heatbath != 0, packed = is_packed(&h->p);
+  const uint32_t d = (uint32_t)h->p.d;
+  ResidentLaunch a;
+  std::memset(&a, 0, sizeof(a));
+  a.g = h->g;
+  a.key = ia.key;
+  // Metropolis: with J0 < 0 the classes that can refuse are those of many
+  // unsatisfied bonds; counting satisfied ones instead makes them 0 .. d - 1
+  const bool flip = !hb && h->p.J0 < 0.0;
+  a.invert = flip ? ~0u : 0u;
+  for (uint32_t q = 0; q < (hb ? 2 * d + 1 : d); ++q) {
+    const uint32_t k = flip ? 2 * d - q : q;
+    a.th[q] = ((k < 4 ? ia.tab.th_lo : ia.tab.th_hi) >> (8 * (k & 3))) & 0xFFu;
+    a.frac[q] = ia.tab.frac[k];
+  }
+  a.Wp = plane_words(h->g);
+  a.own = plan.own;
+  a.rho = plan.rho;
+  a.J0 = h->p.J0;
+  if (h->p.J_kind == SMC_J_PM) {
+    const int rc = check(launch_bond_words(h->g, !packed, h->J, h->work_bonds, h->stream),
+                         "bond words launch");
+    if (rc != SMC_OK) return rc;
+    a.bonds = h->work_bonds;
+  }
+  const uint32_t nc = hb ? 2 * d + 1 : d;
+  // launches run at most 128 half-sweeps (64 sweeps): the plan's shape for a
+  // call of 64 sweeps is repeated on what is left
+  uint32_t at = 0;  // buffer holding the state: 0 the caller's, 1 and 2 the packed copies
+  for (int64_t done = 0; done < n_sweeps;) {
+    const uint32_t S = 2u * (uint32_t)std::min<int64_t>(n_sweeps - done, 64);
+    const bool last_call = done + S / 2 >= n_sweeps;
+    const uint32_t launches = plan.launches == 1 ? 1u : std::min(plan.launches, S);
+    const uint32_t per = (S + launches - 1) / launches;
+    for (uint32_t s0 = 0; s0 < S; s0 += per) {
+      a.steps = std::min(per, S - s0);
+      a.t0 = (uint32_t)h->t;
+      a.step0 = s0;
+      a.halo = a.rho * a.steps;
+      a.chunk = std::min(plan.chunk, a.steps);
+      const uint32_t Wl = a.own + 2 * a.halo;
+      a.mask_words = a.chunk * (Wl - 2 * a.rho) - a.rho * a.chunk * (a.chunk - 1);
+      // twice the ties expected of a wave's share of the words (2^-8 a class
+      // and site), and room for their scatter
+      a.list_words = 32u + nc * ((a.mask_words + plan.threads - 1) / plan.threads) * 16u;
+      if (h->forced_list) a.list_words = h->forced_list;
+      const bool last = last_call && s0 + a.steps >= S;
+      // one workgroup reads all before it writes: in place; else to another buffer
+      const uint32_t to = last || plan.launches == 1 ? 0u : (at == 1 ? 2u : 1u);
+      a.src = at == 0 ? h->spins : (void*)h->work[at - 1];
+      a.dst = to == 0 ? h->spins : (void*)h->work[to - 1];
+      a.src_bytes = at == 0 && !packed;
+      a.dst_bytes = to == 0 && !packed;
+      const bool meas = last && dev_obs != nullptr;
+      const uint32_t groups = (a.Wp + a.own - 1) / a.own;
+      a.parts = meas && groups > 1 ? h->partials : nullptr;
+      a.obs = meas && groups == 1 ? dev_obs : nullptr;
+      a.sweep = (int64_t)h->t + S / 2;
+      int rc = check(launch_resident(a, hb, plan.threads, h->stream), "resident sweeps launch");
+      if (rc == SMC_OK && a.parts)
+        rc = check(launch_finish(measure_args(h, a.sweep), h->partials, groups, dev_obs, h->stream),
+                   "measurement finish launch");
+      if (rc != SMC_OK) return rc;
+      at = to;
+    }
+    h->t += S / 2;
+    done += S / 2;
+  }
+  return SMC_OK;
+}
+
 // Tiled k-hit sweeps: per sweep one pass over each tile colour.
 int tiled_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs) {
   const IsingLaunch a = ising_args(h, beta);
@@ -451,9 +678,19 @@ int tiled_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs) {
   return SMC_OK;
 }
 
-int sweeps_impl(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs) {
+// `half`: one launch a half-sweep in any case (the band-height autotuner).
+int sweeps_impl(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, bool half = false) {
   if (h->p.tile > 0) return tiled_sweeps(h, beta, n_sweeps, dev_obs);
   if (h->use_fused) return fused_sweeps(h, beta, n_sweeps, dev_obs);
+  if (h->multi_ok && !half && n_sweeps > 0) {
+    if (h->plan_sweeps != n_sweeps || h->plan_measured != (dev_obs != nullptr)) {
+      h->plan = plan_sweeps(h, n_sweeps, dev_obs != nullptr);
+      h->plan_sweeps = n_sweeps;
+      h->plan_measured = dev_obs != nullptr;
+    }
+    const SweepPlan plan = h->plan;
+    if (plan.way == kWayResident) return resident_sweeps(h, beta, n_sweeps, dev_obs, plan);
+  }
   for (int64_t k = 0; k < n_sweeps; ++k) {
     const bool last = k + 1 == n_sweeps;
     const bool renorm = h->p.n > 1 && h->p.renorm_every > 0 &&
@@ -622,13 +859,13 @@ int smc_autotune(smc_lattice* h, double beta, void* scratch, size_t scratch_byte
   const bool verbose = vb && *vb && *vb != '0';
   constexpr int kRounds = 3;
   std::vector<std::vector<float>> times(cand.size());
-  rc = sweeps_impl(h, beta, 2 * K, nullptr);
+  rc = sweeps_impl(h, beta, 2 * K, nullptr, true);
   for (int round = 0; round < kRounds && rc == SMC_OK; ++round) {
     for (size_t i = 0; i < cand.size() && rc == SMC_OK; ++i) {
       *field = cand[i];
-      rc = sweeps_impl(h, beta, 1, nullptr);  // a launch at the new height before timing it
+      rc = sweeps_impl(h, beta, 1, nullptr, true);  // a launch at the new height before timing it
       if (rc == SMC_OK) rc = check(hipEventRecord(e0, h->stream), "event record");
-      if (rc == SMC_OK) rc = sweeps_impl(h, beta, K, nullptr);
+      if (rc == SMC_OK) rc = sweeps_impl(h, beta, K, nullptr, true);
       if (rc == SMC_OK) rc = check(hipEventRecord(e1, h->stream), "event record");
       if (rc == SMC_OK) rc = check(hipEventSynchronize(e1), "event synchronise");
       float ms = 0.0f;
@@ -692,6 +929,7 @@ size_t smc_workspace_bytes(const smc_params* p) {
   size_t b = 2 * kAlign;  // observable slot + counter
   b += partial_bytes(p);
   if ((p->flags & SMC_FLAG_SCHEDULE_FUSED) && !is_packed(p)) b += round_up(spin_bytes(p), kAlign);
+  b += multi_bytes(p);
   return b;
 }
 
@@ -791,6 +1029,30 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
                  (p->flags & SMC_FLAG_SCHEDULE_FUSED) &&
                  !(p->flags & SMC_FLAG_GENERIC_KERNEL) &&
                  ising_fused_supported(h->g, p->J_kind, h->fused_rows);
+  // a kernel or band height asked for by name is the one that runs
+  h->multi_ok = multi_params(p) && h->ising_variant == kVariantAuto;
+  for (const char* v : {"SMC_STREAM_ROWS", "SMC_PACKED_ROWS", "SMC_PACKED_TIES"})
+    if (std::getenv(v)) h->multi_ok = false;
+  h->forced_steps = h->forced_own = h->forced_list = 0;
+  h->plan_sweeps = 0;
+  if (const char* v = std::getenv("SMC_RESIDENT")) {
+    char* end = nullptr;
+    const long st = std::strtol(v, &end, 10), own = *end == ',' ? std::strtol(end + 1, &end, 10) : 0;
+    const long list = *end == ',' ? std::strtol(end + 1, nullptr, 10) : 0;
+    if (st <= 0) h->multi_ok = false;
+    if (st > 0 && own > 0) {
+      h->forced_steps = (uint32_t)std::min(st, 128l);
+      h->forced_own = (uint32_t)std::min(own, 2048l);
+      h->forced_list = list > 0 ? (uint32_t)std::min(list, 64l) : 0u;
+    }
+  }
+  {
+    char* w = h->ws + 2 * kAlign + partial_bytes(p);
+    const size_t plane = 4 * (size_t)plane_words(h->g);
+    h->work[0] = (uint32_t*)w;
+    h->work[1] = (uint32_t*)(w + round_up(2 * plane, kAlign));
+    h->work_bonds = (uint32_t*)(w + 2 * round_up(2 * plane, kAlign));
+  }
   const RngKey key = key_of(h);
   int rc = SMC_OK;
   if (p->tile > 0)
