@@ -45,6 +45,7 @@ hipError_t smc::allow_dynamic_lds(const void* fn, size_t bytes) {
 // the same chain.
 enum SweepWay {
   kWayHalf = 0,      // one launch a half-sweep on the caller's buffer
+  kWayPackedCopy,    // the same on a packed copy of an int8 lattice
   kWayResident       // several half-sweeps a launch (resident.hip)
 };
 
@@ -86,7 +87,7 @@ struct smc_lattice {
   int64_t plan_sweeps;       // the call the plan below is for (0: none yet)
   bool plan_measured;
   SweepPlan plan;
-  uint32_t* work_bonds;      // bond-sign words (+-1 couplings)
+  uint32_t* work_bonds;      // bond-sign words, or the packed couplings (+-1 couplings)
   // workspace carve-up
   void* obs_slot;      // smc_obs (64 B)
   uint32_t* counter;   // validation counter
@@ -572,6 +573,14 @@ SweepPlan plan_sweeps(const smc_lattice* h, int64_t n_sweeps, bool measured) {
     }
     return best;
   }
+  if (!packed && !hb && packed_supported(h->g, h->p.J_kind)) {
+    const double bytes = 2.25 * N + (pm ? 1.125 * h->p.d * N : 0.0);
+    const double us = S * half_us(h, true) + finish + 2 * kLaunch + (pm ? kLaunch : 0.0) + bytes / 5.5e6;
+    if (us < best.us) {
+      best.way = kWayPackedCopy;
+      best.us = us;
+    }
+  }
   const uint32_t Wp = plane_words(h->g);
   const double bonds = pm ? std::max(kLaunch, N / 1e6) : 0.0;
   SweepPlan o;
@@ -660,6 +669,38 @@ int resident_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs
   return SMC_OK;
 }
 
+// n sweeps of an int8 lattice on a packed copy (L % 64 == 0).
+int packed_copy_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs) {
+  const int64_t words = n_sites(&h->p) / 32;
+  IsingLaunch a = ising_args(h, beta);
+  a.rows_per_band = h->packed_rows;
+  uint32_t* s = h->work[0];
+  const uint32_t* J = nullptr;
+  int rc = check(launch_pack((const int8_t*)h->spins, s, words, h->stream), "pack launch");
+  if (rc == SMC_OK && h->p.J_kind == SMC_J_PM) {
+    rc = check(launch_pack((const int8_t*)h->J, h->work_bonds, words * h->p.d, h->stream),
+               "coupling pack launch");
+    J = h->work_bonds;
+  }
+  int64_t nparts = 0;
+  for (int64_t k = 0; k < n_sweeps && rc == SMC_OK; ++k) {
+    const bool meas = dev_obs && k + 1 == n_sweeps;
+    rc = check(launch_packed_half_sweep(a, s, J, (uint32_t)(h->t + k), 0u, nullptr, nullptr, h->stream),
+               "packed Ising half-sweep launch");
+    if (rc == SMC_OK)
+      rc = check(launch_packed_half_sweep(a, s, J, (uint32_t)(h->t + k), 1u, meas ? h->partials : nullptr,
+                                          &nparts, h->stream),
+                 "packed Ising half-sweep launch");
+  }
+  if (rc == SMC_OK) rc = check(launch_unpack(s, (int8_t*)h->spins, words, h->stream), "unpack launch");
+  if (rc != SMC_OK) return rc;
+  h->t += n_sweeps;
+  if (dev_obs)
+    rc = check(launch_finish(measure_args(h, h->t), h->partials, nparts, dev_obs, h->stream),
+               "measurement finish launch");
+  return rc;
+}
+
 // Tiled k-hit sweeps: per sweep one pass over each tile colour.
 int tiled_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs) {
   const IsingLaunch a = ising_args(h, beta);
@@ -690,6 +731,7 @@ int sweeps_impl(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, bo
     }
     const SweepPlan plan = h->plan;
     if (plan.way == kWayResident) return resident_sweeps(h, beta, n_sweeps, dev_obs, plan);
+    if (plan.way == kWayPackedCopy) return packed_copy_sweeps(h, beta, n_sweeps, dev_obs);
   }
   for (int64_t k = 0; k < n_sweeps; ++k) {
     const bool last = k + 1 == n_sweeps;
