@@ -153,7 +153,8 @@ size_t tile_lds_bytes(int d, uint32_t T);
 bool tile_supported(const Geom& g, uint32_t T);
 hipError_t tile_allow_lds(int d, size_t bytes);
 hipError_t launch_tile_pass(const IsingLaunch& a, bool heatbath, uint32_t T, uint32_t hits,
-                            int8_t* spins, uint32_t t, uint32_t tc, hipStream_t st, bool packed);
+                            int8_t* spins, uint32_t t, uint32_t tc, hipStream_t st, bool packed,
+                            uint32_t groups);
 bool tile_packed_supported(const Geom& g, uint32_t T, bool heatbath);
 
 }  // namespace smc

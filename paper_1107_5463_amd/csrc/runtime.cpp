@@ -77,6 +77,7 @@ struct smc_lattice {
   uint32_t packed_rows;      // packed kernel band height (SMC_PACKED_ROWS overrides)
   int packed_ties;           // packed kernels' ties: 0 group, 1 lane, 2 group fallback (SMC_PACKED_TIES)
   bool tile_packed;          // tiled schedule: bit-packed tiles where they apply (SMC_TILE_KERNEL=byte: off)
+  uint32_t tile_group;       // lanes of their workgroups (SMC_TILE_KERNEL=wave: 64, group: 256), 0: chosen
   int cont_variant;          // ContVariant (SMC_CONT_KERNEL overrides the automatic choice)
   uint32_t cont_rows;        // continuous streaming band height (SMC_CONT_ROWS overrides)
   uint32_t cont_spl;         // continuous streaming sites per lane (SMC_CONT_SPL overrides)
@@ -709,7 +710,7 @@ int tiled_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs) {
     for (uint32_t tc = 0; tc < 2; ++tc) {
       const int rc = check(launch_tile_pass(a, hb, (uint32_t)h->p.tile, (uint32_t)h->p.hits,
                                             (int8_t*)h->spins, (uint32_t)h->t, tc, h->stream,
-                                            h->tile_packed),
+                                            h->tile_packed, h->tile_group),
                            "tile pass launch");
       if (rc != SMC_OK) return rc;
     }
@@ -1036,7 +1037,12 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
   h->packed_rows = packed_rows_per_band(h->g, 8192);
   h->packed_ties = 0;
   h->tile_packed = true;
-  if (const char* v = std::getenv("SMC_TILE_KERNEL")) h->tile_packed = std::string(v) != "byte";
+  h->tile_group = 0;
+  if (const char* v = std::getenv("SMC_TILE_KERNEL")) {
+    const std::string s(v);
+    h->tile_packed = s != "byte";
+    h->tile_group = s == "wave" ? 64u : s == "group" ? 256u : 0u;
+  }
   if (const char* v = std::getenv("SMC_PACKED_TIES")) {
     const std::string s(v);
     if (s == "lane") h->packed_ties = 1;

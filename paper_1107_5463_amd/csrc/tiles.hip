@@ -404,26 +404,28 @@ __global__ __launch_bounds__(256) void tile16_kernel(const Geom g, const RngKey 
 // one wave draws where every wave did (a lane's own ties cost its wave one
 // draw each, and some lane of a wave almost always has one).  A workgroup
 // with a lane holding 8 or more tied sites, or more than `cap` in all (at
-// most kTileTieCap; 0 takes this path always), lets each lane draw its own.
-// Every thread of the 256-thread workgroup calls this once per pass, after
+// most tile_tie_cap; 0 takes this path always), lets each lane draw its own.
+// Every thread of the workgroup (BS of them) calls this once per pass, after
 // storing its word; the caller's barrier after the pass orders the flips
 // before the next reads.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kTileTieCap = 512;  // entries of the workgroup's list of tied sites
+// entries of the workgroup's list of tied sites, by its lanes BS
+constexpr uint32_t tile_tie_cap(uint32_t BS) { return 2u * BS; }
 
+template <uint32_t BS>
 struct TileTies {
-  uint4 ent[256];             // per thread: k0, k1, first site, LDS index of its word
-  uint32_t k2[256];           // per thread: k2 (classes of 4 or more, K2)
-  uint16_t idx[kTileTieCap];  // thread | bit << 8
-  uint32_t wsum[4];           // the waves' counts of tied sites
+  uint4 ent[BS];                   // per thread: k0, k1, first site, LDS index of its word
+  uint32_t k2[BS];                 // per thread: k2 (classes of 4 or more, K2)
+  uint16_t idx[tile_tie_cap(BS)];  // thread | bit << 8
+  uint32_t wsum[BS / 64];          // the waves' counts of tied sites
 };
 
 // ROWS8: bit b of a word is site base + (b >> 3) R + (b & 7) (four tile rows
 // of 8 sites), else site base + b.  K2: a tied site's class can reach 4 (the
 // general decision), else it is k0 + 2 k1 (the fast decision: only k < 2
 // refuses).
-template <bool ROWS8, bool K2>
-__device__ __forceinline__ void tile_ties_group(TileTies& tt, uint32_t ties, uint32_t k0,
+template <uint32_t BS, bool ROWS8, bool K2>
+__device__ __forceinline__ void tile_ties_group(TileTies<BS>& tt, uint32_t ties, uint32_t k0,
                                                 uint32_t k1, uint32_t k2, uint32_t base, uint32_t R,
                                                 uint32_t* words, uint32_t off, const TabRegs& tab,
                                                 const RngKey& key, uint32_t t, uint32_t c,
@@ -447,17 +449,26 @@ __device__ __forceinline__ void tile_ties_group(TileTies& tt, uint32_t ties, uin
     wtotal = (uint32_t)__popcll(b0) + 2u * (uint32_t)__popcll(b1) + 4u * (uint32_t)__popcll(b2);
     first = below(b0) + 2u * below(b1) + 4u * below(b2);
   }
-  if (lane == 0) tt.wsum[wave] = few ? wtotal : kTileTieCap + 1u;
-  __syncthreads();
-  const uint32_t s0 = tt.wsum[0], s1 = tt.wsum[1], s2 = tt.wsum[2], s3 = tt.wsum[3];
-  const uint32_t total = s0 + s1 + s2 + s3;  // above kTileTieCap if any wave could not number
+  const uint32_t mine = few ? wtotal : tile_tie_cap(BS) + 1u;
+  uint32_t total = mine;  // above tile_tie_cap if any wave could not number
+  if constexpr (BS > 64u) {
+    if (lane == 0) tt.wsum[wave] = mine;
+    __syncthreads();
+    total = 0u;
+#pragma unroll
+    for (uint32_t w = 0; w < BS / 64u; ++w) {
+      const uint32_t v = tt.wsum[w];
+      first += wave > w ? v : 0u;
+      total += v;
+    }
+  }
   if (total == 0u) return;  // the same for every thread
   if (total <= cap) {
-    uint32_t k = first + (wave > 0 ? s0 : 0u) + (wave > 1 ? s1 : 0u) + (wave > 2 ? s2 : 0u);
+    uint32_t k = first;
     for (uint32_t m = ties; m; m &= m - 1)
       tt.idx[k++] = (uint16_t)(threadIdx.x | ((uint32_t)__builtin_ctz(m) << 8));
     __syncthreads();
-    for (uint32_t r0 = 0; r0 < total; r0 += 256u) {
+    for (uint32_t r0 = 0; r0 < total; r0 += BS) {
       const uint32_t i = r0 + threadIdx.x;
       if (i < total) {
         const uint32_t id = tt.idx[i], b = id >> 8;
@@ -495,10 +506,10 @@ __device__ __forceinline__ void tile_ties_group(TileTies& tt, uint32_t ties, uin
 // by the workgroup, tile_ties_group).  Every site
 // makes the int8 tile kernel's decision, so the chain is the same bit for
 // bit.  T = 64 (a tile is one wave, four to a workgroup) or T = 128 (a tile
-// is one 256-lane workgroup).
+// is one 256-lane workgroup); BS = 64: one tile of 64 a workgroup.
 // ---------------------------------------------------------------------------
-template <bool FAST, bool HB>
-__global__ __launch_bounds__(256) void tile_packed_kernel(const Geom g, const RngKey key,
+template <bool FAST, bool HB, uint32_t BS>
+__global__ __launch_bounds__(BS) void tile_packed_kernel(const Geom g, const RngKey key,
                                                           const IsingTable table, const uint32_t T,
                                                           const uint32_t hits, const uint32_t t,
                                                           const uint32_t tc, const uint32_t ntiles,
@@ -511,7 +522,7 @@ __global__ __launch_bounds__(256) void tile_packed_kernel(const Geom g, const Rn
   const uint32_t TR = T + 2;             // rows with the boundary rows
   const uint32_t PL = TR * RW;           // LDS words per colour
   const uint32_t items = T * WT;         // words a colour of one tile
-  const uint32_t G = blockDim.x / items; // tiles of the workgroup (>= 1)
+  const uint32_t G = BS / items; // tiles of the workgroup (>= 1)
   const uint32_t gi = threadIdx.x / items, li = threadIdx.x - gi * items;
   const uint32_t bt = blockIdx.x * G + gi;  // tile of this lane among the colour's tiles
   const bool valid = bt < ntiles;
@@ -554,7 +565,7 @@ __global__ __launch_bounds__(256) void tile_packed_kernel(const Geom g, const Rn
   const uint32_t y = Y0 + ry - 1;
   const uint32_t rb = ry * RW + i;
   const uint32_t wi = (y * R + xw0) / 32u + (i - 1);  // global word index (R % 32 == 0)
-  __shared__ TileTies tt;
+  __shared__ TileTies<BS> tt;
   uint32_t* const words = reinterpret_cast<uint32_t*>(lds_raw);
   for (uint32_t h = 0; h < hits; ++h) {
 #pragma unroll
@@ -583,7 +594,7 @@ __global__ __launch_bounds__(256) void tile_packed_kernel(const Geom g, const Rn
         own[rb] = HB ? ~flip : o ^ flip;
         off = (uint32_t)(own - words) + rb;
       }
-      tile_ties_group<false, !FAST>(tt, ties, k0, k1, k2, wi * 32u, R, words, off, tab, key, t, c, h,
+      tile_ties_group<BS, false, !FAST>(tt, ties, k0, k1, k2, wi * 32u, R, words, off, tab, key, t, c, h,
                                     tie_cap);
       __syncthreads();
     }
@@ -620,22 +631,22 @@ __global__ __launch_bounds__(256) void tile_packed_kernel(const Geom g, const Rn
 // words 2 h0, 2 h0 + 1 of its 16-site Philox block, as in the int8 16 x 16
 // kernel, so a word takes four blocks; the transpose to bit planes and the
 // compare are the packed kernel's.  Exact ties take their refinement draws
-// before the pass ends, as in the tiles of 64.  Four lanes a tile, 64 tiles a
-// workgroup.
+// before the pass ends, as in the tiles of 64.  Four lanes a tile, BS / 4 tiles
+// a workgroup.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kT16Words = 14;  // per tile and colour: column (6), left (4), right (4)
 
-template <bool FAST, bool HB>
-__global__ __launch_bounds__(256) void tile16_packed_kernel(const Geom g, const RngKey key,
+template <bool FAST, bool HB, uint32_t BS>
+__global__ __launch_bounds__(BS) void tile16_packed_kernel(const Geom g, const RngKey key,
                                                             const IsingTable table,
                                                             const uint32_t hits, const uint32_t t,
                                                             const uint32_t tc, const uint32_t ntiles,
                                                             const uint32_t tie_cap,
                                                             int8_t* __restrict__ s) {
-  __shared__ uint32_t lw[64 * 2 * kT16Words];
+  __shared__ uint32_t lw[BS / 4 * 2 * kT16Words];
   const uint32_t L = (uint32_t)g.L, R = (uint32_t)g.R;
   const uint32_t gi = threadIdx.x >> 2, i = threadIdx.x & 3u;  // tile of the workgroup, word
-  const uint32_t bt = blockIdx.x * 64u + gi;
+  const uint32_t bt = blockIdx.x * (BS / 4u) + gi;
   const bool valid = bt < ntiles;
   const uint32_t half = L / 32;  // tiles of one colour per tile row
   const uint32_t bv = valid ? bt : 0u;
@@ -677,7 +688,7 @@ __global__ __launch_bounds__(256) void tile16_packed_kernel(const Geom g, const 
   FastTab ft;
   if (FAST) ft = fast_tab<2>(tab);
   const uint32_t j0 = (Y0 + 4 * i) * R + x0;  // in-colour index of the word's first site
-  __shared__ TileTies tt;
+  __shared__ TileTies<BS> tt;
   for (uint32_t h = 0; h < hits; ++h) {
 #pragma unroll
     for (uint32_t c = 0; c < 2; ++c) {
@@ -717,7 +728,7 @@ __global__ __launch_bounds__(256) void tile16_packed_kernel(const Geom g, const 
                                    : packed_compare<2>(tab, B, k0, k1, k2, ties);
         own[1 + i] = HB ? ~flip : o ^ flip;
       }
-      tile_ties_group<true, !FAST>(tt, ties, k0, k1, k2, j0, R, lw,
+      tile_ties_group<BS, true, !FAST>(tt, ties, k0, k1, k2, j0, R, lw,
                                    gi * 2u * kT16Words + c * kT16Words + 1u + i, tab, key, t, c,
                                    h, tie_cap);
       __syncthreads();
@@ -759,8 +770,8 @@ __global__ __launch_bounds__(256) void tile16_packed_kernel(const Geom g, const 
 // ---------------------------------------------------------------------------
 constexpr uint32_t kT3Planes = 18;  // the tile's 16 planes and the two boundary planes
 
-template <bool FAST, bool HB>
-__global__ __launch_bounds__(256) void tile16_packed3d_kernel(const Geom g, const RngKey key,
+template <bool FAST, bool HB, uint32_t BS>
+__global__ __launch_bounds__(BS) void tile16_packed3d_kernel(const Geom g, const RngKey key,
                                                               const IsingTable table,
                                                               const uint32_t hits, const uint32_t t,
                                                               const uint32_t tc,
@@ -768,10 +779,10 @@ __global__ __launch_bounds__(256) void tile16_packed3d_kernel(const Geom g, cons
                                                               const uint32_t tie_cap,
                                                               int8_t* __restrict__ s) {
   constexpr uint32_t CW = kT3Planes * kT16Words;  // words of a colour of one tile
-  __shared__ uint32_t lw[4 * 2 * CW];
+  __shared__ uint32_t lw[BS / 64 * 2 * CW];
   const uint32_t L = (uint32_t)g.L, R = (uint32_t)g.R;
   const uint32_t gi = threadIdx.x >> 6, z = (threadIdx.x >> 2) & 15u, i = threadIdx.x & 3u;
-  const uint32_t bt = blockIdx.x * 4u + gi;
+  const uint32_t bt = blockIdx.x * (BS / 64u) + gi;
   const bool valid = bt < ntiles;
   const uint32_t nt = L / 16, half = nt / 2;
   const uint32_t bv = valid ? bt : 0u;
@@ -826,7 +837,7 @@ __global__ __launch_bounds__(256) void tile16_packed3d_kernel(const Geom g, cons
   FastTab ft;
   if (FAST) ft = fast_tab<3>(tab);
   const uint32_t j0 = ((uint32_t)Zg * L + Y0 + 4 * i) * R + x0;  // in-colour index of the word's first site
-  __shared__ TileTies tt;
+  __shared__ TileTies<BS> tt;
   for (uint32_t h = 0; h < hits; ++h) {
 #pragma unroll
     for (uint32_t c = 0; c < 2; ++c) {
@@ -866,7 +877,7 @@ __global__ __launch_bounds__(256) void tile16_packed3d_kernel(const Geom g, cons
                                    : packed_compare<3>(tab, B, k0, k1, k2, ties);
         own[1 + i] = HB ? ~flip : o ^ flip;
       }
-      tile_ties_group<true, !FAST>(tt, ties, k0, k1, k2, j0, R, lw,
+      tile_ties_group<BS, true, !FAST>(tt, ties, k0, k1, k2, j0, R, lw,
                                    gi * 2u * CW + c * CW + (z + 1) * kT16Words + 1u + i, tab, key,
                                    t, c, h, tie_cap);
       __syncthreads();
@@ -900,11 +911,8 @@ bool tile_packed_supported(const Geom& g, uint32_t T, bool heatbath) {
   return shape && (uint32_t)g.L % T == 0 && ((uint32_t)g.L / T) % 2 == 0;
 }
 
-// 256 lanes a workgroup: four tiles of 64 (64 words a colour each) or one of 128
-static uint32_t tile_packed_group(uint32_t T) { return T == 64 ? 4u : 1u; }
-
-static size_t tile_packed_lds_bytes(uint32_t T) {
-  return (size_t)tile_packed_group(T) * 2 * (T + 2) * (T / 64 + 2) * 4;
+static size_t tile_packed_lds_bytes(uint32_t T, uint32_t tiles) {
+  return (size_t)tiles * 2 * (T + 2) * (T / 64 + 2) * 4;
 }
 
 size_t tile_lds_bytes(int d, uint32_t T) {
@@ -939,10 +947,19 @@ hipError_t tile_allow_lds(int d, size_t bytes) {
   return hipSuccess;
 }
 
+// Below this many waves a SIMD a packed tile pass runs in workgroups of one
+// wave: the barriers and the one drawing wave of a 256-lane group then leave
+// the SIMD idle (us a sweep of k = 100, groups of 256 / of 64: 2D L = 1024
+// T = 16 487 / 389, L = 4096 673 / 595, T = 64 558 / 494, 3D L = 128 504 /
+// 402); above it the shared round of tie draws wins (8 waves a SIMD: 1845 /
+// 1847 and 1444 / 1473; L = 16384: 6628 / 6886).
+constexpr uint32_t kTileWaves = 4;
+
 // One tile-colour pass (k hits) of the tiled schedule; `packed`: the bit-packed
-// kernel where it applies.
+// kernel where it applies, in workgroups of `groups` lanes (64 or 256; 0: chosen here).
 hipError_t launch_tile_pass(const IsingLaunch& a, bool heatbath, uint32_t T, uint32_t hits,
-                            int8_t* spins, uint32_t t, uint32_t tc, hipStream_t st, bool packed) {
+                            int8_t* spins, uint32_t t, uint32_t tc, hipStream_t st, bool packed,
+                            uint32_t groups) {
   const uint32_t nt = (uint32_t)a.g.L / T;
   const uint32_t tiles = (a.g.d == 3 ? nt * nt * nt : nt * nt) / 2;
   if (packed && tile_packed_supported(a.g, T, heatbath)) {
@@ -950,46 +967,31 @@ hipError_t launch_tile_pass(const IsingLaunch& a, bool heatbath, uint32_t T, uin
     bool fast = true;
     for (int k = a.g.d; k <= 2 * a.g.d; ++k)
       if ((((k < 4 ? a.tab.al_lo : a.tab.al_hi) >> (8 * (k & 3))) & 0xFFu) != 0xFFu) fast = false;
+    const uint32_t items = a.g.d == 3 ? 64u : T == 16 ? 4u : T * T / 64u;  // lanes of a tile
+    // Workgroups of one wave where a tile fits one and the launch leaves a
+    // SIMD fewer than kTileWaves waves; else 256 lanes, whose ties share one
+    // round of draws.
+    const bool one_wave = items <= 64u && groups != 256u &&
+                          (groups == 64u || (uint64_t)tiles * items < 64ull * 1024 * kTileWaves);
+    const uint32_t bs = one_wave ? 64u : 256u, G = bs / items;
+    const dim3 grid((tiles + G - 1) / G), block(bs);
     // the workgroup's list of tied sites (packed_ties other than 0: each lane its own)
-    const uint32_t tie_cap = a.packed_ties == 0 ? kTileTieCap : 0u;
-    if (T == 16 && a.g.d == 3) {
-      const dim3 grid((tiles + 3) / 4), block(256);
-      if (heatbath)
-        hipLaunchKernelGGL((tile16_packed3d_kernel<false, true>), grid, block, 0, st, a.g, a.key, a.tab,
-                           hits, t, tc, tiles, tie_cap, spins);
-      else if (fast)
-        hipLaunchKernelGGL((tile16_packed3d_kernel<true, false>), grid, block, 0, st, a.g, a.key, a.tab,
-                           hits, t, tc, tiles, tie_cap, spins);
-      else
-        hipLaunchKernelGGL((tile16_packed3d_kernel<false, false>), grid, block, 0, st, a.g, a.key, a.tab,
-                           hits, t, tc, tiles, tie_cap, spins);
-      return hipGetLastError();
-    }
-    if (T == 16) {
-      const dim3 grid((tiles + 63) / 64), block(256);
-      if (heatbath)
-        hipLaunchKernelGGL((tile16_packed_kernel<false, true>), grid, block, 0, st, a.g, a.key, a.tab, hits, t,
-                           tc, tiles, tie_cap, spins);
-      else if (fast)
-        hipLaunchKernelGGL((tile16_packed_kernel<true, false>), grid, block, 0, st, a.g, a.key, a.tab, hits, t,
-                           tc, tiles, tie_cap, spins);
-      else
-        hipLaunchKernelGGL((tile16_packed_kernel<false, false>), grid, block, 0, st, a.g, a.key, a.tab, hits, t,
-                           tc, tiles, tie_cap, spins);
-      return hipGetLastError();
-    }
-    const uint32_t G = tile_packed_group(T);
-    const dim3 grid((tiles + G - 1) / G), block(256);
-    const size_t lds = tile_packed_lds_bytes(T);
-    if (heatbath)
-      hipLaunchKernelGGL((tile_packed_kernel<false, true>), grid, block, lds, st, a.g, a.key, a.tab, T, hits, t,
-                         tc, tiles, tie_cap, spins);
-    else if (fast)
-      hipLaunchKernelGGL((tile_packed_kernel<true, false>), grid, block, lds, st, a.g, a.key, a.tab, T, hits, t,
-                         tc, tiles, tie_cap, spins);
-    else
-      hipLaunchKernelGGL((tile_packed_kernel<false, false>), grid, block, lds, st, a.g, a.key, a.tab, T, hits, t,
-                         tc, tiles, tie_cap, spins);
+    const uint32_t cap = a.packed_ties == 0 ? tile_tie_cap(bs) : 0u;
+#define SMC_TP(K, LDS, ...)                                                                        \
+  do {                                                                                             \
+    if (one_wave) SMC_TPB(K, 64, LDS, __VA_ARGS__); else SMC_TPB(K, 256, LDS, __VA_ARGS__);        \
+  } while (0)
+#define SMC_TPB(K, BS, LDS, ...)                                                                   \
+  do {                                                                                             \
+    if (heatbath) hipLaunchKernelGGL((K<false, true, BS>), grid, block, LDS, st, a.g, a.key, a.tab, __VA_ARGS__, t, tc, tiles, cap, spins); \
+    else if (fast) hipLaunchKernelGGL((K<true, false, BS>), grid, block, LDS, st, a.g, a.key, a.tab, __VA_ARGS__, t, tc, tiles, cap, spins); \
+    else hipLaunchKernelGGL((K<false, false, BS>), grid, block, LDS, st, a.g, a.key, a.tab, __VA_ARGS__, t, tc, tiles, cap, spins); \
+  } while (0)
+    if (T == 16 && a.g.d == 3) SMC_TP(tile16_packed3d_kernel, 0, hits);
+    else if (T == 16) SMC_TP(tile16_packed_kernel, 0, hits);
+    else SMC_TP(tile_packed_kernel, tile_packed_lds_bytes(T, G), T, hits);
+#undef SMC_TPB
+#undef SMC_TP
     return hipGetLastError();
   }
   if (T == 16) {
