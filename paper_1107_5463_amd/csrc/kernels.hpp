@@ -36,6 +36,10 @@ bool ising_chunk_supported(const Geom& g, int J_kind);
 // two words of a colour per lane.
 hipError_t launch_resident(const ResidentLaunch& a, bool heatbath, uint32_t threads,
                            hipStream_t st);
+// The masks of steps 0 .. steps - 1 of a call into `out` (a.drawn_stride apart
+// by class), for launches with a.drawn = out.
+hipError_t launch_draws(const ResidentLaunch& a, bool heatbath, uint32_t steps, uint32_t* out,
+                        hipStream_t st);
 // Bond signs (int8 or packed +-1 couplings) as words aligned with the sites.
 hipError_t launch_bond_words(const Geom& g, bool bytes, const void* J, uint32_t* out,
                              hipStream_t st);

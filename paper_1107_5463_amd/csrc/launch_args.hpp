@@ -56,11 +56,12 @@ struct ResidentLaunch {
   uint32_t halo;       // rho * steps
   uint32_t chunk;      // half-sweeps whose masks are formed together
   uint32_t mask_words; // capacity of a class's masks
-  uint32_t list_words; // capacity of a wave's tie list
   uint32_t src_bytes, dst_bytes;  // 1: int8 planes, 0: words
   const void* src;
   void* dst;
   const uint32_t* bonds;  // bond-sign words (+-1 couplings) or null
+  const uint32_t* drawn;  // masks of the call's steps from memory, or null: formed in the kernel;
+  uint64_t drawn_stride;  // class q's of step k at q drawn_stride + k Wp
   void* parts;         // reduction partials of the final state (several workgroups), or null
   void* obs;           // its record (one workgroup), or null
   double J0;

@@ -30,6 +30,8 @@ namespace smc {
 namespace {
 
 constexpr uint32_t kListBits = 12;  // local word index in a tie entry
+// A wave's tie list: drained whenever it holds 64, and a push adds at most 64.
+constexpr uint32_t kListWords = 128;
 // Plane stride in LDS: local words -1 .. kMaxWords + 1.  A constant, so that
 // the plane of a neighbour read is an immediate offset.
 constexpr uint32_t kMaxWords = 2048, kPlane = kMaxWords + 4;
@@ -78,6 +80,34 @@ __device__ __forceinline__ void store_signs(int8_t* p, uint32_t v, uint32_t nv) 
   }
 }
 
+// The masks of one word: bit s of lt[q] set where site s's prefix byte is below
+// th[q], and the sites `any` whose byte equals some class's (eq[q]).
+template <int NC>
+__device__ __forceinline__ uint32_t word_masks(const uint32_t th[NC], const RngKey& key, uint32_t t,
+                                               uint32_t c, uint32_t gw, uint32_t lt[NC],
+                                               uint32_t eq[NC]) {
+  uint32_t B[8], any = 0u;
+  word_prefix(key, t, c, gw, B);
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    uint32_t l = 0u, e = ~0u;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const uint32_t X = 0u - ((th[q] >> b) & 1u);  // wave-uniform
+      l = __builtin_amdgcn_bitop3_b32(B[b], X, l, 0x8E);
+      e = __builtin_amdgcn_bitop3_b32(B[b], X, e, 0x82);
+    }
+    lt[q] = l;
+    eq[q] = e;
+    any |= e;
+  }
+  return any;
+}
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 // f, or f - n where f >= n, twice: f mod n for f < 3 n.
 __device__ __forceinline__ uint32_t mod3(uint32_t f, uint32_t n) {
   f = f >= n ? f - n : f;
@@ -97,7 +127,7 @@ __global__ __launch_bounds__(1024) void resident_kernel(const ResidentLaunch a) 
   uint32_t* const sp = lds + 1;  // word l of colour c at sp[c kPlane + l]
   uint32_t* const masks = lds + 2u * kPlane;
   const uint32_t lane = __lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  uint32_t* const list = masks + NC * a.mask_words + wave * a.list_words;
+  uint32_t* const list = masks + NC * a.mask_words + wave * kListWords;
   // global word of local word 0
   const uint32_t base = (w0 + a.Wp * ((a.halo + a.Wp - 1u) / a.Wp) - a.halo) % a.Wp;
   const uint32_t L = (uint32_t)a.g.L, R = (uint32_t)a.g.R;
@@ -293,35 +323,61 @@ __global__ __launch_bounds__(1024) void resident_kernel(const ResidentLaunch a) 
     // class) go to the wave's own list, numbered by ballots: no atomic, and
     // no barrier before the wave draws their refinements.
     uint32_t nt = 0u;  // wave-uniform: entries of the list
-    uint32_t k = ka, r = tid;
+    // the list's entries from `from` on, a lane each
+    auto draw_ties = [&](uint32_t from) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (from + lane < nt) resolve(list[from + lane], ka, f0);
+      nt = from;
+    };
+    // the lane's word: r-th of step k, whose words start at lo and number n
+    uint32_t k = ka, r = tid, lo = lo_of(ka), n = Wl - 2u * lo;
+    if (a.drawn) {  // made by draw_kernel: four words' loads in flight a lane
+#pragma unroll 1
+      for (uint32_t i0 = tid; i0 < M; i0 += 4u * T) {
+        uint32_t v[4][NC];
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; ++j) {
+          if (i0 + j * T < M) {
+            while (r >= n) {
+              r -= n;
+              n -= 2u * a.rho;
+              lo += a.rho;
+              ++k;
+            }
+            const uint32_t* src = a.drawn + (uint64_t)(a.step0 + k) * a.Wp + word_of_local(lo + r);
+#pragma unroll
+            for (int q = 0; q < NC; ++q) v[j][q] = src[(uint64_t)q * a.drawn_stride];
+            r += T;
+          }
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; ++j) {
+          if (i0 + j * T < M) {
+#pragma unroll
+            for (int q = 0; q < NC; ++q) masks[(uint32_t)q * a.mask_words + i0 + j * T] = v[j][q];
+          }
+        }
+      }
+    } else
 #pragma unroll 1
     for (uint32_t i0 = wave * 64u; i0 < M; i0 += T, r += T) {
       const uint32_t i = i0 + lane;
       uint32_t any = 0u, eq[NC], tie = 0u;
       if (i < M) {
-        uint32_t n = Wl - 2u * lo_of(k);
         while (r >= n) {
           r -= n;
           n -= 2u * a.rho;
+          lo += a.rho;
           ++k;
         }
-        const uint32_t l = lo_of(k) + r, gw = word_of_local(l);
+        const uint32_t l = lo + r, gw = word_of_local(l);
         const uint32_t h = a.step0 + k, t = a.t0 + (h >> 1), c = h & 1u;
-        uint32_t B[8];
-        word_prefix(a.key, t, c, gw, B);
+        uint32_t lt[NC];
+        any = word_masks<NC>(th, a.key, t, c, gw, lt, eq);
 #pragma unroll
-        for (int q = 0; q < NC; ++q) {
-          uint32_t lt = 0u, e = ~0u;
-#pragma unroll
-          for (int b = 0; b < 8; ++b) {
-            const uint32_t X = 0u - ((th[q] >> b) & 1u);  // wave-uniform
-            lt = __builtin_amdgcn_bitop3_b32(B[b], X, lt, 0x8E);
-            e = __builtin_amdgcn_bitop3_b32(B[b], X, e, 0x82);
-          }
-          masks[(uint32_t)q * a.mask_words + i] = lt;
-          eq[q] = e;
-          any |= e;
-        }
+        for (int q = 0; q < NC; ++q) masks[(uint32_t)q * a.mask_words + i] = lt[q];
         any &= valid_bits(gw);
         tie = ((k - ka) << (kListBits + 12u)) | l;
       }
@@ -333,56 +389,60 @@ __global__ __launch_bounds__(1024) void resident_kernel(const ResidentLaunch a) 
           uint32_t cls = 0u;
 #pragma unroll
           for (int q = 0; q < NC; ++q) cls |= ((eq[q] >> b) & 1u) << q;
-          const uint32_t at = nt + __builtin_amdgcn_mbcnt_hi((uint32_t)(more >> 32),
-                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)more, 0u));
-          const uint32_t entry = tie | (cls << (kListBits + 5u)) | (b << kListBits);
-          if (at < a.list_words) list[at] = entry;
-          else resolve(entry, ka, f0);  // more ties than the list holds
+          list[nt + lanes_below(more)] =
+              tie | (cls << (kListBits + 5u)) | (b << kListBits);
         }
         nt += (uint32_t)__popcll(more);
+        if (nt >= 64u) draw_ties(nt - 64u);  // a full wave of them
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    nt = min(nt, a.list_words);
-#pragma unroll 1
-    for (uint32_t i = lane; i < nt; i += 64u) resolve(list[i], ka, f0);
+    draw_ties(0u);
     __syncthreads();
     // ---- the chunk's half-sweeps ----
-    // the masks of a step are read before the barrier that ends the one before
-    uint32_t A[WPL][NC];
-    auto fetch = [&](uint32_t kk) {
-      const uint32_t lo = lo_of(kk), mb = first(kk) - f0 - lo;
+    // A step reads its neighbour words and the next step's masks together.  A
+    // wave none of whose words the step needs skips it; the other words a
+    // step does not need may take any value: no later step reads them.
+    uint32_t A[2][WPL][NC];  // by colour
+    auto fetch = [&](uint32_t kk, auto cc) {
+      constexpr uint32_t c = decltype(cc)::value;
+      const uint32_t mb = first(kk) - f0 - lo_of(kk);
 #pragma unroll
       for (int p = 0; p < WPL; ++p) {
-        const uint32_t l = tid + (uint32_t)p * T;
-        if (l >= lo && l + lo < Wl) {
+        const uint32_t at = min(mb + tid + (uint32_t)p * T, a.mask_words - 1u);
 #pragma unroll
-          for (int q = 0; q < NC; ++q) A[p][q] = masks[(uint32_t)q * a.mask_words + mb + l];
-        }
+        for (int q = 0; q < NC; ++q) A[c][p][q] = masks[(uint32_t)q * a.mask_words + at];
       }
     };
+    const uint32_t w64 = wave * 64u;
     auto step = [&](uint32_t kk, auto cc) {
       constexpr uint32_t c = decltype(cc)::value;
-      const uint32_t lo = lo_of(kk);
+      const uint32_t slo = lo_of(kk);
+      bool used = false;
 #pragma unroll
       for (int p = 0; p < WPL; ++p) {
-        const uint32_t l = tid + (uint32_t)p * T;
-        if (l >= lo && l + lo < Wl) {
-          uint32_t nb[6], u[6];
+        const uint32_t wl = w64 + (uint32_t)p * T;
+        used = used || (wl + 64u > slo && wl + slo < Wl);
+      }
+      if (used) {
+        uint32_t nb[WPL][6];
+#pragma unroll
+        for (int p = 0; p < WPL; ++p) neighbours(gt[p], cc, nb[p]);
+        if (kk + 1u < kb) fetch(kk + 1u, std::integral_constant<uint32_t, 1u - c>());
+#pragma unroll
+        for (int p = 0; p < WPL; ++p) {
+          const uint32_t l = tid + (uint32_t)p * T;
+          uint32_t u[6];
           const uint32_t o = ow[p][c];
-          neighbours(gt[p], cc, nb);
 #pragma unroll
           for (int m = 0; m < 2 * D; ++m) {
             // Metropolis: unsatisfied bonds (satisfied ones when J0 < 0);
             // heat bath: up neighbours
-            u[m] = HB ? ~nb[m] : o ^ nb[m] ^ a.invert;
+            u[m] = HB ? ~nb[p][m] : o ^ nb[p][m] ^ a.invert;
             if (PM) u[m] ^= jb[p][c * 2 * D + m];
           }
           uint32_t k0, k1, k2;
           count_planes<D>(u, k0, k1, k2);
-          const uint32_t* M = A[p];
+          const uint32_t* M = A[c][p];
           uint32_t nw;
           if constexpr (HB) {
             const uint32_t a01 = sel(k0, M[1], M[0]), a23 = sel(k0, M[3], M[2]);
@@ -399,19 +459,24 @@ __global__ __launch_bounds__(1024) void resident_kernel(const ResidentLaunch a) 
             nw = o ^ (k2 | (k1 & k0) | sel(k1, M[2], sel(k0, M[1], M[0])));
           }
           ow[p][c] = nw;
-          sp[c * kPlane + l] = nw;
+          if (l < Wl) sp[c * kPlane + l] = nw;
         }
       }
-      if (kk + 1u < kb) fetch(kk + 1u);
       __syncthreads();
     };
-    fetch(ka);
+    using C0 = std::integral_constant<uint32_t, 0>;
+    using C1 = std::integral_constant<uint32_t, 1>;
     uint32_t kk = ka;
-    if ((a.step0 + kk) & 1u) step(kk++, std::integral_constant<uint32_t, 1>());
+    if ((a.step0 + kk) & 1u) {
+      fetch(kk, C1());
+      step(kk++, C1());
+    } else {
+      fetch(kk, C0());
+    }
 #pragma unroll 1
     while (kk < kb) {
-      step(kk++, std::integral_constant<uint32_t, 0>());
-      if (kk < kb) step(kk++, std::integral_constant<uint32_t, 1>());
+      step(kk++, C0());
+      if (kk < kb) step(kk++, C1());
     }
   }
 
@@ -467,6 +532,83 @@ __global__ __launch_bounds__(1024) void resident_kernel(const ResidentLaunch a) 
   *(ObsOut*)a.obs = o;
 }
 
+// The masks of a call's half-sweeps, a word and step a lane, into memory: what
+// the workgroups of resident_kernel would each form for their halo is formed
+// once (a launch and a read of the masks against two to five times the draws).
+// blockIdx.y is the step: its counter words are scalar.  The ties of the four
+// waves share a round of draws.
+template <int NC>
+__global__ __launch_bounds__(256) void draw_kernel(const ResidentLaunch a, uint32_t* __restrict__ out) {
+  __shared__ uint32_t mask[NC][256], list[4][256], count[4];
+  const uint32_t tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
+  const uint32_t gw = blockIdx.x * 256u + tid, k = blockIdx.y;
+  const uint32_t t = a.t0 + (k >> 1), c = k & 1u;
+  const uint32_t tail = a.Wp * 32u - (uint32_t)a.g.Nh;
+  uint32_t th[NC], lt[NC], eq[NC];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) th[q] = a.th[q];
+  uint32_t any = word_masks<NC>(th, a.key, t, c, gw, lt, eq);
+  if (gw + 1u >= a.Wp) any &= gw + 1u == a.Wp ? ~0u >> tail : 0u;
+#pragma unroll
+  for (int q = 0; q < NC; ++q) mask[q][tid] = lt[q];
+  uint32_t nt = 0u;
+#pragma unroll 1
+  for (uint64_t more = __ballot(any != 0u); more && nt <= 192u; more = __ballot(any != 0u)) {
+    if (any) {
+      const uint32_t b = __builtin_ctz(any);
+      any &= any - 1u;
+      uint32_t cls = 0u;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) cls |= ((eq[q] >> b) & 1u) << q;
+      list[wave][nt + lanes_below(more)] = (cls << 13) | (b << 8) | tid;
+    }
+    nt += (uint32_t)__popcll(more);
+  }
+  if (lane == 0u) count[wave] = nt;
+  __syncthreads();
+  auto draw = [&](uint32_t b) -> uint32_t {
+    return philox(32u * (blockIdx.x * 256u) + b, t, a.key.replica, tag(c, kIsingRefine), a.key.k0, a.key.k1).w[0] & 0xFFFFFFu;
+  };
+  const uint32_t n0 = count[0], n1 = n0 + count[1], n2 = n1 + count[2], n3 = n2 + count[3];
+#pragma unroll 1
+  for (uint32_t i = tid; i < n3; i += 256u) {
+    const uint32_t w = (i >= n0 ? 1u : 0u) + (i >= n1 ? 1u : 0u) + (i >= n2 ? 1u : 0u);
+    const uint32_t e = list[w][i - (w == 0u ? 0u : w == 1u ? n0 : w == 2u ? n1 : n2)];
+    const uint32_t who = e & 255u, b = (e >> 8) & 31u, cls = e >> 13;
+    const uint32_t u = draw(32u * who + b);
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+      if (((cls >> q) & 1u) && u < a.frac[q]) atomicOr(&mask[q][who], 1u << b);
+  }
+#pragma unroll 1
+  while (any) {  // more ties in the wave than its list holds: the lane's own
+    const uint32_t b = __builtin_ctz(any);
+    any &= any - 1u;
+    const uint32_t u = draw(32u * tid + b);
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+      if (((eq[q] >> b) & 1u) && u < a.frac[q]) atomicOr(&mask[q][tid], 1u << b);
+  }
+  __syncthreads();
+  if (gw < a.Wp) {
+#pragma unroll
+    for (int q = 0; q < NC; ++q) out[(uint64_t)q * a.drawn_stride + (uint64_t)k * a.Wp + gw] = mask[q][tid];
+  }
+}
+
+hipError_t launch_draws(const ResidentLaunch& a, bool heatbath, uint32_t steps, uint32_t* out,
+                        hipStream_t st) {
+  const dim3 grid((a.Wp + 255u) / 256u, steps), block(256);
+  if (a.g.d == 2) {
+    if (heatbath) hipLaunchKernelGGL(draw_kernel<5>, grid, block, 0, st, a, out);
+    else hipLaunchKernelGGL(draw_kernel<2>, grid, block, 0, st, a, out);
+  } else {
+    if (heatbath) hipLaunchKernelGGL(draw_kernel<7>, grid, block, 0, st, a, out);
+    else hipLaunchKernelGGL(draw_kernel<3>, grid, block, 0, st, a, out);
+  }
+  return hipGetLastError();
+}
+
 // The signs of every site's 2 d bonds as words aligned with the sites':
 // out[(c 2d + m) Wp + w], m = +x, -x, +y, -y, ...  One lane a site; a wave's
 // ballot is two words.
@@ -517,7 +659,7 @@ hipError_t launch_bond_words(const Geom& g, bool bytes, const void* J, uint32_t*
 
 static size_t resident_lds_bytes(const ResidentLaunch& a, bool heatbath, uint32_t threads) {
   const uint32_t nc = (uint32_t)(heatbath ? 2 * a.g.d + 1 : a.g.d);
-  return 4u * (2u * (size_t)kPlane + (size_t)nc * a.mask_words + (threads / 64u) * (size_t)a.list_words);
+  return 4u * (2u * (size_t)kPlane + (size_t)nc * a.mask_words + (threads / 64u) * (size_t)kListWords);
 }
 
 template <int D, bool HB, bool PM, bool AL>

@@ -52,7 +52,9 @@ enum SweepWay {
 struct SweepPlan {
   SweepWay way;
   uint32_t launches;                        // resident: how many,
-  uint32_t own, rho, threads, chunk;        // and their shape
+  uint32_t own, rho, threads, chunk;        // and their shape;
+  uint32_t steps;                           // half-sweeps they run together: a longer call repeats them
+  bool drawn;                               // their masks come from draw_kernel
   double us;                                // estimated time of the call
 };
 
@@ -83,12 +85,14 @@ struct smc_lattice {
   uint32_t cont_spl;         // continuous streaming sites per lane (SMC_CONT_SPL overrides)
   FastDiv divQc;             // continuous streaming lanes per plane row
   bool multi_ok;             // multi-sweep calls may leave the half-sweep kernels (plan_sweeps)
-  uint32_t forced_steps, forced_own, forced_list;  // SMC_RESIDENT=steps,own[,list] (tests)
+  uint32_t forced_steps, forced_own;  // SMC_RESIDENT=steps,own[,drawn] (tests): that split always
+  bool forced_drawn;
   uint32_t* work[2];         // two packed copies of the spins (multi-sweep calls)
   int64_t plan_sweeps;       // the call the plan below is for (0: none yet)
   bool plan_measured;
   SweepPlan plan;
   uint32_t* work_bonds;      // bond-sign words, or the packed couplings (+-1 couplings)
+  uint32_t* work_masks;      // masks of a call's half-sweeps (drawn_steps of them)
   // workspace carve-up
   void* obs_slot;      // smc_obs (64 B)
   uint32_t* counter;   // validation counter
@@ -470,37 +474,55 @@ bool multi_params(const smc_params* p) {
 
 uint32_t plane_words(const Geom& g) { return (uint32_t)((g.Nh + 31) / 32); }
 
+uint32_t mask_classes(const smc_params* p) {
+  return (uint32_t)((p->flags & SMC_FLAG_HEATBATH) ? 2 * p->d + 1 : p->d);
+}
+
+// Half-sweeps whose masks the workspace holds: whole sweeps, at most 64 of
+// them and 8 MiB.
+uint32_t drawn_steps(const smc_params* p) {
+  const size_t step = 4 * (size_t)mask_classes(p) * plane_words(make_geom(p));
+  return (uint32_t)std::min<size_t>(128, ((size_t)8 << 20) / step / 2 * 2);
+}
+
+size_t bonds_bytes(const smc_params* p) {
+  return p->J_kind == SMC_J_PM ? round_up(16 * (size_t)p->d * plane_words(make_geom(p)), kAlign) : 0;
+}
+
 size_t multi_bytes(const smc_params* p) {
   if (!multi_params(p)) return 0;
   const size_t plane = 4 * (size_t)plane_words(make_geom(p));
-  return 2 * round_up(2 * plane, kAlign) +
-         (p->J_kind == SMC_J_PM ? round_up(4 * (size_t)p->d * plane, kAlign) : 0);
+  return 2 * round_up(2 * plane, kAlign) + bonds_bytes(p) + drawn_steps(p) * mask_classes(p) * plane;
 }
 
-// Times in us, measured on the device.  A launch occupies the stream for
-// kLaunch at least.  A launch of the resident kernel takes kStage (start,
-// staging, stores), kChunk for the ties of a chunk, kRoundWave a round of the
-// draws and wave of a SIMD (kRoundMin: a wave alone), kStep a half-sweep and
-// kWordStep a word's step in the workgroup.
-constexpr double kLaunch = 3.5, kFinish = 3.0, kStage = 4.5, kChunk = 0.5, kStep = 0.25, kWordStep = 0.4e-3,
-                 kRoundMin = 1.2, kRoundWave = 0.42;
+// Times in us, fitted to the device times of 30 shapes from 2D L = 32 to 4096
+// and 3D L = 40 to 100 (3.4 to 28 us a launch; most within 15 %).  A launch
+// occupies the stream for kLaunch at least.  A launch of the resident kernel
+// takes kStage (start, staging, stores), kStep a half-sweep and kWordStep a
+// word's step in the workgroup (kWordStepAny where rows split words), and for
+// the masks either kRoundWave a round of draws and wave of a SIMD (kRoundMin:
+// a wave alone; more with more classes) or, from memory, kRead and kWordRead a
+// mask -- then the launch that draws them takes kDraws and kWordDraws a mask;
+// kReadRate is bytes read by all workgroups a us.
+constexpr double kLaunch = 3.5, kFinish = 3.0, kStage = 4.4, kStep = 0.17, kWordStep = 0.3e-3,
+                 kWordStepAny = 0.5e-3, kRoundMin = 1.3, kRoundWave = 0.6, kRead = 0.8,
+                 kWordRead = 0.2e-3, kReadRate = 5e6, kDraws = 3.4, kWordDraws = 4.0e-6;
 constexpr uint32_t kCUs = 256;
 
 // The resident kernel with `launches` launches of at most `steps` half-sweeps
 // and `own` words a workgroup; false if it does not fit.
 bool resident_shape(const smc_lattice* h, uint32_t S, uint32_t launches, uint32_t own, bool whole,
-                    SweepPlan& o) {
+                    bool drawn, SweepPlan& o) {
   const Geom& g = h->g;
-  const bool hb = (h->p.flags & SMC_FLAG_HEATBATH) != 0;
   const uint32_t Wp = plane_words(g), tail = Wp * 32u - (uint32_t)g.Nh;
   const uint32_t steps = (S + launches - 1) / launches;
   const uint32_t reach = (uint32_t)(g.d == 2 ? g.R : g.L * g.R) + tail;
   const uint64_t rho = whole ? 0 : (reach + 31u) / 32u;
   const uint64_t Wl = own + 2 * rho * steps;
   if (Wl > 2048 || (!whole && (own < 8 || Wl > 2 * (uint64_t)Wp))) return false;
-  const uint32_t nc = hb ? 2 * g.d + 1 : g.d;
-  // masks and tie list of a chunk: at most 96 KiB of LDS
-  const uint32_t room = 96u * 1024u / (4u * (nc + 1u));  // a list entry a word is ample
+  const uint32_t nc = mask_classes(&h->p);
+  // masks of a chunk: at most 96 KiB of LDS
+  const uint32_t room = 96u * 1024u / (4u * nc);
   const uint32_t chunk = std::min<uint32_t>({steps, 128u, std::max<uint32_t>(1u, room / (uint32_t)Wl)});
   if ((uint64_t)chunk * Wl > room) return false;
   // workgroup size: the draws of a chunk are rounds of `waves` waves, four
@@ -510,26 +532,41 @@ bool resident_shape(const smc_lattice* h, uint32_t S, uint32_t launches, uint32_
   double draw = 1e30;
   for (uint32_t w = std::max(1u, need); w <= 16; ++w) {
     const double rounds = (double)((M + 64 * w - 1) / (64 * w));
-    const double us = rounds * std::max(kRoundMin, kRoundWave * ((w + 3) / 4)) * (1.0 + 0.2 * (nc - 2));
+    const double us = rounds * std::max(kRoundMin, kRoundWave * ((w + 3) / 4)) * (1.0 + 0.22 * (nc - 2));
     if (us < 0.98 * draw) {
       draw = us;
       o.threads = 64 * w;
     }
   }
-  draw *= (double)((steps + chunk - 1) / chunk);
-  double step = 0;
-  for (uint32_t k = 0; k < steps; ++k)
-    step += kStep + (double)(Wl - 2 * rho * (k + 1)) * kWordStep;
-  const uint32_t groups = (Wp + own - 1) / own;
   const double chunks = (steps + chunk - 1) / chunk;
-  const double one = kStage + (h->p.J_kind == SMC_J_PM ? 0.5 : 0.0) + draw + step + kChunk * chunks;
+  draw *= chunks;
+  double step = 0, words = 0;
+  for (uint32_t k = 0; k < steps; ++k) {
+    const double n = (double)(Wl - 2 * rho * (k + 1));
+    step += kStep + n * (g.R % 32 ? kWordStepAny : kWordStep);
+    words += n;
+  }
+  if (drawn) {
+    draw = chunks * kRead + kWordRead * words * nc;
+    o.threads = 64 * std::min(16u, std::max(need, (uint32_t)(Wl + 63) / 64));
+  }
+  const uint32_t groups = (Wp + own - 1) / own;
+  const double one = kStage + (h->p.J_kind == SMC_J_PM ? 0.5 : 0.0) + draw + step;
   const uint32_t rounds = (groups + kCUs - 1) / kCUs;
   o.way = kWayResident;
+  o.steps = S;
+  o.drawn = drawn;
   o.launches = launches;
   o.own = own;
   o.rho = (uint32_t)rho;
   o.chunk = chunk;
-  o.us = launches * (rounds == 1 ? one : 0.9 * one * rounds);
+  // what the workgroups read, halos and all: words or the first launch's
+  // bytes, bond signs, masks
+  const double bytes = groups * ((double)Wl * (8.0 + (is_packed(&h->p) ? 0.0 : 56.0 / launches) +
+                                               (h->p.J_kind == SMC_J_PM ? 16.0 * g.d : 0.0)) +
+                                 (drawn ? 4.0 * nc * words : 0.0));
+  o.us = launches * ((rounds == 1 ? one : 0.9 * one * rounds) + bytes / kReadRate);
+  if (drawn) o.us += kDraws + kWordDraws * (double)S * Wp * nc;
   return true;
 }
 
@@ -562,13 +599,18 @@ SweepPlan plan_sweeps(const smc_lattice* h, int64_t n_sweeps, bool measured) {
   const bool hb = (h->p.flags & SMC_FLAG_HEATBATH) != 0;
   const double N = 2.0 * (double)h->g.Nh;
   const double finish = measured ? kFinish : 0.0;
-  best.us = S * half_us(h, packed) + finish;
+  // the half-sweeps are left only for a clear gain: the estimates are within 15 %
+  best.us = 0.88 * (S * half_us(h, packed) + finish);
   if (!h->multi_ok) return best;
+  const uint32_t Wp = plane_words(h->g);
+  // steps run together with their masks from memory
+  const uint32_t Sd = std::min(S, drawn_steps(&h->p));
+  SweepPlan o;
   if (h->forced_steps) {
-    SweepPlan o;
-    const bool whole = h->forced_own >= plane_words(h->g);
-    const uint32_t launches = whole ? 1u : std::max(2u, (S + h->forced_steps - 1) / h->forced_steps);
-    if (resident_shape(h, S, launches, std::min(h->forced_own, plane_words(h->g)), whole, o)) {
+    const bool whole = h->forced_own >= Wp;
+    const uint32_t So = h->forced_drawn ? Sd : S;
+    const uint32_t launches = whole ? 1u : std::max(2u, (So + h->forced_steps - 1) / h->forced_steps);
+    if (So && resident_shape(h, So, launches, std::min(h->forced_own, Wp), whole, h->forced_drawn, o)) {
       if (whole) o.chunk = std::min(o.chunk, h->forced_steps);
       return o;
     }
@@ -582,15 +624,20 @@ SweepPlan plan_sweeps(const smc_lattice* h, int64_t n_sweeps, bool measured) {
       best.us = us;
     }
   }
-  const uint32_t Wp = plane_words(h->g);
-  const double bonds = pm ? std::max(kLaunch, N / 1e6) : 0.0;
-  SweepPlan o;
-  if (Wp <= 2048 && resident_shape(h, S, 1, Wp, true, o) && (o.us += bonds) < best.us) best = o;
-  for (uint32_t launches = 2; launches <= S; launches = launches < 8 ? launches + 1 : launches * 5 / 4) {
-    for (uint32_t own = 16; own <= 2048; own = own * 3 / 2) {
-      if (!resident_shape(h, S, launches, own, false, o)) continue;
-      o.us += bonds + finish;
-      if (o.us < best.us) best = o;
+  const double bonds = pm ? std::max(kLaunch, 2.0 + 1.25e-6 * h->p.d * N) : 0.0;
+  for (int drawn = 0; drawn < 2; ++drawn) {
+    const uint32_t So = drawn ? Sd : S;
+    if (So == 0) continue;
+    const double calls = (double)S / So;
+    if (Wp <= 2048 && resident_shape(h, So, 1, Wp, true, drawn != 0, o) &&
+        (o.us = calls * o.us + bonds) < best.us)
+      best = o;
+    for (uint32_t launches = 2; launches <= So; launches = launches < 8 ? launches + 1 : launches * 5 / 4) {
+      for (uint32_t own = 16; own <= 2048; own = own * 3 / 2) {
+        if (!resident_shape(h, So, launches, own, false, drawn != 0, o)) continue;
+        o.us = calls * o.us + bonds + finish;
+        if (o.us < best.us) best = o;
+      }
     }
   }
   return best;
@@ -624,27 +671,26 @@ int resident_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs
     if (rc != SMC_OK) return rc;
     a.bonds = h->work_bonds;
   }
-  const uint32_t nc = hb ? 2 * d + 1 : d;
-  // launches run at most 128 half-sweeps (64 sweeps): the plan's shape for a
-  // call of 64 sweeps is repeated on what is left
+  a.drawn = plan.drawn ? h->work_masks : nullptr;
   uint32_t at = 0;  // buffer holding the state: 0 the caller's, 1 and 2 the packed copies
   for (int64_t done = 0; done < n_sweeps;) {
-    const uint32_t S = 2u * (uint32_t)std::min<int64_t>(n_sweeps - done, 64);
+    const uint32_t S = (uint32_t)std::min<int64_t>(2 * (n_sweeps - done), plan.steps);
     const bool last_call = done + S / 2 >= n_sweeps;
     const uint32_t launches = plan.launches == 1 ? 1u : std::min(plan.launches, S);
     const uint32_t per = (S + launches - 1) / launches;
+    a.t0 = (uint32_t)h->t;
+    if (plan.drawn) {
+      a.drawn_stride = (uint64_t)S * a.Wp;
+      const int rc = check(launch_draws(a, hb, S, h->work_masks, h->stream), "draws launch");
+      if (rc != SMC_OK) return rc;
+    }
     for (uint32_t s0 = 0; s0 < S; s0 += per) {
       a.steps = std::min(per, S - s0);
-      a.t0 = (uint32_t)h->t;
       a.step0 = s0;
       a.halo = a.rho * a.steps;
       a.chunk = std::min(plan.chunk, a.steps);
       const uint32_t Wl = a.own + 2 * a.halo;
       a.mask_words = a.chunk * (Wl - 2 * a.rho) - a.rho * a.chunk * (a.chunk - 1);
-      // twice the ties expected of a wave's share of the words (2^-8 a class
-      // and site), and room for their scatter
-      a.list_words = 32u + nc * ((a.mask_words + plan.threads - 1) / plan.threads) * 16u;
-      if (h->forced_list) a.list_words = h->forced_list;
       const bool last = last_call && s0 + a.steps >= S;
       // one workgroup reads all before it writes: in place; else to another buffer
       const uint32_t to = last || plan.launches == 1 ? 0u : (at == 1 ? 2u : 1u);
@@ -1081,17 +1127,17 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
   h->multi_ok = multi_params(p) && h->ising_variant == kVariantAuto;
   for (const char* v : {"SMC_STREAM_ROWS", "SMC_PACKED_ROWS", "SMC_PACKED_TIES"})
     if (std::getenv(v)) h->multi_ok = false;
-  h->forced_steps = h->forced_own = h->forced_list = 0;
+  h->forced_drawn = false;
+  h->forced_steps = h->forced_own = 0;
   h->plan_sweeps = 0;
   if (const char* v = std::getenv("SMC_RESIDENT")) {
     char* end = nullptr;
     const long st = std::strtol(v, &end, 10), own = *end == ',' ? std::strtol(end + 1, &end, 10) : 0;
-    const long list = *end == ',' ? std::strtol(end + 1, nullptr, 10) : 0;
+    h->forced_drawn = std::string(end) == ",drawn";
     if (st <= 0) h->multi_ok = false;
     if (st > 0 && own > 0) {
       h->forced_steps = (uint32_t)std::min(st, 128l);
       h->forced_own = (uint32_t)std::min(own, 2048l);
-      h->forced_list = list > 0 ? (uint32_t)std::min(list, 64l) : 0u;
     }
   }
   {
@@ -1100,6 +1146,7 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
     h->work[0] = (uint32_t*)w;
     h->work[1] = (uint32_t*)(w + round_up(2 * plane, kAlign));
     h->work_bonds = (uint32_t*)(w + 2 * round_up(2 * plane, kAlign));
+    h->work_masks = (uint32_t*)(w + 2 * round_up(2 * plane, kAlign) + bonds_bytes(p));
   }
   const RngKey key = key_of(h);
   int rc = SMC_OK;

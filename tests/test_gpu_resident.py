@@ -2,8 +2,9 @@
 in LDS), or on a packed copy of an int8 lattice: bit for bit the oracle's
 chain, and the half-sweep kernels' chain where the oracle is too slow.
 
-SMC_RESIDENT=steps,own[,entries] fixes the half-sweeps of a launch and the words a
-workgroup owns (own at least the plane's words: one workgroup and no halo) and the entries of a wave's list of ties;
+SMC_RESIDENT=steps,own[,drawn] fixes the half-sweeps of a launch and the words a
+workgroup owns (own at least the plane's words: one workgroup and no halo) and
+whether the masks are formed by a launch of their own;
 SMC_RESIDENT=0 keeps one launch a half-sweep."""
 import numpy as np
 import pytest
@@ -44,9 +45,16 @@ CASES = [  # d, L, kind, heatbath, packed, J0, beta, sweeps, "steps,own"
     (3, 22, 0, False, False, 1.0, 0.2216546, 4, "2,60"),
     (3, 64, 1, False, False, 1.0, 1.0, 2, "2,64"),
     (3, 64, 1, False, True, -1.0, 1.0, 2, "4,100"),
-    # tie lists of three entries: most ties are drawn on the spot
-    (2, 100, 0, False, False, 1.0, 0.4406868, 3, "128,2048,3"),
-    (3, 16, 1, True, False, 1.0, 1.0, 3, "2,24,3"),
+    # the masks from memory: either shape, every class count, last words partly
+    # filled, more steps than the masks held in LDS
+    (2, 4, 0, False, False, 1.0, 0.4406868, 6, "128,2048,drawn"),
+    (2, 100, 1, True, False, 1.0, 0.9, 3, "3,40,drawn"),
+    (2, 102, 1, False, False, -1.0, 0.9, 4, "1,8,drawn"),
+    (2, 256, 0, False, True, 1.0, 0.0, 5, "3,2048,drawn"),
+    (2, 128, 0, False, False, 1.0, 0.4406868, 70, "7,33,drawn"),
+    (3, 10, 1, True, False, 1.0, 1.0, 3, "3,2048,drawn"),
+    (3, 22, 0, False, False, 1.0, INF, 4, "2,60,drawn"),
+    (3, 64, 1, False, False, 1.0, 1.0, 2, "4,100,drawn"),
 ]
 
 
