@@ -28,7 +28,8 @@
 
 namespace smc {
 
-constexpr size_t kRed = 32;  // doubles of reduction scratch (one per wave + the total)
+constexpr size_t kRed = 32;       // doubles of reduction scratch (one per wave + the total)
+constexpr size_t kPairRed = 136;  // the pair kernel's: eight sweeps' totals and 16 waves of each
 
 // In-plane indices of the 2d neighbours (+x, -x, +y, -y, +z, -z) of site
 // (c, j) of the other colour's plane, in 32-bit arithmetic.
@@ -264,7 +265,7 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
   const bool active = q < pairs;
   int8_t* gs = spins + (uint64_t)chain * N;
   double* red = reinterpret_cast<double*>(smem);
-  int8_t* lat = reinterpret_cast<int8_t*>(smem + kRed * sizeof(double));
+  int8_t* lat = reinterpret_cast<int8_t*>(smem + kPairRed * sizeof(double));
   const float bl2e = beta_log2e(a.beta);
 
   for (uint32_t w = q; w < N / 4; w += blockDim.x)
@@ -314,7 +315,61 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
     }
 
   const uint32_t odd = q & 1u;
-  double Gsum = 0.0, G2sum = 0.0;
+  // Covariance: the bond products of up to eight sweeps (a byte each of xs)
+  // wait for one reduction of their eight G's -- per sweep it was a chain of
+  // six double shuffles, two barriers and a serial sum over the waves, a third
+  // of the replay (256 chains of L = 64, 100 sweeps: 248 us).
+  uint32_t xs[2] = {0u, 0u};
+  double Gsum = 0.0, G2sum = 0.0;  // thread s < 8: of the sweeps in slot s
+  auto flush = [&](uint32_t n) {  // n sweeps wait (uniform)
+    // G of each: the lane's signed weights, then over the wave by exchanging
+    // halves -- after three steps a lane holds slot (lane & 7) alone
+    double v[8];
+#pragma unroll
+    for (uint32_t s = 0; s < 8u; ++s) {
+      const uint32_t bits = xs[s >> 2] >> (8u * (s & 3u));
+      v[s] = 0.0;
+#pragma unroll
+      for (uint32_t b = 0; b < 2; ++b)
+#pragma unroll
+        for (int m = 0; m < B; ++m) v[s] += ((bits >> (b * B + m)) & 1u) ? -gv[b][m] : gv[b][m];
+    }
+    const uint32_t lane = q & 63u, wave = q >> 6, nw = (blockDim.x + 63) >> 6;
+#pragma unroll
+    for (uint32_t w = 0; w < 3u; ++w) {
+      const bool up = (lane >> w) & 1u;
+#pragma unroll
+      for (uint32_t i = 0; i < (4u >> w); ++i) {
+        const double keep = up ? v[2 * i + 1] : v[2 * i], send = up ? v[2 * i] : v[2 * i + 1];
+        v[i] = keep + __shfl_xor(send, 1 << w);
+      }
+    }
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) v[0] += __shfl_xor(v[0], o);
+    if (lane < 8u) red[8u + 16u * lane + wave] = v[0];
+    __syncthreads();
+    if (q < n) {
+      double sg = 0.0;
+      for (uint32_t k = 0; k < nw; ++k) sg += red[8u + 16u * q + k];
+      red[q] = sg - gc;
+      Gsum += sg - gc;
+      G2sum += (sg - gc) * (sg - gc);
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t s = 0; s < 8u; ++s) {
+      if (s < n) {
+        const double Gc = red[s];
+        const uint32_t bits = xs[s >> 2] >> (8u * (s & 3u));
+#pragma unroll
+        for (uint32_t b = 0; b < 2; ++b)
+#pragma unroll
+          for (int m = 0; m < B; ++m) accd[b][m] += ((bits >> (b * B + m)) & 1u) ? -Gc : Gc;
+      }
+    }
+    xs[0] = xs[1] = 0u;
+    // red is rewritten only after the next sweep's two barriers
+  };
   for (uint32_t sw = 0; sw < n_sweeps; ++sw) {
     const uint32_t t = t0 + sw;
     // the even lane draws colour 0's block of this pair's four sites, the
@@ -357,36 +412,30 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
       __syncthreads();
     }
     if (MODE != 1) continue;
-    // G of this sample (wave sums, then the waves in order), then (G - c) x_b
-    double Gp = 0.0;
-#pragma unroll
-    for (uint32_t b = 0; b < 2; ++b)
-#pragma unroll
-      for (int m = 0; m < B; ++m) Gp += ((xneg >> (b * B + m)) & 1u) ? -gv[b][m] : gv[b][m];
-    double v = Gp;
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    const uint32_t wave = q >> 6, nw = (blockDim.x + 63) >> 6;
-    if ((q & 63) == 0) red[1 + wave] = v;
-    __syncthreads();
-    if (q == 0) {
-      double sg = 0.0;
-      for (uint32_t k = 0; k < nw; ++k) sg += red[1 + k];
-      red[0] = sg;
-      const double gcen = sg - gc;
-      Gsum += gcen;
-      G2sum += gcen * gcen;
-    }
-    __syncthreads();
-    const double Gc = red[0] - gc;
-#pragma unroll
-    for (uint32_t b = 0; b < 2; ++b)
-#pragma unroll
-      for (int m = 0; m < B; ++m) accd[b][m] += ((xneg >> (b * B + m)) & 1u) ? -Gc : Gc;
-    // red[0] is rewritten only after the next sweep's two barriers
+    const uint32_t slot = sw & 7u;  // 2 B = 8 bits a sweep (D = 2)
+    if (slot < 4u) xs[0] |= xneg << (8u * slot);
+    else xs[1] |= xneg << (8u * (slot - 4u));
+    if (slot == 7u || sw + 1u == n_sweeps) flush(slot + 1u);
   }
 
   for (uint32_t w = q; w < N / 4; w += blockDim.x)
     reinterpret_cast<uint32_t*>(gs)[w] = reinterpret_cast<const uint32_t*>(lat)[w];
+  if (MODE == 1) {
+    __syncthreads();
+    if (q < 8u) {
+      red[q] = Gsum;
+      red[8u + q] = G2sum;
+    }
+    __syncthreads();
+    if (q == 0) {
+      for (uint32_t s = 1; s < 8u; ++s) {
+        Gsum += red[s];
+        G2sum += red[8u + s];
+      }
+      gpart[2 * chain] = Gsum;
+      gpart[2 * chain + 1] = G2sum;
+    }
+  }
   if (MODE == 2 || !active) return;
   const uint32_t nbonds = (uint32_t)D * N;
 #pragma unroll
@@ -400,30 +449,48 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
       else
         part[(uint64_t)chain * nbonds + bond] = accd[b][m];
     }
-  if (MODE == 1 && q == 0) {
-    gpart[2 * chain] = Gsum;
-    gpart[2 * chain + 1] = G2sum;
-  }
 }
 
-// Sum the per-chain covariance partials into the caller's accumulators in
-// chain order (deterministic).
-__global__ __launch_bounds__(256) void chains_reduce_kernel(const double* __restrict__ part,
-                                                            const double* __restrict__ gpart,
-                                                            const uint32_t n_chains,
-                                                            const uint32_t nb,
-                                                            double* __restrict__ cov_acc,
-                                                            double* __restrict__ G_acc) {
-  const uint32_t b = blockIdx.x * 256 + threadIdx.x;
-  if (b < nb) {
-    double s = 0.0;
-    for (uint32_t k = 0; k < n_chains; ++k) s += part[(uint64_t)k * nb + b];
-    cov_acc[b] += s;
+// Sum the per-chain covariance partials into the caller's accumulators: 64
+// bonds a workgroup, its 16 waves taking a run of chains each (four loads in
+// flight), then the runs in chain order -- a fixed order, deterministic.  One
+// thread a bond over all chains left 32 workgroups waiting on one load at a
+// time (256 chains of 8192 bonds, 16.8 MB: 82 us).  The last workgroup sums
+// G and G^2.
+__global__ __launch_bounds__(1024) void chains_reduce_kernel(const double* __restrict__ part,
+                                                             const double* __restrict__ gpart,
+                                                             const uint32_t n_chains,
+                                                             const uint32_t nb,
+                                                             double* __restrict__ cov_acc,
+                                                             double* __restrict__ G_acc) {
+  __shared__ double sh[16][64];
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const bool last = blockIdx.x + 1u == gridDim.x;
+  // element `lane` of a chain's row: a bond, or (last) G or G^2
+  const double* src = last ? gpart : part;
+  const uint32_t row = last ? 2u : nb, b = last ? lane : blockIdx.x * 64u + lane;
+  const uint32_t per = (n_chains + 15u) / 16u;
+  const uint32_t k0 = wave * per, k1 = min(k0 + per, n_chains);
+  double s = 0.0;
+  if (b < row) {
+    uint32_t k = k0;
+    for (; k + 4u <= k1; k += 4u) {
+      double v[4];
+#pragma unroll
+      for (uint32_t u = 0; u < 4u; ++u) v[u] = src[(uint64_t)(k + u) * row + b];
+#pragma unroll
+      for (uint32_t u = 0; u < 4u; ++u) s += v[u];
+    }
+    for (; k < k1; ++k) s += src[(uint64_t)k * row + b];
   }
-  if (blockIdx.x == 0 && threadIdx.x < 2) {
-    double s = 0.0;
-    for (uint32_t k = 0; k < n_chains; ++k) s += gpart[2 * k + threadIdx.x];
-    G_acc[threadIdx.x] += s;
+  sh[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0u && b < row) {
+    double t = 0.0;
+#pragma unroll
+    for (uint32_t w = 0; w < 16u; ++w) t += sh[w][lane];
+    double* dst = last ? G_acc : cov_acc;
+    dst[b] += t;
   }
 }
 
@@ -438,19 +505,17 @@ __global__ __launch_bounds__(256) void chains_reduce_kernel(const double* __rest
 //   ln Z: d/dJ_b = beta <x_b>, d/dbeta = sum_b J_b <x_b>;
 //   moment matching: J_b += lr beta (target_b - <x_b>).
 // ---------------------------------------------------------------------------
-constexpr int kFinishThreads = 256;
+constexpr int kFinishThreads = 1024;  // one workgroup: latency, hidden by lanes and loads in flight
 
-// Sum of v over the workgroup in a fixed order (all threads get it).
+// Sum of v over the workgroup in a fixed order (thread 0 gets it): within the
+// waves by shuffles, then over the waves.
 __device__ double block_sum_fixed(double v, double* sh) {
-  sh[threadIdx.x] = v;
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
+  if ((threadIdx.x & 63u) == 0u) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (unsigned s = kFinishThreads / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
+  if (threadIdx.x == 0)
+    for (int w = 1; w < kFinishThreads / 64; ++w) v += sh[w];
+  return v;
 }
 
 __global__ __launch_bounds__(256) void chains_mean_kernel(const int64_t* __restrict__ sum,
@@ -465,8 +530,9 @@ __global__ __launch_bounds__(kFinishThreads) void chains_dot_kernel(const double
                                                                     const double* __restrict__ w,
                                                                     const uint32_t nb,
                                                                     double* __restrict__ out) {
-  __shared__ double sh[kFinishThreads];
+  __shared__ double sh[kFinishThreads / 64];
   double v = 0.0;
+#pragma unroll 8
   for (uint32_t b = threadIdx.x; b < nb; b += kFinishThreads) v += a[b] * w[b];
   v = block_sum_fixed(v, sh);
   if (threadIdx.x == 0) out[0] = v;
@@ -476,9 +542,10 @@ __global__ __launch_bounds__(kFinishThreads) void chains_vjp_kernel(
     const double* __restrict__ cov_acc, const double* __restrict__ G_acc,
     const double* __restrict__ mean, const float* __restrict__ J, const uint32_t nb,
     const double S, const double beta, float* __restrict__ grad_J, double* __restrict__ grad_beta) {
-  __shared__ double sh[kFinishThreads];
+  __shared__ double sh[kFinishThreads / 64];
   const double gm = G_acc[0] / S;
   double v = 0.0;
+#pragma unroll 8
   for (uint32_t b = threadIdx.x; b < nb; b += kFinishThreads) {
     const double cov = cov_acc[b] / S - gm * mean[b];
     grad_J[b] = (float)(beta * cov);
@@ -494,10 +561,11 @@ __global__ __launch_bounds__(kFinishThreads) void chains_lnz_grad_kernel(
     const double* __restrict__ mean, const float* __restrict__ J, const uint32_t nb,
     const double beta, const double* __restrict__ scale, float* __restrict__ gJ32,
     double* __restrict__ gJ64, double* __restrict__ grad_beta) {
-  __shared__ double sh[kFinishThreads];
+  __shared__ double sh[kFinishThreads / 64];
   const double sc = scale ? scale[0] : 1.0;
   const double sb = sc * beta;
   double v = 0.0;
+#pragma unroll 8
   for (uint32_t b = threadIdx.x; b < nb; b += kFinishThreads) {
     const double gj = sb * mean[b];
     if (gJ32) gJ32[b] = (float)gj;
@@ -572,7 +640,7 @@ static size_t chains_lds_bytes_jl(const Geom& g, int mode) {
 }
 
 // LDS of the pair kernel: reduction scratch and both planes.
-static size_t chains_pair_lds_bytes(const Geom& g) { return kRed * sizeof(double) + 2 * (size_t)g.Nh; }
+static size_t chains_pair_lds_bytes(const Geom& g) { return kPairRed * sizeof(double) + 2 * (size_t)g.Nh; }
 
 bool chains_pair_supported(const Geom& g) { return g.Nh / 2 <= 1024; }
 
@@ -659,7 +727,7 @@ hipError_t launch_chains_covariance(const ChainsLaunch& a, int8_t* spins, uint32
   hipError_t e = launch_chains(a, 1, spins, t0, n_sweeps, -1, nullptr, g, gc, part, gpart, st);
   if (e != hipSuccess) return e;
   const uint32_t nb = (uint32_t)(a.g.d * 2 * a.g.Nh);
-  hipLaunchKernelGGL(chains_reduce_kernel, dim3((nb + 255) / 256), dim3(256), 0, st, part, gpart,
+  hipLaunchKernelGGL(chains_reduce_kernel, dim3((nb + 63) / 64 + 1), dim3(1024), 0, st, part, gpart,
                      a.n_chains, nb, cov_acc, G_acc);
   return hipGetLastError();
 }
