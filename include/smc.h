@@ -368,7 +368,7 @@ int smc_chains_sample(smc_chains* h, double beta, int64_t n_sweeps, int64_t* dev
  * (asynchronous): for every chain and sweep, with the sample's
  * G = sum_b g_b x_b - g_center, adds G x_b to dev_cov_acc[b] and G, G^2 to
  * dev_G_acc[0], dev_G_acc[1] (double, 8-byte aligned; summed over chains in
- * chain order, deterministic).  Started from the state and counter a
+ * a fixed order, deterministic).  Started from the state and counter a
  * smc_chains_sample call started from, it visits the same configurations,
  * so that Cov(G, x_b) = cov_acc[b] / S - (G_acc[0] / S) <x_b> over its
  * S = n_chains n_sweeps samples, and the vector-Jacobian product of the
