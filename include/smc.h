@@ -311,11 +311,12 @@ int smc_batch_set_schedule(smc_batch* b, int32_t threads, int32_t largest_first)
 int smc_batch_get_schedule(const smc_batch* b, int32_t* threads, int32_t* largest_first);
 
 /* 1 if lattice r takes the packed path at the handle's current workgroup size
- * (3D, L % 8 == 0, L <= 40, at most two 32-site words of a colour per lane:
- * one bit per site in LDS, the bit-sliced decision of SMC_FLAG_PACKED -- Sec.
- * 2, multi-spin coding; the chain is the same), 0 if it takes the one byte
- * per site path (also for every lattice when SMC_BATCH_PACKED=0 was set at
- * init), negative on error. */
+ * (at most two 32-site words of a colour per lane -- 2D L^2 / 64, 3D L^3 / 64
+ * words, the last one maybe partly filled: one bit per site in LDS, the
+ * bit-sliced decision of SMC_FLAG_PACKED -- Sec. 2, multi-spin coding; the
+ * chain is the same; lattices of at most 64 words are a wave's, several to a
+ * workgroup), 0 if it takes the one byte per site path (also for every lattice
+ * when SMC_BATCH_PACKED=0 was set at init), negative on error. */
 int smc_batch_lattice_packed(const smc_batch* b, int32_t r);
 
 /* With enable != 0 later smc_batch_sweep calls replay one instantiated

@@ -35,62 +35,71 @@ namespace smc {
 constexpr uint32_t kBatchTieSlots = 4;  // deferred ties per lane before a flush
 
 // ---------------------------------------------------------------------------
-// Packed path (3D lattices with L % 4 == 0, L <= 40, at most two 32-site
-// words of a colour per lane): the lattice sits in LDS at one bit per site --
-// word w of colour c holds sites 32 w .. 32 w + 31 of that plane, the two
-// colours' words side by side (byte 12 (w + 1) + 4 c, a zero pad pair at each
-// end) -- with the signs of each site's 2d bonds as six words aligned with it
-// (the -mu bonds gathered from the neighbours' planes when the lattice is
-// staged; 52 bytes per word).  A lane owns words w = lane and w = lane + blockDim of both
-// colours for the whole call.  The neighbour words of the other colour come
-// from funnel shifts of LDS words: in-row x +- 1 (with the wrap at row ends
-// and the row parity as per-word masks), y +- 1 (a shift by R = L / 2 sites,
-// with the rows at y = L - 1 or 0 taking the wrapped source), and z +- 1 (a
-// shift by L^2 / 2 sites: a whole word when L % 8 == 0, otherwise a funnel
-// shift with the planes at z = L - 1 or 0 taking the wrapped source).
-// Counts, the decision with
-// its prefix bit planes and exact ties, and the random bytes per site are
-// those of the packed single-lattice kernel, so every lattice keeps the
-// chain of its replica bit for bit.
+// Packed path (any even edge whose words number at most two per lane): the
+// lattice sits in LDS at one bit per site -- word w of colour c holds sites
+// 32 w .. 32 w + 31 of that plane (the last word may be partly filled), the
+// two colours' words side by side (byte 12 (w + 1) + 4 c, a zero pad pair at
+// each end) -- with the signs of each site's 2d bonds as 2d words aligned with
+// it (the -mu bonds by the gather of the -mu neighbours' spins, run on the
+// coupling planes when the lattice is staged).  A lane owns words w = lane and
+// w = lane + T of both colours for the whole call.  The neighbour words of the
+// other colour come from funnel shifts of LDS words, with the row ends, the
+// row parity and the periodic wraps as per-word masks: in-row x +- 1, y +- 1 a
+// shift by R = L / 2 sites, z +- 1 a shift by L^2 / 2 sites (a whole word when
+// L % 8 == 0).  Counts, the decision with its prefix bit planes and exact
+// ties, and the random bytes per site are those of the packed single-lattice
+// kernel, so every lattice keeps the chain of its replica bit for bit.
+//
+// A lattice of at most 64 words a colour (2D L <= 64, 3D L <= 16) is one
+// wave's (WAVE): blockDim / 64 of them share a workgroup and none waits at a
+// barrier.  With a workgroup each, three of its four waves idled and held
+// their registers: 2048 spin-glass samples of L = 8 .. 32, 100 sweeps recorded
+// every 10: 957 -> 738 us, of which 85 us were the couplings' bit-by-bit
+// staging.  Edges that are no multiple of four, and 2D, took the byte path:
+// 512 samples, 100 sweeps: 3D L = 10 1103 -> 159 us, L = 30 5692 -> 579, 2D
+// L = 100 1343 -> 262, L = 128 640 -> 273.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kPackedBatchWordsPerLane = 2;
+constexpr uint32_t kWaveWords = 64;  // words a colour of a lattice that one wave takes
 // LDS strides of a word's spin pair (colour 0, colour 1, unused) and of its
-// twelve bond-sign words (+ one unused): an odd number of dwords, so that 32
+// 4 d bond-sign words (+ one unused): an odd number of dwords, so that 32
 // lanes reading consecutive words touch 32 different banks.
-constexpr uint32_t kPkSpin = 12, kPkBond = 52;
+constexpr uint32_t kPkSpin = 12;
+__host__ __device__ constexpr uint32_t pk_bond(int d) { return 16u * d + 4u; }
+
+__host__ __device__ inline uint32_t batch_words(int d, uint32_t L) {
+  return (L * L * (d == 3 ? L : 1u) / 2u + 31u) / 32u;
+}
 
 __host__ __device__ inline bool batch_packed_ok(int d, uint32_t L, uint32_t threads) {
-  if (d != 3 || L % 4u != 0u || L > 40u) return false;
-  const uint32_t Wp = L * L * L / 64u;  // words per colour
-  return Wp <= kPackedBatchWordsPerLane * threads;
+  return (d == 2 || L <= 40u) && batch_words(d, L) <= kPackedBatchWordsPerLane * threads;
 }
 
-// LDS bytes of the packed path for edge L: the spin pairs with their pads and
-// the aligned bond-sign words (+-1 couplings).  (A lane's tied words -- at
-// most one per word it owns -- wait in registers until the end of the
-// half-sweep.)
-__host__ __device__ inline size_t batch_packed_lds_bytes(uint32_t L, bool pm, uint32_t threads) {
-  const size_t Wp = (size_t)L * L * L / 64;
-  const size_t sb = (kPkSpin * (Wp + 2) + 15) / 16 * 16;
-  const size_t jb = pm ? (kPkBond * Wp + 15) / 16 * 16 : 0;
-  (void)threads;
-  return sb + jb;
+bool batch_lattice_wave(int d, uint32_t L) { return batch_words(d, L) <= kWaveWords; }
+
+// LDS bytes of the packed path for `words` words a colour: the spin pairs with
+// their pads and the aligned bond-sign words (+-1 couplings).  (A lane's tied
+// words -- at most one per word it owns -- wait in registers until the end of
+// the half-sweep.)
+__host__ __device__ constexpr uint32_t batch_packed_lds_bytes(int d, uint32_t words, bool pm) {
+  return (kPkSpin * (words + 2u) + 15u) / 16u * 16u + (pm ? (pk_bond(d) * words + 15u) / 16u * 16u : 0u);
 }
 
+template <int D>
 struct PackedWord {  // per-call constants of one word of the lane
   uint32_t E, S, Pm0, Ymp, Ymm;  // row end / start, rows of colour-0 parity 1, y = L-1 / y = 0
   uint32_t Zmp, Zmm;             // sites at z = L-1 / z = 0 (used when z-planes split words)
   uint32_t ayp, aym;             // LDS byte addresses (colour 0) of the y wrap sources
-  uint32_t azp, azm;             // z +- 1 sources (low words of the funnels)
-  uint32_t azpw, azmw;           // z wrap sources (z-planes that split words)
+  uint32_t azp, azm;             // z +- 1 sources (low words of the funnels); 2D: y +- 1
+  uint32_t azpw, azmw;           // z wrap sources (z-planes that split words); 2D: the x wraps
   uint32_t a0;                   // LDS byte address of word w, colour 0
   uint32_t aj;                   // LDS byte address of its bond-sign words
-  bool valid;
+  uint32_t ok;                   // its sites that exist (0: the lane has no such word)
 };
 
 // Funnel shifts of the wrap and z gathers (site offset mod 32).  LR = L^2/2
-// sites per z-plane of one colour; when LR % 32 == 0 the z neighbours are
-// whole words (zs == 0).
+// sites per z-plane of one colour (2D: of the lattice); when LR % 32 == 0 the
+// z neighbours are whole words (zs == 0).
 struct PackedZ {
   uint32_t ysw, ysmw;     // y wraps: R - LR, LR - R
   uint32_t zs, zsw;       // +z: LR, LR (1 - L)
@@ -98,115 +107,96 @@ struct PackedZ {
 };
 
 // Neighbour words (+x, -x, +y, -y, +z, -z) of word `pw` of colour C from the
-// other colour's words.
-template <uint32_t C>
-__device__ __forceinline__ void packed_neighbours(const unsigned char* lds, const PackedWord& pw,
+// other colour's words.  In 3D a row is at most 20 sites, so its wrap and the
+// rows around it lie in the words beside the own one; in 2D they have sources
+// of their own.
+template <int D, uint32_t C>
+__device__ __forceinline__ void packed_neighbours(const unsigned char* lds, const PackedWord<D>& pw,
                                                   uint32_t R, const PackedZ& pz, uint32_t nb[6]) {
   constexpr uint32_t O = 4u * (1u - C);  // the other colour's word in a pair
   auto ldw = [&](uint32_t a) -> uint32_t { return *reinterpret_cast<const uint32_t*>(lds + a); };
+  auto fun = [&](uint32_t a, uint32_t sh) -> uint32_t {
+    return __builtin_amdgcn_alignbit(ldw(a + kPkSpin + O), ldw(a + O), sh);
+  };
   const uint32_t wp = ldw(pw.a0 - kPkSpin + O), wc = ldw(pw.a0 + O), wn = ldw(pw.a0 + kPkSpin + O);
   const uint32_t next = __builtin_amdgcn_alignbit(wn, wc, 1u);        // site + 1
   const uint32_t prev = __builtin_amdgcn_alignbit(wc, wp, 31u);       // site - 1
-  const uint32_t wst = __builtin_amdgcn_alignbit(wc, wp, 33u - R);    // site - (R - 1): row start
-  const uint32_t wen = __builtin_amdgcn_alignbit(wn, wc, R - 1u);     // site + (R - 1): row end
+  // site - (R - 1): row start; site + (R - 1): row end
+  const uint32_t wst = D == 3 ? __builtin_amdgcn_alignbit(wc, wp, 33u - R) : fun(pw.azpw, (1u - R) & 31u);
+  const uint32_t wen = D == 3 ? __builtin_amdgcn_alignbit(wn, wc, R - 1u) : fun(pw.azmw, (R - 1u) & 31u);
   // row parity of colour C: p = 1 rows take x + 1 = in-row index + 1
   const uint32_t Pm = C == 0 ? pw.Pm0 : ~pw.Pm0;
   nb[0] = __builtin_amdgcn_bitop3_b32(Pm, __builtin_amdgcn_bitop3_b32(pw.E, wst, next, 0xCA), wc, 0xCA);
   nb[1] = __builtin_amdgcn_bitop3_b32(Pm, wc, __builtin_amdgcn_bitop3_b32(pw.S, wen, prev, 0xCA), 0xCA);
-  const uint32_t yp = __builtin_amdgcn_alignbit(wn, wc, R);
-  const uint32_t ypw = __builtin_amdgcn_alignbit(ldw(pw.ayp + kPkSpin + O), ldw(pw.ayp + O), pz.ysw);
-  nb[2] = __builtin_amdgcn_bitop3_b32(pw.Ymp, ypw, yp, 0xCA);
-  const uint32_t ym = __builtin_amdgcn_alignbit(wc, wp, 32u - R);
-  const uint32_t ymw = __builtin_amdgcn_alignbit(ldw(pw.aym + kPkSpin + O), ldw(pw.aym + O), pz.ysmw);
-  nb[3] = __builtin_amdgcn_bitop3_b32(pw.Ymm, ymw, ym, 0xCA);
-  if (pz.zs == 0u) {  // z-planes hold whole words
-    nb[4] = ldw(pw.azp + O);
-    nb[5] = ldw(pw.azm + O);
-  } else {
-    const uint32_t zp = __builtin_amdgcn_alignbit(ldw(pw.azp + kPkSpin + O), ldw(pw.azp + O), pz.zs);
-    const uint32_t zpw = __builtin_amdgcn_alignbit(ldw(pw.azpw + kPkSpin + O), ldw(pw.azpw + O), pz.zsw);
-    nb[4] = __builtin_amdgcn_bitop3_b32(pw.Zmp, zpw, zp, 0xCA);
-    const uint32_t zm = __builtin_amdgcn_alignbit(ldw(pw.azm + kPkSpin + O), ldw(pw.azm + O), pz.zsm);
-    const uint32_t zmw = __builtin_amdgcn_alignbit(ldw(pw.azmw + kPkSpin + O), ldw(pw.azmw + O), pz.zsmw);
-    nb[5] = __builtin_amdgcn_bitop3_b32(pw.Zmm, zmw, zm, 0xCA);
+  const uint32_t yp = D == 3 ? __builtin_amdgcn_alignbit(wn, wc, R) : fun(pw.azp, R & 31u);
+  nb[2] = __builtin_amdgcn_bitop3_b32(pw.Ymp, fun(pw.ayp, pz.ysw), yp, 0xCA);
+  const uint32_t ym = D == 3 ? __builtin_amdgcn_alignbit(wc, wp, 32u - R) : fun(pw.azm, (0u - R) & 31u);
+  nb[3] = __builtin_amdgcn_bitop3_b32(pw.Ymm, fun(pw.aym, pz.ysmw), ym, 0xCA);
+  nb[4] = nb[5] = 0u;
+  if constexpr (D == 3) {
+    if (pz.zs == 0u) {  // z-planes hold whole words
+      nb[4] = ldw(pw.azp + O);
+      nb[5] = ldw(pw.azm + O);
+    } else {
+      nb[4] = __builtin_amdgcn_bitop3_b32(pw.Zmp, fun(pw.azpw, pz.zsw), fun(pw.azp, pz.zs), 0xCA);
+      nb[5] = __builtin_amdgcn_bitop3_b32(pw.Zmm, fun(pw.azmw, pz.zsmw), fun(pw.azm, pz.zsm), 0xCA);
+    }
   }
 }
 
 // Count planes of word `pw` of colour C: unsatisfied bonds (spin bits differ,
 // xor the bond's sign bit).
-template <uint32_t C, bool PM>
-__device__ __forceinline__ uint32_t packed_word_counts(const unsigned char* lds, const PackedWord& pw,
+template <int D, uint32_t C, bool PM>
+__device__ __forceinline__ uint32_t packed_word_counts(const unsigned char* lds, const PackedWord<D>& pw,
                                                        uint32_t R, const PackedZ& pz, uint32_t& k0,
                                                        uint32_t& k1, uint32_t& k2) {
   const uint32_t o = *reinterpret_cast<const uint32_t*>(lds + pw.a0 + 4u * C);
   uint32_t nb[6];
-  packed_neighbours<C>(lds, pw, R, pz, nb);
+  packed_neighbours<D, C>(lds, pw, R, pz, nb);
   uint32_t u[6];
 #pragma unroll
-  for (int m = 0; m < 6; ++m) {
+  for (int m = 0; m < 2 * D; ++m) {
     const uint32_t js = PM ? *reinterpret_cast<const uint32_t*>(lds + pw.aj + 4u * (2u * m + C)) : 0u;
     u[m] = o ^ nb[m] ^ js;
   }
-  count_planes<3>(u, k0, k1, k2);
+  count_planes<D>(u, k0, k1, k2);
   return o;
 }
 
-template <bool PM, bool MEASURE>
-__device__ void batch_packed_lattice(unsigned char* lds, const BatchDesc* dp, uint32_t li,
+// WPL words a lane; WAVE: the lattice is the wave's, `lds` its part.
+template <int D, bool PM, bool MEASURE, int WPL, bool WAVE>
+__device__ __forceinline__ void batch_packed_lattice(unsigned char* lds, const BatchDesc* dp, uint32_t li,
                                      const RngKey& key0, int8_t* gs, const int8_t* gJ,
                                      uint32_t L, uint32_t R, uint32_t Nh, uint32_t replica,
                                      const TabRegs& tab, uint32_t t0, uint32_t n_sweeps,
                                      uint32_t every, uint32_t n_lattices, ObsOut* obs) {
-  constexpr int D = 3;
-  const uint32_t T = blockDim.x, q = threadIdx.x;
-  const uint32_t Wp = Nh / 32u;
-  const uint32_t LR = L * R;  // sites of a z-plane of one colour (a multiple of 32)
-  const uint32_t SB = 0, JB = (kPkSpin * (Wp + 2u) + 15u) / 16u * 16u;
+  const uint32_t T = WAVE ? 64u : blockDim.x, q = WAVE ? __lane_id() : threadIdx.x;
+  const uint32_t Wp = (Nh + 31u) / 32u, tail = 32u * Wp - Nh;
+  const uint32_t LR = L * R;  // sites of a z-plane of one colour
+  constexpr uint32_t SB = 0;
+  const uint32_t JB = (kPkSpin * (Wp + 2u) + 15u) / 16u * 16u;
   const RngKey key{key0.k0, key0.k1, replica};
-
-  // stage the spins: sign bits of 32 int8 sites per word, zero pad words
-  for (uint32_t i = q; i < 2u * Wp; i += T) {
-    const uint32_t c = i & 1u, w = i >> 1;
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(gs + (size_t)c * Nh + 32u * w);
-    uint32_t v = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v |= gather7(src[k]) << (4 * k);
-    *reinterpret_cast<uint32_t*>(lds + SB + kPkSpin * (w + 1u) + 4u * c) = v;
-  }
+  auto sync = [&]() {
+    if constexpr (WAVE) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+      __syncthreads();
+    }
+  };
+  auto word_sites = [&](uint32_t w) -> uint32_t { return w + 1u == Wp ? 32u - tail : 32u; };
+  // sign bits of a pair of int8 planes into the spin pairs
+  auto stage = [&](const int8_t* planes) {
+    for (uint32_t i = q; i < 2u * Wp; i += T) {
+      const uint32_t c = i & 1u, w = i >> 1;
+      *reinterpret_cast<uint32_t*>(lds + SB + kPkSpin * (w + 1u) + 4u * c) =
+          load_signs(planes + (size_t)c * Nh + 32u * w, word_sites(w));
+    }
+  };
   if (q < 2u) {
     *reinterpret_cast<uint32_t*>(lds + SB + 4u * q) = 0u;
     *reinterpret_cast<uint32_t*>(lds + SB + kPkSpin * (Wp + 1u) + 4u * q) = 0u;
-  }
-  // in-plane index of the -mu neighbour of site (c, j)
-  const uint32_t sYw = (L - 1) * R, sZ = L * R, sZw = (L - 1) * L * R;
-  auto minus_nb = [&](uint32_t c, uint32_t j, int mu) -> uint32_t {
-    const uint32_t r = j / R, rowb = r * R, jx = j - rowb;
-    const uint32_t z = r / L, y = r - z * L;
-    const uint32_t p = (c + y + z) & 1u;
-    if (mu == 0) return jx + p == 0 ? rowb + R - 1 : j + p - 1;
-    if (mu == 1) return y == 0 ? j + sYw : j - R;
-    return z == 0 ? j + sZw : j - sZ;
-  };
-  if (PM) {
-    for (uint32_t i = q; i < 2u * Wp; i += T) {
-      const uint32_t c = i & 1u, w = i >> 1;
-#pragma unroll
-      for (int mu = 0; mu < 3; ++mu) {
-        // +mu bond of the site itself: J[mu][c][j]
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(gJ + (size_t)(2 * mu + c) * Nh + 32u * w);
-        uint32_t vp = 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) vp |= gather7(src[k]) << (4 * k);
-        // -mu bond: the +mu bond of the -mu neighbour, J[mu][1 - c][nb]
-        const int8_t* Jn = gJ + (size_t)(2 * mu + 1 - c) * Nh;
-        uint32_t vm = 0;
-#pragma unroll 1  // set-up only: unrolled, it raised the kernel's registers into spills
-        for (uint32_t b = 0; b < 32u; ++b)
-          vm |= (Jn[minus_nb(c, 32u * w + b, mu)] < 0 ? 1u : 0u) << b;
-        *reinterpret_cast<uint32_t*>(lds + JB + kPkBond * w + 4u * (2u * (2u * mu) + c)) = vp;
-        *reinterpret_cast<uint32_t*>(lds + JB + kPkBond * w + 4u * (2u * (2u * mu + 1u) + c)) = vm;
-      }
-    }
   }
   // funnel shifts of the wrap and z gathers
   PackedZ pz;
@@ -217,34 +207,43 @@ __device__ void batch_packed_lattice(unsigned char* lds, const BatchDesc* dp, ui
   pz.zsm = (0u - LR) & 31u;
   pz.zsmw = (LR * (L - 1u)) & 31u;
   // the lane's words: row masks, wrap and z sources
-  PackedWord pw[kPackedBatchWordsPerLane];
+  PackedWord<D> pw[WPL];
 #pragma unroll
-  for (uint32_t p = 0; p < kPackedBatchWordsPerLane; ++p) {
+  for (uint32_t p = 0; p < (uint32_t)WPL; ++p) {
     const uint32_t w = q + p * T;
-    PackedWord& x = pw[p];
-    x.valid = w < Wp;
-    const uint32_t wv = x.valid ? w : 0u;
+    PackedWord<D>& x = pw[p];
+    const bool valid = w < Wp;
+    const uint32_t wv = valid ? w : 0u, nv = word_sites(wv);
+    x.ok = valid ? ~0u >> (32u - nv) : 0u;
     x.E = x.S = x.Pm0 = x.Ymp = x.Ymm = x.Zmp = x.Zmm = 0;
-#pragma unroll 1  // as above
-    for (uint32_t b = 0; b < 32u; ++b) {
-      const uint32_t j = 32u * wv + b;
-      const uint32_t r = j / R, jx = j - r * R;
-      const uint32_t z = r / L, y = r - z * L;
-      x.E |= (jx == R - 1 ? 1u : 0u) << b;
-      x.S |= (jx == 0 ? 1u : 0u) << b;
-      x.Pm0 |= ((y + z) & 1u) << b;
-      x.Ymp |= (y == L - 1 ? 1u : 0u) << b;
-      x.Ymm |= (y == 0 ? 1u : 0u) << b;
-      x.Zmp |= (z == L - 1 ? 1u : 0u) << b;
-      x.Zmm |= (z == 0 ? 1u : 0u) << b;
+    const uint32_t j0 = 32u * wv;
+    uint32_t r = j0 / R, jx = j0 - r * R;
+    uint32_t z = D == 3 ? r / L : 0u, y = r - z * L;
+#pragma unroll 1
+    for (uint32_t b = 0; b < nv;) {  // the word's pieces of rows
+      const uint32_t len = min(R - jx, 32u - b);
+      const uint32_t seg = (len == 32u ? ~0u : (1u << len) - 1u) << b;
+      if (jx + len == R) x.E |= 1u << (b + len - 1u);
+      if (jx == 0u) x.S |= 1u << b;
+      if ((y + z) & 1u) x.Pm0 |= seg;
+      if (y + 1u == L) x.Ymp |= seg;
+      if (y == 0u) x.Ymm |= seg;
+      if (z + 1u == L) x.Zmp |= seg;
+      if (z == 0u) x.Zmm |= seg;
+      b += len;
+      jx = 0u;
+      ++y;
+      if (D == 3 && y == L) {
+        y = 0u;
+        ++z;
+      }
     }
-    // Wrap and z sources: bit i of a gather at site offset off is site
-    // 32 w + i + off, from the funnel of words w + floor(off / 32) and the
-    // next; that low word is clamped to the pads (-1 .. Wp - 1) where the
-    // word has no site that uses the gather.  y wraps: rows y = L - 1 take
-    // off = R - LR, rows y = 0 off = LR - R; z (when z-planes split words):
-    // +-LR, and the wrapped LR (1 - L) / LR (L - 1) for the last / first
-    // z-plane.
+    // Sources: bit i of a gather at site offset off is site 32 w + i + off,
+    // from the funnel of words w + floor(off / 32) and the next; that low word
+    // is clamped to the pads (-1 .. Wp - 1) where the word has no site that
+    // uses the gather.  y wraps: rows y = L - 1 take off = R - LR, rows y = 0
+    // off = LR - R; z (when z-planes split words): +-LR, and the wrapped
+    // LR (1 - L) / LR (L - 1) for the last / first z-plane.
     auto lo = [&](int32_t off) -> uint32_t {  // LDS byte address of the clamped low word
       const int32_t i = (int32_t)wv + (off >> 5);
       return SB + kPkSpin * (uint32_t)((i < -1 ? -1 : (i > (int32_t)Wp - 1 ? (int32_t)Wp - 1 : i)) + 1);
@@ -252,7 +251,12 @@ __device__ void batch_packed_lattice(unsigned char* lds, const BatchDesc* dp, ui
     const int32_t lr = (int32_t)LR, l = (int32_t)L, rr = (int32_t)R;
     x.ayp = lo(rr - lr);
     x.aym = lo(lr - rr);
-    if (pz.zs == 0u) {  // z-planes hold whole words: the z neighbours are words
+    if constexpr (D == 2) {
+      x.azp = lo(rr);
+      x.azm = lo(-rr);
+      x.azpw = lo(1 - rr);
+      x.azmw = lo(rr - 1);
+    } else if (pz.zs == 0u) {  // z-planes hold whole words: the z neighbours are words
       const uint32_t zw = LR / 32u;  // words per z-plane
       const uint32_t izp = wv + zw >= Wp ? wv + zw - Wp : wv + zw;
       const uint32_t izm = wv < zw ? wv + Wp - zw : wv - zw;
@@ -266,15 +270,38 @@ __device__ void batch_packed_lattice(unsigned char* lds, const BatchDesc* dp, ui
       x.azmw = lo(lr * (l - 1));
     }
     x.a0 = SB + kPkSpin * (wv + 1u);
-    x.aj = JB + kPkBond * wv;
+    x.aj = JB + pk_bond(D) * wv;
   }
+  if (PM) {
+    // J[mu] in the spin pairs: a word's +mu bonds are its own words, its -mu
+    // bonds those of its -mu neighbours
+#pragma unroll
+    for (int mu = 0; mu < D; ++mu) {
+      stage(gJ + (size_t)(2 * mu) * Nh);
+      sync();
+#pragma unroll
+      for (uint32_t p = 0; p < (uint32_t)WPL; ++p) {
+        if (!pw[p].ok) continue;
+        uint32_t n0[6], n1[6];
+        packed_neighbours<D, 0>(lds, pw[p], R, pz, n0);
+        packed_neighbours<D, 1>(lds, pw[p], R, pz, n1);
+        uint32_t* j = reinterpret_cast<uint32_t*>(lds + pw[p].aj) + 4 * mu;  // (2 (2 mu + s) + c)
+        j[0] = *reinterpret_cast<const uint32_t*>(lds + pw[p].a0);
+        j[1] = *reinterpret_cast<const uint32_t*>(lds + pw[p].a0 + 4u);
+        j[2] = n0[2 * mu + 1];
+        j[3] = n1[2 * mu + 1];
+      }
+      sync();
+    }
+  }
+  stage(gs);
   // thresholds of this lattice: the fast decision when only classes k < d can
   // refuse (every class k >= d always accepts)
   bool fast = true;
 #pragma unroll
   for (int k = D; k <= 2 * D; ++k) fast = fast && table_byte(tab.al_lo, tab.al_hi, k) == 0xFFu;
   FastTab ft = fast_tab<D>(tab);
-  __syncthreads();
+  sync();
 
   // a word's exact ties wait in registers (tie mask and count planes) until
   // the lane's words of the colour are stored, then take their refinement
@@ -292,48 +319,60 @@ __device__ void batch_packed_lattice(unsigned char* lds, const BatchDesc* dp, ui
   };
   auto half = [&](auto cc, uint32_t t) {
     constexpr uint32_t C = decltype(cc)::value;
-    uint4 tie[kPackedBatchWordsPerLane];
+    uint4 tie[WPL];
 #pragma unroll
-    for (uint32_t p = 0; p < kPackedBatchWordsPerLane; ++p) {
+    for (uint32_t p = 0; p < (uint32_t)WPL; ++p) {
       tie[p] = make_uint4(0u, 0u, 0u, 0u);
-      if (!pw[p].valid) continue;
+      if (!pw[p].ok) continue;
       uint32_t k0, k1, k2;
-      const uint32_t o = packed_word_counts<C, PM>(lds, pw[p], R, pz, k0, k1, k2);
+      const uint32_t o = packed_word_counts<D, C, PM>(lds, pw[p], R, pz, k0, k1, k2);
       const uint32_t w = q + p * T;
       uint32_t ties;
       const uint32_t flip = fast ? packed_decide_fast<D>(ft, key, t, C, w, k0, k1, k2, ties)
                                  : packed_decide<D>(tab, key, t, C, w, k0, k1, k2, ties);
       *reinterpret_cast<uint32_t*>(lds + pw[p].a0 + 4u * C) = o ^ flip;
-      tie[p] = make_uint4(ties, k0, k1, k2);
+      tie[p] = make_uint4(ties & pw[p].ok, k0, k1, k2);
     }
 #pragma unroll
-    for (uint32_t p = 0; p < kPackedBatchWordsPerLane; ++p)
+    for (uint32_t p = 0; p < (uint32_t)WPL; ++p)
       if (tie[p].x) resolve(C, t, q + p * T, pw[p].a0, tie[p]);
-    __syncthreads();
+    sync();
   };
   auto measure = [&](uint32_t slot, int64_t sweep) {
     int64_t Esum = 0, Msum = 0;
 #pragma unroll
-    for (uint32_t p = 0; p < kPackedBatchWordsPerLane; ++p) {
-      if (!pw[p].valid) continue;
+    for (uint32_t p = 0; p < (uint32_t)WPL; ++p) {
+      const uint32_t ok = pw[p].ok;
+      if (!ok) continue;
       uint32_t k0, k1, k2;
-      const uint32_t o1 = packed_word_counts<1, PM>(lds, pw[p], R, pz, k0, k1, k2);
+      const uint32_t o1 = packed_word_counts<D, 1, PM>(lds, pw[p], R, pz, k0, k1, k2);
       const uint32_t o0 = *reinterpret_cast<const uint32_t*>(lds + pw[p].a0);
-      const int32_t ks = __builtin_popcount(k0) + 2 * __builtin_popcount(k1) + 4 * __builtin_popcount(k2);
-      Esum += 2 * (int64_t)ks - 32 * 2 * D;
-      Msum += 64 - 2 * (int64_t)(__builtin_popcount(o1) + __builtin_popcount(o0));
+      const int32_t ks = __builtin_popcount(k0 & ok) + 2 * __builtin_popcount(k1 & ok) +
+                         4 * __builtin_popcount(k2 & ok);
+      const int32_t nv = __builtin_popcount(ok);
+      Esum += 2 * (int64_t)ks - nv * 2 * D;
+      Msum += 2 * nv - 2 * (int64_t)(__builtin_popcount(o1 & ok) + __builtin_popcount(o0 & ok));
     }
     __shared__ Partial part[1];
-    block_partial_int(Esum, Msum, part, 0);
+    if constexpr (WAVE) {
+      Esum = wave_sum(Esum);
+      Msum = wave_sum(Msum);
+    } else {
+      block_partial_int(Esum, Msum, part, 0);
+    }
     if (q == 0) {
+      if constexpr (!WAVE) {
+        Esum = part[0].Ei;
+        Msum = part[0].Mi;
+      }
       ObsOut o;
-      o.E_int = part[0].Ei;
-      o.M_int = part[0].Mi;
-      o.E = (double)part[0].Ei * dp->J0;
-      o.M[0] = (double)part[0].Mi;
+      o.E_int = Esum;
+      o.M_int = Msum;
+      o.E = (double)Esum * dp->J0;
+      o.M[0] = (double)Msum;
       o.M[1] = 0.0;
       o.M[2] = 0.0;
-      o.absM = fabs((double)part[0].Mi);
+      o.absM = fabs((double)Msum);
       o.sweep = sweep;
       obs[(uint64_t)slot * n_lattices + li] = o;
     }
@@ -345,17 +384,15 @@ __device__ void batch_packed_lattice(unsigned char* lds, const BatchDesc* dp, ui
     if (MEASURE && (sw + 1) % every == 0) measure((sw + 1) / every - 1, (int64_t)t + 1);
   }
   if (MEASURE && n_sweeps == 0) measure(0, (int64_t)t0);
-  __syncthreads();
-  // write both planes back as +-1 bytes
-  for (uint32_t i = q; i < 2u * Wp; i += T) {
-    const uint32_t c = i & 1u, w = i >> 1;
-    const uint32_t v = *reinterpret_cast<const uint32_t*>(lds + SB + kPkSpin * (w + 1u) + 4u * c);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(gs + (size_t)c * Nh + 32u * w);
+  // the lane's words of both planes back as +-1 bytes
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const uint32_t spread = (((v >> (4 * k)) & 0xFu) * 0x00204081u) & kOnes;
-      dst[k] = kOnes | (spread * 0xFEu);
-    }
+  for (uint32_t p = 0; p < (uint32_t)WPL; ++p) {
+    if (!pw[p].ok) continue;
+    const uint32_t w = q + p * T;
+#pragma unroll 1
+    for (uint32_t c = 0; c < 2u; ++c)
+      store_signs(gs + (size_t)c * Nh + 32u * w,
+                  *reinterpret_cast<const uint32_t*>(lds + pw[p].a0 + 4u * c), word_sites(w));
   }
 }
 
@@ -367,10 +404,16 @@ __global__ __launch_bounds__(1024) void batch_kernel(const BatchDesc* __restrict
                                                     const int8_t* __restrict__ J,
                                                     const uint32_t t0, const uint32_t n_sweeps,
                                                     const uint32_t every, const uint32_t n_lattices,
+                                                    const uint32_t n_single,
                                                     ObsOut* __restrict__ obs) {
   extern __shared__ uint32_t lat_words[];  // [2][Nh] spins of this lattice
   int8_t* const lat = reinterpret_cast<int8_t*>(lat_words);
-  const uint32_t li = __builtin_amdgcn_readfirstlane(order[blockIdx.x]);
+  // workgroups from n_single on: a lattice a wave
+  const bool by_wave = blockIdx.x >= n_single;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t at = by_wave ? n_single + (blockIdx.x - n_single) * (blockDim.x >> 6) + wave : blockIdx.x;
+  if (at >= n_lattices) return;  // a wave beyond the last lattice: the others wait for none
+  const uint32_t li = __builtin_amdgcn_readfirstlane(order[at]);
   const BatchDesc* dp = descs + li;
   const uint32_t L = __builtin_amdgcn_readfirstlane(dp->L);
   const uint32_t R = __builtin_amdgcn_readfirstlane(dp->R);
@@ -394,25 +437,29 @@ __global__ __launch_bounds__(1024) void batch_kernel(const BatchDesc* __restrict
   int8_t* gs = spins + soff;
   const int8_t* gJ = J + joff;
   const uint32_t N = 2 * Nh;  // L^d, a multiple of 4 (L even)
-  if constexpr (D == 3) {
-    if (__builtin_amdgcn_readfirstlane(dp->packed) && batch_packed_ok(D, L, blockDim.x)) {
-      TabRegs tab;
-      tab.th_lo = th_lo;
-      tab.th_hi = th_hi;
-      tab.al_lo = al_lo;
-      tab.al_hi = al_hi;
-      tab.fr.f0 = __builtin_amdgcn_readfirstlane(dp->frac[0]);
-      tab.fr.f1 = __builtin_amdgcn_readfirstlane(dp->frac[1]);
-      tab.fr.f2 = __builtin_amdgcn_readfirstlane(dp->frac[2]);
-      tab.fr.f3 = __builtin_amdgcn_readfirstlane(dp->frac[3]);
-      tab.fr.f4 = __builtin_amdgcn_readfirstlane(dp->frac[4]);
-      tab.fr.f5 = __builtin_amdgcn_readfirstlane(dp->frac[5]);
-      tab.fr.f6 = __builtin_amdgcn_readfirstlane(dp->frac[6]);
-      batch_packed_lattice<PM, MEASURE>(reinterpret_cast<unsigned char*>(lat_words), dp, li, key, gs,
-                                        gJ, L, R, Nh, replica, tab, t0, n_sweeps, every,
-                                        n_lattices, obs);
-      return;
-    }
+  if (__builtin_amdgcn_readfirstlane(dp->packed) && batch_packed_ok(D, L, blockDim.x)) {
+    TabRegs tab;
+    tab.th_lo = th_lo;
+    tab.th_hi = th_hi;
+    tab.al_lo = al_lo;
+    tab.al_hi = al_hi;
+    tab.fr.f0 = __builtin_amdgcn_readfirstlane(dp->frac[0]);
+    tab.fr.f1 = __builtin_amdgcn_readfirstlane(dp->frac[1]);
+    tab.fr.f2 = __builtin_amdgcn_readfirstlane(dp->frac[2]);
+    tab.fr.f3 = __builtin_amdgcn_readfirstlane(dp->frac[3]);
+    tab.fr.f4 = __builtin_amdgcn_readfirstlane(dp->frac[4]);
+    tab.fr.f5 = __builtin_amdgcn_readfirstlane(dp->frac[5]);
+    tab.fr.f6 = __builtin_amdgcn_readfirstlane(dp->frac[6]);
+    unsigned char* lds = reinterpret_cast<unsigned char*>(lat_words);
+    if (by_wave)
+      batch_packed_lattice<D, PM, MEASURE, 1, true>(lds + wave * batch_packed_lds_bytes(D, kWaveWords, PM), dp, li,
+                                                    key, gs, gJ, L, R, Nh, replica, tab, t0, n_sweeps, every,
+                                                    n_lattices, obs);
+    else
+      batch_packed_lattice<D, PM, MEASURE, kPackedBatchWordsPerLane, false>(lds, dp, li, key, gs, gJ, L, R, Nh,
+                                                                            replica, tab, t0, n_sweeps, every,
+                                                                            n_lattices, obs);
+    return;
   }
 
   // Stage both planes into LDS as one byte per site: bit 0 = spin -1, bit
@@ -853,8 +900,10 @@ size_t batch_lds_bytes(int d, bool pm, bool packed, const uint32_t* L, uint32_t 
   size_t bytes = 0;
   for (uint32_t r = 0; r < n; ++r) {
     size_t need;
-    if (packed && batch_packed_ok(d, L[r], threads)) {
-      need = batch_packed_lds_bytes(L[r], pm, threads);
+    if (packed && batch_lattice_wave(d, L[r])) {
+      need = (size_t)(threads / 64) * batch_packed_lds_bytes(d, kWaveWords, pm);
+    } else if (packed && batch_packed_ok(d, L[r], threads)) {
+      need = batch_packed_lds_bytes(d, batch_words(d, L[r]), pm);
     } else {
       size_t N = 1;
       for (int k = 0; k < d; ++k) N *= L[r];
@@ -865,13 +914,18 @@ size_t batch_lds_bytes(int d, bool pm, bool packed, const uint32_t* L, uint32_t 
   return bytes;
 }
 
+uint32_t batch_groups(uint32_t n_lattices, uint32_t n_single, uint32_t threads) {
+  const uint32_t per = threads / 64u;
+  return n_single + (n_lattices - n_single + per - 1u) / per;
+}
+
 hipError_t launch_batch(const BatchLaunch& a, int8_t* spins, const int8_t* J, uint32_t t0,
                         uint32_t n_sweeps, uint32_t every, void* dev_obs, hipStream_t st) {
-  const dim3 grid(a.n_lattices), block(a.threads);
+  const dim3 grid(batch_groups(a.n_lattices, a.n_single, a.threads)), block(a.threads);
   const size_t lds = a.lds_bytes;
 #define SMC_BK(DD, PMM, MM)                                                                      \
   hipLaunchKernelGGL((batch_kernel<DD, PMM, MM>), grid, block, lds, st, a.descs, a.order, a.key, \
-                     spins, J, t0, n_sweeps, every, a.n_lattices, (ObsOut*)dev_obs)
+                     spins, J, t0, n_sweeps, every, a.n_lattices, a.n_single, (ObsOut*)dev_obs)
   const bool m = dev_obs != nullptr;
   if (a.d == 2) {
     if (a.pm) { if (m) SMC_BK(2, true, true); else SMC_BK(2, true, false); }

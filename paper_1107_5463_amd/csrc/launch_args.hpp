@@ -106,7 +106,8 @@ struct BatchLaunch {
   int d;
   bool pm;                 // +-1 couplings (else uniform)
   uint32_t n_lattices;
-  uint32_t threads;        // workgroup size (one workgroup per lattice)
+  uint32_t n_single;       // the first of the order: a workgroup each; the others a wave each
+  uint32_t threads;        // workgroup size
   size_t max_sites;        // the largest L^d
   size_t lds_bytes;        // dynamic LDS of a workgroup (batch_lds_bytes)
   const BatchDesc* descs;  // device

@@ -17,6 +17,39 @@ __device__ __forceinline__ uint32_t gather7(uint32_t v) {
   return ((v & 0x80808080u) * 0x00204081u) >> 28;
 }
 
+// Signs of 32 int8 sites (the first nv of them exist) as a word.
+__device__ __forceinline__ uint32_t load_signs(const int8_t* p, uint32_t nv) {
+  uint32_t v = 0;
+  if (nv == 32u && ((uintptr_t)p & 15u) == 0u) {
+    const uint4 a = reinterpret_cast<const uint4*>(p)[0], b = reinterpret_cast<const uint4*>(p)[1];
+    const uint32_t x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v |= gather7(x[k]) << (4 * k);
+  } else if (((uintptr_t)p & 3u) == 0u && (nv & 3u) == 0u) {
+#pragma unroll 1
+    for (uint32_t k = 0; 4 * k < nv; ++k)
+      v |= gather7(reinterpret_cast<const uint32_t*>(p)[k]) << (4 * k);
+  } else {
+#pragma unroll 1
+    for (uint32_t k = 0; k < nv; ++k) v |= (p[k] < 0 ? 1u : 0u) << k;
+  }
+  return v;
+}
+
+__device__ __forceinline__ void store_signs(int8_t* p, uint32_t v, uint32_t nv) {
+  auto four = [&](uint32_t k) -> uint32_t {  // sites 4k .. 4k + 3 as +-1 bytes
+    return kOnes | ((((((v >> (4 * k)) & 0xFu) * 0x00204081u) & kOnes)) * 0xFEu);
+  };
+  if (nv == 32u && ((uintptr_t)p & 15u) == 0u) {
+    reinterpret_cast<uint4*>(p)[0] = make_uint4(four(0), four(1), four(2), four(3));
+    reinterpret_cast<uint4*>(p)[1] = make_uint4(four(4), four(5), four(6), four(7));
+  } else if (((uintptr_t)p & 3u) == 0u && (nv & 3u) == 0u) {
+    for (uint32_t k = 0; 4 * k < nv; ++k) reinterpret_cast<uint32_t*>(p)[k] = four(k);
+  } else {
+    for (uint32_t k = 0; k < nv; ++k) p[k] = (v >> k) & 1u ? (int8_t)-1 : (int8_t)1;
+  }
+}
+
 // Bit-sliced equality of the 3-bit count (k2 k1 k0) with a constant K.
 template <int K>
 __device__ __forceinline__ uint32_t class_mask(uint32_t k0, uint32_t k1, uint32_t k2) {

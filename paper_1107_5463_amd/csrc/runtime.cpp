@@ -1421,7 +1421,8 @@ struct smc_batch {
   bool packed;               // lattices may take the packed path (SMC_BATCH_PACKED=0 disables)
   std::vector<int64_t> soff, joff;
   std::vector<BatchDesc> desc;
-  std::vector<uint32_t> orders;  // [largest first | as given]
+  std::vector<uint32_t> orders;  // [largest first | as given], one-wave lattices last in either
+  uint32_t n_wave;               // how many of those
   void* spins;
   void* J;
   hipStream_t stream;
@@ -1440,7 +1441,7 @@ struct smc_batch {
   uint32_t graph_every;
   void* graph_obs;
   uint32_t graph_threads;
-  bool graph_largest;
+  bool graph_largest, graph_packed;
 };
 
 namespace {
@@ -1486,12 +1487,16 @@ size_t batch_ws_parts(int32_t d, int32_t n, const int32_t* L, size_t* desc_b, si
   return *desc_b + *order_b + *scratch_b;
 }
 
+// Lattices with a workgroup each (on the byte path every one has).
+uint32_t batch_single(const smc_batch* b) { return (uint32_t)b->n - (b->packed ? b->n_wave : 0u); }
+
 int batch_launch(smc_batch* b, int8_t* spins, uint32_t t0, uint32_t n_sweeps, uint32_t every,
                  void* dev_obs, uint32_t threads, bool largest_first) {
   BatchLaunch a;
   a.d = b->d;
   a.pm = b->J_kind == SMC_J_PM;
   a.n_lattices = (uint32_t)b->n;
+  a.n_single = batch_single(b);
   a.threads = threads;
   a.max_sites = b->max_sites;
   a.lds_bytes = batch_lds_bytes(b->d, b->J_kind == SMC_J_PM, b->packed, b->Lu.data(), (uint32_t)b->n,
@@ -1522,11 +1527,12 @@ int batch_graph_sweep(smc_batch* b, uint32_t n_sweeps, uint32_t every, void* dev
   uint32_t t0 = (uint32_t)b->t;
   void* obs = dev_obs;
   uint32_t nl = (uint32_t)b->n;
-  void* args[] = {&descs, &order, &key, &spins, &J, &t0, &n_sweeps, &every, &nl, &obs};
+  uint32_t ns = batch_single(b);
+  void* args[] = {&descs, &order, &key, &spins, &J, &t0, &n_sweeps, &every, &nl, &ns, &obs};
   hipKernelNodeParams kp;
   std::memset(&kp, 0, sizeof(kp));
   kp.func = const_cast<void*>(batch_kernel_fn(b->d, b->J_kind == SMC_J_PM, dev_obs != nullptr));
-  kp.gridDim = dim3((unsigned)b->n);
+  kp.gridDim = dim3(batch_groups(nl, ns, b->threads));
   kp.blockDim = dim3(b->threads);
   kp.sharedMemBytes =
       (unsigned)batch_lds_bytes(b->d, b->J_kind == SMC_J_PM, b->packed, b->Lu.data(), (uint32_t)b->n,
@@ -1535,7 +1541,8 @@ int batch_graph_sweep(smc_batch* b, uint32_t n_sweeps, uint32_t every, void* dev
   kp.extra = nullptr;
   const bool same = b->exec && b->graph_n == (int64_t)n_sweeps && b->graph_obs == dev_obs &&
                     b->graph_every == every &&
-                    b->graph_threads == b->threads && b->graph_largest == b->largest_first;
+                    b->graph_threads == b->threads && b->graph_largest == b->largest_first &&
+                    b->graph_packed == b->packed;
   if (!same) {
     batch_drop_graph(b);
     int rc = check(hipGraphCreate(&b->graph, 0), "graph create");
@@ -1549,6 +1556,7 @@ int batch_graph_sweep(smc_batch* b, uint32_t n_sweeps, uint32_t every, void* dev
     b->graph_obs = dev_obs;
     b->graph_threads = b->threads;
     b->graph_largest = b->largest_first;
+    b->graph_packed = b->packed;
   } else {
     const int rc = check(hipGraphExecKernelNodeSetParams(b->exec, b->node, &kp), "graph node update");
     if (rc != SMC_OK) return rc;
@@ -1690,6 +1698,10 @@ int smc_batch_init(smc_batch** out, int32_t d, int32_t J_kind, uint64_t seed, do
   std::vector<uint32_t> largest = idx;
   std::stable_sort(largest.begin(), largest.end(),
                    [&](uint32_t a, uint32_t c) { return b->desc[a].Nh > b->desc[c].Nh; });
+  auto single = [&](uint32_t r) { return !batch_lattice_wave(d, b->desc[r].L); };
+  std::stable_partition(largest.begin(), largest.end(), single);
+  b->n_wave = (uint32_t)(n - std::count_if(idx.begin(), idx.end(), single));
+  std::stable_partition(idx.begin(), idx.end(), single);
   b->orders = largest;
   b->orders.insert(b->orders.end(), idx.begin(), idx.end());
   // the largest workgroup (1024 lanes) with the largest lattice may pass the
