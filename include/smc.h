@@ -234,8 +234,9 @@ int smc_set_samples(smc_lattice* h, int64_t samples);
 int smc_autotune(smc_lattice* h, double beta, void* scratch, size_t scratch_bytes,
                  uint32_t* rows_out);
 
-/* Name of the kernel the handle's half-sweeps launch (a call of several plain
- * Ising sweeps may run many half-sweeps in one launch instead, with the same
+/* Name of the kernel the handle's half-sweeps launch (a call of sweeps may take
+ * another where that is faster -- many half-sweeps of a plain Ising lattice in
+ * one launch, the one-site kernel for a small continuous one -- with the same
  * result) -- Ising: "ising_packed"
  * (one bit per site), "ising_fused", "ising_stream", "ising_chunk",
  * "ising_site", and for the tiled schedule "ising_tiles" (int8 tiles) or

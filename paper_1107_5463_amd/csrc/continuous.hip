@@ -595,6 +595,28 @@ static hipError_t launch_cont_stream(const ContLaunch& a, float* s, uint32_t t, 
 
 uint32_t cont_default_sites_per_lane(int n) { return n == 2 ? 4u : 2u; }
 
+// The streaming kernel below about a million sites a colour leaves a SIMD few
+// waves, each waiting on the loads that fill its ring: fewer sites a lane are
+// more waves.  us a half-sweep: XY, 4 / 2 a lane: 2D L = 1000 5.8 / 5.0, 3D
+// L = 64 5.7 / 4.6, L = 96 6.4 / 5.1, but 2D L = 2048 7.9 / 8.5, 3D L = 128
+// 6.7 / 7.0; Heisenberg, 2 / 1 a lane at the best height: 3D L = 64 6.5 / 4.6,
+// L = 128 9.4 / 8.3, L = 192 27.5 / 24.5, L = 256 52.9 / 50.3.  XY rows of an
+// odd number of pairs take 2 where 4 do not divide them (2D L = 1500, else one
+// site a lane: 11.9 / 7.4).
+uint32_t cont_sites_per_lane(const Geom& g, int n) {
+  if (n == 3) return 1u;
+  return g.Nh >= (1 << 20) && g.R % 4 == 0 ? 4u : 2u;
+}
+
+// Smaller lattices still are done in less than the time of a launch by the
+// one-site kernel, whose lanes wait on one round of loads: XY 2D L = 64 2.8
+// against 3.6 us (the launch), L = 512 3.1 / 4.2, L = 700 3.9 / 4.8, L = 1000
+// 5.4 / 5.0; 3D L = 32 3.7 / 4.3, L = 64 5.1 / 4.6; Heisenberg 3D L = 32 2.7 /
+// 4.1, L = 64 5.0 / 4.6.
+bool cont_prefers_row(const Geom& g, int n) {
+  return g.Nh < (n == 2 && g.d == 2 ? 350000 : 100000);
+}
+
 bool cont_sites_per_lane_ok(int n, uint32_t V) {
   return n == 2 ? (V == 2 || V == 4) : (V == 1 || V == 2);
 }
@@ -609,6 +631,9 @@ bool cont_stream_supported(const Geom& g, uint32_t V, uint32_t H) {
 uint32_t cont_rows_per_band(const Geom& g, uint32_t V, uint32_t min_waves) {
   const uint32_t Q = (uint32_t)g.R / V;
   uint32_t best = 4;
+  // one site a lane (Heisenberg): taller bands lose more in waves than they
+  // save in halo rows (3D L = 256, H = 4 / 8 / 16 / 32: 50 / 57 / 68 / 76 us)
+  if (V == 1) return best;
   for (uint32_t H = 4; H <= 64; H *= 2) {
     if (g.L % H) break;
     const uint64_t waves = (uint64_t)Q * (uint64_t)(g.rows / H) / 64;

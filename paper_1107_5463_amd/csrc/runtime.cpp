@@ -83,6 +83,7 @@ struct smc_lattice {
   int cont_variant;          // ContVariant (SMC_CONT_KERNEL overrides the automatic choice)
   uint32_t cont_rows;        // continuous streaming band height (SMC_CONT_ROWS overrides)
   uint32_t cont_spl;         // continuous streaming sites per lane (SMC_CONT_SPL overrides)
+  bool cont_row_sweeps;      // sweeps launch the one-site kernel where they need no measurement
   FastDiv divQc;             // continuous streaming lanes per plane row
   bool multi_ok;             // multi-sweep calls may leave the half-sweep kernels (plan_sweeps)
   uint32_t forced_steps, forced_own;  // SMC_RESIDENT=steps,own[,drawn] (tests): that split always
@@ -359,7 +360,8 @@ ContLaunch cont_args(const smc_lattice* h, double beta) {
   return a;
 }
 
-int half_sweep_impl(smc_lattice* h, double beta, uint32_t t, uint32_t colour) {
+// `sweep`: part of a sweep, which may take the one-site continuous kernel.
+int half_sweep_impl(smc_lattice* h, double beta, uint32_t t, uint32_t colour, bool sweep = false) {
   if (is_packed(&h->p)) {
     IsingLaunch a = ising_args(h, beta);
     a.rows_per_band = h->packed_rows;
@@ -372,7 +374,8 @@ int half_sweep_impl(smc_lattice* h, double beta, uint32_t t, uint32_t colour) {
     return check(launch_ising_half_sweep(a, (int8_t*)h->spins, t, colour, h->stream),
                  "Ising half-sweep launch");
   }
-  const ContLaunch a = cont_args(h, beta);
+  ContLaunch a = cont_args(h, beta);
+  if (sweep && h->cont_row_sweeps) a.variant = kContRow;
   return check(launch_cont_half_sweep(a, (float*)h->spins, t, colour, h->stream),
                "continuous half-sweep launch");
 }
@@ -380,8 +383,9 @@ int half_sweep_impl(smc_lattice* h, double beta, uint32_t t, uint32_t colour) {
 // One in-place two-pass sweep with counter t; with dev_obs the observables of
 // the result are written there (fused into the colour-1 pass when the
 // streaming kernel runs, else by a separate measurement).
-int two_pass_sweep(smc_lattice* h, double beta, uint32_t t, void* dev_obs) {
-  int rc = half_sweep_impl(h, beta, t, 0u);
+// `half`: by the handle's half-sweep kernel in any case.
+int two_pass_sweep(smc_lattice* h, double beta, uint32_t t, void* dev_obs, bool half = false) {
+  int rc = half_sweep_impl(h, beta, t, 0u, !half);
   if (rc != SMC_OK) return rc;
   if (dev_obs && is_packed(&h->p)) {
     IsingLaunch a = ising_args(h, beta);
@@ -416,7 +420,7 @@ int two_pass_sweep(smc_lattice* h, double beta, uint32_t t, void* dev_obs) {
                    "measurement finish launch");
     }
   }
-  rc = half_sweep_impl(h, beta, t, 1u);
+  rc = half_sweep_impl(h, beta, t, 1u, !half);
   if (rc != SMC_OK) return rc;
   if (dev_obs)
     return check(measure_any(h, (int64_t)t + 1, dev_obs),
@@ -784,7 +788,7 @@ int sweeps_impl(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, bo
     const bool last = k + 1 == n_sweeps;
     const bool renorm = h->p.n > 1 && h->p.renorm_every > 0 &&
                         (h->t + 1) % (uint64_t)h->p.renorm_every == 0;
-    int rc = two_pass_sweep(h, beta, (uint32_t)h->t, (last && !renorm) ? dev_obs : nullptr);
+    int rc = two_pass_sweep(h, beta, (uint32_t)h->t, (last && !renorm) ? dev_obs : nullptr, half);
     if (rc != SMC_OK) return rc;
     h->t += 1;
     if (renorm) {
@@ -1105,12 +1109,20 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
     if (s == "row") h->cont_variant = kContRow;
     if (s == "stream") h->cont_variant = kContStream;
   }
-  h->cont_spl = p->n > 1 ? cont_default_sites_per_lane(p->n) : 1;
-  if (const char* v = std::getenv("SMC_CONT_SPL")) {
-    const long V = std::strtol(v, nullptr, 10);
-    if (p->n > 1 && V > 0 && cont_sites_per_lane_ok(p->n, (uint32_t)V)) h->cont_spl = (uint32_t)V;
+  h->cont_spl = 1;
+  h->cont_rows = 4;
+  h->cont_row_sweeps = false;
+  if (p->n > 1) {
+    const bool named = std::getenv("SMC_CONT_KERNEL") != nullptr;
+    h->cont_spl = named ? cont_default_sites_per_lane(p->n) : cont_sites_per_lane(h->g, p->n);
+    if (const char* v = std::getenv("SMC_CONT_SPL")) {
+      const long V = std::strtol(v, nullptr, 10);
+      if (V > 0 && cont_sites_per_lane_ok(p->n, (uint32_t)V)) h->cont_spl = (uint32_t)V;
+    }
+    h->cont_rows = cont_rows_per_band(h->g, h->cont_spl, 2048);
+    h->cont_row_sweeps = !named && !std::getenv("SMC_CONT_ROWS") && !std::getenv("SMC_CONT_SPL") &&
+                         cont_prefers_row(h->g, p->n);
   }
-  h->cont_rows = p->n > 1 ? cont_rows_per_band(h->g, h->cont_spl, 2048) : 4;
   if (const char* v = std::getenv("SMC_CONT_ROWS")) {
     const long H = std::strtol(v, nullptr, 10);
     if (H >= 4 && H <= 64 && H % 4 == 0 && H <= h->g.L && h->g.L % H == 0) h->cont_rows = (uint32_t)H;

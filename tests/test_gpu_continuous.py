@@ -299,3 +299,26 @@ def test_sweep_measure_matches_oracle(smc_gpu, oracle_mod, d, n, L, kind, kernel
         assert abs(o.E - r.E) <= 1e-12 * max(1.0, abs(r.E)) * L ** d, (k, o.E, r.E)
         assert np.allclose(o.M[:n], r.M[:n], rtol=0, atol=1e-9 * L ** d), (k, o.M, r.M)
         assert abs(o.absM - r.absM) <= 1e-9 * L ** d
+
+
+@pytest.mark.parametrize("d,n,L,kind", [(2, 2, 64, 0), (2, 2, 36, 1), (3, 2, 12, 2), (3, 3, 16, 0), (2, 3, 20, 2),
+                                        (3, 3, 10, 1), (2, 2, 1000, 0), (3, 3, 64, 0), (2, 2, 2048, 0)])
+def test_chosen_kernels_run_the_same_chain(smc_gpu, monkeypatch, d, n, L, kind):
+    """The kernels a call of sweeps picks by size (one-site or streaming,
+    sites per lane) against the one-site kernel throughout: the same bits."""
+    import torch
+    print(f"chosen kernels d={d} n={n} L={L} kind={kind}", flush=True)
+    kw = dict(J_kind=kind, J_sigma=0.3, delta=1.3, renorm_every=4)
+    _set_kernel(monkeypatch, "row")
+    ref = smc_gpu.Lattice(d, n, L, 17, **kw)
+    for v in ("SMC_CONT_KERNEL", "SMC_CONT_ROWS", "SMC_CONT_SPL"):
+        monkeypatch.delenv(v, raising=False)
+    lat = smc_gpu.Lattice(d, n, L, 17, **kw)
+    a = torch.zeros(8, dtype=torch.int64, device="cuda")
+    b = torch.zeros_like(a)
+    for k in (1, 2, 3):
+        lat.sweep_measure(0.8, k, a)
+        ref.sweep_measure(0.8, k, b)
+        assert torch.equal(lat.spins, ref.spins), k
+        x, y = a.view(torch.float64)[2:7], b.view(torch.float64)[2:7]
+        assert torch.allclose(x, y, rtol=1e-12, atol=1e-9 * L ** d), k
