@@ -29,7 +29,9 @@
  *          reduction partials, an observable slot, for the fused schedule the
  *          second spin buffer and, for plain sweeps of Ising spins with
  *          uniform or +-1 couplings, two copies at one bit per site (and the
- *          bonds' signs) that calls of several sweeps may work on.
+ *          bonds' signs) that calls of several sweeps may work on, or, for
+ *          continuous spins and FP32 couplings up to 2^21 sites, two copies
+ *          of the spins for such calls.
  * Random numbers.  Philox4x32-10 (Salmon et al., SC'11), key = seed, counter
  *   = (block, sweep t, replica, colour | purpose << 1); the same (seed,
  *   replica) gives the same chain whatever the launch geometry or schedule.
@@ -235,9 +237,9 @@ int smc_autotune(smc_lattice* h, double beta, void* scratch, size_t scratch_byte
                  uint32_t* rows_out);
 
 /* Name of the kernel the handle's half-sweeps launch (a call of sweeps may take
- * another where that is faster -- many half-sweeps of a plain Ising lattice in
- * one launch, the one-site kernel for a small continuous one -- with the same
- * result) -- Ising: "ising_packed"
+ * another where that is faster -- many half-sweeps of a small lattice in one
+ * launch, the one-site kernel for a continuous one -- with the same result) --
+ * Ising: "ising_packed"
  * (one bit per site), "ising_fused", "ising_stream", "ising_chunk",
  * "ising_site", and for the tiled schedule "ising_tiles" (int8 tiles) or
  * "ising_tiles_packed" (tiles at one bit per site in LDS, Metropolis or heat

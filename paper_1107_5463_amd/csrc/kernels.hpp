@@ -44,6 +44,10 @@ hipError_t launch_draws(const ResidentLaunch& a, bool heatbath, uint32_t steps, 
 hipError_t launch_bond_words(const Geom& g, bool bytes, const void* J, uint32_t* out,
                              hipStream_t st);
 
+// Sweeps of bricks of the lattice held in LDS (brick.hip).
+hipError_t launch_brick(const BrickLaunch& a, hipStream_t st);
+size_t brick_lds_bytes(int n, uint32_t positions);
+
 uint32_t cont_default_sites_per_lane(int n);
 // Sites per lane for a lattice, and whether its sweeps are faster by the
 // one-site kernel (rules with their figures in continuous.hip).

@@ -87,6 +87,30 @@ struct ContLaunch {
   double J0d;               // uniform coupling in FP64 (fused measurement)
 };
 
+// Several sweeps of one lattice of real-valued updates (FP32 couplings, or XY
+// and Heisenberg spins) with bricks of it in LDS (brick.hip).
+struct BrickLaunch {
+  Geom g;
+  int n;               // spin components
+  RngKey key;
+  int J_kind;
+  const void* J;
+  float J0, beta;
+  float param;         // XY max angle, Heisenberg 1 - cos(theta_max)
+  double J0d;
+  uint32_t V;          // positions of a row a lane holds
+  uint32_t nb[3];      // bricks along x, y, z; 1: the whole edge, no halo
+  uint32_t halo_x;     // halo in positions (pairs of sites) along x, a multiple of V
+  uint32_t steps;      // half-sweeps of the launch (whole sweeps): the halo in sites along y, z
+  uint32_t positions;  // the largest brick with its halo
+  uint32_t t0;         // sweep counter of the launch's first
+  const void* src;     // FP32 components, or int8 signs (n = 1)
+  void* dst;           // src itself with one brick only
+  void* parts;         // reduction partials of the final state (several bricks), or null
+  void* obs;           // its record (one brick), or null
+  int64_t sweep;
+};
+
 enum ContVariant { kContAuto = 0, kContRow = 1, kContStream = 2 };
 
 // One lattice of a batch (device table, written by the host runtime).

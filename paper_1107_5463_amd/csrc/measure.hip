@@ -208,25 +208,7 @@ __global__ __launch_bounds__(256) void finish_kernel(const Partial* __restrict__
     for (int w = 1; w < 4; ++w) add(sh[0], sh[w]);
   }
   if (threadIdx.x == 0) {
-    const Partial a = sh[0];
-    ObsOut o;
-    if (ising) {
-      o.E_int = int_couplings ? a.Ei : 0;
-      o.M_int = a.Mi;
-      o.E = int_couplings ? J0 * (double)a.Ei : a.E;
-      o.M[0] = (double)a.Mi;
-      o.M[1] = 0.0;
-      o.M[2] = 0.0;
-      o.absM = fabs((double)a.Mi);
-    } else {
-      o.E_int = 0;
-      o.M_int = 0;
-      o.E = a.E;
-      for (int k = 0; k < 3; ++k) o.M[k] = a.M[k];
-      o.absM = sqrt(a.M[0] * a.M[0] + a.M[1] * a.M[1] + a.M[2] * a.M[2]);
-    }
-    o.sweep = sweep;
-    *obs = o;
+    write_obs(sh[0], ising != 0, int_couplings != 0, J0, sweep, obs);
   }
 }
 

@@ -76,4 +76,51 @@ __device__ __forceinline__ void block_partial_int(int64_t E, int64_t M, Partial*
   }
 }
 
+// Any block of whole waves (up to 1024 threads): all fields of this block's
+// partial, in a fixed order; the sum is returned to thread 0.
+__device__ __forceinline__ Partial block_sum(Partial v) {
+  __shared__ Partial sh[16];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  v.Ei = wave_sum(v.Ei);
+  v.Mi = wave_sum(v.Mi);
+  v.E = wave_sum(v.E);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) v.M[k] = wave_sum(v.M[k]);
+  if (lane == 0) sh[wv] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int nw = (int)((blockDim.x + 63) >> 6);
+    for (int w = 1; w < nw; ++w) {
+      v.Ei += sh[w].Ei;
+      v.Mi += sh[w].Mi;
+      v.E += sh[w].E;
+      for (int k = 0; k < 3; ++k) v.M[k] += sh[w].M[k];
+    }
+  }
+  return v;
+}
+
+// The record of a state whose sums over the lattice are `a`.
+__device__ __forceinline__ void write_obs(const Partial& a, bool ising, bool int_couplings, double J0,
+                                          int64_t sweep, ObsOut* obs) {
+  ObsOut o;
+  if (ising) {
+    o.E_int = int_couplings ? a.Ei : 0;
+    o.M_int = a.Mi;
+    o.E = int_couplings ? J0 * (double)a.Ei : a.E;
+    o.M[0] = (double)a.Mi;
+    o.M[1] = 0.0;
+    o.M[2] = 0.0;
+    o.absM = fabs((double)a.Mi);
+  } else {
+    o.E_int = 0;
+    o.M_int = 0;
+    o.E = a.E;
+    for (int k = 0; k < 3; ++k) o.M[k] = a.M[k];
+    o.absM = sqrt(a.M[0] * a.M[0] + a.M[1] * a.M[1] + a.M[2] * a.M[2]);
+  }
+  o.sweep = sweep;
+  *obs = o;
+}
+
 }  // namespace smc

@@ -58,6 +58,13 @@ struct SweepPlan {
   double us;                                // estimated time of the call
 };
 
+// How a call's sweeps are cut into launches of bricks (brick.hip).
+struct BrickPlan {
+  uint32_t launches;   // 0: by half-sweeps
+  uint32_t nb[3], V;
+  double us;
+};
+
 struct smc_lattice {
   smc_params p;
   Geom g;
@@ -92,6 +99,11 @@ struct smc_lattice {
   int64_t plan_sweeps;       // the call the plan below is for (0: none yet)
   bool plan_measured;
   SweepPlan plan;
+  bool brick_ok;             // calls of real-valued sweeps may run in bricks
+  uint32_t forced_brick[5];  // SMC_BRICK=sweeps,nx,ny,nz,V (tests): that cut always
+  char* brick_work[2];       // two copies of the spins (several bricks)
+  int64_t brick_sweeps;      // the call the plan below is for (0: none yet)
+  BrickPlan brick;
   uint32_t* work_bonds;      // bond-sign words, or the packed couplings (+-1 couplings)
   uint32_t* work_masks;      // masks of a call's half-sweeps (drawn_steps of them)
   // workspace carve-up
@@ -195,9 +207,20 @@ size_t spin_bytes(const smc_params* p) {
   return (size_t)n_sites(p) * (p->n == 1 ? 1 : 4 * (size_t)p->n);
 }
 
+// Calls of real-valued sweeps that may run in bricks, and the most bricks (a
+// reduction partial each).
+constexpr uint32_t kBricks = 1024;
+
+bool brick_params(const smc_params* p) {
+  return (p->n > 1 || p->J_kind == SMC_J_FP32) && p->tile == 0 &&
+         n_sites(p) <= (p->n == 1 ? 1 << 21 : 7 << 18) &&
+         !(p->flags & (SMC_FLAG_GENERIC_KERNEL | SMC_FLAG_FAST_MATH | SMC_FLAG_SCHEDULE_FUSED));
+}
+
 size_t partial_bytes(const smc_params* p) {
-  const Geom g = make_geom(p);
-  return round_up((size_t)measure_partials(g) * kPartialBytes, kAlign);
+  int64_t n = measure_partials(make_geom(p));
+  if (brick_params(p)) n = std::max<int64_t>(n, kBricks);
+  return round_up((size_t)n * kPartialBytes, kAlign);
 }
 
 bool beta_ok(double beta) { return !std::isnan(beta) && beta >= 0.0; }
@@ -752,6 +775,194 @@ int packed_copy_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_
   return rc;
 }
 
+// ---------------------------------------------------------------------------
+// Calls of real-valued sweeps in bricks.
+// ---------------------------------------------------------------------------
+size_t brick_bytes(const smc_params* p) {
+  return brick_params(p) ? 2 * round_up(spin_bytes(p), kAlign) : 0;
+}
+
+// The launch of `sweeps` sweeps in nb bricks with V positions a lane; false if
+// it does not fit.
+bool brick_shape(const smc_lattice* h, uint32_t sweeps, const uint32_t nb[3], uint32_t V, BrickLaunch& a) {
+  const uint32_t L = (uint32_t)h->g.L, R = (uint32_t)h->g.R, K = 2 * sweeps;
+  if (R % V) return false;
+  a.V = V;
+  a.halo_x = (sweeps + V - 1) / V * V;
+  a.steps = K;
+  a.positions = 1;
+  const uint32_t edge[3] = {R, L, h->g.d == 3 ? L : 1u};
+  for (int k = 0; k < 3; ++k) {
+    const uint32_t unit = k == 0 ? V : 1u, halo = k == 0 ? a.halo_x : K;
+    a.nb[k] = nb[k];
+    uint32_t n = (edge[k] / unit + nb[k] - 1) / nb[k] * unit;
+    if (nb[k] > 1) n += 2 * halo;
+    if (nb[k] == 0 || n > edge[k] || nb[k] > edge[k] / unit) return false;
+    a.positions *= n;
+    if (a.positions > 1024 * V) return false;
+  }
+  if ((uint64_t)nb[0] * nb[1] * nb[2] > kBricks) return false;
+  return brick_lds_bytes(h->p.n, a.positions) <= 60 * 1024;
+}
+
+// Time of a launch of that shape in us, fitted to 590 of them (2D L = 32 to
+// 1000, 3D L = 16 to 64; 2.6 to 40 us, half within 8 %).  A step takes a
+// latency of the lane's V sites in turn and, for the waves of a SIMD whose
+// sites are still right (fewer as the halo is used up), their issue slots; the
+// start takes a term a wave and, in 3D where bricks have short rows, their
+// bytes in parts of cache lines.
+double brick_us(const smc_lattice* h, const BrickLaunch& a) {
+  static const double kFit[3][9] = {
+      // start, step, step V, wave step V, wave V, wave, MB, MB of lines, MB of lines V
+      {1.80, 0.25, 0.080, 0.000, 0.39, 0.21, 0.000, 0.0100, 0.0220},
+      {1.80, 0.22, 0.190, 0.031, 0.28, 0.26, 0.008, 0.1350, 0.0000},
+      {1.88, 0.17, 0.310, 0.069, 0.45, 0.30, 0.043, 0.0760, 0.0000}};
+  const double* f = kFit[h->p.n - 1];
+  const uint32_t edge[3] = {(uint32_t)h->g.R, (uint32_t)h->g.L, h->g.d == 3 ? (uint32_t)h->g.L : 1u};
+  const uint32_t groups = a.nb[0] * a.nb[1] * a.nb[2], per = (groups + kCUs - 1) / kCUs;
+  const double K = a.steps, V = a.V;
+  uint32_t own[3];
+  for (int k = 0; k < 3; ++k) {
+    const uint32_t unit = k == 0 ? a.V : 1u;
+    own[k] = (edge[k] / unit + a.nb[k] - 1) / a.nb[k] * unit;
+  }
+  auto waves = [&](uint32_t left) {  // of a SIMD, with that many steps left
+    double n = 1;
+    for (int k = 0; k < 3; ++k)
+      n *= own[k] + (a.nb[k] == 1 ? 0 : 2 * (k == 0 ? std::min(a.halo_x, (left + 1) / 2 + a.V - 1) : left));
+    return per * std::max(1.0, std::ceil(n / V / 64)) / 4;
+  };
+  double w = 0;
+  for (uint32_t k = 0; k < std::min(a.steps, 16u); ++k) w += waves(a.steps - 1 - k);
+  if (a.steps > 16) w *= K / 16;  // one workgroup: every step alike
+  const double start = waves(a.steps), d = h->p.d;
+  const double site = (h->p.n == 1 ? 2.0 : 8.0 * h->p.n) +
+                      (h->p.J_kind == SMC_J_FP32 ? 16 * d : h->p.J_kind == SMC_J_PM ? 4 * d : 0.0);
+  const double mb = 1e-6 * groups * a.positions * site;
+  const double lines = h->g.d == 3 ? mb * 32 / (own[0] + (a.nb[0] == 1 ? 0 : 2 * a.halo_x)) : mb;
+  // shapes of several workgroups a CU, and vector spins with a coupling a bond,
+  // are fitted least well: a margin
+  return (per > 1 ? 1.35 : 1.0) * (h->p.n > 1 && h->p.J_kind != SMC_J_UNIFORM && h->g.d == 3 ? 1.25 : 1.0) *
+         std::max(2.6, f[0] + K * (f[1] + f[2] * V) + f[3] * w * V + start * (f[4] * V + f[5]) +
+                                f[6] * mb + lines * (f[7] + f[8] * V));
+}
+
+// The cut of a call: for each number of sweeps a launch the bricks of least
+// time, against the half-sweeps at the times of their launches.  us a
+// half-sweep, those / bricks: FP32 couplings 2D L = 32 2.4 / 0.42, L = 256
+// 3.8 / 0.69, L = 1000 4.7 / 1.9, 3D L = 40 2.8 / 2.2 (L = 64 3.1 / 3.6: stays);
+// XY 2D L = 256 2.8 / 0.80, L = 1000 4.9 / 2.6, 3D L = 40 3.5 / 1.9, L = 64 4.6 /
+// 3.3; Heisenberg 3D L = 16 2.8 / 2.1, L = 40 3.9 / 2.6.  Half-sweeps are left
+// for a clear gain only.
+BrickPlan plan_bricks(const smc_lattice* h, int64_t n_sweeps) {
+  BrickPlan best;
+  std::memset(&best, 0, sizeof(best));
+  if (!h->brick_ok || n_sweeps < 1) return best;
+  BrickLaunch a;
+  if (h->forced_brick[0]) {
+    const uint32_t* f = h->forced_brick;
+    const bool whole = f[1] * f[2] * f[3] == 1;
+    const uint32_t launches = (uint32_t)((n_sweeps + f[0] - 1) / f[0]);
+    const uint32_t per = (uint32_t)((n_sweeps + launches - 1) / launches);
+    if (brick_shape(h, per, f + 1, f[4], a) && (whole || launches > 1)) {
+      best.launches = launches;
+      std::memcpy(best.nb, f + 1, sizeof(best.nb));
+      best.V = f[4];
+    }
+    return best;
+  }
+  const double Nh = (double)h->g.Nh;
+  double half = 2.6 + Nh / (h->g.d == 3 && h->p.n > 1 ? 0.08e6 : 0.2e6);
+  if (h->p.n > 1) half = std::min(half, h->p.n == 2 ? 4.0 + Nh / 0.45e6 : 4.2 + Nh / 0.26e6);  // streaming
+  half = std::max(3.2, half);
+  best.us = 0.9 * 2.0 * (double)n_sweeps * half;
+  static const uint32_t kCuts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64};
+  const uint32_t vmax = h->p.n == 3 ? 2 : 4;
+  auto consider = [&](uint32_t launches, const uint32_t nb[3]) {
+    for (uint32_t V = 1; V <= vmax; V *= 2) {
+      const uint32_t per = (uint32_t)((n_sweeps + launches - 1) / launches);
+      if (!brick_shape(h, per, nb, V, a)) continue;
+      const double us = launches * brick_us(h, a);
+      if (us < best.us) {
+        best.us = us;
+        best.launches = launches;
+        best.V = V;
+        std::memcpy(best.nb, nb, sizeof(best.nb));
+      }
+    }
+  };
+  const uint32_t one[3] = {1, 1, 1};
+  if (n_sweeps <= (1 << 20)) consider(1, one);
+  uint32_t last = 0;
+  for (uint32_t m = 1; m <= 6 && m < n_sweeps; ++m) {
+    if (n_sweeps > (int64_t)m << 20) break;
+    const uint32_t launches = (uint32_t)((n_sweeps + m - 1) / m);
+    if (launches == last || launches < 2) continue;
+    last = launches;
+    for (const uint32_t nx : kCuts) {
+      if (nx > (uint32_t)h->g.R) break;
+      for (const uint32_t ny : kCuts) {
+        if (ny > (uint32_t)h->g.L || nx * ny > kBricks) break;
+        if (h->g.d == 2) {
+          const uint32_t nb[3] = {nx, ny, 1};
+          consider(launches, nb);
+          continue;
+        }
+        for (const uint32_t nz : kCuts) {
+          if (nz < ny) continue;
+          if (nz > (uint32_t)h->g.L || nx * ny * nz > kBricks) break;
+          const uint32_t nb[3] = {nx, ny, nz};
+          consider(launches, nb);
+        }
+      }
+    }
+  }
+  return best;
+}
+
+// n sweeps in bricks, without a renormalisation among them.
+int brick_run(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, const BrickPlan& plan) {
+  const ContLaunch ca = cont_args(h, beta);
+  BrickLaunch a;
+  std::memset(&a, 0, sizeof(a));
+  a.g = h->g;
+  a.n = h->p.n;
+  a.key = ca.key;
+  a.J_kind = h->p.J_kind;
+  a.J = h->J;
+  a.J0 = ca.J0;
+  a.J0d = h->p.J0;
+  a.beta = ca.beta;
+  a.param = h->p.n == 2 ? ca.delta : ca.one_minus_cos_cap;
+  const uint32_t groups = plan.nb[0] * plan.nb[1] * plan.nb[2];
+  int64_t done = 0;
+  uint32_t at = 0;  // buffer holding the state: 0 the caller's, 1 and 2 the copies
+  for (uint32_t l = 0; l < plan.launches; ++l) {
+    const int64_t m = (n_sweeps - done + (plan.launches - l) - 1) / (plan.launches - l);
+    const bool last = l + 1 == plan.launches;
+    if (!brick_shape(h, (uint32_t)m, plan.nb, plan.V, a))
+      return fail(SMC_EINVAL, "brick launch does not fit");
+    // one workgroup reads all before it writes: in place; else to another buffer
+    const uint32_t to = last || groups == 1 ? 0u : (at == 1 ? 2u : 1u);
+    a.src = at == 0 ? h->spins : (void*)h->brick_work[at - 1];
+    a.dst = to == 0 ? h->spins : (void*)h->brick_work[to - 1];
+    a.t0 = (uint32_t)h->t;
+    a.sweep = (int64_t)h->t + m;
+    const bool meas = last && dev_obs != nullptr;
+    a.parts = meas && groups > 1 ? h->partials : nullptr;
+    a.obs = meas && groups == 1 ? dev_obs : nullptr;
+    int rc = check(launch_brick(a, h->stream), "brick sweeps launch");
+    if (rc == SMC_OK && a.parts)
+      rc = check(launch_finish(measure_args(h, a.sweep), h->partials, groups, dev_obs, h->stream),
+                 "measurement finish launch");
+    if (rc != SMC_OK) return rc;
+    at = to;
+    h->t += (uint64_t)m;
+    done += m;
+  }
+  return SMC_OK;
+}
+
 // Tiled k-hit sweeps: per sweep one pass over each tile colour.
 int tiled_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs) {
   const IsingLaunch a = ising_args(h, beta);
@@ -784,7 +995,30 @@ int sweeps_impl(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, bo
     if (plan.way == kWayResident) return resident_sweeps(h, beta, n_sweeps, dev_obs, plan);
     if (plan.way == kWayPackedCopy) return packed_copy_sweeps(h, beta, n_sweeps, dev_obs);
   }
+  int64_t planned = 0;  // sweeps before it run as planned
   for (int64_t k = 0; k < n_sweeps; ++k) {
+    if (h->brick_ok && !half && k >= planned) {
+      // up to the next renormalisation, the sweep before it included
+      const uint64_t every = h->p.n > 1 ? (uint64_t)h->p.renorm_every : 0;
+      int64_t m = n_sweeps - k;
+      if (every) m = (int64_t)std::min<uint64_t>((uint64_t)m, every - h->t % every);
+      if (h->brick_sweeps != m) {
+        h->brick = plan_bricks(h, m);
+        h->brick_sweeps = m;
+      }
+      if (h->brick.launches) {
+        const bool end = k + m == n_sweeps, renorm = every && (h->t + (uint64_t)m) % every == 0;
+        int rc = brick_run(h, beta, m, end && !renorm ? dev_obs : nullptr, h->brick);
+        if (rc == SMC_OK && renorm)
+          rc = check(launch_renormalize(h->g, h->p.n, (float*)h->spins, h->stream), "renormalisation launch");
+        if (rc == SMC_OK && renorm && end && dev_obs)
+          rc = check(measure_any(h, h->t, dev_obs), "measurement launch");
+        if (rc != SMC_OK) return rc;
+        k += m - 1;
+        continue;
+      }
+      planned = k + m;
+    }
     const bool last = k + 1 == n_sweeps;
     const bool renorm = h->p.n > 1 && h->p.renorm_every > 0 &&
                         (h->t + 1) % (uint64_t)h->p.renorm_every == 0;
@@ -1023,6 +1257,7 @@ size_t smc_workspace_bytes(const smc_params* p) {
   b += partial_bytes(p);
   if ((p->flags & SMC_FLAG_SCHEDULE_FUSED) && !is_packed(p)) b += round_up(spin_bytes(p), kAlign);
   b += multi_bytes(p);
+  b += brick_bytes(p);
   return b;
 }
 
@@ -1131,6 +1366,21 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
     const uint32_t Qc = (uint32_t)h->g.R / h->cont_spl;
     h->divQc = make_fastdiv(Qc > 0 ? Qc : 1);
   }
+  h->brick_ok = brick_params(p) && (p->n == 1 ? h->ising_variant == kVariantAuto : true);
+  if (p->n > 1)
+    for (const char* v : {"SMC_CONT_KERNEL", "SMC_CONT_ROWS", "SMC_CONT_SPL"})
+      if (std::getenv(v)) h->brick_ok = false;
+  std::memset(h->forced_brick, 0, sizeof(h->forced_brick));
+  h->brick_sweeps = 0;
+  std::memset(&h->brick, 0, sizeof(h->brick));
+  if (const char* v = std::getenv("SMC_BRICK")) {
+    unsigned f[5] = {0, 0, 0, 0, 0};
+    const int got = std::sscanf(v, "%u,%u,%u,%u,%u", f, f + 1, f + 2, f + 3, f + 4);
+    if (got < 1 || f[0] == 0) h->brick_ok = false;
+    const bool v_ok = f[4] == 1 || f[4] == 2 || (f[4] == 4 && p->n < 3);
+    if (got == 5 && v_ok && f[0] <= 1024 && std::max({f[1], f[2], f[3]}) <= 4096 && (p->d == 3 || f[3] == 1))
+      for (int k = 0; k < 5; ++k) h->forced_brick[k] = f[k];
+  }
   h->use_fused = p->n == 1 && !is_packed(p) && p->tile == 0 && !(p->flags & SMC_FLAG_HEATBATH) &&
                  (p->flags & SMC_FLAG_SCHEDULE_FUSED) &&
                  !(p->flags & SMC_FLAG_GENERIC_KERNEL) &&
@@ -1154,6 +1404,8 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
   }
   {
     char* w = h->ws + 2 * kAlign + partial_bytes(p);
+    h->brick_work[0] = w;  // (never with the buffers below: brick_params, multi_params)
+    h->brick_work[1] = w + round_up(spin_bytes(p), kAlign);
     const size_t plane = 4 * (size_t)plane_words(h->g);
     h->work[0] = (uint32_t*)w;
     h->work[1] = (uint32_t*)(w + round_up(2 * plane, kAlign));
