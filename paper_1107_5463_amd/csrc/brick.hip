@@ -21,8 +21,8 @@
 // proposal and exponential in turn, and a barrier), the launch 2 us before the
 // first; where a SIMD has three waves or more, their issue slots.  us a
 // half-sweep, launches of single half-sweeps / bricks: FP32 couplings 2D L = 32
-// 2.4 / 0.42 (one workgroup), L = 256 3.8 / 0.69 (four sweeps a launch, 256
-// bricks of 8 x 16 positions), L = 1000 4.7 / 1.9, 3D L = 40 2.8 / 2.2; XY 2D
+// 2.4 / 0.42 (one workgroup), L = 256 2.8 / 0.69 (four sweeps a launch, 256
+// bricks of 8 x 16 positions), L = 1000 3.2 / 1.9, 3D L = 40 2.8 / 2.2; XY 2D
 // L = 256 2.8 / 0.80; Heisenberg 3D L = 40 3.9 / 2.6.
 // V = 1 leaves a SIMD the most waves and is fastest where a brick fits 1024
 // lanes; V = 2 and 4 share a Philox block between sites and hold larger bricks

@@ -17,126 +17,112 @@
 
 namespace smc {
 
-// Site geometry of a row-based launch: block -> (plane row r = y + L z,
-// segment), lane -> in-row index jx.  The row decomposition is a scalar
-// division per block; neighbours are row offsets plus jx or jx +- 1.
-struct RowSite {
-  int64_t j;          // in-colour index of the site
-  int64_t row_ym, row_yp, row_zm, row_zp;  // plane offsets of the neighbour rows (+ jx)
-  int64_t xp, xm;     // plane offsets of the x+1 / x-1 neighbours
-  int32_t jx;
-};
-
-template <int D>
-__device__ __forceinline__ RowSite row_site(const Geom& g, uint32_t c, uint32_t r, int32_t jx) {
-  const int32_t L = g.L, R = g.R;
-  const int32_t y = (int32_t)(r % (uint32_t)L), z = (int32_t)(r / (uint32_t)L);  // uniform
-  const int32_t p = (int32_t)((c + (uint32_t)y + (uint32_t)z) & 1u);
-  RowSite s;
-  s.jx = jx;
-  const int64_t rowoff = (int64_t)r * R;
-  s.j = rowoff + jx;
-  // x+1 / x-1 neighbours: in-row indices jx + p and jx + p - 1 (periodic)
-  const int32_t jxp = jx + p == R ? 0 : jx + p;
-  const int32_t jxm = jx + p - 1 < 0 ? R - 1 : jx + p - 1;
-  s.xp = rowoff + jxp;
-  s.xm = rowoff + jxm;
-  const int32_t ym = y == 0 ? L - 1 : y - 1, yp = y + 1 == L ? 0 : y + 1;
-  s.row_ym = ((int64_t)z * L + ym) * R + jx;
-  s.row_yp = ((int64_t)z * L + yp) * R + jx;
-  s.row_zm = s.row_zp = 0;
-  if (D == 3) {
-    const int32_t zm = z == 0 ? L - 1 : z - 1, zp = z + 1 == L ? 0 : z + 1;
-    s.row_zm = ((int64_t)zm * L + y) * R + jx;
-    s.row_zp = ((int64_t)zp * L + y) * R + jx;
-  }
-  return s;
-}
-
-// Local field h = sum_mu [J(i,mu) s_{i+mu} + J(i-mu,mu) s_{i-mu}] in the order
-// +x, -x, +y, -y, +z, -z.
-template <int D, int N, int JK>
-__device__ __forceinline__ void field_row(const Geom& g, const float* __restrict__ s, const void* J,
-                                          float J0, uint32_t c, const RowSite& st, float h[3]) {
+// One lane a Philox block: two sites of XY (j = 2 b, 2 b + 1, which an odd row
+// length may put into two rows), one of Heisenberg.  Lanes run over the plane,
+// not over its rows: a block of 256 lanes a row leaves most of them idle where
+// L / 2 is not near a multiple of 256 (us a half-sweep, lanes of
+// rows / of the plane: XY 3D L = 100 9.4 / 6.7, L = 138 19.4 / 13.8; Heisenberg
+// 3D L = 90 7.9 / 5.0, L = 154 24.6 / 13.6).  What bounds it then is the address
+// unit: 2 d + 1 loads a component and site.
+//
+// MEASURE (colour 1 only): the energy of the bonds of the updated sites and the
+// magnetisation, as in the streaming kernel below; block sums go to
+// parts[block].
+template <int D, int N, int JK, bool FAST, bool MEASURE>
+__global__ __launch_bounds__(256) void cont_site_kernel(
+    const Geom g, const RngKey key, const void* __restrict__ J, const float J0, const float beta,
+    const float param, const FastDiv divR, const FastDiv divL, float* __restrict__ s,
+    const uint32_t t, const uint32_t c, const double J0d, Partial* __restrict__ parts) {
+  constexpr int SPL = N == 2 ? 2 : 1;
+  const uint32_t L = (uint32_t)g.L, R = (uint32_t)g.R;
   const int64_t Nh = g.Nh, Nfull = 2 * Nh;
-  const float* oth = s + (int64_t)(1 - c) * Nh;
-  const int64_t ip[3] = {st.xp, st.row_yp, st.row_zp};
-  const int64_t im[3] = {st.xm, st.row_ym, st.row_zm};
-  h[0] = h[1] = h[2] = 0.0f;
+  const uint32_t gid = xcd_remap(blockIdx.x, gridDim.x) * 256u + threadIdx.x;
+  Partial part{0, 0, 0.0, {0.0, 0.0, 0.0}};
+  if (gid < (uint32_t)(Nh / SPL)) {
+    float* own = s + (int64_t)c * Nh;
+    const float* oth = s + (int64_t)(1 - c) * Nh;
+    uint32_t j = SPL * gid;
+    uint32_t r = fdiv(j, divR);
+    uint32_t jx = j - r * R;
+    uint32_t z = D == 3 ? fdiv(r, divL) : 0u, y = r - z * L;
+    const Rand4 rnd = philox(gid, t, key.replica, tag(c, kContinuous), key.k0, key.k1);
 #pragma unroll
-  for (int mu = 0; mu < D; ++mu) {
-    const float jp = bond<JK>(J, J0, Nh, mu, c, st.j);
-    const float jm = bond<JK>(J, J0, Nh, mu, 1 - c, im[mu]);
+    for (int v = 0; v < SPL; ++v) {
+      const uint32_t p = (c + y + z) & 1u;
+      // x + 1 and x - 1: in-row indices jx + p and jx + p - 1 (periodic)
+      uint32_t ip[3], im[3];
+      ip[0] = jx + p == R ? j - jx : j + p;
+      im[0] = jx + p == 0u ? j + R - 1u : j + p - 1u;
+      ip[1] = y + 1u == L ? j - (L - 1u) * R : j + R;
+      im[1] = y == 0u ? j + (L - 1u) * R : j - R;
+      if (D == 3) {
+        ip[2] = z + 1u == L ? j - (L - 1u) * L * R : j + L * R;
+        im[2] = z == 0u ? j + (L - 1u) * L * R : j - L * R;
+      }
+      float nb[2 * D][N], sv[3] = {0.0f, 0.0f, 0.0f}, h[3] = {0.0f, 0.0f, 0.0f};
+      float jb[2 * D];
 #pragma unroll
-    for (int k = 0; k < N; ++k) h[k] += jp * oth[k * Nfull + ip[mu]];
+      for (int mu = 0; mu < D; ++mu) {
+        jb[2 * mu] = bond<JK>(J, J0, Nh, mu, c, j);
+        jb[2 * mu + 1] = bond<JK>(J, J0, Nh, mu, 1 - c, im[mu]);
 #pragma unroll
-    for (int k = 0; k < N; ++k) h[k] += jm * oth[k * Nfull + im[mu]];
-  }
-}
-
-// Blocks of 256 lanes over (row, segment); segments per row = ceil(R / (256 spt)).
-__device__ __forceinline__ void row_block(uint32_t segs, uint32_t& r, uint32_t& seg) {
-  const uint32_t b = xcd_remap(blockIdx.x, gridDim.x);
-  r = b / segs;  // wave-uniform: scalar division
-  seg = b - r * segs;
-}
-
-// XY.  PAIRED (L/2 even): a lane updates the two in-row sites (jx, jx + 1)
-// that share Philox block j >> 1; otherwise one site per lane, drawing its
-// words 2(j&1), 2(j&1)+1 of block j >> 1.
-template <int D, int JK, bool FAST, bool PAIRED>
-__global__ __launch_bounds__(256) void xy_kernel(const Geom g, const RngKey key,
-                                                 const void* __restrict__ J, const float J0,
-                                                 const float beta, const float delta,
-                                                 const uint32_t segs, float* __restrict__ s,
-                                                 const uint32_t t, const uint32_t c) {
-  uint32_t r, seg;
-  row_block(segs, r, seg);
-  constexpr int SPL = PAIRED ? 2 : 1;  // sites per lane
-  const int32_t jx0 = (int32_t)(seg * 256 * SPL + SPL * threadIdx.x);
-  if (jx0 >= g.R) return;
-  const int64_t Nh = g.Nh, Nfull = 2 * Nh;
-  float* own = s + (int64_t)c * Nh;
-  const int64_t j0 = (int64_t)r * g.R + jx0;
-  const Rand4 rnd = philox((uint32_t)(j0 >> 1), t, key.replica, tag(c, kContinuous), key.k0,
-                           key.k1);
+        for (int k = 0; k < N; ++k) {
+          nb[2 * mu][k] = oth[k * Nfull + ip[mu]];
+          nb[2 * mu + 1][k] = oth[k * Nfull + im[mu]];
+        }
+      }
 #pragma unroll
-  for (int half = 0; half < SPL; ++half) {
-    const RowSite st = row_site<D>(g, c, r, jx0 + half);
-    float h[3];
-    field_row<D, 2, JK>(g, s, J, J0, c, st, h);
-    float s0 = own[st.j], s1 = own[Nfull + st.j];
-    const bool odd = PAIRED ? half == 1 : (st.j & 1) != 0;
-    if (xy_update<FAST>(s0, s1, h, odd ? rnd.w[2] : rnd.w[0], odd ? rnd.w[3] : rnd.w[1], beta,
-                        beta_log2e(beta), delta)) {
-      own[st.j] = s0;
-      own[Nfull + st.j] = s1;
+      for (int k = 0; k < N; ++k) sv[k] = own[k * Nfull + j];
+#pragma unroll
+      for (int b = 0; b < 2 * D; ++b)
+#pragma unroll
+        for (int k = 0; k < N; ++k) h[k] += jb[b] * nb[b][k];
+      bool accept;
+      if (N == 2)
+        accept = xy_update<FAST>(sv[0], sv[1], h, rnd.w[2 * v], rnd.w[2 * v + 1], beta,
+                                 beta_log2e(beta), param);
+      else
+        accept = heis_update<FAST>(sv, h, rnd.w[0], rnd.w[1], rnd.w[2], beta, beta_log2e(beta), param);
+      if (accept) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) own[k * Nfull + j] = sv[k];
+      }
+      if (MEASURE) {
+        double e = 0.0;
+#pragma unroll
+        for (int mu = 0; mu < D; ++mu) {
+          double dp = 0.0, dm = 0.0;
+#pragma unroll
+          for (int k = 0; k < N; ++k) {
+            dp += (double)sv[k] * (double)nb[2 * mu][k];
+            dm += (double)sv[k] * (double)nb[2 * mu + 1][k];
+          }
+          double jp = J0d, jm = J0d;
+          if (JK == 1) {
+            const int8_t* Jb = (const int8_t*)J;
+            jp = J0d * Jb[((int64_t)mu * 2 + 1) * Nh + j];
+            jm = J0d * Jb[((int64_t)mu * 2 + 0) * Nh + im[mu]];
+          } else if (JK == 2) {
+            jp = (double)jb[2 * mu];
+            jm = (double)jb[2 * mu + 1];
+          }
+          e -= jp * dp + jm * dm;
+        }
+        part.E += e;
+#pragma unroll
+        for (int k = 0; k < N; ++k) part.M[k] += (double)sv[k] + (double)oth[k * Nfull + j];
+      }
+      ++j;
+      if (++jx == R) {
+        jx = 0u;
+        if (++y == L) {
+          y = 0u;
+          ++z;
+        }
+      }
     }
   }
-}
-
-template <int D, int JK, bool FAST>
-__global__ __launch_bounds__(256) void heis_kernel(const Geom g, const RngKey key,
-                                                   const void* __restrict__ J, const float J0,
-                                                   const float beta, const float omc,
-                                                   const uint32_t segs, float* __restrict__ s,
-                                                   const uint32_t t, const uint32_t c) {
-  uint32_t r, seg;
-  row_block(segs, r, seg);
-  const int32_t jx = (int32_t)(seg * 256 + threadIdx.x);
-  if (jx >= g.R) return;
-  const int64_t Nh = g.Nh, Nfull = 2 * Nh;
-  float* own = s + (int64_t)c * Nh;
-  const RowSite st = row_site<D>(g, c, r, jx);
-  const Rand4 rnd = philox((uint32_t)st.j, t, key.replica, tag(c, kContinuous), key.k0, key.k1);
-  float h[3];
-  field_row<D, 3, JK>(g, s, J, J0, c, st, h);
-  float sv[3] = {own[st.j], own[Nfull + st.j], own[2 * Nfull + st.j]};
-  if (heis_update<FAST>(sv, h, rnd.w[0], rnd.w[1], rnd.w[2], beta, beta_log2e(beta), omc)) {
-    own[st.j] = sv[0];
-    own[Nfull + st.j] = sv[1];
-    own[2 * Nfull + st.j] = sv[2];
-  }
+  if (MEASURE) block_partial(part, parts);
 }
 
 // Streaming variant (the layout of the int8 streaming kernel with FP32
@@ -411,30 +397,24 @@ __global__ __launch_bounds__(256) void cont_stream_kernel(
 }
 
 template <int D, int JK>
-static hipError_t launch_cont_dj(const ContLaunch& a, float* s, uint32_t t, uint32_t c,
-                                 hipStream_t st) {
-  const bool paired = a.n == 2 && (a.g.R % 2) == 0;
-  const uint32_t per_block = paired ? 512u : 256u;  // sites per block
-  const uint32_t segs = ((uint32_t)a.g.R + per_block - 1) / per_block;
-  const dim3 grid((unsigned)((uint64_t)a.g.rows * segs));
-#define SMC_XY(F, P)                                                                        \
-  hipLaunchKernelGGL((xy_kernel<D, JK, F, P>), grid, dim3(256), 0, st, a.g, a.key, a.J, a.J0, \
-                     a.beta, a.delta, segs, s, t, c)
-  if (a.n == 2) {
-    if (a.fast_math) {
-      if (paired) SMC_XY(true, true); else SMC_XY(true, false);
-    } else {
-      if (paired) SMC_XY(false, true); else SMC_XY(false, false);
-    }
-  } else {
-    if (a.fast_math)
-      hipLaunchKernelGGL((heis_kernel<D, JK, true>), grid, dim3(256), 0, st, a.g, a.key, a.J,
-                         a.J0, a.beta, a.one_minus_cos_cap, segs, s, t, c);
-    else
-      hipLaunchKernelGGL((heis_kernel<D, JK, false>), grid, dim3(256), 0, st, a.g, a.key, a.J,
-                         a.J0, a.beta, a.one_minus_cos_cap, segs, s, t, c);
-  }
-#undef SMC_XY
+static hipError_t launch_cont_site(const ContLaunch& a, float* s, uint32_t t, uint32_t c,
+                                   hipStream_t st, void* partials = nullptr,
+                                   int64_t* nparts = nullptr) {
+  const int64_t lanes = a.g.Nh / (a.n == 2 ? 2 : 1);
+  const dim3 grid((unsigned)((lanes + 255) / 256));
+  const float param = a.n == 2 ? a.delta : a.one_minus_cos_cap;
+  if (partials && nparts) *nparts = grid.x;
+#define SMC_CS(N, F, M)                                                                         \
+  hipLaunchKernelGGL((cont_site_kernel<D, N, JK, F, M>), grid, dim3(256), 0, st, a.g, a.key, a.J, \
+                     a.J0, a.beta, param, a.divR, a.divL, s, t, c, a.J0d, (Partial*)partials)
+#define SMC_CSM(N)                                                                \
+  do {                                                                            \
+    if (partials) { if (a.fast_math) SMC_CS(N, true, true); else SMC_CS(N, false, true); } \
+    else { if (a.fast_math) SMC_CS(N, true, false); else SMC_CS(N, false, false); }        \
+  } while (0)
+  if (a.n == 2) SMC_CSM(2); else SMC_CSM(3);
+#undef SMC_CSM
+#undef SMC_CS
   return hipGetLastError();
 }
 
@@ -484,12 +464,12 @@ uint32_t cont_sites_per_lane(const Geom& g, int n) {
 }
 
 // Smaller lattices still are done in less than the time of a launch by the
-// one-site kernel, whose lanes wait on one round of loads: XY 2D L = 64 2.8
-// against 3.6 us (the launch), L = 512 3.1 / 4.2, L = 700 3.9 / 4.8, L = 1000
-// 5.4 / 5.0; 3D L = 32 3.7 / 4.3, L = 64 5.1 / 4.6; Heisenberg 3D L = 32 2.7 /
-// 4.1, L = 64 5.0 / 4.6.
+// one-site kernel, whose lanes wait on one round of loads.  us a half-sweep,
+// one site / streaming: XY 2D L = 256 2.9 / 4.1, L = 512 3.1 / 4.2, L = 700 3.9 /
+// 4.8, L = 1000 5.5 / 5.0; 3D L = 64 3.4 / 4.6, L = 96 6.5 / 5.1; Heisenberg 3D
+// L = 64 3.1 / 4.6, L = 112 7.4 / 7.0, 2D L = 512 3.1 / 4.1, L = 1000 6.4 / 5.6.
 bool cont_prefers_row(const Geom& g, int n) {
-  return g.Nh < (n == 2 && g.d == 2 ? 350000 : 100000);
+  return g.Nh < (n == 3 ? 250000 : g.d == 2 ? 350000 : 200000);
 }
 
 bool cont_sites_per_lane_ok(int n, uint32_t V) {
@@ -527,9 +507,9 @@ static hipError_t launch_cont_d(const ContLaunch& a, float* s, uint32_t t, uint3
                                 hipStream_t st) {
   const bool stream = cont_variant_used(a) == kContStream;
   switch (a.J_kind) {
-    case 0: return stream ? launch_cont_stream<D, 0>(a, s, t, c, st) : launch_cont_dj<D, 0>(a, s, t, c, st);
-    case 1: return stream ? launch_cont_stream<D, 1>(a, s, t, c, st) : launch_cont_dj<D, 1>(a, s, t, c, st);
-    default: return stream ? launch_cont_stream<D, 2>(a, s, t, c, st) : launch_cont_dj<D, 2>(a, s, t, c, st);
+    case 0: return stream ? launch_cont_stream<D, 0>(a, s, t, c, st) : launch_cont_site<D, 0>(a, s, t, c, st);
+    case 1: return stream ? launch_cont_stream<D, 1>(a, s, t, c, st) : launch_cont_site<D, 1>(a, s, t, c, st);
+    default: return stream ? launch_cont_stream<D, 2>(a, s, t, c, st) : launch_cont_site<D, 2>(a, s, t, c, st);
   }
 }
 
@@ -539,19 +519,16 @@ hipError_t launch_cont_half_sweep(const ContLaunch& a, float* spins, uint32_t t,
                     : launch_cont_d<3>(a, spins, t, colour, st);
 }
 
-bool cont_half_sweep_measured(const ContLaunch& a, float* spins, uint32_t t, void* partials,
-                              int64_t* nparts, hipStream_t st, hipError_t* err) {
-  if (cont_variant_used(a) != kContStream) return false;
-  if (a.g.d == 2) {
-    *err = a.J_kind == 0 ? launch_cont_stream<2, 0>(a, spins, t, 1u, st, partials, nparts)
-         : a.J_kind == 1 ? launch_cont_stream<2, 1>(a, spins, t, 1u, st, partials, nparts)
-                         : launch_cont_stream<2, 2>(a, spins, t, 1u, st, partials, nparts);
-  } else {
-    *err = a.J_kind == 0 ? launch_cont_stream<3, 0>(a, spins, t, 1u, st, partials, nparts)
-         : a.J_kind == 1 ? launch_cont_stream<3, 1>(a, spins, t, 1u, st, partials, nparts)
-                         : launch_cont_stream<3, 2>(a, spins, t, 1u, st, partials, nparts);
-  }
-  return true;
+hipError_t cont_half_sweep_measured(const ContLaunch& a, float* spins, uint32_t t, void* partials,
+                                    int64_t* nparts, hipStream_t st) {
+  const bool stream = cont_variant_used(a) == kContStream;
+#define SMC_CM(D, JK)                                                                     \
+  (stream ? launch_cont_stream<D, JK>(a, spins, t, 1u, st, partials, nparts)              \
+          : launch_cont_site<D, JK>(a, spins, t, 1u, st, partials, nparts))
+  if (a.g.d == 2)
+    return a.J_kind == 0 ? SMC_CM(2, 0) : a.J_kind == 1 ? SMC_CM(2, 1) : SMC_CM(2, 2);
+    return a.J_kind == 0 ? SMC_CM(3, 0) : a.J_kind == 1 ? SMC_CM(3, 1) : SMC_CM(3, 2);
+#undef SMC_CM
 }
 
 template <int N>

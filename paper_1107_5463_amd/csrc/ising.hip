@@ -9,8 +9,9 @@
 // it equals T[k] >> 24 (probability 2^-8), and only then is the refinement
 // block drawn.
 //
-// Two kernels give bit-identical results:
-//  * ising_site_kernel -- one site per thread, any even L, any coupling kind;
+// Two kernels of the integer rules give bit-identical results (a third, below,
+// has the real-valued rule of FP32 couplings):
+//  * ising_site_kernel -- one site per thread, any even L;
 //  * ising_chunk_kernel -- one 16-byte chunk (16 consecutive same-colour
 //    sites of a plane row) per lane, L % 32 == 0, uniform or +-1 couplings.
 //    Neighbour chunks are loaded as whole 16-byte vectors; the in-row
@@ -42,7 +43,6 @@ template <int D, int JK>
 __global__ __launch_bounds__(256) void ising_site_kernel(const Geom g, const RngKey key,
                                                          const IsingTable tab,
                                                          const void* __restrict__ J,
-                                                         const float beta,
                                                          int8_t* __restrict__ s,
                                                          const uint32_t t, const uint32_t c,
                                                          const int heatbath) {
@@ -55,7 +55,6 @@ __global__ __launch_bounds__(256) void ising_site_kernel(const Geom g, const Rng
   site_coords(g, c, j, x, y, z);
   const int si = own[j];
   int kunsat = 0;
-  float h = 0.0f;
 #pragma unroll
   for (int mu = 0; mu < D; ++mu) {
     int32_t xp = x, yp = y, zp = z, xm = x, ym = y, zm = z;
@@ -65,59 +64,141 @@ __global__ __launch_bounds__(256) void ising_site_kernel(const Geom g, const Rng
     const int64_t ip = plane_index(g, xp, yp, zp);
     const int64_t im = plane_index(g, xm, ym, zm);
     const int sp = oth[ip], sm = oth[im];
-    if (JK == 2) {
-      const float* Jf = (const float*)J;
-      const float jp = Jf[((int64_t)mu * 2 + c) * Nh + j];
-      const float jm = Jf[((int64_t)mu * 2 + (1 - c)) * Nh + im];
-      h += jp * (float)sp;
-      h += jm * (float)sm;
-    } else {
-      int sgp = 1, sgm = 1;
-      if (JK == 1) {
-        const int8_t* Jb = (const int8_t*)J;
-        sgp = Jb[((int64_t)mu * 2 + c) * Nh + j];
-        sgm = Jb[((int64_t)mu * 2 + (1 - c)) * Nh + im];
-      }
-      kunsat += (sgp * si * sp < 0) + (sgm * si * sm < 0);
+    int sgp = 1, sgm = 1;
+    if (JK == 1) {
+      const int8_t* Jb = (const int8_t*)J;
+      sgp = Jb[((int64_t)mu * 2 + c) * Nh + j];
+      sgm = Jb[((int64_t)mu * 2 + (1 - c)) * Nh + im];
     }
+    kunsat += (sgp * si * sp < 0) + (sgm * si * sm < 0);
   }
-  bool accept;
-  if (JK == 2) {
-    const float dE = 2.0f * (float)si * h;
-    if (dE <= 0.0f) {
-      accept = true;
-    } else {
-      const Rand4 r = philox((uint32_t)(j >> 2), t, key.replica, tag(c, kContinuous), key.k0,
-                             key.k1);
-      accept = metropolis_fp32(dE, u01f(pick4(r, (uint32_t)j & 3u)), beta_log2e(beta));
-    }
-  } else {
-    const uint32_t k = (uint32_t)kunsat;
-    const Rand4 r = philox((uint32_t)(j >> 4), t, key.replica, tag(c, kIsingPrefix), key.k0,
-                           key.k1);
-    const uint32_t P = (pick4(r, ((uint32_t)j >> 2) & 3u) >> (8 * ((uint32_t)j & 3u))) & 0xFFu;
-    if (heatbath) {
-      // class: neighbours with sign(J) s_nb = +1; new spin +1 iff u32 < T_hb
-      const uint32_t npos = si > 0 ? 2u * D - k : k;
-      const uint32_t Th = table_byte(tab.th_lo, tab.th_hi, npos);
-      bool upv = P < Th;
-      if (P == Th) {
-        const Rand4 rr = philox((uint32_t)j, t, key.replica, tag(c, kIsingRefine), key.k0, key.k1);
-        upv = (rr.w[0] & 0xFFFFFFu) < frac_of(tab, npos);
-      }
-      const int8_t nv = upv ? (int8_t)1 : (int8_t)-1;
-      if (nv != si) own[j] = nv;
-      return;
-    }
-    const uint32_t Th = table_byte(tab.th_lo, tab.th_hi, k);
-    const bool always = table_byte(tab.al_lo, tab.al_hi, k) != 0;
-    accept = always || P < Th;
-    if (!accept && P == Th) {
+  const uint32_t k = (uint32_t)kunsat;
+  const Rand4 r = philox((uint32_t)(j >> 4), t, key.replica, tag(c, kIsingPrefix), key.k0,
+                         key.k1);
+  const uint32_t P = (pick4(r, ((uint32_t)j >> 2) & 3u) >> (8 * ((uint32_t)j & 3u))) & 0xFFu;
+  if (heatbath) {
+    // class: neighbours with sign(J) s_nb = +1; new spin +1 iff u32 < T_hb
+    const uint32_t npos = si > 0 ? 2u * D - k : k;
+    const uint32_t Th = table_byte(tab.th_lo, tab.th_hi, npos);
+    bool upv = P < Th;
+    if (P == Th) {
       const Rand4 rr = philox((uint32_t)j, t, key.replica, tag(c, kIsingRefine), key.k0, key.k1);
-      accept = (rr.w[0] & 0xFFFFFFu) < frac_of(tab, k);
+      upv = (rr.w[0] & 0xFFFFFFu) < frac_of(tab, npos);
     }
+    const int8_t nv = upv ? (int8_t)1 : (int8_t)-1;
+    if (nv != si) own[j] = nv;
+    return;
+  }
+  const uint32_t Th = table_byte(tab.th_lo, tab.th_hi, k);
+  const bool always = table_byte(tab.al_lo, tab.al_hi, k) != 0;
+  bool accept = always || P < Th;
+  if (!accept && P == Th) {
+    const Rand4 rr = philox((uint32_t)j, t, key.replica, tag(c, kIsingRefine), key.k0, key.k1);
+    accept = (rr.w[0] & 0xFFFFFFu) < frac_of(tab, k);
   }
   if (accept) own[j] = (int8_t)(-si);
+}
+
+// ---------------------------------------------------------------------------
+// FP32 couplings: V sites of a row per lane.  A half-sweep reads every
+// coupling (4 N d bytes) for N / 2 sites, so with V = 4 they come in 16-byte
+// loads, one Philox block serves the lane, and the row is found by two
+// multiplications; V = 1 where rows are no multiple of four.  MEASURE
+// (colour 1): energy and magnetisation of the result on the way.
+// us a half-sweep, one site a lane by divisions / V = 1 / V = 4: 2D L = 1440
+// 7.2 / 4.8 / 3.4, L = 2048 11.3 / 7.8 / 6.3 (33.5 MB of couplings: 5.3 TB/s),
+// 3D L = 128 7.6 / 5.4 / 3.8; a measured sweep of 2D L = 1856 33.8 / 28.2 / 15.6.
+// ---------------------------------------------------------------------------
+template <int D, int V, bool MEASURE>
+__global__ __launch_bounds__(256) void ising_real_kernel(const Geom g, const RngKey key,
+                                                         const float* __restrict__ J,
+                                                         const float beta, const FastDiv divR,
+                                                         const FastDiv divL,
+                                                         int8_t* __restrict__ s, const uint32_t t,
+                                                         const uint32_t c, Partial* __restrict__ parts) {
+  const uint32_t L = (uint32_t)g.L, R = (uint32_t)g.R;
+  const int64_t Nh = g.Nh;
+  const uint32_t gid = xcd_remap(blockIdx.x, gridDim.x) * 256u + threadIdx.x;
+  Partial part{0, 0, 0.0, {0.0, 0.0, 0.0}};
+  if (gid < (uint32_t)(Nh / V)) {
+    int8_t* own = s + (int64_t)c * Nh;
+    const int8_t* oth = s + (int64_t)(1 - c) * Nh;
+    const uint32_t j = V * gid;
+    const uint32_t r = fdiv(j, divR), jx = j - r * R;
+    const uint32_t z = D == 3 ? fdiv(r, divL) : 0u, y = r - z * L;
+    const bool p = ((c + y + z) & 1u) != 0u;
+    // y and z neighbours; x: the row's sites j .. j + V - 1 and the one beyond
+    // them (p: after, else before)
+    uint32_t ip[3], im[3];
+    ip[1] = y + 1u == L ? j - (L - 1u) * R : j + R;
+    im[1] = y == 0u ? j + (L - 1u) * R : j - R;
+    if (D == 3) {
+      ip[2] = z + 1u == L ? j - (L - 1u) * L * R : j + L * R;
+      im[2] = z == 0u ? j + (L - 1u) * L * R : j - L * R;
+    }
+    const uint32_t edge = p ? (jx + V == R ? j - jx : j + V) : (jx == 0u ? j + R - 1u : j - 1u);
+    auto signs = [&](const int8_t* from, uint32_t at, int o[V]) {
+      if (V == 4) {
+        const char4 q = *reinterpret_cast<const char4*>(from + at);
+        o[0] = q.x; o[V > 1 ? 1 : 0] = q.y; o[V > 2 ? 2 : 0] = q.z; o[V > 3 ? 3 : 0] = q.w;
+      } else {
+        o[0] = from[at];
+      }
+    };
+    auto bonds = [&](int mu, uint32_t colour, uint32_t at, float o[V]) {
+      const float* from = J + ((int64_t)mu * 2 + colour) * Nh;
+      if (V == 4) {
+        const float4 q = *reinterpret_cast<const float4*>(from + at);
+        o[0] = q.x; o[V > 1 ? 1 : 0] = q.y; o[V > 2 ? 2 : 0] = q.z; o[V > 3 ? 3 : 0] = q.w;
+      } else {
+        o[0] = from[at];
+      }
+    };
+    int si[V], ctr[V], sn[2 * D][V];
+    float jb[2 * D][V];
+    signs(own, j, si);
+    signs(oth, j, ctr);
+    const int es = oth[edge];
+    bonds(0, c, j, jb[0]);
+    float jc[V];
+    // the -x bonds belong to the other colour's sites: p: the row's, else one back
+    const float* Jx = J + (int64_t)(1 - c) * Nh;
+    bonds(0, 1 - c, j, jc);
+    const float je = Jx[edge];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      sn[0][v] = p ? (v + 1 < V ? ctr[(v + 1) % V] : es) : ctr[v];
+      sn[1][v] = p ? ctr[v] : (v > 0 ? ctr[(v + V - 1) % V] : es);
+      jb[1][v] = p ? jc[v] : (v > 0 ? jc[(v + V - 1) % V] : je);
+    }
+#pragma unroll
+    for (int mu = 1; mu < D; ++mu) {
+      signs(oth, ip[mu], sn[2 * mu]);
+      signs(oth, im[mu], sn[2 * mu + 1]);
+      bonds(mu, c, j, jb[2 * mu]);
+      bonds(mu, 1 - c, im[mu], jb[2 * mu + 1]);
+    }
+    const Rand4 rnd = philox(j >> 2, t, key.replica, tag(c, kContinuous), key.k0, key.k1);
+    const float bl2e = beta_log2e(beta);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      float h = 0.0f;
+#pragma unroll
+      for (int b = 0; b < 2 * D; ++b) h += jb[b][v] * (float)sn[b][v];
+      const float dE = 2.0f * (float)si[v] * h;
+      const uint32_t w = V == 4 ? rnd.w[v] : pick4(rnd, j & 3u);
+      if (metropolis_fp32(dE, u01f(w), bl2e)) {
+        si[v] = -si[v];
+        own[j + v] = (int8_t)si[v];
+      }
+      if (MEASURE) {
+#pragma unroll
+        for (int b = 0; b < 2 * D; ++b) part.E -= (double)jb[b][v] * (double)(si[v] * sn[b][v]);
+        part.Mi += si[v] + ctr[v];
+      }
+    }
+  }
+  if (MEASURE) block_partial(part, parts);
 }
 
 // ---------------------------------------------------------------------------
@@ -296,24 +377,36 @@ bool ising_chunk_supported(const Geom& g, int J_kind) {
   return J_kind != 2 && (g.L % 32) == 0;
 }
 
+// Four sites a lane wherever their loads are aligned, unless the one-site
+// kernel is asked for by name.
+template <int D>
+static hipError_t launch_real(const IsingLaunch& a, int8_t* s, uint32_t t, uint32_t c, hipStream_t st,
+                              void* partials = nullptr, int64_t* nparts = nullptr) {
+  const bool four = a.variant != kVariantSite && a.g.R % 4 == 0 && ((uintptr_t)a.J & 15u) == 0u &&
+                    ((uintptr_t)s & 3u) == 0u;
+  const int64_t lanes = a.g.Nh / (four ? 4 : 1);
+  const dim3 grid((unsigned)((lanes + 255) / 256));
+  if (partials && nparts) *nparts = grid.x;
+#define SMC_REAL(V, M)                                                                             \
+  hipLaunchKernelGGL((ising_real_kernel<D, V, M>), grid, dim3(256), 0, st, a.g, a.key,             \
+                     (const float*)a.J, a.beta, a.divR, a.divL, s, t, c, (Partial*)partials)
+  if (four) { if (partials) SMC_REAL(4, true); else SMC_REAL(4, false); }
+  else { if (partials) SMC_REAL(1, true); else SMC_REAL(1, false); }
+#undef SMC_REAL
+  return hipGetLastError();
+}
+
 template <int D>
 static hipError_t launch_site(const IsingLaunch& a, int8_t* spins, uint32_t t, uint32_t c,
                               hipStream_t st) {
+  if (a.J_kind == 2) return launch_real<D>(a, spins, t, c, st);
   const dim3 grid((unsigned)((a.g.Nh + 255) / 256));
-  switch (a.J_kind) {
-    case 0:
-      hipLaunchKernelGGL((ising_site_kernel<D, 0>), grid, dim3(256), 0, st, a.g, a.key, a.tab,
-                         a.J, a.beta, spins, t, c, a.heatbath);
-      break;
-    case 1:
-      hipLaunchKernelGGL((ising_site_kernel<D, 1>), grid, dim3(256), 0, st, a.g, a.key, a.tab,
-                         a.J, a.beta, spins, t, c, a.heatbath);
-      break;
-    default:
-      hipLaunchKernelGGL((ising_site_kernel<D, 2>), grid, dim3(256), 0, st, a.g, a.key, a.tab,
-                         a.J, a.beta, spins, t, c, a.heatbath);
-      break;
-  }
+  if (a.J_kind == 0)
+    hipLaunchKernelGGL((ising_site_kernel<D, 0>), grid, dim3(256), 0, st, a.g, a.key, a.tab, a.J,
+                       spins, t, c, a.heatbath);
+  else
+    hipLaunchKernelGGL((ising_site_kernel<D, 1>), grid, dim3(256), 0, st, a.g, a.key, a.tab, a.J,
+                       spins, t, c, a.heatbath);
   return hipGetLastError();
 }
 
@@ -362,11 +455,16 @@ static hipError_t launch_stream(const IsingLaunch& a, int8_t* spins, uint32_t t,
   return hipGetLastError();
 }
 
-// Colour-1 half-sweep of the streaming kernel with the observables of the
-// resulting state reduced on the way; false if the handle's kernel is not
-// the streaming one (the caller measures separately).
+// Colour-1 half-sweep of the streaming kernel, or of the kernel of FP32
+// couplings, with the observables of the resulting state reduced on the way;
+// false for the others (the caller measures separately).
 bool ising_half_sweep_measured(const IsingLaunch& a, int8_t* spins, uint32_t t, void* partials,
                                int64_t* nparts, hipStream_t st, hipError_t* err) {
+  if (a.J_kind == 2) {
+    *err = a.g.d == 2 ? launch_real<2>(a, spins, t, 1u, st, partials, nparts)
+                      : launch_real<3>(a, spins, t, 1u, st, partials, nparts);
+    return true;
+  }
   if (ising_variant_used(a) != kVariantStream) return false;
   *err = a.g.d == 2 ? launch_stream<2>(a, spins, t, 1u, st, partials, nparts)
                     : launch_stream<3>(a, spins, t, 1u, st, partials, nparts);

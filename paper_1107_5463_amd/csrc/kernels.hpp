@@ -57,11 +57,10 @@ bool cont_sites_per_lane_ok(int n, uint32_t V);
 bool cont_stream_supported(const Geom& g, uint32_t V, uint32_t H);
 uint32_t cont_rows_per_band(const Geom& g, uint32_t V, uint32_t min_waves);
 int cont_variant_used(const ContLaunch& a);
-// Colour-1 half-sweep of the continuous streaming kernel with E and M of the
-// resulting state reduced on the way (partials per block); false if the
-// handle's kernel is not the streaming one.
-bool cont_half_sweep_measured(const ContLaunch& a, float* spins, uint32_t t, void* partials,
-                              int64_t* nparts, hipStream_t st, hipError_t* err);
+// Colour-1 half-sweep of the continuous kernels with E and M of the resulting
+// state reduced on the way (partials per block).
+hipError_t cont_half_sweep_measured(const ContLaunch& a, float* spins, uint32_t t, void* partials,
+                                    int64_t* nparts, hipStream_t st);
 
 hipError_t launch_cont_half_sweep(const ContLaunch& a, float* spins, uint32_t t,
                                   uint32_t colour, hipStream_t st);

@@ -38,6 +38,7 @@ struct IsingLaunch {
                      // the tile kernels: each lane)
   FastDiv divQ;      // chunks per plane row
   FastDiv divL;      // edge length
+  FastDiv divR;      // plane row length
 };
 
 // Several half-sweeps of one Ising lattice with its words in LDS (resident.hip).
@@ -84,6 +85,7 @@ struct ContLaunch {
   uint32_t sites_per_lane;  // streaming kernel: XY 4 or 2, Heisenberg 2 or 1
   FastDiv divQ;             // lanes per plane row (R / sites per lane)
   FastDiv divL;             // edge length
+  FastDiv divR;             // plane row length
   double J0d;               // uniform coupling in FP64 (fused measurement)
 };
 

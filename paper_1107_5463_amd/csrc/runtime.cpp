@@ -78,7 +78,7 @@ struct smc_lattice {
   bool tab_valid;
   double tab_beta;
   IsingTable tab;
-  FastDiv divQ, divL;
+  FastDiv divQ, divL, divR;
   int ising_variant;         // IsingVariant (SMC_ISING_KERNEL overrides the automatic choice)
   uint32_t rows_per_band;    // streaming kernel band height (SMC_STREAM_ROWS overrides)
   bool use_fused;            // SMC_FLAG_SCHEDULE_FUSED and the fused kernel supports the shape
@@ -90,7 +90,7 @@ struct smc_lattice {
   int cont_variant;          // ContVariant (SMC_CONT_KERNEL overrides the automatic choice)
   uint32_t cont_rows;        // continuous streaming band height (SMC_CONT_ROWS overrides)
   uint32_t cont_spl;         // continuous streaming sites per lane (SMC_CONT_SPL overrides)
-  bool cont_row_sweeps;      // sweeps launch the one-site kernel where they need no measurement
+  bool cont_row_sweeps;      // sweeps launch the one-site kernel
   FastDiv divQc;             // continuous streaming lanes per plane row
   bool multi_ok;             // multi-sweep calls may leave the half-sweep kernels (plan_sweeps)
   uint32_t forced_steps, forced_own;  // SMC_RESIDENT=steps,own[,drawn] (tests): that split always
@@ -330,6 +330,7 @@ IsingLaunch ising_args(smc_lattice* h, double beta) {
   a.rows_per_band = h->rows_per_band;
   a.divQ = h->divQ;
   a.divL = h->divL;
+  a.divR = h->divR;
   a.heatbath = (h->p.flags & SMC_FLAG_HEATBATH) ? 1 : 0;
   a.packed_ties = h->packed_ties;
   return a;
@@ -380,6 +381,7 @@ ContLaunch cont_args(const smc_lattice* h, double beta) {
   a.sites_per_lane = h->cont_spl;
   a.divQ = h->divQc;
   a.divL = h->divL;
+  a.divR = h->divR;
   return a;
 }
 
@@ -433,15 +435,14 @@ int two_pass_sweep(smc_lattice* h, double beta, uint32_t t, void* dev_obs, bool 
     }
   }
   if (dev_obs && h->p.n > 1) {
-    const ContLaunch a = cont_args(h, beta);
+    ContLaunch a = cont_args(h, beta);
+    if (!half && h->cont_row_sweeps) a.variant = kContRow;
     int64_t nparts = 0;
-    hipError_t err = hipSuccess;
-    if (cont_half_sweep_measured(a, (float*)h->spins, t, h->partials, &nparts, h->stream, &err)) {
-      rc = check(err, "measured continuous half-sweep launch");
-      if (rc != SMC_OK) return rc;
-      return check(launch_finish(measure_args(h, (int64_t)t + 1), h->partials, nparts, dev_obs, h->stream),
-                   "measurement finish launch");
-    }
+    rc = check(cont_half_sweep_measured(a, (float*)h->spins, t, h->partials, &nparts, h->stream),
+               "measured continuous half-sweep launch");
+    if (rc != SMC_OK) return rc;
+    return check(launch_finish(measure_args(h, (int64_t)t + 1), h->partials, nparts, dev_obs, h->stream),
+                 "measurement finish launch");
   }
   rc = half_sweep_impl(h, beta, t, 1u, !half);
   if (rc != SMC_OK) return rc;
@@ -850,7 +851,7 @@ double brick_us(const smc_lattice* h, const BrickLaunch& a) {
 // The cut of a call: for each number of sweeps a launch the bricks of least
 // time, against the half-sweeps at the times of their launches.  us a
 // half-sweep, those / bricks: FP32 couplings 2D L = 32 2.4 / 0.42, L = 256
-// 3.8 / 0.69, L = 1000 4.7 / 1.9, 3D L = 40 2.8 / 2.2 (L = 64 3.1 / 3.6: stays);
+// 2.8 / 0.69, L = 1000 3.2 / 1.9, 3D L = 40 2.8 / 2.2 (L = 64 3.1 / 3.6: stays);
 // XY 2D L = 256 2.8 / 0.80, L = 1000 4.9 / 2.6, 3D L = 40 3.5 / 1.9, L = 64 4.6 /
 // 3.3; Heisenberg 3D L = 16 2.8 / 2.1, L = 40 3.9 / 2.6.  Half-sweeps are left
 // for a clear gain only.
@@ -874,6 +875,7 @@ BrickPlan plan_bricks(const smc_lattice* h, int64_t n_sweeps) {
   const double Nh = (double)h->g.Nh;
   double half = 2.6 + Nh / (h->g.d == 3 && h->p.n > 1 ? 0.08e6 : 0.2e6);
   if (h->p.n > 1) half = std::min(half, h->p.n == 2 ? 4.0 + Nh / 0.45e6 : 4.2 + Nh / 0.26e6);  // streaming
+  else half = 2.6 + Nh / (h->g.R % 4 == 0 ? 1.0e6 : 0.4e6);
   half = std::max(3.2, half);
   best.us = 0.9 * 2.0 * (double)n_sweeps * half;
   static const uint32_t kCuts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64};
@@ -1295,6 +1297,7 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
   h->tab_valid = false;
   h->divQ = make_fastdiv((uint32_t)(h->g.R / 16 > 0 ? h->g.R / 16 : 1));
   h->divL = make_fastdiv((uint32_t)h->g.L);
+  h->divR = make_fastdiv((uint32_t)h->g.R);
   h->ising_variant = kVariantAuto;
   if (const char* v = std::getenv("SMC_ISING_KERNEL")) {
     const std::string s(v);
