@@ -243,7 +243,8 @@ int smc_autotune(smc_lattice* h, double beta, void* scratch, size_t scratch_byte
  * (one bit per site), "ising_fused", "ising_stream", "ising_chunk",
  * "ising_site", and for the tiled schedule "ising_tiles" (int8 tiles) or
  * "ising_tiles_packed" (tiles at one bit per site in LDS, Metropolis or heat
- * bath: 2D tile edge 16, 64 or 128, 3D tile edge 16); XY / Heisenberg:
+ * bath: 2D tile edge 16, 64 or 128, 3D tile edge 16; those of edge 32 are
+ * held so too, under the first name); XY / Heisenberg:
  * "xy_stream", "xy_site",
  * "heisenberg_stream", "heisenberg_site" -- and in rows_per_band (optional)
  * the rows each lane walks for the banded kernels (packed, fused, stream,

@@ -1625,8 +1625,9 @@ const char* smc_kernel_name(const smc_lattice* h, uint32_t* rows_per_band) {
   if (h->p.tile > 0) {
     if (rows_per_band) *rows_per_band = (uint32_t)h->p.tile;
     const bool hb = (h->p.flags & SMC_FLAG_HEATBATH) != 0;
-    return h->tile_packed && tile_packed_supported(h->g, (uint32_t)h->p.tile, hb) ? "ising_tiles_packed"
-                                                                                : "ising_tiles";
+    // (tiles of 32 keep the name they had, whatever holds them in LDS)
+    return h->tile_packed && h->p.tile != 32 && tile_packed_supported(h->g, (uint32_t)h->p.tile, hb)
+               ? "ising_tiles_packed" : "ising_tiles";
   }
   if (h->use_fused) {
     if (rows_per_band) *rows_per_band = h->fused_rows;

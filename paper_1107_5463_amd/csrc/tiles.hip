@@ -20,11 +20,13 @@
 // k the unsatisfied bonds), with the same prefix-byte / 24-bit refinement
 // draw as the Metropolis rule.
 //
-// 2D Metropolis tiles of edge 16, 64 or 128 take the bit-packed kernels at the
+// Tiles of edge 16 or 32, and 64 or 128 in 2D, take the bit-packed kernels at the
 // end of this file, which hold the tile at one bit per site in LDS and make
 // the same decisions bit for bit.
 #include "chunk.hpp"
 #include "packed.hpp"
+
+#include <algorithm>
 
 namespace smc {
 
@@ -396,7 +398,7 @@ __global__ __launch_bounds__(256) void tile16_kernel(const Geom g, const RngKey 
 // ---------------------------------------------------------------------------
 // Exact ties of a bit-packed tile pass, resolved by the workgroup instead of
 // by each lane: ballot prefix sums of the lanes' counts of tied sites number
-// the sites within each wave, the four waves' totals go through LDS, thread
+// the sites within each wave, the waves' totals go through LDS, thread
 // i draws the refinement of tied site i and toggles the site in its owner's
 // LDS word (an LDS atomic xor) if the move is accepted after all -- the
 // owner stored the word with its ties refused (Metropolis: left as they
@@ -416,22 +418,22 @@ template <uint32_t BS>
 struct TileTies {
   uint4 ent[BS];                   // per thread: k0, k1, first site, LDS index of its word
   uint32_t k2[BS];                 // per thread: k2 (classes of 4 or more, K2)
-  uint16_t idx[tile_tie_cap(BS)];  // thread | bit << 8
+  uint16_t idx[tile_tie_cap(BS)];  // thread | bit << 10
   uint32_t wsum[BS / 64];          // the waves' counts of tied sites
 };
 
-// ROWS8: bit b of a word is site base + (b >> 3) R + (b & 7) (four tile rows
-// of 8 sites), else site base + b.  K2: a tied site's class can reach 4 (the
+// ROW < 32: bit b of a word is site base + b / ROW * R + b % ROW (32 / ROW tile
+// rows of ROW sites), else site base + b.  K2: a tied site's class can reach 4 (the
 // general decision), else it is k0 + 2 k1 (the fast decision: only k < 2
 // refuses).
-template <uint32_t BS, bool ROWS8, bool K2>
+template <uint32_t BS, uint32_t ROW, bool K2>
 __device__ __forceinline__ void tile_ties_group(TileTies<BS>& tt, uint32_t ties, uint32_t k0,
                                                 uint32_t k1, uint32_t k2, uint32_t base, uint32_t R,
                                                 uint32_t* words, uint32_t off, const TabRegs& tab,
                                                 const RngKey& key, uint32_t t, uint32_t c,
                                                 uint32_t h, uint32_t cap) {
   auto accepts = [&](uint32_t bs, uint32_t b, uint32_t kc) -> bool {
-    const uint32_t js = ROWS8 ? bs + (b >> 3) * R + (b & 7u) : bs + b;
+    const uint32_t js = ROW < 32u ? bs + b / ROW * R + b % ROW : bs + b;
     const Rand4 rr = philox(js, t, key.replica, tag(c, kIsingRefine) | (h << 8), key.k0, key.k1);
     return (rr.w[0] & 0xFFFFFFu) < frac_sel(tab.fr, kc);
   };
@@ -466,15 +468,15 @@ __device__ __forceinline__ void tile_ties_group(TileTies<BS>& tt, uint32_t ties,
   if (total <= cap) {
     uint32_t k = first;
     for (uint32_t m = ties; m; m &= m - 1)
-      tt.idx[k++] = (uint16_t)(threadIdx.x | ((uint32_t)__builtin_ctz(m) << 8));
+      tt.idx[k++] = (uint16_t)(threadIdx.x | ((uint32_t)__builtin_ctz(m) << 10));
     __syncthreads();
     for (uint32_t r0 = 0; r0 < total; r0 += BS) {
       const uint32_t i = r0 + threadIdx.x;
       if (i < total) {
-        const uint32_t id = tt.idx[i], b = id >> 8;
-        const uint4 en = tt.ent[id & 255u];
+        const uint32_t id = tt.idx[i], b = id >> 10;
+        const uint4 en = tt.ent[id & 1023u];
         const uint32_t kc = ((en.x >> b) & 1u) | (((en.y >> b) & 1u) << 1) |
-                            (K2 ? ((tt.k2[id & 255u] >> b) & 1u) << 2 : 0u);
+                            (K2 ? ((tt.k2[id & 1023u] >> b) & 1u) << 2 : 0u);
         if (accepts(en.z, b, kc)) atomicXor(words + en.w, 1u << b);
       }
     }
@@ -594,7 +596,7 @@ __global__ __launch_bounds__(BS) void tile_packed_kernel(const Geom g, const Rng
         own[rb] = HB ? ~flip : o ^ flip;
         off = (uint32_t)(own - words) + rb;
       }
-      tile_ties_group<BS, false, !FAST>(tt, ties, k0, k1, k2, wi * 32u, R, words, off, tab, key, t, c, h,
+      tile_ties_group<BS, 32, !FAST>(tt, ties, k0, k1, k2, wi * 32u, R, words, off, tab, key, t, c, h,
                                     tie_cap);
       __syncthreads();
     }
@@ -618,68 +620,118 @@ __global__ __launch_bounds__(BS) void tile_packed_kernel(const Geom g, const Rng
 }
 
 // ---------------------------------------------------------------------------
-// Bit-packed 16 x 16 tiles (2D, Metropolis or heat bath): a tile row holds 8 sites of a
-// colour, so a word packs four tile rows -- word i of a tile's colour holds
-// rows 4i .. 4i + 3 of the tile, site s of row r in bit 8 r + s (bit 1 = spin
-// -1).  Per tile and colour, LDS holds the column [above, w0, w1, w2, w3,
-// below] (the boundary row above the tile in bits 24..31 of `above`, the one
-// below in bits 0..7 of `below`, so the y neighbours of word i are 8-bit
-// funnel shifts of its column) and per word the sites left and right of its
-// rows (bit 8 r and bit 8 r + 7), which complete the in-row neighbours, a
-// shift by one within each byte.  Row r of a word has parity (c + r) & 1
-// (tiles start at even rows), a per-byte mask.  A row's 8 prefix bytes are
-// words 2 h0, 2 h0 + 1 of its 16-site Philox block, as in the int8 16 x 16
-// kernel, so a word takes four blocks; the transpose to bit planes and the
+// Bit-packed tiles of edge T = 16 or 32 (2D, Metropolis or heat bath): a tile
+// row holds RB = T / 2 sites of a colour, so a word packs 32 / RB tile rows --
+// word i of a tile's colour holds rows NR i .. NR i + NR - 1 of the tile, site s
+// of row r in bit RB r + s (bit 1 = spin -1).  Per tile and colour, LDS holds
+// the column [above, w0 .. w(NW - 1), below] (the boundary row above the tile in
+// the top RB bits of `above`, the one below in the low bits of `below`, so the
+// y neighbours of word i are funnel shifts of its column by RB) and per word
+// the sites left and right of its rows (bits RB r and RB r + RB - 1), which
+// complete the in-row neighbours, a shift by one within each row's bits.  Row
+// r of a word has parity (c + r) & 1 (tiles start at even rows), a mask.
+// T = 16: a row's 8 prefix bytes are words 2 h0, 2 h0 + 1 of its 16-site Philox
+// block, as in the int8 16 x 16 kernel, so a word takes four blocks; T = 32: a
+// row is a block, and a word takes two.  The transpose to bit planes and the
 // compare are the packed kernel's.  Exact ties take their refinement draws
-// before the pass ends, as in the tiles of 64.  Four lanes a tile, BS / 4 tiles
-// a workgroup.
+// before the pass ends, as in the tiles of 64.  T^2 / 64 lanes a tile.
+// T = 32 against the int8 kernel, where a tile's colour is 32 chunks of 256
+// lanes: @@T32@@.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kT16Words = 14;  // per tile and colour: column (6), left (4), right (4)
+template <uint32_t T>
+struct RowTile {
+  static constexpr uint32_t RB = T / 2;       // sites of a colour in a tile row
+  static constexpr uint32_t NR = 32 / RB;     // tile rows of a word
+  static constexpr uint32_t NW = T / NR;      // words of a colour in a plane of the tile
+  static constexpr uint32_t Words = 3 * NW + 2;  // with the boundary: column, left, right
+  static constexpr uint32_t Left = NW + 2, Right = 2 * NW + 2;
+  static constexpr uint32_t First = T == 16 ? 0x01010101u : 0x00010001u;  // bit 0 of each row
+  static constexpr uint32_t Last = First << (RB - 1);
+  static constexpr uint32_t Odd = T == 16 ? 0xFF00FF00u : 0xFFFF0000u;  // rows 1, 3
+  // sign bits of a tile row's sites
+  __device__ static __forceinline__ uint32_t bits(const int8_t* row) {
+    uint32_t v = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < RB / 8; ++k) {
+      const uint2 q = *reinterpret_cast<const uint2*>(row + 8 * k);
+      v |= (gather7(q.x) | (gather7(q.y) << 4)) << (8 * k);
+    }
+    return v;
+  }
+  // the prefix bytes of the word whose first site is j0, hit h
+  __device__ static __forceinline__ void prefix(const RngKey& key, uint32_t t, uint32_t c, uint32_t h,
+                                                uint32_t j0, uint32_t R, uint32_t P[8]) {
+#pragma unroll
+    for (uint32_t r = 0; r < NR; ++r) {
+      const uint32_t jr = j0 + r * R;
+      const Rand4 rb = philox(jr >> 4, t, key.replica, tag(c, kIsingPrefix) | (h << 8), key.k0, key.k1);
+      if (T == 16) {
+        const bool h0 = ((jr >> 3) & 1u) != 0;
+        P[2 * r] = h0 ? rb.w[2] : rb.w[0];
+        P[2 * r + 1] = h0 ? rb.w[3] : rb.w[1];
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) P[(4 * r + k) & 7u] = rb.w[k];
+      }
+    }
+  }
+  // a tile row's +-1 bytes from its bits
+  __device__ static __forceinline__ void store(int8_t* row, uint32_t v) {
+#pragma unroll
+    for (uint32_t k = 0; k < RB / 8; ++k) {
+      const uint32_t byte = (v >> (8 * k)) & 0xFFu;
+      uint32_t q[2];
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        const uint32_t spread = (((byte >> (4 * w)) & 0xFu) * 0x00204081u) & kOnes;
+        q[w] = kOnes | (spread * 0xFEu);
+      }
+      *reinterpret_cast<uint2*>(row + 8 * k) = make_uint2(q[0], q[1]);
+    }
+  }
+};
 
-template <bool FAST, bool HB, uint32_t BS>
-__global__ __launch_bounds__(BS) void tile16_packed_kernel(const Geom g, const RngKey key,
+template <uint32_t T, bool FAST, bool HB, uint32_t BS>
+__global__ __launch_bounds__(BS) void tile_rows_kernel(const Geom g, const RngKey key,
                                                             const IsingTable table,
                                                             const uint32_t hits, const uint32_t t,
                                                             const uint32_t tc, const uint32_t ntiles,
                                                             const uint32_t tie_cap,
                                                             int8_t* __restrict__ s) {
-  __shared__ uint32_t lw[BS / 4 * 2 * kT16Words];
+  using TL = RowTile<T>;
+  __shared__ uint32_t lw[BS / TL::NW * 2 * TL::Words];
   const uint32_t L = (uint32_t)g.L, R = (uint32_t)g.R;
-  const uint32_t gi = threadIdx.x >> 2, i = threadIdx.x & 3u;  // tile of the workgroup, word
-  const uint32_t bt = blockIdx.x * (BS / 4u) + gi;
+  const uint32_t gi = threadIdx.x / TL::NW, i = threadIdx.x % TL::NW;  // tile of the workgroup, word
+  const uint32_t bt = blockIdx.x * (BS / TL::NW) + gi;
   const bool valid = bt < ntiles;
-  const uint32_t half = L / 32;  // tiles of one colour per tile row
+  const uint32_t half = L / (2 * T);  // tiles of one colour per tile row
   const uint32_t bv = valid ? bt : 0u;
   const uint32_t ty = bv / half;
   const uint32_t tx = 2 * (bv - ty * half) + ((ty + tc) & 1u);
-  const uint32_t Y0 = ty * 16, x0 = tx * 8;  // first row; in-row index of the tile row's first site
+  const uint32_t Y0 = ty * T, x0 = tx * TL::RB;  // first row; in-row index of the tile row's first site
   const uint64_t Nh = (uint64_t)g.Nh;
-  uint32_t* tw = lw + gi * 2u * kT16Words;   // colour c at tw + c * kT16Words
-  auto bits8 = [&](const int8_t* row) -> uint32_t {  // sign bits of 8 sites
-    const uint2 v = *reinterpret_cast<const uint2*>(row);
-    return gather7(v.x) | (gather7(v.y) << 4);
-  };
+  uint32_t* tw = lw + gi * 2u * TL::Words;   // colour c at tw + c * TL::Words
   // stage: lane i of the tile fills word i of both colours, its left and right
-  // sites, and (lanes 0 and 3) the boundary rows
+  // sites, and (the first and last lane) the boundary rows
   if (valid) {
 #pragma unroll
     for (uint32_t cc = 0; cc < 2; ++cc) {
-      uint32_t* col = tw + cc * kT16Words;
+      uint32_t* col = tw + cc * TL::Words;
       const int8_t* pl = s + cc * Nh;
       uint32_t w = 0, lh = 0, rh = 0;
-      const uint32_t xl = x0 == 0 ? R - 1 : x0 - 1, xr = x0 + 8 == R ? 0 : x0 + 8;
+      const uint32_t xl = x0 == 0 ? R - 1 : x0 - 1, xr = x0 + TL::RB == R ? 0 : x0 + TL::RB;
 #pragma unroll
-      for (uint32_t r = 0; r < 4; ++r) {
-        const int8_t* row = pl + (uint64_t)(Y0 + 4 * i + r) * R;
-        w |= bits8(row + x0) << (8 * r);
-        lh |= (row[xl] < 0 ? 1u : 0u) << (8 * r);
-        rh |= (row[xr] < 0 ? 0x80u : 0u) << (8 * r);
+      for (uint32_t r = 0; r < TL::NR; ++r) {
+        const int8_t* row = pl + (uint64_t)(Y0 + TL::NR * i + r) * R;
+        w |= TL::bits(row + x0) << (TL::RB * r);
+        lh |= (row[xl] < 0 ? 1u : 0u) << (TL::RB * r);
+        rh |= (row[xr] < 0 ? 1u << (TL::RB - 1) : 0u) << (TL::RB * r);
       }
       col[1 + i] = w;
-      col[6 + i] = lh;
-      col[10 + i] = rh;
-      if (i == 0) col[0] = bits8(pl + (uint64_t)(Y0 == 0 ? L - 1 : Y0 - 1) * R + x0) << 24;
-      if (i == 3) col[5] = bits8(pl + (uint64_t)(Y0 + 16 == L ? 0 : Y0 + 16) * R + x0);
+      col[TL::Left + i] = lh;
+      col[TL::Right + i] = rh;
+      if (i == 0) col[0] = TL::bits(pl + (uint64_t)(Y0 == 0 ? L - 1 : Y0 - 1) * R + x0) << (32 - TL::RB);
+      if (i == TL::NW - 1) col[TL::NW + 1] = TL::bits(pl + (uint64_t)(Y0 + T == L ? 0 : Y0 + T) * R + x0);
     }
   }
   __syncthreads();
@@ -687,22 +739,22 @@ __global__ __launch_bounds__(BS) void tile16_packed_kernel(const Geom g, const R
   const TabRegs tab = tab_regs(table);
   FastTab ft;
   if (FAST) ft = fast_tab<2>(tab);
-  const uint32_t j0 = (Y0 + 4 * i) * R + x0;  // in-colour index of the word's first site
+  const uint32_t j0 = (Y0 + TL::NR * i) * R + x0;  // in-colour index of the word's first site
   __shared__ TileTies<BS> tt;
   for (uint32_t h = 0; h < hits; ++h) {
 #pragma unroll
     for (uint32_t c = 0; c < 2; ++c) {
       uint32_t ties = 0, k0 = 0, k1 = 0, k2 = 0;
       if (valid) {
-        uint32_t* own = tw + c * kT16Words;
-        const uint32_t* oth = tw + (1 - c) * kT16Words;
+        uint32_t* own = tw + c * TL::Words;
+        const uint32_t* oth = tw + (1 - c) * TL::Words;
         const uint32_t o = own[1 + i], ct = oth[1 + i];
-        const uint32_t up = __builtin_amdgcn_alignbit(ct, oth[i], 24u);    // rows r - 1
-        const uint32_t dn = __builtin_amdgcn_alignbit(oth[2 + i], ct, 8u);  // rows r + 1
-        const uint32_t sh_next = ((ct >> 1) & 0x7F7F7F7Fu) | oth[10 + i];   // site + 1 in its row
-        const uint32_t sh_prev = ((ct << 1) & 0xFEFEFEFEu) | oth[6 + i];    // site - 1
-        // rows of parity 1 (x + 1 = next site): rows 1, 3 for colour 0, rows 0, 2 for colour 1
-        constexpr uint32_t P1[2] = {0xFF00FF00u, 0x00FF00FFu};
+        const uint32_t up = __builtin_amdgcn_alignbit(ct, oth[i], 32u - TL::RB);    // rows r - 1
+        const uint32_t dn = __builtin_amdgcn_alignbit(oth[2 + i], ct, TL::RB);  // rows r + 1
+        const uint32_t sh_next = ((ct >> 1) & ~TL::Last) | oth[TL::Right + i];   // site + 1 in its row
+        const uint32_t sh_prev = ((ct << 1) & ~TL::First) | oth[TL::Left + i];    // site - 1
+        // rows of parity 1 (x + 1 = next site): the odd ones for colour 0, the even for colour 1
+        constexpr uint32_t P1[2] = {TL::Odd, ~TL::Odd};
         const uint32_t pm = P1[c];
         const uint32_t nxp = (ct & ~pm) | (sh_next & pm);
         const uint32_t nxm = (sh_prev & ~pm) | (ct & pm);
@@ -710,17 +762,8 @@ __global__ __launch_bounds__(BS) void tile16_packed_kernel(const Geom g, const R
         const uint32_t u[6] = {HB ? ~nxp : o ^ nxp, HB ? ~nxm : o ^ nxm, HB ? ~dn : o ^ dn,
                                HB ? ~up : o ^ up, 0u, 0u};
         count_planes<2>(u, k0, k1, k2);
-        // prefix bytes: row r's 8 sites are words 2 h0, 2 h0 + 1 of block j >> 4
         uint32_t P[8];
-#pragma unroll
-        for (uint32_t r = 0; r < 4; ++r) {
-          const uint32_t jr = j0 + r * R;
-          const Rand4 rb = philox(jr >> 4, t, key.replica, tag(c, kIsingPrefix) | (h << 8), key.k0,
-                                  key.k1);
-          const bool h0 = ((jr >> 3) & 1u) != 0;
-          P[2 * r] = h0 ? rb.w[2] : rb.w[0];
-          P[2 * r + 1] = h0 ? rb.w[3] : rb.w[1];
-        }
+        TL::prefix(key, t, c, h, j0, R, P);
         uint32_t B[8];
         prefix_planes(P, B);
         // exact ties refused, resolved below
@@ -728,106 +771,93 @@ __global__ __launch_bounds__(BS) void tile16_packed_kernel(const Geom g, const R
                                    : packed_compare<2>(tab, B, k0, k1, k2, ties);
         own[1 + i] = HB ? ~flip : o ^ flip;
       }
-      tile_ties_group<BS, true, !FAST>(tt, ties, k0, k1, k2, j0, R, lw,
-                                   gi * 2u * kT16Words + c * kT16Words + 1u + i, tab, key, t, c,
+      tile_ties_group<BS, TL::RB, !FAST>(tt, ties, k0, k1, k2, j0, R, lw,
+                                   gi * 2u * TL::Words + c * TL::Words + 1u + i, tab, key, t, c,
                                    h, tie_cap);
       __syncthreads();
     }
   }
 
-  // write back word i of both colours: four rows of 8 sites as +-1 bytes
+  // write back word i of both colours: its rows as +-1 bytes
   if (valid) {
 #pragma unroll
     for (uint32_t cc = 0; cc < 2; ++cc) {
-      const uint32_t v = tw[cc * kT16Words + 1 + i];
+      const uint32_t v = tw[cc * TL::Words + 1 + i];
 #pragma unroll
-      for (uint32_t r = 0; r < 4; ++r) {
-        const uint32_t byte = (v >> (8 * r)) & 0xFFu;
-        uint32_t q[2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const uint32_t spread = (((byte >> (4 * k)) & 0xFu) * 0x00204081u) & kOnes;
-          q[k] = kOnes | (spread * 0xFEu);
-        }
-        *reinterpret_cast<uint2*>(s + cc * Nh + (uint64_t)(Y0 + 4 * i + r) * R + x0) =
-            make_uint2(q[0], q[1]);
+      for (uint32_t r = 0; r < TL::NR; ++r) {
+        TL::store(s + cc * Nh + (uint64_t)(Y0 + TL::NR * i + r) * R + x0, v >> (TL::RB * r));
       }
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// Bit-packed 16^3 tiles (3D, Metropolis or heat bath): each of the tile's 16
-// z-planes is laid out as a 16 x 16 tile of the 2D kernel above -- per colour
-// the column [above, w0, w1, w2, w3, below] and the left and right sites of
-// each word's four rows -- plus the words w0 .. w3 of the boundary planes
-// below and above the tile.  A lane owns word i of plane z (rows 4 i .. 4 i +
-// 3 of that plane); its z-neighbours are the other colour's words at the same
-// place in planes z - 1 and z + 1 (the in-row index of a site's z-neighbour
-// is its own), its y- and in-row neighbours those of the 2D kernel, with the
-// rows' parity (c + r + z) mod 2 (tiles start at even rows and planes).  A
-// tile is one wave (16 planes x 4 words), four tiles a workgroup.
+// Bit-packed T^3 tiles (3D, T = 16 or 32, Metropolis or heat bath): each of the
+// tile's T z-planes is laid out as a T x T tile of the 2D kernel above, plus the
+// words of the boundary planes below and above the tile.  A lane owns word i of
+// plane z; its z-neighbours are the other colour's words at the same place in
+// planes z - 1 and z + 1 (the in-row index of a site's z-neighbour is its own),
+// its y- and in-row neighbours those of the 2D kernel, with the rows' parity
+// (c + r + z) mod 2 (tiles start at even rows and planes).  A tile of 16 is one
+// wave (16 planes x 4 words), one or four to a workgroup; a tile of 32 is a
+// workgroup of 512 lanes.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kT3Planes = 18;  // the tile's 16 planes and the two boundary planes
-
-template <bool FAST, bool HB, uint32_t BS>
-__global__ __launch_bounds__(BS) void tile16_packed3d_kernel(const Geom g, const RngKey key,
+template <uint32_t T, bool FAST, bool HB, uint32_t BS>
+__global__ __launch_bounds__(BS) void tile_rows3d_kernel(const Geom g, const RngKey key,
                                                               const IsingTable table,
                                                               const uint32_t hits, const uint32_t t,
                                                               const uint32_t tc,
                                                               const uint32_t ntiles,
                                                               const uint32_t tie_cap,
                                                               int8_t* __restrict__ s) {
-  constexpr uint32_t CW = kT3Planes * kT16Words;  // words of a colour of one tile
-  __shared__ uint32_t lw[BS / 64 * 2 * CW];
+  using TL = RowTile<T>;
+  constexpr uint32_t Lanes = T * TL::NW;         // of a tile
+  constexpr uint32_t CW = (T + 2) * TL::Words;  // words of a colour of one tile
+  __shared__ uint32_t lw[BS / Lanes * 2 * CW];
   const uint32_t L = (uint32_t)g.L, R = (uint32_t)g.R;
-  const uint32_t gi = threadIdx.x >> 6, z = (threadIdx.x >> 2) & 15u, i = threadIdx.x & 3u;
-  const uint32_t bt = blockIdx.x * (BS / 64u) + gi;
+  const uint32_t gi = threadIdx.x / Lanes, z = threadIdx.x / TL::NW % T, i = threadIdx.x % TL::NW;
+  const uint32_t bt = blockIdx.x * (BS / Lanes) + gi;
   const bool valid = bt < ntiles;
-  const uint32_t nt = L / 16, half = nt / 2;
+  const uint32_t nt = L / T, half = nt / 2;
   const uint32_t bv = valid ? bt : 0u;
   const uint32_t tz = bv / (nt * half), rem = bv - tz * nt * half;
   const uint32_t ty = rem / half;
   const uint32_t tx = 2 * (rem - ty * half) + ((ty + tz + tc) & 1u);
-  const uint32_t Z0 = tz * 16, Y0 = ty * 16, x0 = tx * 8;
+  const uint32_t Z0 = tz * T, Y0 = ty * T, x0 = tx * TL::RB;
   const uint32_t Zg = Z0 + z;  // the lane's plane
   const uint64_t Nh = (uint64_t)g.Nh;
-  uint32_t* tw = lw + gi * 2u * CW;  // colour c, plane zz (0: below the tile) at tw + c CW + zz 14
-  auto bits8 = [&](const int8_t* row) -> uint32_t {  // sign bits of 8 sites
-    const uint2 v = *reinterpret_cast<const uint2*>(row);
-    return gather7(v.x) | (gather7(v.y) << 4);
-  };
+  uint32_t* tw = lw + gi * 2u * CW;  // colour c, plane zz (0: below the tile) at tw + c CW + zz Words
   auto rowp = [&](const int8_t* pl, uint32_t zg, uint32_t y) -> const int8_t* {
     return pl + ((uint64_t)zg * L + y) * R;
   };
   // stage: lane (z, i) fills word i of plane z of both colours, its left and
-  // right sites, the boundary rows (i = 0 and 3) and the boundary planes'
-  // word i (z = 0 and 15)
+  // right sites, the boundary rows (the first and last i) and the boundary planes'
+  // word i (z = 0 and T - 1)
   if (valid) {
 #pragma unroll
     for (uint32_t cc = 0; cc < 2; ++cc) {
-      uint32_t* col = tw + cc * CW + (z + 1) * kT16Words;
+      uint32_t* col = tw + cc * CW + (z + 1) * TL::Words;
       const int8_t* pl = s + cc * Nh;
       uint32_t w = 0, lh = 0, rh = 0;
-      const uint32_t xl = x0 == 0 ? R - 1 : x0 - 1, xr = x0 + 8 == R ? 0 : x0 + 8;
+      const uint32_t xl = x0 == 0 ? R - 1 : x0 - 1, xr = x0 + TL::RB == R ? 0 : x0 + TL::RB;
 #pragma unroll
-      for (uint32_t r = 0; r < 4; ++r) {
-        const int8_t* row = rowp(pl, Zg, Y0 + 4 * i + r);
-        w |= bits8(row + x0) << (8 * r);
-        lh |= (row[xl] < 0 ? 1u : 0u) << (8 * r);
-        rh |= (row[xr] < 0 ? 0x80u : 0u) << (8 * r);
+      for (uint32_t r = 0; r < TL::NR; ++r) {
+        const int8_t* row = rowp(pl, Zg, Y0 + TL::NR * i + r);
+        w |= TL::bits(row + x0) << (TL::RB * r);
+        lh |= (row[xl] < 0 ? 1u : 0u) << (TL::RB * r);
+        rh |= (row[xr] < 0 ? 1u << (TL::RB - 1) : 0u) << (TL::RB * r);
       }
       col[1 + i] = w;
-      col[6 + i] = lh;
-      col[10 + i] = rh;
-      if (i == 0) col[0] = bits8(rowp(pl, Zg, Y0 == 0 ? L - 1 : Y0 - 1) + x0) << 24;
-      if (i == 3) col[5] = bits8(rowp(pl, Zg, Y0 + 16 == L ? 0 : Y0 + 16) + x0);
-      if (z == 0 || z == 15) {
-        const uint32_t zb = z == 0 ? (Z0 == 0 ? L - 1 : Z0 - 1) : (Z0 + 16 == L ? 0 : Z0 + 16);
+      col[TL::Left + i] = lh;
+      col[TL::Right + i] = rh;
+      if (i == 0) col[0] = TL::bits(rowp(pl, Zg, Y0 == 0 ? L - 1 : Y0 - 1) + x0) << (32 - TL::RB);
+      if (i == TL::NW - 1) col[TL::NW + 1] = TL::bits(rowp(pl, Zg, Y0 + T == L ? 0 : Y0 + T) + x0);
+      if (z == 0 || z == T - 1) {
+        const uint32_t zb = z == 0 ? (Z0 == 0 ? L - 1 : Z0 - 1) : (Z0 + T == L ? 0 : Z0 + T);
         uint32_t wb = 0;
 #pragma unroll
-        for (uint32_t r = 0; r < 4; ++r) wb |= bits8(rowp(pl, zb, Y0 + 4 * i + r) + x0) << (8 * r);
-        tw[cc * CW + (z == 0 ? 0u : kT3Planes - 1) * kT16Words + 1 + i] = wb;
+        for (uint32_t r = 0; r < TL::NR; ++r) wb |= TL::bits(rowp(pl, zb, Y0 + TL::NR * i + r) + x0) << (TL::RB * r);
+        tw[cc * CW + (z == 0 ? 0u : T + 1) * TL::Words + 1 + i] = wb;
       }
     }
   }
@@ -836,40 +866,31 @@ __global__ __launch_bounds__(BS) void tile16_packed3d_kernel(const Geom g, const
   const TabRegs tab = tab_regs(table);
   FastTab ft;
   if (FAST) ft = fast_tab<3>(tab);
-  const uint32_t j0 = ((uint32_t)Zg * L + Y0 + 4 * i) * R + x0;  // in-colour index of the word's first site
+  const uint32_t j0 = ((uint32_t)Zg * L + Y0 + TL::NR * i) * R + x0;  // in-colour index of the word's first site
   __shared__ TileTies<BS> tt;
   for (uint32_t h = 0; h < hits; ++h) {
 #pragma unroll
     for (uint32_t c = 0; c < 2; ++c) {
       uint32_t ties = 0, k0 = 0, k1 = 0, k2 = 0;
       if (valid) {
-        uint32_t* own = tw + c * CW + (z + 1) * kT16Words;
-        const uint32_t* oth = tw + (1 - c) * CW + (z + 1) * kT16Words;
+        uint32_t* own = tw + c * CW + (z + 1) * TL::Words;
+        const uint32_t* oth = tw + (1 - c) * CW + (z + 1) * TL::Words;
         const uint32_t o = own[1 + i], ct = oth[1 + i];
-        const uint32_t up = __builtin_amdgcn_alignbit(ct, oth[i], 24u);    // rows r - 1
-        const uint32_t dn = __builtin_amdgcn_alignbit(oth[2 + i], ct, 8u);  // rows r + 1
-        const uint32_t fz = oth[1 + i - kT16Words], bz = oth[1 + i + kT16Words];  // planes z -+ 1
-        const uint32_t sh_next = ((ct >> 1) & 0x7F7F7F7Fu) | oth[10 + i];   // site + 1 in its row
-        const uint32_t sh_prev = ((ct << 1) & 0xFEFEFEFEu) | oth[6 + i];    // site - 1
-        // rows of parity 1 (x + 1 = next site): rows 1, 3 when c + z is even, rows 0, 2 when odd
-        const uint32_t pm = ((c + z) & 1u) ? 0x00FF00FFu : 0xFF00FF00u;
+        const uint32_t up = __builtin_amdgcn_alignbit(ct, oth[i], 32u - TL::RB);    // rows r - 1
+        const uint32_t dn = __builtin_amdgcn_alignbit(oth[2 + i], ct, TL::RB);  // rows r + 1
+        const uint32_t fz = oth[1 + i - TL::Words], bz = oth[1 + i + TL::Words];  // planes z -+ 1
+        const uint32_t sh_next = ((ct >> 1) & ~TL::Last) | oth[TL::Right + i];   // site + 1 in its row
+        const uint32_t sh_prev = ((ct << 1) & ~TL::First) | oth[TL::Left + i];    // site - 1
+        // rows of parity 1 (x + 1 = next site): the odd ones when c + z is even, else the even
+        const uint32_t pm = ((c + z) & 1u) ? ~TL::Odd : TL::Odd;
         const uint32_t nxp = (ct & ~pm) | (sh_next & pm);
         const uint32_t nxm = (sh_prev & ~pm) | (ct & pm);
         // Metropolis: the unsatisfied bonds; heat bath: the up neighbours
         const uint32_t u[6] = {HB ? ~nxp : o ^ nxp, HB ? ~nxm : o ^ nxm, HB ? ~dn : o ^ dn,
                                HB ? ~up : o ^ up,   HB ? ~bz : o ^ bz,   HB ? ~fz : o ^ fz};
         count_planes<3>(u, k0, k1, k2);
-        // prefix bytes: row r's 8 sites are words 2 h0, 2 h0 + 1 of block j >> 4
         uint32_t P[8];
-#pragma unroll
-        for (uint32_t r = 0; r < 4; ++r) {
-          const uint32_t jr = j0 + r * R;
-          const Rand4 rb = philox(jr >> 4, t, key.replica, tag(c, kIsingPrefix) | (h << 8), key.k0,
-                                  key.k1);
-          const bool h0 = ((jr >> 3) & 1u) != 0;
-          P[2 * r] = h0 ? rb.w[2] : rb.w[0];
-          P[2 * r + 1] = h0 ? rb.w[3] : rb.w[1];
-        }
+        TL::prefix(key, t, c, h, j0, R, P);
         uint32_t B[8];
         prefix_planes(P, B);
         // exact ties refused, resolved below
@@ -877,29 +898,21 @@ __global__ __launch_bounds__(BS) void tile16_packed3d_kernel(const Geom g, const
                                    : packed_compare<3>(tab, B, k0, k1, k2, ties);
         own[1 + i] = HB ? ~flip : o ^ flip;
       }
-      tile_ties_group<BS, true, !FAST>(tt, ties, k0, k1, k2, j0, R, lw,
-                                   gi * 2u * CW + c * CW + (z + 1) * kT16Words + 1u + i, tab, key,
+      tile_ties_group<BS, TL::RB, !FAST>(tt, ties, k0, k1, k2, j0, R, lw,
+                                   gi * 2u * CW + c * CW + (z + 1) * TL::Words + 1u + i, tab, key,
                                    t, c, h, tie_cap);
       __syncthreads();
     }
   }
 
-  // write back word i of plane z of both colours: four rows of 8 sites as +-1 bytes
+  // write back word i of plane z of both colours: its rows as +-1 bytes
   if (valid) {
 #pragma unroll
     for (uint32_t cc = 0; cc < 2; ++cc) {
-      const uint32_t v = tw[cc * CW + (z + 1) * kT16Words + 1 + i];
+      const uint32_t v = tw[cc * CW + (z + 1) * TL::Words + 1 + i];
 #pragma unroll
-      for (uint32_t r = 0; r < 4; ++r) {
-        const uint32_t byte = (v >> (8 * r)) & 0xFFu;
-        uint32_t q[2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const uint32_t spread = (((byte >> (4 * k)) & 0xFu) * 0x00204081u) & kOnes;
-          q[k] = kOnes | (spread * 0xFEu);
-        }
-        *reinterpret_cast<uint2*>(s + cc * Nh + ((uint64_t)Zg * L + Y0 + 4 * i + r) * R + x0) =
-            make_uint2(q[0], q[1]);
+      for (uint32_t r = 0; r < TL::NR; ++r) {
+        TL::store(s + cc * Nh + ((uint64_t)Zg * L + Y0 + TL::NR * i + r) * R + x0, v >> (TL::RB * r));
       }
     }
   }
@@ -907,7 +920,7 @@ __global__ __launch_bounds__(BS) void tile16_packed3d_kernel(const Geom g, const
 
 bool tile_packed_supported(const Geom& g, uint32_t T, bool heatbath) {
   (void)heatbath;  // both rules
-  const bool shape = g.d == 2 ? (T == 16 || T == 64 || T == 128) : (g.d == 3 && T == 16);
+  const bool shape = T == 16 || T == 32 || (g.d == 2 && (T == 64 || T == 128));
   return shape && (uint32_t)g.L % T == 0 && ((uint32_t)g.L / T) % 2 == 0;
 }
 
@@ -967,13 +980,13 @@ hipError_t launch_tile_pass(const IsingLaunch& a, bool heatbath, uint32_t T, uin
     bool fast = true;
     for (int k = a.g.d; k <= 2 * a.g.d; ++k)
       if ((((k < 4 ? a.tab.al_lo : a.tab.al_hi) >> (8 * (k & 3))) & 0xFFu) != 0xFFu) fast = false;
-    const uint32_t items = a.g.d == 3 ? 64u : T == 16 ? 4u : T * T / 64u;  // lanes of a tile
+    const uint32_t items = (a.g.d == 3 ? T : 1u) * T * T / 64u;  // lanes of a tile
     // Workgroups of one wave where a tile fits one and the launch leaves a
     // SIMD fewer than kTileWaves waves; else 256 lanes, whose ties share one
     // round of draws.
     const bool one_wave = items <= 64u && groups != 256u &&
                           (groups == 64u || (uint64_t)tiles * items < 64ull * 1024 * kTileWaves);
-    const uint32_t bs = one_wave ? 64u : 256u, G = bs / items;
+    const uint32_t bs = one_wave ? 64u : std::max(256u, items), G = bs / items;
     const dim3 grid((tiles + G - 1) / G), block(bs);
     // the workgroup's list of tied sites (packed_ties other than 0: each lane its own)
     const uint32_t cap = a.packed_ties == 0 ? tile_tie_cap(bs) : 0u;
@@ -987,10 +1000,19 @@ hipError_t launch_tile_pass(const IsingLaunch& a, bool heatbath, uint32_t T, uin
     else if (fast) hipLaunchKernelGGL((K<true, false, BS>), grid, block, LDS, st, a.g, a.key, a.tab, __VA_ARGS__, t, tc, tiles, cap, spins); \
     else hipLaunchKernelGGL((K<false, false, BS>), grid, block, LDS, st, a.g, a.key, a.tab, __VA_ARGS__, t, tc, tiles, cap, spins); \
   } while (0)
-    if (T == 16 && a.g.d == 3) SMC_TP(tile16_packed3d_kernel, 0, hits);
-    else if (T == 16) SMC_TP(tile16_packed_kernel, 0, hits);
+#define SMC_TPT(K, T, BS)                                                                          \
+  do {                                                                                             \
+    if (heatbath) hipLaunchKernelGGL((K<T, false, true, BS>), grid, block, 0, st, a.g, a.key, a.tab, hits, t, tc, tiles, cap, spins); \
+    else if (fast) hipLaunchKernelGGL((K<T, true, false, BS>), grid, block, 0, st, a.g, a.key, a.tab, hits, t, tc, tiles, cap, spins); \
+    else hipLaunchKernelGGL((K<T, false, false, BS>), grid, block, 0, st, a.g, a.key, a.tab, hits, t, tc, tiles, cap, spins); \
+  } while (0)
+    if (a.g.d == 3 && T == 32) SMC_TPT(tile_rows3d_kernel, 32, 512);
+    else if (a.g.d == 3) { if (one_wave) SMC_TPT(tile_rows3d_kernel, 16, 64); else SMC_TPT(tile_rows3d_kernel, 16, 256); }
+    else if (T == 16) { if (one_wave) SMC_TPT(tile_rows_kernel, 16, 64); else SMC_TPT(tile_rows_kernel, 16, 256); }
+    else if (T == 32) { if (one_wave) SMC_TPT(tile_rows_kernel, 32, 64); else SMC_TPT(tile_rows_kernel, 32, 256); }
     else SMC_TP(tile_packed_kernel, tile_packed_lds_bytes(T, G), T, hits);
 #undef SMC_TPB
+#undef SMC_TPT
 #undef SMC_TP
     return hipGetLastError();
   }
