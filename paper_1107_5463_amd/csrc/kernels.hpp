@@ -44,6 +44,12 @@ hipError_t launch_draws(const ResidentLaunch& a, bool heatbath, uint32_t steps, 
 hipError_t launch_bond_words(const Geom& g, bool bytes, const void* J, uint32_t* out,
                              hipStream_t st);
 
+// Tile passes with the masks of several hits formed ahead (tiles_ahead.hip).
+bool tile_ahead_supported(const Geom& g, uint32_t T);
+uint32_t tile_ahead_waves(const Geom& g, uint32_t T, bool heatbath);
+hipError_t launch_tile_ahead_pass(const IsingLaunch& a, bool heatbath, uint32_t T, uint32_t hits,
+                                  int8_t* spins, uint32_t t, uint32_t tc, hipStream_t st, uint32_t waves);
+
 // Sweeps of bricks of the lattice held in LDS (brick.hip).
 hipError_t launch_brick(const BrickLaunch& a, hipStream_t st);
 size_t brick_lds_bytes(int n, uint32_t positions);

@@ -87,6 +87,7 @@ struct smc_lattice {
   int packed_ties;           // packed kernels' ties: 0 group, 1 lane, 2 group fallback (SMC_PACKED_TIES)
   bool tile_packed;          // tiled schedule: bit-packed tiles where they apply (SMC_TILE_KERNEL=byte: off)
   uint32_t tile_group;       // lanes of their workgroups (SMC_TILE_KERNEL=wave: 64, group: 256), 0: chosen
+  uint32_t tile_ahead;       // waves of a workgroup with masks ahead (SMC_TILE_KERNEL=ahead,waves), 0: in the pass
   int cont_variant;          // ContVariant (SMC_CONT_KERNEL overrides the automatic choice)
   uint32_t cont_rows;        // continuous streaming band height (SMC_CONT_ROWS overrides)
   uint32_t cont_spl;         // continuous streaming sites per lane (SMC_CONT_SPL overrides)
@@ -971,9 +972,13 @@ int tiled_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs) {
   const bool hb = (h->p.flags & SMC_FLAG_HEATBATH) != 0;
   for (int64_t k = 0; k < n_sweeps; ++k) {
     for (uint32_t tc = 0; tc < 2; ++tc) {
-      const int rc = check(launch_tile_pass(a, hb, (uint32_t)h->p.tile, (uint32_t)h->p.hits,
-                                            (int8_t*)h->spins, (uint32_t)h->t, tc, h->stream,
-                                            h->tile_packed, h->tile_group),
+      const int rc = check(h->tile_ahead
+                               ? launch_tile_ahead_pass(a, hb, (uint32_t)h->p.tile, (uint32_t)h->p.hits,
+                                                        (int8_t*)h->spins, (uint32_t)h->t, tc, h->stream,
+                                                        h->tile_ahead)
+                               : launch_tile_pass(a, hb, (uint32_t)h->p.tile, (uint32_t)h->p.hits,
+                                                  (int8_t*)h->spins, (uint32_t)h->t, tc, h->stream,
+                                                  h->tile_packed, h->tile_group),
                            "tile pass launch");
       if (rc != SMC_OK) return rc;
     }
@@ -1326,11 +1331,17 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
   h->packed_ties = 0;
   h->tile_packed = true;
   h->tile_group = 0;
+  const bool heatbath = (p->flags & SMC_FLAG_HEATBATH) != 0;
+  h->tile_ahead = p->tile > 0 ? tile_ahead_waves(h->g, (uint32_t)p->tile, heatbath) : 0u;
   if (const char* v = std::getenv("SMC_TILE_KERNEL")) {
     const std::string s(v);
     h->tile_packed = s != "byte";
     h->tile_group = s == "wave" ? 64u : s == "group" ? 256u : 0u;
+    const unsigned long w = s.compare(0, 6, "ahead,") == 0 ? std::strtoul(s.c_str() + 6, nullptr, 10) : 0;
+    if (w >= 2 && w <= 12 && tile_ahead_supported(h->g, (uint32_t)p->tile)) h->tile_ahead = (uint32_t)w;
+    if (s == "byte" || (heatbath && h->tile_group)) h->tile_ahead = 0u;
   }
+  if (heatbath && std::getenv("SMC_PACKED_TIES")) h->tile_ahead = 0u;
   if (const char* v = std::getenv("SMC_PACKED_TIES")) {
     const std::string s(v);
     if (s == "lane") h->packed_ties = 1;

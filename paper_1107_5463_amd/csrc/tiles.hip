@@ -620,7 +620,8 @@ __global__ __launch_bounds__(BS) void tile_packed_kernel(const Geom g, const Rng
 }
 
 // ---------------------------------------------------------------------------
-// Bit-packed tiles of edge T = 16 or 32 (2D, Metropolis or heat bath): a tile
+// Bit-packed tiles of edge T = 16 or 32 (2D, heat bath in launches
+// that fill the chip; the others form their decisions ahead, tiles_ahead.hip): a tile
 // row holds RB = T / 2 sites of a colour, so a word packs 32 / RB tile rows --
 // word i of a tile's colour holds rows NR i .. NR i + NR - 1 of the tile, site s
 // of row r in bit RB r + s (bit 1 = spin -1).  Per tile and colour, LDS holds
@@ -636,7 +637,7 @@ __global__ __launch_bounds__(BS) void tile_packed_kernel(const Geom g, const Rng
 // compare are the packed kernel's.  Exact ties take their refinement draws
 // before the pass ends, as in the tiles of 64.  T^2 / 64 lanes a tile.
 // T = 32 against the int8 kernel, where a tile's colour is 32 chunks of 256
-// lanes: @@T32@@.
+// lanes (us a sweep of k = 100, int8 / here): 2D L = 4096 1458 / 484, 3D L = 256 1368 / 607.
 // ---------------------------------------------------------------------------
 template <uint32_t T>
 struct RowTile {
@@ -691,7 +692,7 @@ struct RowTile {
   }
 };
 
-template <uint32_t T, bool FAST, bool HB, uint32_t BS>
+template <uint32_t T, uint32_t BS>
 __global__ __launch_bounds__(BS) void tile_rows_kernel(const Geom g, const RngKey key,
                                                             const IsingTable table,
                                                             const uint32_t hits, const uint32_t t,
@@ -737,8 +738,6 @@ __global__ __launch_bounds__(BS) void tile_rows_kernel(const Geom g, const RngKe
   __syncthreads();
 
   const TabRegs tab = tab_regs(table);
-  FastTab ft;
-  if (FAST) ft = fast_tab<2>(tab);
   const uint32_t j0 = (Y0 + TL::NR * i) * R + x0;  // in-colour index of the word's first site
   __shared__ TileTies<BS> tt;
   for (uint32_t h = 0; h < hits; ++h) {
@@ -748,7 +747,7 @@ __global__ __launch_bounds__(BS) void tile_rows_kernel(const Geom g, const RngKe
       if (valid) {
         uint32_t* own = tw + c * TL::Words;
         const uint32_t* oth = tw + (1 - c) * TL::Words;
-        const uint32_t o = own[1 + i], ct = oth[1 + i];
+        const uint32_t ct = oth[1 + i];
         const uint32_t up = __builtin_amdgcn_alignbit(ct, oth[i], 32u - TL::RB);    // rows r - 1
         const uint32_t dn = __builtin_amdgcn_alignbit(oth[2 + i], ct, TL::RB);  // rows r + 1
         const uint32_t sh_next = ((ct >> 1) & ~TL::Last) | oth[TL::Right + i];   // site + 1 in its row
@@ -758,20 +757,17 @@ __global__ __launch_bounds__(BS) void tile_rows_kernel(const Geom g, const RngKe
         const uint32_t pm = P1[c];
         const uint32_t nxp = (ct & ~pm) | (sh_next & pm);
         const uint32_t nxm = (sh_prev & ~pm) | (ct & pm);
-        // Metropolis: the unsatisfied bonds; heat bath: the up neighbours
-        const uint32_t u[6] = {HB ? ~nxp : o ^ nxp, HB ? ~nxm : o ^ nxm, HB ? ~dn : o ^ dn,
-                               HB ? ~up : o ^ up, 0u, 0u};
+        // the up neighbours
+        const uint32_t u[6] = {~nxp, ~nxm, ~dn, ~up, 0u, 0u};
         count_planes<2>(u, k0, k1, k2);
         uint32_t P[8];
         TL::prefix(key, t, c, h, j0, R, P);
         uint32_t B[8];
         prefix_planes(P, B);
         // exact ties refused, resolved below
-        const uint32_t flip = FAST ? packed_compare_fast<2>(ft, B, k0, k1, k2, ties)
-                                   : packed_compare<2>(tab, B, k0, k1, k2, ties);
-        own[1 + i] = HB ? ~flip : o ^ flip;
+        own[1 + i] = ~packed_compare<2>(tab, B, k0, k1, k2, ties);
       }
-      tile_ties_group<BS, TL::RB, !FAST>(tt, ties, k0, k1, k2, j0, R, lw,
+      tile_ties_group<BS, TL::RB, true>(tt, ties, k0, k1, k2, j0, R, lw,
                                    gi * 2u * TL::Words + c * TL::Words + 1u + i, tab, key, t, c,
                                    h, tie_cap);
       __syncthreads();
@@ -962,10 +958,9 @@ hipError_t tile_allow_lds(int d, size_t bytes) {
 
 // Below this many waves a SIMD a packed tile pass runs in workgroups of one
 // wave: the barriers and the one drawing wave of a 256-lane group then leave
-// the SIMD idle (us a sweep of k = 100, groups of 256 / of 64: 2D L = 1024
-// T = 16 487 / 389, L = 4096 673 / 595, T = 64 558 / 494, 3D L = 128 504 /
-// 402); above it the shared round of tie draws wins (8 waves a SIMD: 1845 /
-// 1847 and 1444 / 1473; L = 16384: 6628 / 6886).
+// the SIMD idle (heat bath, us a sweep of k = 100, groups of 256 / of 64: 2D T =
+// 16 L = 4096 772 / 703, T = 64 657 / 581, 3D T = 16 L = 256 838 / 786); above it
+// the shared round of tie draws catches up (L = 8192: 2215 / 2224).
 constexpr uint32_t kTileWaves = 4;
 
 // One tile-colour pass (k hits) of the tiled schedule; `packed`: the bit-packed
@@ -975,7 +970,8 @@ hipError_t launch_tile_pass(const IsingLaunch& a, bool heatbath, uint32_t T, uin
                             uint32_t groups) {
   const uint32_t nt = (uint32_t)a.g.L / T;
   const uint32_t tiles = (a.g.d == 3 ? nt * nt * nt : nt * nt) / 2;
-  if (packed && tile_packed_supported(a.g, T, heatbath)) {
+  // (the Metropolis rule of the other edges: launch_tile_ahead_pass)
+  if (packed && tile_packed_supported(a.g, T, heatbath) && (heatbath || T == 128 || (a.g.d == 3 && T == 32))) {
     // the fast decision when every class k >= d always accepts (J0 > 0)
     bool fast = true;
     for (int k = a.g.d; k <= 2 * a.g.d; ++k)
@@ -990,29 +986,29 @@ hipError_t launch_tile_pass(const IsingLaunch& a, bool heatbath, uint32_t T, uin
     const dim3 grid((tiles + G - 1) / G), block(bs);
     // the workgroup's list of tied sites (packed_ties other than 0: each lane its own)
     const uint32_t cap = a.packed_ties == 0 ? tile_tie_cap(bs) : 0u;
-#define SMC_TP(K, LDS, ...)                                                                        \
-  do {                                                                                             \
-    if (one_wave) SMC_TPB(K, 64, LDS, __VA_ARGS__); else SMC_TPB(K, 256, LDS, __VA_ARGS__);        \
-  } while (0)
-#define SMC_TPB(K, BS, LDS, ...)                                                                   \
-  do {                                                                                             \
-    if (heatbath) hipLaunchKernelGGL((K<false, true, BS>), grid, block, LDS, st, a.g, a.key, a.tab, __VA_ARGS__, t, tc, tiles, cap, spins); \
-    else if (fast) hipLaunchKernelGGL((K<true, false, BS>), grid, block, LDS, st, a.g, a.key, a.tab, __VA_ARGS__, t, tc, tiles, cap, spins); \
-    else hipLaunchKernelGGL((K<false, false, BS>), grid, block, LDS, st, a.g, a.key, a.tab, __VA_ARGS__, t, tc, tiles, cap, spins); \
-  } while (0)
-#define SMC_TPT(K, T, BS)                                                                          \
-  do {                                                                                             \
-    if (heatbath) hipLaunchKernelGGL((K<T, false, true, BS>), grid, block, 0, st, a.g, a.key, a.tab, hits, t, tc, tiles, cap, spins); \
-    else if (fast) hipLaunchKernelGGL((K<T, true, false, BS>), grid, block, 0, st, a.g, a.key, a.tab, hits, t, tc, tiles, cap, spins); \
-    else hipLaunchKernelGGL((K<T, false, false, BS>), grid, block, 0, st, a.g, a.key, a.tab, hits, t, tc, tiles, cap, spins); \
-  } while (0)
-    if (a.g.d == 3 && T == 32) SMC_TPT(tile_rows3d_kernel, 32, 512);
-    else if (a.g.d == 3) { if (one_wave) SMC_TPT(tile_rows3d_kernel, 16, 64); else SMC_TPT(tile_rows3d_kernel, 16, 256); }
-    else if (T == 16) { if (one_wave) SMC_TPT(tile_rows_kernel, 16, 64); else SMC_TPT(tile_rows_kernel, 16, 256); }
-    else if (T == 32) { if (one_wave) SMC_TPT(tile_rows_kernel, 32, 64); else SMC_TPT(tile_rows_kernel, 32, 256); }
-    else SMC_TP(tile_packed_kernel, tile_packed_lds_bytes(T, G), T, hits);
-#undef SMC_TPB
-#undef SMC_TPT
+#define SMC_TP(K, ...) hipLaunchKernelGGL((K), grid, block, lds, st, a.g, a.key, a.tab, __VA_ARGS__, t, tc, tiles, cap, spins)
+    const size_t lds = a.g.d == 2 && T >= 64 ? tile_packed_lds_bytes(T, G) : 0;
+    if (a.g.d == 3 && T == 32) {
+      if (heatbath) SMC_TP((tile_rows3d_kernel<32, false, true, 512>), hits);
+      else if (fast) SMC_TP((tile_rows3d_kernel<32, true, false, 512>), hits);
+      else SMC_TP((tile_rows3d_kernel<32, false, false, 512>), hits);
+    } else if (a.g.d == 3) {
+      if (one_wave) SMC_TP((tile_rows3d_kernel<16, false, true, 64>), hits);
+      else SMC_TP((tile_rows3d_kernel<16, false, true, 256>), hits);
+    } else if (T == 128) {
+      if (heatbath) SMC_TP((tile_packed_kernel<false, true, 256>), T, hits);
+      else if (fast) SMC_TP((tile_packed_kernel<true, false, 256>), T, hits);
+      else SMC_TP((tile_packed_kernel<false, false, 256>), T, hits);
+    } else if (T == 64) {
+      if (one_wave) SMC_TP((tile_packed_kernel<false, true, 64>), T, hits);
+      else SMC_TP((tile_packed_kernel<false, true, 256>), T, hits);
+    } else if (T == 32) {
+      if (one_wave) SMC_TP((tile_rows_kernel<32, 64>), hits);
+      else SMC_TP((tile_rows_kernel<32, 256>), hits);
+    } else {
+      if (one_wave) SMC_TP((tile_rows_kernel<16, 64>), hits);
+      else SMC_TP((tile_rows_kernel<16, 256>), hits);
+    }
 #undef SMC_TP
     return hipGetLastError();
   }
