@@ -18,8 +18,10 @@ hipError_t allow_dynamic_lds(const void* fn, size_t bytes);
 
 uint32_t stream_rows_per_band(const Geom& g, uint32_t min_waves);
 int ising_variant_used(const IsingLaunch& a);  // the variant a launch resolves to
-bool ising_half_sweep_measured(const IsingLaunch& a, int8_t* spins, uint32_t t, void* partials,
-                               int64_t* nparts, hipStream_t st, hipError_t* err);
+// Colour-1 half-sweep with E and M of the resulting state reduced on the way
+// (partials per block).
+hipError_t ising_half_sweep_measured(const IsingLaunch& a, int8_t* spins, uint32_t t, void* partials,
+                                     int64_t* nparts, hipStream_t st);
 
 // Fused one-pass sweep (2D, uniform couplings): src -> dst, both [2][N/2].
 bool ising_fused_supported(const Geom& g, int J_kind, uint32_t rows_per_band);

@@ -407,50 +407,31 @@ int half_sweep_impl(smc_lattice* h, double beta, uint32_t t, uint32_t colour, bo
 }
 
 // One in-place two-pass sweep with counter t; with dev_obs the observables of
-// the result are written there (fused into the colour-1 pass when the
-// streaming kernel runs, else by a separate measurement).
+// the result, reduced by the colour-1 pass, are written there.
 // `half`: by the handle's half-sweep kernel in any case.
 int two_pass_sweep(smc_lattice* h, double beta, uint32_t t, void* dev_obs, bool half = false) {
   int rc = half_sweep_impl(h, beta, t, 0u, !half);
   if (rc != SMC_OK) return rc;
-  if (dev_obs && is_packed(&h->p)) {
-    IsingLaunch a = ising_args(h, beta);
-    a.rows_per_band = h->packed_rows;
-    int64_t nparts = 0;
-    rc = check(launch_packed_half_sweep(a, (uint32_t*)h->spins, (const uint32_t*)h->J, t, 1u,
-                                        h->partials, &nparts, h->stream),
-               "measured packed half-sweep launch");
-    if (rc != SMC_OK) return rc;
-    return check(launch_finish(measure_args(h, (int64_t)t + 1), h->partials, nparts, dev_obs, h->stream),
-                 "measurement finish launch");
-  }
-  if (dev_obs && h->p.n == 1) {
-    const IsingLaunch a = ising_args(h, beta);
-    int64_t nparts = 0;
-    hipError_t err = hipSuccess;
-    if (ising_half_sweep_measured(a, (int8_t*)h->spins, t, h->partials, &nparts, h->stream, &err)) {
-      rc = check(err, "measured Ising half-sweep launch");
-      if (rc != SMC_OK) return rc;
-      return check(launch_finish(measure_args(h, (int64_t)t + 1), h->partials, nparts, dev_obs, h->stream),
-                   "measurement finish launch");
-    }
-  }
-  if (dev_obs && h->p.n > 1) {
+  if (!dev_obs) return half_sweep_impl(h, beta, t, 1u, !half);
+  int64_t nparts = 0;
+  hipError_t err;
+  if (h->p.n > 1) {
     ContLaunch a = cont_args(h, beta);
     if (!half && h->cont_row_sweeps) a.variant = kContRow;
-    int64_t nparts = 0;
-    rc = check(cont_half_sweep_measured(a, (float*)h->spins, t, h->partials, &nparts, h->stream),
-               "measured continuous half-sweep launch");
-    if (rc != SMC_OK) return rc;
-    return check(launch_finish(measure_args(h, (int64_t)t + 1), h->partials, nparts, dev_obs, h->stream),
-                 "measurement finish launch");
+    err = cont_half_sweep_measured(a, (float*)h->spins, t, h->partials, &nparts, h->stream);
+  } else if (is_packed(&h->p)) {
+    IsingLaunch a = ising_args(h, beta);
+    a.rows_per_band = h->packed_rows;
+    err = launch_packed_half_sweep(a, (uint32_t*)h->spins, (const uint32_t*)h->J, t, 1u, h->partials,
+                                   &nparts, h->stream);
+  } else {
+    err = ising_half_sweep_measured(ising_args(h, beta), (int8_t*)h->spins, t, h->partials, &nparts,
+                                    h->stream);
   }
-  rc = half_sweep_impl(h, beta, t, 1u, !half);
+  rc = check(err, "measured half-sweep launch");
   if (rc != SMC_OK) return rc;
-  if (dev_obs)
-    return check(measure_any(h, (int64_t)t + 1, dev_obs),
-                 "measurement launch");
-  return SMC_OK;
+  return check(launch_finish(measure_args(h, (int64_t)t + 1), h->partials, nparts, dev_obs, h->stream),
+               "measurement finish launch");
 }
 
 // n sweeps from t with the fused kernel, ping-ponging through the workspace
@@ -613,8 +594,8 @@ double half_us(const smc_lattice* h, bool packed) {
   a.heatbath = (h->p.flags & SMC_FLAG_HEATBATH) ? 1 : 0;
   switch (ising_variant_used(a)) {
     case kVariantStream: return std::max(5.2, 2.5 + n / 2.1e6);
-    case kVariantChunk: return std::max(4.1, 3.5 + n / 1.2e6);
-    default: return 3.8 + n / 0.21e6;
+    case kVariantChunk: return std::max(3.9, 3.4 + n / 1.6e6);
+    default: return std::max(3.3, 2.5 + n / 0.28e6);
   }
 }
 
