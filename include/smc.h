@@ -383,6 +383,15 @@ int smc_chains_sample(smc_chains* h, double beta, int64_t n_sweeps, int64_t* dev
 int smc_chains_covariance(smc_chains* h, double beta, int64_t n_sweeps, const double* dev_g,
                           const double* dev_g_center, double* dev_cov_acc, double* dev_G_acc);
 
+/* The same replay from spins and couplings held elsewhere (dev_start like the
+ * chains' spins, 16-byte aligned; dev_J like their couplings) at counter t0:
+ * the chains, their couplings and counter stay as they are, and dev_cov and
+ * dev_G are overwritten.  n_sweeps >= 1.  What a backward pass needs of a
+ * forward one whose start it kept, without moving the chains there and back. */
+int smc_chains_replay(smc_chains* h, double beta, int64_t n_sweeps, uint64_t t0, const float* dev_J,
+                      const void* dev_start, const double* dev_g, const double* dev_g_center,
+                      double* dev_cov, double* dev_G);
+
 /* Finishing the estimates (FP64 device arithmetic over the d N bonds, every
  * sum in a fixed order; all asynchronous on the handle's stream; arrays over
  * bonds in the coupling layout, double 8-byte and float 4-byte aligned).

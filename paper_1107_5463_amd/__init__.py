@@ -52,7 +52,7 @@ EXPORTS = ["smc_spin_bytes", "smc_coupling_bytes", "smc_workspace_bytes", "smc_b
            "smc_batch_destroy",
            "smc_chains_spin_bytes", "smc_chains_coupling_bytes", "smc_chains_bond_bytes",
            "smc_chains_workspace_bytes", "smc_chains_init", "smc_chains_sample",
-           "smc_chains_covariance", "smc_chains_half_sweep", "smc_chains_kernel_name",
+           "smc_chains_covariance", "smc_chains_replay", "smc_chains_half_sweep", "smc_chains_kernel_name",
            "smc_chains_mean", "smc_chains_dot", "smc_chains_vjp", "smc_chains_lnz_grad",
            "smc_chains_fit_step",
            "smc_chains_get_sweep_index", "smc_chains_set_sweep_index",
@@ -158,6 +158,7 @@ def load_library():
                                     C.c_uint32, C.c_int32, vp, vp, vp, sz, vp]
     lib.smc_chains_sample.argtypes = [vp, C.c_double, C.c_int64, vp]
     lib.smc_chains_covariance.argtypes = [vp, C.c_double, C.c_int64, vp, vp, vp, vp]
+    lib.smc_chains_replay.argtypes = [vp, C.c_double, C.c_int64, C.c_uint64, vp, vp, vp, vp, vp, vp]
     lib.smc_chains_mean.argtypes = [vp, vp, C.c_int64, vp]
     lib.smc_chains_dot.argtypes = [vp, vp, vp, vp]
     lib.smc_chains_vjp.argtypes = [vp, C.c_double, C.c_int64, vp, vp, vp, vp, vp, vp]
@@ -652,6 +653,24 @@ class Chains:
                                                     C.c_void_p(g.data_ptr()), gc,
                                                     C.c_void_p(cov_acc.data_ptr()),
                                                     C.c_void_p(G_acc.data_ptr())))
+
+    def replay(self, beta: float, n_sweeps: int, t0: int, J, start, g, g_center):
+        """The covariance replay of n_sweeps sampling sweeps from the spins
+        `start`, couplings J (float32) and counter t0; the chains themselves
+        stay where they are.  Returns (cov_acc, G_acc)."""
+        t = self.torch
+        self._bonds_f32(J)
+        self._bonds_f64(g)
+        self._bonds_f64(g_center, full=False)
+        assert start.dtype == t.int8 and start.is_contiguous() and start.is_cuda
+        assert start.numel() == self.n_chains * self.N
+        cov = t.empty((self.d, 2, self.N // 2), dtype=t.float64, device=self.device)
+        G = t.empty(2, dtype=t.float64, device=self.device)
+        _check(load_library().smc_chains_replay(self._h, float(beta), int(n_sweeps), int(t0),
+                                                C.c_void_p(J.data_ptr()), C.c_void_p(start.data_ptr()),
+                                                C.c_void_p(g.data_ptr()), C.c_void_p(g_center.data_ptr()),
+                                                C.c_void_p(cov.data_ptr()), C.c_void_p(G.data_ptr())))
+        return cov, G
 
     # -- finishing the estimates (the library's FP64 kernels) ---------------
     def _bonds_f64(self, a, full=True):

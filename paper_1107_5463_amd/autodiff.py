@@ -9,7 +9,7 @@ product across bond b, real couplings J_b):
     d <x_a> / d beta = Cov(x_a, sum_b J_b x_b)
 
 Every step runs in the library's kernels: `smc_chains_sample` sums x_b over
-chains and sweeps; `smc_chains_mean` forms <x_b>; `smc_chains_covariance`
+chains and sweeps; `smc_chains_mean` forms <x_b>; `smc_chains_replay`
 replays the same sweeps from the saved start state and counter
 (counter-based random numbers make the replay exact) and sums (G - c) x_b for
 G = sum_a g_a x_a, the vector-Jacobian product's weights, centred on
@@ -65,20 +65,18 @@ class BondCorrelations(torch.autograd.Function):
     def backward(ctx, grad):
         J, mean, start = ctx.saved_tensors
         ch = ctx.chains
-        # replay the forward sweeps from their start, then put the chains back
-        end, t_end, J_now = ch.spins.clone(), ch.t, ch.J.clone()
-        ch.set_couplings(J)
-        ch.spins.copy_(start)
-        ch.t = ctx.t0
+        # (a saved-tensor hook may hand back another layout or device)
+        start = start.to(ch.device).contiguous()
+        if start.data_ptr() % 16:
+            start = start.clone()
         g = grad.to(torch.float64).contiguous()
         center = ch.dot(g, mean)
-        cov_acc = torch.zeros_like(mean)
-        G_acc = torch.zeros(2, dtype=torch.float64, device=mean.device)
-        ch.covariance(ctx.b, ctx.n_sweeps, g, center, cov_acc, G_acc)
+        # the chains stay where they are: the replay reads the kept start
+        cov_acc, G_acc = ch.replay(ctx.b, ctx.n_sweeps, ctx.t0, J, start, g, center)
         grad_J, grad_beta = ch.vjp(ctx.b, ch.n_chains * ctx.n_sweeps, cov_acc, G_acc, mean, J)
-        ch.spins.copy_(end)
-        ch.t = t_end
-        ch.set_couplings(J_now)
+        if isinstance(ch.stream, torch.cuda.Stream) and ch.stream != torch.cuda.current_stream(ch.device):
+            for x in (start, J, mean, g, center, cov_acc, G_acc):
+                x.record_stream(ch.stream)
         return (grad_J.to(ctx.J_dtype), grad_beta.reshape(()).to(ctx.beta_dtype), None, None,
                 None)
 

@@ -82,6 +82,7 @@ __global__ __launch_bounds__(1024) void chains_kernel(const ChainsLaunch a, int8
   const uint32_t chain = blockIdx.x;
   const uint32_t replica = a.key.replica + chain;
   int8_t* gs = spins + (uint64_t)chain * N;
+  const int8_t* from = a.start ? a.start + (uint64_t)chain * N : gs;
   // LDS: kRed doubles of reduction scratch, the accumulator (4 or 8 bytes per
   // bond), the couplings (JL), then both colour planes
   constexpr size_t kAcc = MODE == 1 ? 8 : 4;  // bytes per bond (chains_lds_bytes)
@@ -95,7 +96,7 @@ __global__ __launch_bounds__(1024) void chains_kernel(const ChainsLaunch a, int8
   const float bl2e = beta_log2e(a.beta);
 
   for (uint32_t w = threadIdx.x; w < N / 4; w += blockDim.x)
-    reinterpret_cast<uint32_t*>(lat)[w] = reinterpret_cast<const uint32_t*>(gs)[w];
+    reinterpret_cast<uint32_t*>(lat)[w] = reinterpret_cast<const uint32_t*>(from)[w];
   if (JL)
     for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x) Jl[b] = a.J[b];
   for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x) {
@@ -198,8 +199,9 @@ __global__ __launch_bounds__(1024) void chains_kernel(const ChainsLaunch a, int8
     // the next colour-0 pass writes only sites whose bonds this lane owns
   }
   __syncthreads();
-  for (uint32_t w = threadIdx.x; w < N / 4; w += blockDim.x)
-    reinterpret_cast<uint32_t*>(gs)[w] = reinterpret_cast<const uint32_t*>(lat)[w];
+  if (MODE != 1 || !a.start)
+    for (uint32_t w = threadIdx.x; w < N / 4; w += blockDim.x)
+      reinterpret_cast<uint32_t*>(gs)[w] = reinterpret_cast<const uint32_t*>(lat)[w];
   if (MODE == 0) {
     for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x)
       if (acc_i[b] != 0)
@@ -264,12 +266,13 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
   const uint32_t q = threadIdx.x;
   const bool active = q < pairs;
   int8_t* gs = spins + (uint64_t)chain * N;
+  const int8_t* from = a.start ? a.start + (uint64_t)chain * N : gs;
   double* red = reinterpret_cast<double*>(smem);
   int8_t* lat = reinterpret_cast<int8_t*>(smem + kPairRed * sizeof(double));
   const float bl2e = beta_log2e(a.beta);
 
   for (uint32_t w = q; w < N / 4; w += blockDim.x)
-    reinterpret_cast<uint32_t*>(lat)[w] = reinterpret_cast<const uint32_t*>(gs)[w];
+    reinterpret_cast<uint32_t*>(lat)[w] = reinterpret_cast<const uint32_t*>(from)[w];
   __syncthreads();
 
   // the lane's four sites: (c, 2q + b)
@@ -418,8 +421,9 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
     if (slot == 7u || sw + 1u == n_sweeps) flush(slot + 1u);
   }
 
-  for (uint32_t w = q; w < N / 4; w += blockDim.x)
-    reinterpret_cast<uint32_t*>(gs)[w] = reinterpret_cast<const uint32_t*>(lat)[w];
+  if (MODE != 1 || !a.start)
+    for (uint32_t w = q; w < N / 4; w += blockDim.x)
+      reinterpret_cast<uint32_t*>(gs)[w] = reinterpret_cast<const uint32_t*>(lat)[w];
   if (MODE == 1) {
     __syncthreads();
     if (q < 8u) {
@@ -451,7 +455,7 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
     }
 }
 
-// Sum the per-chain covariance partials into the caller's accumulators: 64
+// Sum the per-chain covariance partials into (add), or to, the caller's accumulators: 64
 // bonds a workgroup, its 16 waves taking a run of chains each (four loads in
 // flight), then the runs in chain order -- a fixed order, deterministic.  One
 // thread a bond over all chains left 32 workgroups waiting on one load at a
@@ -460,7 +464,7 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
 __global__ __launch_bounds__(1024) void chains_reduce_kernel(const double* __restrict__ part,
                                                              const double* __restrict__ gpart,
                                                              const uint32_t n_chains,
-                                                             const uint32_t nb,
+                                                             const uint32_t nb, const int add,
                                                              double* __restrict__ cov_acc,
                                                              double* __restrict__ G_acc) {
   __shared__ double sh[16][64];
@@ -490,7 +494,7 @@ __global__ __launch_bounds__(1024) void chains_reduce_kernel(const double* __res
 #pragma unroll
     for (uint32_t w = 0; w < 16u; ++w) t += sh[w][lane];
     double* dst = last ? G_acc : cov_acc;
-    dst[b] += t;
+    dst[b] = add ? dst[b] + t : t;
   }
 }
 
@@ -728,7 +732,7 @@ hipError_t launch_chains_covariance(const ChainsLaunch& a, int8_t* spins, uint32
   if (e != hipSuccess) return e;
   const uint32_t nb = (uint32_t)(a.g.d * 2 * a.g.Nh);
   hipLaunchKernelGGL(chains_reduce_kernel, dim3((nb + 63) / 64 + 1), dim3(1024), 0, st, part, gpart,
-                     a.n_chains, nb, cov_acc, G_acc);
+                     a.n_chains, nb, a.start ? 0 : 1, cov_acc, G_acc);
   return hipGetLastError();
 }
 

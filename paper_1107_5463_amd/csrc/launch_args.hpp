@@ -158,6 +158,8 @@ struct ChainsLaunch {
   float beta;
   uint32_t n_chains;
   FastDiv divR, divL;  // plane row length L/2, edge L
+  const int8_t* start; // covariance replay from these spins, which stay as they are (sums
+                       // overwritten), or null: from the chains' own, which move (sums added to)
   int pair_kernel;     // one pair of sites per lane, state in registers (N/4 <= 1024)
 };
 

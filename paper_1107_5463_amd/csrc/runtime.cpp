@@ -2228,6 +2228,7 @@ ChainsLaunch chains_args(const smc_chains* h, double beta) {
   a.divR = make_fastdiv((uint32_t)h->g.R);
   a.divL = make_fastdiv((uint32_t)h->g.L);
   a.pair_kernel = h->pair_kernel;
+  a.start = nullptr;
   return a;
 }
 
@@ -2378,6 +2379,26 @@ int smc_chains_covariance(smc_chains* h, double beta, int64_t n_sweeps, const do
   if (rc != SMC_OK) return rc;
   h->t += (uint64_t)n_sweeps;
   return SMC_OK;
+}
+
+int smc_chains_replay(smc_chains* h, double beta, int64_t n_sweeps, uint64_t t0, const float* dev_J,
+                      const void* dev_start, const double* dev_g, const double* dev_g_center,
+                      double* dev_cov, double* dev_G) {
+  if (!h) return fail(SMC_EINVAL, "handle is NULL");
+  if (!beta_ok(beta)) return fail(SMC_EINVAL, "beta must be >= 0 (or +inf), not NaN");
+  if (n_sweeps < 1) return fail(SMC_EINVAL, "n_sweeps must be >= 1");
+  if (!al4(dev_J)) return fail(SMC_EINVAL, "J must be non-NULL and 4-byte aligned");
+  if (!dev_start || ((uintptr_t)dev_start & 15)) return fail(SMC_EINVAL, "start must be 16-byte aligned");
+  if (!al8(dev_g) || !al8(dev_cov) || !al8(dev_G) || ((uintptr_t)dev_g_center & 7))
+    return fail(SMC_EINVAL, "g, cov and G must be non-NULL and 8-byte aligned, g_center so or NULL");
+  if (t0 > 4294967296ull || (uint64_t)n_sweeps > 4294967296ull - t0)
+    return fail(SMC_ERANGE, "sweep counter would exceed 2^32");
+  ChainsLaunch a = chains_args(h, beta);
+  a.J = dev_J;
+  a.start = (const int8_t*)dev_start;
+  return check(launch_chains_covariance(a, (int8_t*)h->spins, (uint32_t)t0, (uint32_t)n_sweeps, dev_g,
+                                        dev_g_center, h->part, h->gpart, dev_cov, dev_G, h->stream),
+               "chains covariance launch");
 }
 
 int smc_chains_mean(smc_chains* h, const int64_t* dev_bond_sum, int64_t n_samples,

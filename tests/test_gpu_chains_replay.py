@@ -1,0 +1,40 @@
+"""The covariance replay from a kept start: the sums of the replay that moves
+the chains, bit for bit, with the chains left where they are."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kernel", ["pair", "lds"])
+@pytest.mark.parametrize("d,L,count,sweeps", [(2, 4, 3, 1), (2, 64, 20, 9), (2, 96, 5, 8), (3, 8, 17, 10)])
+def test_replay_equals_covariance(smc_gpu, monkeypatch, d, L, count, sweeps, kernel):
+    print(f"replay d={d} L={L} count={count} {kernel}", flush=True)
+    if kernel == "lds":
+        monkeypatch.setenv("SMC_CHAINS_KERNEL", "lds")
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    shape = (d, 2, L ** d // 2)
+    J = 1.0 + 0.2 * torch.randn(shape, generator=gen, device="cuda")
+    g = torch.randn(shape, generator=gen, device="cuda", dtype=torch.float64)
+    centre = torch.full((1,), 0.7, dtype=torch.float64, device="cuda")
+    ch = smc_gpu.Chains(d, L, count, 5, J=J)
+    ch.sample(0.4, 3)
+    start, t0 = ch.spins.clone(), ch.t
+    cov = torch.zeros(shape, dtype=torch.float64, device="cuda")
+    G = torch.zeros(2, dtype=torch.float64, device="cuda")
+    ch.covariance(0.4, sweeps, g, centre, cov, G)
+    # the chains move on, under other couplings
+    ch.set_couplings(J * 0.5)
+    ch.sample(0.4, 4)
+    end, t_end, J_end = ch.spins.clone(), ch.t, ch.J.clone()
+    for _ in range(2):  # into fresh buffers, whatever they hold
+        cov2, G2 = ch.replay(0.4, sweeps, t0, J, start, g, centre)
+        assert torch.equal(cov, cov2) and torch.equal(G, G2)
+    assert torch.equal(ch.spins, end) and ch.t == t_end and torch.equal(ch.J, J_end)
+
+
+def test_replay_refuses_no_sweeps(smc_gpu):
+    ch = smc_gpu.Chains(2, 8, 2, 5)
+    z = torch.zeros((2, 2, 32), dtype=torch.float64, device="cuda")
+    with pytest.raises(smc_gpu.SmcError):
+        ch.replay(0.4, 0, 0, ch.J, ch.spins, z, torch.zeros(1, dtype=torch.float64, device="cuda"))
