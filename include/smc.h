@@ -31,7 +31,7 @@
  *          uniform or +-1 couplings, two copies at one bit per site (and the
  *          bonds' signs) that calls of several sweeps may work on, or, for
  *          continuous spins and FP32 couplings up to 2^21 sites, two copies
- *          of the spins for such calls.
+ *          of the spins for such calls (one, for larger 2D XY lattices).
  * Random numbers.  Philox4x32-10 (Salmon et al., SC'11), key = seed, counter
  *   = (block, sweep t, replica, colour | purpose << 1); the same (seed,
  *   replica) gives the same chain whatever the launch geometry or schedule.

@@ -13,7 +13,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libsmc.so")
-SOURCES = ["ising.hip", "fused.hip", "packed.hip", "resident.hip", "tiles.hip", "tiles_ahead.hip", "batch.hip", "chains.hip", "continuous.hip", "brick.hip", "init.hip", "measure.hip",
+SOURCES = ["ising.hip", "fused.hip", "packed.hip", "resident.hip", "tiles.hip", "tiles_ahead.hip", "batch.hip", "chains.hip", "continuous.hip", "brick.hip", "march.hip", "init.hip", "measure.hip",
            "probe.hip", "runtime.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

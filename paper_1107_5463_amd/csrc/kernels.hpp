@@ -52,6 +52,13 @@ uint32_t tile_ahead_waves(const Geom& g, uint32_t T, bool heatbath);
 hipError_t launch_tile_ahead_pass(const IsingLaunch& a, bool heatbath, uint32_t T, uint32_t hits,
                                   int8_t* spins, uint32_t t, uint32_t tc, hipStream_t st, uint32_t waves);
 
+// One or two sweeps of a 2D XY lattice from src to dst in one pass, in bands of
+// about `rows` rows (march.hip).
+bool xy_march_supported(const Geom& g);
+uint32_t xy_march_rows(const Geom& g);  // 0: half-sweeps in place are faster
+hipError_t launch_xy_march(const ContLaunch& a, int sweeps, uint32_t rows, const float* src, float* dst,
+                           uint32_t t0, void* partials, int64_t* nparts, hipStream_t st);
+
 // Sweeps of bricks of the lattice held in LDS (brick.hip).
 hipError_t launch_brick(const BrickLaunch& a, hipStream_t st);
 size_t brick_lds_bytes(int n, uint32_t positions);

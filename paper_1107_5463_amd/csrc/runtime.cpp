@@ -105,6 +105,8 @@ struct smc_lattice {
   char* brick_work[2];       // two copies of the spins (several bricks)
   int64_t brick_sweeps;      // the call the plan below is for (0: none yet)
   BrickPlan brick;
+  uint32_t march_rows;       // rows of a band of the 2D XY pass (SMC_XY_MARCH overrides; 0: off)
+  char* march_work;          // its second buffer
   uint32_t* work_bonds;      // bond-sign words, or the packed couplings (+-1 couplings)
   uint32_t* work_masks;      // masks of a call's half-sweeps (drawn_steps of them)
   // workspace carve-up
@@ -765,6 +767,36 @@ size_t brick_bytes(const smc_params* p) {
   return brick_params(p) ? 2 * round_up(spin_bytes(p), kAlign) : 0;
 }
 
+// 2D XY lattices whose calls of several sweeps may run from one buffer to the
+// other (march.hip).
+bool march_params(const smc_params* p) {
+  return p->n == 2 && p->J_kind == SMC_J_UNIFORM && p->tile == 0 && xy_march_supported(make_geom(p)) &&
+         n_sites(p) <= (1 << 28) &&
+         !(p->flags & (SMC_FLAG_GENERIC_KERNEL | SMC_FLAG_FAST_MATH | SMC_FLAG_SCHEDULE_FUSED));
+}
+
+// n >= 2 sweeps in an even number of passes of two sweeps or one.
+int march_run(smc_lattice* h, double beta, int64_t n, void* dev_obs) {
+  const ContLaunch a = cont_args(h, beta);
+  const int64_t passes = (n + 3) / 4 * 2;
+  for (int64_t k = 0; k < passes; ++k) {
+    const int sweeps = k < n - passes ? 2 : 1;
+    const float* src = (const float*)(k % 2 ? (void*)h->march_work : h->spins);
+    float* dst = (float*)(k % 2 ? h->spins : (void*)h->march_work);
+    const bool meas = dev_obs && k + 1 == passes;
+    int64_t nparts = 0;
+    int rc = check(launch_xy_march(a, sweeps, h->march_rows, src, dst, (uint32_t)h->t,
+                                   meas ? h->partials : nullptr, &nparts, h->stream),
+                   "XY pass launch");
+    if (rc != SMC_OK) return rc;
+    h->t += (uint64_t)sweeps;
+    if (meas)
+      return check(launch_finish(measure_args(h, (int64_t)h->t), h->partials, nparts, dev_obs, h->stream),
+                   "measurement finish launch");
+  }
+  return SMC_OK;
+}
+
 // The launch of `sweeps` sweeps in nb bricks with V positions a lane; false if
 // it does not fit.
 bool brick_shape(const smc_lattice* h, uint32_t sweeps, const uint32_t nb[3], uint32_t V, BrickLaunch& a) {
@@ -985,7 +1017,7 @@ int sweeps_impl(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, bo
   }
   int64_t planned = 0;  // sweeps before it run as planned
   for (int64_t k = 0; k < n_sweeps; ++k) {
-    if (h->brick_ok && !half && k >= planned) {
+    if ((h->brick_ok || h->march_rows) && !half && k >= planned) {
       // up to the next renormalisation, the sweep before it included
       const uint64_t every = h->p.n > 1 ? (uint64_t)h->p.renorm_every : 0;
       int64_t m = n_sweeps - k;
@@ -994,9 +1026,10 @@ int sweeps_impl(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, bo
         h->brick = plan_bricks(h, m);
         h->brick_sweeps = m;
       }
-      if (h->brick.launches) {
+      if (h->brick.launches || (h->march_rows && m >= 2)) {
         const bool end = k + m == n_sweeps, renorm = every && (h->t + (uint64_t)m) % every == 0;
-        int rc = brick_run(h, beta, m, end && !renorm ? dev_obs : nullptr, h->brick);
+        void* obs = end && !renorm ? dev_obs : nullptr;
+        int rc = h->brick.launches ? brick_run(h, beta, m, obs, h->brick) : march_run(h, beta, m, obs);
         if (rc == SMC_OK && renorm)
           rc = check(launch_renormalize(h->g, h->p.n, (float*)h->spins, h->stream), "renormalisation launch");
         if (rc == SMC_OK && renorm && end && dev_obs)
@@ -1246,6 +1279,7 @@ size_t smc_workspace_bytes(const smc_params* p) {
   if ((p->flags & SMC_FLAG_SCHEDULE_FUSED) && !is_packed(p)) b += round_up(spin_bytes(p), kAlign);
   b += multi_bytes(p);
   b += brick_bytes(p);
+  if (march_params(p)) b += round_up(spin_bytes(p), kAlign);
   return b;
 }
 
@@ -1376,6 +1410,15 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
     if (got == 5 && v_ok && f[0] <= 1024 && std::max({f[1], f[2], f[3]}) <= 4096 && (p->d == 3 || f[3] == 1))
       for (int k = 0; k < 5; ++k) h->forced_brick[k] = f[k];
   }
+  h->march_rows = march_params(p) ? xy_march_rows(h->g) : 0u;
+  if (p->n > 1)
+    for (const char* v : {"SMC_CONT_KERNEL", "SMC_CONT_ROWS", "SMC_CONT_SPL"})
+      if (std::getenv(v)) h->march_rows = 0u;
+  if (const char* v = std::getenv("SMC_XY_MARCH"))
+    if (march_params(p)) {
+      const long rows = std::strtol(v, nullptr, 10);
+      h->march_rows = rows < 2 ? 0u : (uint32_t)std::min(rows, 65536l);
+    }
   h->use_fused = p->n == 1 && !is_packed(p) && p->tile == 0 && !(p->flags & SMC_FLAG_HEATBATH) &&
                  (p->flags & SMC_FLAG_SCHEDULE_FUSED) &&
                  !(p->flags & SMC_FLAG_GENERIC_KERNEL) &&
@@ -1401,6 +1444,7 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
     char* w = h->ws + 2 * kAlign + partial_bytes(p);
     h->brick_work[0] = w;  // (never with the buffers below: brick_params, multi_params)
     h->brick_work[1] = w + round_up(spin_bytes(p), kAlign);
+    h->march_work = w + brick_bytes(p);
     const size_t plane = 4 * (size_t)plane_words(h->g);
     h->work[0] = (uint32_t*)w;
     h->work[1] = (uint32_t*)(w + round_up(2 * plane, kAlign));

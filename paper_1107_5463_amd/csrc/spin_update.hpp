@@ -73,9 +73,11 @@ __device__ __forceinline__ bool xy_update(float& s0, float& s1, const float h[3]
     sincos_f<true>(delta * (2.0f * u01f(wprop) - 1.0f), &sD, &cD);
   else
     sincos_turns((delta * 0.159154943091895335769f) * (2.0f * u01f(wprop) - 1.0f), &sD, &cD);
-  const float n0 = s0 * cD - s1 * sD;
-  const float n1 = s1 * cD + s0 * sD;
-  const float dE = -((n0 - s0) * h[0] + (n1 - s1) * h[1]);
+  // (the fused products written out: left to the compiler, which of two products
+  // is fused depends on the code around them, and kernels must agree in all bits)
+  const float n0 = fmaf(s0, cD, -(s1 * sD));
+  const float n1 = fmaf(s0, sD, s1 * cD);
+  const float dE = -fmaf(n0 - s0, h[0], (n1 - s1) * h[1]);
   const bool accept = cont_accept<FAST>(dE, wacc, beta, bl2e);
   if (accept) {
     s0 = n0;
