@@ -7,8 +7,9 @@ start from seed 2, beta = 0.4406868, 1000 sweeps with energy and
 magnetisation measured every 10 sweeps.  One step = 10 sweeps + one
 measurement written to a device ring (no host synchronisation inside the
 timed region).  Ising spins are stored at one bit per site by default (the
-same chain, bit for bit, as int8 spins); the int8 two-pass schedule, which is
-HBM-bound, is measured beside it in the same run.  Other workloads
+same chain, bit for bit, as int8 spins); int8 spins, whose calls of several
+sweeps run on a copy at one bit per site, and the int8 two-pass schedule, which
+is HBM-bound, are measured beside it in the same run.  Other workloads
 (--workload): 3D Ising L = 512, 2D XY L = 4096, 3D Heisenberg L = 256 (FP32
 spins), the batched +-J spin glass (2048 lattices of L in {8,12,16,24,32},
 32 temperatures), and the derivatives of ln Z (256 chains of a 2D L = 64
@@ -24,7 +25,8 @@ Prints one JSON line:
             count over 78.6 Tops/s); `traffic` is the HBM bytes per launch read
             from the committed rocprofv3 counter summary when it was taken on
             the current kernel sources, else null;
-  int8_two_pass  the same workload with int8 spins (its HBM roofline);
+  int8       the same workload with int8 spins, as a program's calls run;
+  int8_two_pass  the same by the two-pass int8 kernel (its HBM roofline);
   cpu_baseline  the FP64 CPU oracle timed on the host on a bounded sample of
             the same workload, whose result is also compared with the GPU's.
 """
@@ -68,10 +70,12 @@ KERNEL_SOURCES = {
     "ising_fused": ["fused.hip", "chunk.hpp", "device.hpp", "launch_args.hpp", "reduce.hpp"],
     "ising_packed": ["packed.hip", "packed.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp",
                      "reduce.hpp"],
-    "ising_tiles": ["tiles.hip", "packed.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp"],
-    "ising_tiles_packed": ["tiles.hip", "packed.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp"],
-    "xy_stream": ["continuous.hip", "chunk.hpp", "device.hpp", "launch_args.hpp"],
-    "heisenberg_stream": ["continuous.hip", "chunk.hpp", "device.hpp", "launch_args.hpp"],
+    "ising_tiles": ["tiles.hip", "tiles_ahead.hip", "packed.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp"],
+    "ising_tiles_packed": ["tiles.hip", "tiles_ahead.hip", "packed.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp"],
+    "xy_stream": ["continuous.hip", "spin_update.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp"],
+    "xy_march": ["march.hip", "spin_update.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp"],
+    "heisenberg_stream": ["continuous.hip", "spin_update.hpp", "chunk.hpp", "device.hpp",
+                          "launch_args.hpp"],
     "batch": ["batch.hip", "packed.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp", "reduce.hpp"],
     "chains": ["chains.hip", "chunk.hpp", "device.hpp", "launch_args.hpp"],
     "probe": ["probe.hip", "device.hpp"],
@@ -94,10 +98,10 @@ def parse():
                     help="2D Ising only -- fused: one kernel per sweep with ping-pong buffers "
                          "(2 B/attempt); two-pass: one in-place kernel per colour (3 B/attempt)")
     ap.add_argument("--spins", choices=["packed", "int8"], default="packed",
-                    help="Ising plain sweeps: one bit per site (default; the int8 two-pass "
-                         "line is measured beside it) or int8 -- the same chain")
+                    help="Ising plain sweeps: one bit per site (default; the int8 lines are "
+                         "measured beside it) or int8 by the two-pass kernel -- the same chain")
     ap.add_argument("--no-int8-line", action="store_true",
-                    help="skip the int8 two-pass comparison line of a packed run")
+                    help="skip the int8 comparison lines of a packed run")
     ap.add_argument("--tile", type=int, default=0,
                     help="Ising workloads: the tiled k-hit schedule with tiles of this edge")
     ap.add_argument("--hits", type=int, default=100, help="k of the tiled schedule")
@@ -231,8 +235,18 @@ def timed_steps(lat, beta, K, W, S, torch):
     return ev_start.elapsed_time(ev_end), wall, obs
 
 
-def kernel_model(kname, n, N, sweeps, tile, hits):
+def without_env(name):
+    """An environment variable's value, removed until the caller puts it back."""
+    return os.environ.pop(name, None)
+
+
+def kernel_model(kname, n, N, sweeps, tile, hits, per_call=0):
     """(launches, algorithmic HBM bytes per launch, schedule) of the dominant kernel."""
+    if kname == "xy_march":
+        # a call of S sweeps: an even number of passes of two sweeps or one, each
+        # reading and writing both planes once
+        passes = (per_call + 3) // 4 * 2
+        return sweeps // per_call * passes, 2.0 * N * n * 4, "two sweeps a pass, ping-pong buffers, FP32 components"
     if kname in ("ising_tiles", "ising_tiles_packed"):
         # one launch per tile colour: its half of both planes read and written once
         return 2 * sweeps, 1.0 * N, f"tiled k-hit, T={tile}, k={hits}"
@@ -315,6 +329,8 @@ def run_lattice(args, wl, torch, smc):
     else:
         kw = dict(packed=packed, heatbath=args.heatbath, tile=args.tile,
                   hits=args.hits if args.tile else 0)
+    if n == 1 and args.spins == "int8" and not special:
+        os.environ["SMC_RESIDENT"] = "0"  # one launch a half-sweep
     lat = smc.Lattice(d, n, L, seed=wl["seed"], fused=fused, **kw)
     default_rows = lat.kernel()[1]
     if not args.no_autotune:
@@ -330,11 +346,15 @@ def run_lattice(args, wl, torch, smc):
     hits = args.hits if (n == 1 and args.tile) else 1
     attempts = N * sweeps * hits
     kname, band_rows = lat.kernel()
-    launches, bytes_per_launch, schedule = kernel_model(kname, n, N, sweeps, args.tile, args.hits)
+    if kname == "xy_stream" and d == 2 and L >= 2600 and S >= 2 and "SMC_XY_MARCH" not in os.environ:
+        kname = "xy_march"  # calls of several sweeps of a large 2D XY lattice
+    launches, bytes_per_launch, schedule = kernel_model(kname, n, N, sweeps, args.tile, args.hits, S)
+    if n == 1 and args.heatbath and not args.tile and S >= 2:
+        kname, schedule = "ising_resident", "several half-sweeps a launch, words in LDS"
     # the step time also holds the measurement finish (and renormalisation)
     # kernels: a conservative average of the dominant kernel
     kernel_ms = total_ms / launches
-    if kname in ("ising_packed", "ising_tiles", "ising_tiles_packed"):
+    if kname in ("ising_packed", "ising_tiles", "ising_tiles_packed", "ising_resident", "xy_march"):
         variant = None
         if kname in ("ising_tiles", "ising_tiles_packed"):
             variant = f"T={args.tile} k={args.hits} {'heat bath' if args.heatbath else 'Metropolis'}"
@@ -380,25 +400,38 @@ def run_lattice(args, wl, torch, smc):
         roof["copy_ceiling_GBps"] = copy_ceiling(torch, lat.device,
                                                  lat.spins.numel() * lat.spins.element_size())
     if packed and not args.no_int8_line:
-        # the same chain with int8 spins: the HBM-bound two-pass schedule
-        lat8 = smc.Lattice(d, n, L, seed=wl["seed"])
-        if not args.no_autotune:
-            lat8.autotune(beta)
-        ms8, _, obs8 = timed_steps(lat8, beta, K, W, S, torch)
-        k8, rows8 = lat8.kernel()
-        l8, b8, sch8 = kernel_model(k8, n, N, sweeps, 0, 1)
-        roof8 = hbm_roofline(k8, args.workload, b8, ms8 / l8)
-        roof8["copy_ceiling_GBps"] = copy_ceiling(torch, lat8.device,
-                                                  lat8.spins.numel() * lat8.spins.element_size())
-        result["int8_two_pass"] = {
-            "value": round(attempts / (ms8 * 1e6), 2),
-            "unit": "attempts/ns",
-            "ms_per_step": round(ms8 / max(K, 1), 4),
-            "schedule": sch8, "rows_per_band": rows8,
-            "roofline": roof8,
-            "same_final_state": bool(obs8 is not None and obs is not None and obs8.E_int == obs.E_int
-                                     and obs8.M_int == obs.M_int),
-        }
+        # the same chain with int8 spins: as a program's calls run (on a copy at
+        # one bit per site), then by the HBM-bound two-pass kernel
+        for key in ("int8", "int8_two_pass"):
+            resident = without_env("SMC_RESIDENT")
+            if key == "int8_two_pass":
+                os.environ["SMC_RESIDENT"] = "0"  # one launch a half-sweep
+            lat8 = smc.Lattice(d, n, L, seed=wl["seed"])
+            if not args.no_autotune:
+                lat8.autotune(beta)
+            ms8, _, obs8 = timed_steps(lat8, beta, K, W, S, torch)
+            k8, rows8 = lat8.kernel()
+            l8, b8, sch8 = kernel_model(k8, n, N, sweeps, 0, 1)
+            result[key] = {
+                "value": round(attempts / (ms8 * 1e6), 2),
+                "unit": "attempts/ns",
+                "ms_per_step": round(ms8 / max(K, 1), 4),
+                "same_final_state": bool(obs8 is not None and obs is not None and obs8.E_int == obs.E_int
+                                         and obs8.M_int == obs.M_int),
+            }
+            if key == "int8_two_pass":
+                roof8 = hbm_roofline(k8, args.workload, b8, ms8 / l8)
+                roof8["copy_ceiling_GBps"] = copy_ceiling(torch, lat8.device,
+                                                          lat8.spins.numel() * lat8.spins.element_size())
+                result[key].update(schedule=sch8, rows_per_band=rows8, roofline=roof8)
+            else:
+                result[key]["schedule"] = "each call on a copy at one bit per site, two-pass"
+            if resident is None:
+                os.environ.pop("SMC_RESIDENT", None)
+            else:
+                os.environ["SMC_RESIDENT"] = resident
+            if key == "int8":
+                del lat8
         del lat8
 
     if args.cpu_seconds > 0:
@@ -772,8 +805,9 @@ def attach_other_workloads(args, result, torch, smc):
         o["workload"] = r["config"]["workload"]
         o["kernel"], o["rows_per_band"] = r["config"]["kernel"], r["config"]["rows_per_band"]
         o["rows_autotuned"] = r["config"]["rows_autotuned"]
-        if "int8_two_pass" in r:
-            o["int8_two_pass"] = r["int8_two_pass"]
+        for key in ("int8", "int8_two_pass"):
+            if key in r:
+                o[key] = r[key]
         result[name] = o
         torch.cuda.empty_cache()
     # the paper's tiled k-hit schedule (k = 100) on the 2D lattice: its 16 x 16
