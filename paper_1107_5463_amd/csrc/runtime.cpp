@@ -65,6 +65,25 @@ struct BrickPlan {
   double us;
 };
 
+// The plans of a handle's last eight call lengths (a plan takes 20 to 40 us to
+// work out; calls of alternating lengths, or cut by renormalisations, reuse them).
+template <class P>
+struct PlanCache {
+  static constexpr uint32_t kSlots = 8;
+  int64_t key[kSlots];  // 0: empty
+  P plan[kSlots];
+  uint32_t next;
+  template <class Make>
+  const P& get(int64_t k, Make make) {
+    for (uint32_t i = 0; i < kSlots; ++i)
+      if (key[i] == k) return plan[i];
+    const uint32_t i = next++ % kSlots;
+    plan[i] = make();
+    key[i] = k;
+    return plan[i];
+  }
+};
+
 struct smc_lattice {
   smc_params p;
   Geom g;
@@ -97,14 +116,11 @@ struct smc_lattice {
   uint32_t forced_steps, forced_own;  // SMC_RESIDENT=steps,own[,drawn] (tests): that split always
   bool forced_drawn;
   uint32_t* work[2];         // two packed copies of the spins (multi-sweep calls)
-  int64_t plan_sweeps;       // the call the plan below is for (0: none yet)
-  bool plan_measured;
-  SweepPlan plan;
+  PlanCache<SweepPlan> plans;  // by 2 sweeps + measured
   bool brick_ok;             // calls of real-valued sweeps may run in bricks
   uint32_t forced_brick[5];  // SMC_BRICK=sweeps,nx,ny,nz,V (tests): that cut always
   char* brick_work[2];       // two copies of the spins (several bricks)
-  int64_t brick_sweeps;      // the call the plan below is for (0: none yet)
-  BrickPlan brick;
+  PlanCache<BrickPlan> bricks;  // by sweeps
   uint32_t march_rows;       // rows of a band of the 2D XY pass (SMC_XY_MARCH overrides; 0: off)
   char* march_work;          // its second buffer
   uint32_t* work_bonds;      // bond-sign words, or the packed couplings (+-1 couplings)
@@ -826,7 +842,8 @@ bool brick_shape(const smc_lattice* h, uint32_t sweeps, const uint32_t nb[3], ui
 // sites are still right (fewer as the halo is used up), their issue slots; the
 // start takes a term a wave and, in 3D where bricks have short rows, their
 // bytes in parts of cache lines.
-double brick_us(const smc_lattice* h, const BrickLaunch& a) {
+// `limit`: larger times are not worked out (any larger one is returned).
+double brick_us(const smc_lattice* h, const BrickLaunch& a, double limit) {
   static const double kFit[3][9] = {
       // start, step, step V, wave step V, wave V, wave, MB, MB of lines, MB of lines V
       {1.80, 0.25, 0.080, 0.000, 0.39, 0.21, 0.000, 0.0100, 0.0220},
@@ -836,6 +853,9 @@ double brick_us(const smc_lattice* h, const BrickLaunch& a) {
   const uint32_t edge[3] = {(uint32_t)h->g.R, (uint32_t)h->g.L, h->g.d == 3 ? (uint32_t)h->g.L : 1u};
   const uint32_t groups = a.nb[0] * a.nb[1] * a.nb[2], per = (groups + kCUs - 1) / kCUs;
   const double K = a.steps, V = a.V;
+  const double most = per * (double)((a.positions / a.V + 63) / 64) / 4;  // waves of a SIMD
+  const double least = f[0] + K * (f[1] + f[2] * V) + most * (f[4] * V + f[5]);
+  if (least >= limit) return least;
   uint32_t own[3];
   for (int k = 0; k < 3; ++k) {
     const uint32_t unit = k == 0 ? a.V : 1u;
@@ -894,11 +914,11 @@ BrickPlan plan_bricks(const smc_lattice* h, int64_t n_sweeps) {
   best.us = 0.9 * 2.0 * (double)n_sweeps * half;
   static const uint32_t kCuts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64};
   const uint32_t vmax = h->p.n == 3 ? 2 : 4;
-  auto consider = [&](uint32_t launches, const uint32_t nb[3]) {
+  const uint32_t L = (uint32_t)h->g.L, R = (uint32_t)h->g.R;
+  auto consider = [&](uint32_t launches, uint32_t per, const uint32_t nb[3]) {
     for (uint32_t V = 1; V <= vmax; V *= 2) {
-      const uint32_t per = (uint32_t)((n_sweeps + launches - 1) / launches);
       if (!brick_shape(h, per, nb, V, a)) continue;
-      const double us = launches * brick_us(h, a);
+      const double us = launches * brick_us(h, a, best.us / launches);
       if (us < best.us) {
         best.us = us;
         best.launches = launches;
@@ -908,27 +928,40 @@ BrickPlan plan_bricks(const smc_lattice* h, int64_t n_sweeps) {
     }
   };
   const uint32_t one[3] = {1, 1, 1};
-  if (n_sweeps <= (1 << 20)) consider(1, one);
+  if (n_sweeps <= (1 << 20)) consider(1, (uint32_t)n_sweeps, one);
+  // extent of a brick with its halo, 0: none of that cut (a smaller one gives
+  // the same bricks, or the halo does not fit).  (A few hundred cuts are worked
+  // out, 20 to 40 us, once a handle and call length.)
+  auto extent = [&](uint32_t edge, size_t k, uint32_t halo) -> uint32_t {
+    const uint32_t n = kCuts[k], own = (edge + n - 1) / n;
+    if (n == 1) return edge;
+    if (n > edge || own + 2 * halo > edge || own == (edge + kCuts[k - 1] - 1) / kCuts[k - 1]) return 0u;
+    return own + 2 * halo;
+  };
+  constexpr size_t kN = sizeof(kCuts) / sizeof(kCuts[0]);
   uint32_t last = 0;
   for (uint32_t m = 1; m <= 6 && m < n_sweeps; ++m) {
     if (n_sweeps > (int64_t)m << 20) break;
     const uint32_t launches = (uint32_t)((n_sweeps + m - 1) / m);
     if (launches == last || launches < 2) continue;
     last = launches;
-    for (const uint32_t nx : kCuts) {
-      if (nx > (uint32_t)h->g.R) break;
-      for (const uint32_t ny : kCuts) {
-        if (ny > (uint32_t)h->g.L || nx * ny > kBricks) break;
+    const uint32_t per = (uint32_t)((n_sweeps + launches - 1) / launches);
+    for (size_t ix = 0; ix < kN; ++ix) {
+      const uint32_t ex = extent(R, ix, per);
+      if (!ex) continue;
+      for (size_t iy = 0; iy < kN; ++iy) {
+        const uint32_t ey = extent(L, iy, 2 * per);
+        if (!ey || ex * ey > 1024 * vmax) continue;
         if (h->g.d == 2) {
-          const uint32_t nb[3] = {nx, ny, 1};
-          consider(launches, nb);
+          const uint32_t nb[3] = {kCuts[ix], kCuts[iy], 1};
+          consider(launches, per, nb);
           continue;
         }
-        for (const uint32_t nz : kCuts) {
-          if (nz < ny) continue;
-          if (nz > (uint32_t)h->g.L || nx * ny * nz > kBricks) break;
-          const uint32_t nb[3] = {nx, ny, nz};
-          consider(launches, nb);
+        for (size_t iz = iy; iz < kN; ++iz) {
+          const uint32_t ez = extent(L, iz, 2 * per);
+          if (!ez || ex * ey * ez > 1024 * vmax) continue;
+          const uint32_t nb[3] = {kCuts[ix], kCuts[iy], kCuts[iz]};
+          consider(launches, per, nb);
         }
       }
     }
@@ -1006,12 +1039,10 @@ int sweeps_impl(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, bo
   if (h->p.tile > 0) return tiled_sweeps(h, beta, n_sweeps, dev_obs);
   if (h->use_fused) return fused_sweeps(h, beta, n_sweeps, dev_obs);
   if (h->multi_ok && !half && n_sweeps > 0) {
-    if (h->plan_sweeps != n_sweeps || h->plan_measured != (dev_obs != nullptr)) {
-      h->plan = plan_sweeps(h, n_sweeps, dev_obs != nullptr);
-      h->plan_sweeps = n_sweeps;
-      h->plan_measured = dev_obs != nullptr;
-    }
-    const SweepPlan plan = h->plan;
+    const bool measured = dev_obs != nullptr;
+    // (a long call runs as several of at most 64 sweeps, planned alike)
+    const SweepPlan plan = h->plans.get(2 * std::min<int64_t>(n_sweeps, 64) + measured,
+                                        [&] { return plan_sweeps(h, n_sweeps, measured); });
     if (plan.way == kWayResident) return resident_sweeps(h, beta, n_sweeps, dev_obs, plan);
     if (plan.way == kWayPackedCopy) return packed_copy_sweeps(h, beta, n_sweeps, dev_obs);
   }
@@ -1022,14 +1053,11 @@ int sweeps_impl(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, bo
       const uint64_t every = h->p.n > 1 ? (uint64_t)h->p.renorm_every : 0;
       int64_t m = n_sweeps - k;
       if (every) m = (int64_t)std::min<uint64_t>((uint64_t)m, every - h->t % every);
-      if (h->brick_sweeps != m) {
-        h->brick = plan_bricks(h, m);
-        h->brick_sweeps = m;
-      }
-      if (h->brick.launches || (h->march_rows && m >= 2)) {
+      const BrickPlan brick = h->bricks.get(m, [&] { return plan_bricks(h, m); });
+      if (brick.launches || (h->march_rows && m >= 2)) {
         const bool end = k + m == n_sweeps, renorm = every && (h->t + (uint64_t)m) % every == 0;
         void* obs = end && !renorm ? dev_obs : nullptr;
-        int rc = h->brick.launches ? brick_run(h, beta, m, obs, h->brick) : march_run(h, beta, m, obs);
+        int rc = brick.launches ? brick_run(h, beta, m, obs, brick) : march_run(h, beta, m, obs);
         if (rc == SMC_OK && renorm)
           rc = check(launch_renormalize(h->g, h->p.n, (float*)h->spins, h->stream), "renormalisation launch");
         if (rc == SMC_OK && renorm && end && dev_obs)
@@ -1400,8 +1428,7 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
     for (const char* v : {"SMC_CONT_KERNEL", "SMC_CONT_ROWS", "SMC_CONT_SPL"})
       if (std::getenv(v)) h->brick_ok = false;
   std::memset(h->forced_brick, 0, sizeof(h->forced_brick));
-  h->brick_sweeps = 0;
-  std::memset(&h->brick, 0, sizeof(h->brick));
+  std::memset(&h->bricks, 0, sizeof(h->bricks));
   if (const char* v = std::getenv("SMC_BRICK")) {
     unsigned f[5] = {0, 0, 0, 0, 0};
     const int got = std::sscanf(v, "%u,%u,%u,%u,%u", f, f + 1, f + 2, f + 3, f + 4);
@@ -1429,7 +1456,7 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
     if (std::getenv(v)) h->multi_ok = false;
   h->forced_drawn = false;
   h->forced_steps = h->forced_own = 0;
-  h->plan_sweeps = 0;
+  std::memset(&h->plans, 0, sizeof(h->plans));
   if (const char* v = std::getenv("SMC_RESIDENT")) {
     char* end = nullptr;
     const long st = std::strtol(v, &end, 10), own = *end == ',' ? std::strtol(end + 1, &end, 10) : 0;
