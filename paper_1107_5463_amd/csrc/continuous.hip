@@ -481,14 +481,19 @@ bool cont_stream_supported(const Geom& g, uint32_t V, uint32_t H) {
          g.Nh < ((int64_t)1 << 30);  // 32-bit byte offsets within a plane
 }
 
-// Band height of the streaming kernel: the largest divisor of L up to 64 that
-// still gives at least `min_waves` waves.
+// Band height of the streaming kernel: the largest power of two up to 64 that
+// divides L and still gives at least `min_waves` waves (1536: XY, H = 4 / 8 / 16 /
+// 32, waves in brackets: 3D L = 192 18.3 (3456) / 15.8 (1728) / 18.2 / 33 us, L = 256
+// 40.6 / 38.3 / 32.2 (2048) / 34.5 (1024); 2D L = 2600 16.1 (3300) / 14.8 (1650)).
 uint32_t cont_rows_per_band(const Geom& g, uint32_t V, uint32_t min_waves) {
   const uint32_t Q = (uint32_t)g.R / V;
   uint32_t best = 4;
   // one site a lane (Heisenberg): taller bands lose more in waves than they
-  // save in halo rows (3D L = 256, H = 4 / 8 / 16 / 32: 50 / 57 / 68 / 76 us)
-  if (V == 1) return best;
+  // save in halo rows (3D L = 128, H = 4 / 8 / 16: 8.4 / 9.0 / 12.1 us, L = 256, H =
+  // 4 / 8 / 16 / 32: 50 / 57 / 68 / 76), but for half as many partials where the
+  // state is a few times the L2s (a measured sweep, H = 4 / 8: L = 144 32.3 / 30.0,
+  // L = 160 41.0 / 38.7, L = 192 59.9 / 57.4)
+  if (V == 1) return g.L % 8 == 0 && g.Nh >= 1400000 && g.Nh < 5000000 ? 8u : best;
   for (uint32_t H = 4; H <= 64; H *= 2) {
     if (g.L % H) break;
     const uint64_t waves = (uint64_t)Q * (uint64_t)(g.rows / H) / 64;

@@ -1411,7 +1411,7 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
       const long V = std::strtol(v, nullptr, 10);
       if (V > 0 && cont_sites_per_lane_ok(p->n, (uint32_t)V)) h->cont_spl = (uint32_t)V;
     }
-    h->cont_rows = cont_rows_per_band(h->g, h->cont_spl, 2048);
+    h->cont_rows = cont_rows_per_band(h->g, h->cont_spl, 1536);
     h->cont_row_sweeps = !named && !std::getenv("SMC_CONT_ROWS") && !std::getenv("SMC_CONT_SPL") &&
                          cont_prefers_row(h->g, p->n);
   }
