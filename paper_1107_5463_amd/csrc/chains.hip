@@ -245,8 +245,14 @@ __device__ __forceinline__ uint32_t swap_pair_lanes(uint32_t v) {
 // iff dE <= 0 or u < exp(-beta dE) (metropolis_fp32).
 // MODE 0: sample (bond sums), 1: covariance replay, 2: sweeps only (with
 // only_colour >= 0 and one sweep: that colour's half of sweep t0 alone).
+// The covariance replay of 3D lattices holds 96 registers of couplings, offsets,
+// weights and sums: workgroups of at most kPairCov3 lanes (L <= 12), above
+// which it runs chains_kernel (26 chains of L = 8, 80 sweeps: 272 us there, 101
+// here; 256 of L = 12, 100 sweeps: 510 / 169).
+constexpr uint32_t kPairCov3 = 512;
+
 template <int D, int MODE>
-__global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
+__global__ __launch_bounds__(D == 3 && MODE == 1 ? kPairCov3 : 1024u) void chains_pair_kernel(const ChainsLaunch a,
                                                           int8_t* __restrict__ spins,
                                                           const uint32_t t0, const uint32_t n_sweeps,
                                                           const int only_colour,
@@ -298,9 +304,7 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
 
   // colour-1 sites' bonds: m = 2 mu -> bond (mu, 1, j), m = 2 mu + 1 -> bond
   // (mu, 0, -mu neighbour of j)
-  // (with the covariance weights g_b of those bonds: the covariance replay of
-  // 3D lattices runs chains_kernel, whose chains are the same)
-  static_assert(MODE != 1 || D == 2, "3D covariance replays run chains_kernel");
+  // (with the covariance weights g_b of those bonds)
   auto bond_of = [&](uint32_t b, int m) -> uint32_t {
     const uint32_t mu = (uint32_t)m >> 1;
     return (m & 1) ? (2 * mu) * NhU + off[1][b][m] : (2 * mu + 1) * NhU + 2 * q + b;
@@ -318,11 +322,14 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
     }
 
   const uint32_t odd = q & 1u;
-  // Covariance: the bond products of up to eight sweeps (a byte each of xs)
+  // Covariance: the bond products of up to eight sweeps (2 B bits each of xs)
   // wait for one reduction of their eight G's -- per sweep it was a chain of
   // six double shuffles, two barriers and a serial sum over the waves, a third
   // of the replay (256 chains of L = 64, 100 sweeps: 248 us).
-  uint32_t xs[2] = {0u, 0u};
+  constexpr uint32_t kSlot = D == 2 ? 8u : 16u, kPer = 32u / kSlot;  // bits of a sweep, sweeps a word
+  uint32_t xs[8 / kPer];
+#pragma unroll
+  for (uint32_t w = 0; w < 8u / kPer; ++w) xs[w] = 0u;
   double Gsum = 0.0, G2sum = 0.0;  // thread s < 8: of the sweeps in slot s
   auto flush = [&](uint32_t n) {  // n sweeps wait (uniform)
     // G of each: the lane's signed weights, then over the wave by exchanging
@@ -330,7 +337,7 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
     double v[8];
 #pragma unroll
     for (uint32_t s = 0; s < 8u; ++s) {
-      const uint32_t bits = xs[s >> 2] >> (8u * (s & 3u));
+      const uint32_t bits = xs[s / kPer] >> (kSlot * (s % kPer));
       v[s] = 0.0;
 #pragma unroll
       for (uint32_t b = 0; b < 2; ++b)
@@ -363,14 +370,15 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
     for (uint32_t s = 0; s < 8u; ++s) {
       if (s < n) {
         const double Gc = red[s];
-        const uint32_t bits = xs[s >> 2] >> (8u * (s & 3u));
+        const uint32_t bits = xs[s / kPer] >> (kSlot * (s % kPer));
 #pragma unroll
         for (uint32_t b = 0; b < 2; ++b)
 #pragma unroll
           for (int m = 0; m < B; ++m) accd[b][m] += ((bits >> (b * B + m)) & 1u) ? -Gc : Gc;
       }
     }
-    xs[0] = xs[1] = 0u;
+#pragma unroll
+    for (uint32_t w = 0; w < 8u / kPer; ++w) xs[w] = 0u;
     // red is rewritten only after the next sweep's two barriers
   };
   for (uint32_t sw = 0; sw < n_sweeps; ++sw) {
@@ -415,9 +423,10 @@ __global__ __launch_bounds__(1024) void chains_pair_kernel(const ChainsLaunch a,
       __syncthreads();
     }
     if (MODE != 1) continue;
-    const uint32_t slot = sw & 7u;  // 2 B = 8 bits a sweep (D = 2)
-    if (slot < 4u) xs[0] |= xneg << (8u * slot);
-    else xs[1] |= xneg << (8u * (slot - 4u));
+    const uint32_t slot = sw & 7u;
+#pragma unroll
+    for (uint32_t w = 0; w < 8u / kPer; ++w)
+      if (slot / kPer == w) xs[w] |= xneg << (kSlot * (slot % kPer));
     if (slot == 7u || sw + 1u == n_sweeps) flush(slot + 1u);
   }
 
@@ -682,7 +691,7 @@ static hipError_t launch_chains(const ChainsLaunch& a, int mode, int8_t* spins, 
                                 const double* g, const double* gc, double* part, double* gpart,
                                 hipStream_t st) {
   const dim3 grid(a.n_chains), block(chains_threads(a.g));
-  if (a.pair_kernel && !(mode == 1 && a.g.d == 3)) {
+  if (a.pair_kernel && !(mode == 1 && a.g.d == 3 && chains_threads(a.g) > kPairCov3)) {
     const size_t lds = chains_pair_lds_bytes(a.g);
 #define SMC_CP(DD, MM)                                                                              \
   hipLaunchKernelGGL((chains_pair_kernel<DD, MM>), grid, block, lds, st, a, spins, t0, n_sweeps, \
@@ -690,7 +699,7 @@ static hipError_t launch_chains(const ChainsLaunch& a, int mode, int8_t* spins, 
     if (a.g.d == 2) {
       if (mode == 0) SMC_CP(2, 0); else if (mode == 1) SMC_CP(2, 1); else SMC_CP(2, 2);
     } else {
-      if (mode == 0) SMC_CP(3, 0); else SMC_CP(3, 2);
+      if (mode == 0) SMC_CP(3, 0); else if (mode == 1) SMC_CP(3, 1); else SMC_CP(3, 2);
     }
 #undef SMC_CP
     return hipGetLastError();

@@ -33,6 +33,39 @@ def test_replay_equals_covariance(smc_gpu, monkeypatch, d, L, count, sweeps, ker
     assert torch.equal(ch.spins, end) and ch.t == t_end and torch.equal(ch.J, J_end)
 
 
+@pytest.mark.parametrize("d,L,count,sweeps", [(3, 4, 9, 1), (3, 6, 5, 8), (3, 8, 7, 19), (3, 12, 3, 9), (3, 14, 2, 5),
+                                              (2, 16, 6, 17)])
+def test_covariance_pair_and_lds(smc_gpu, monkeypatch, d, L, count, sweeps):
+    """Both kernels' replays: the same chains; sums of the same terms in two
+    orders (3D: one wave, several, the most lanes the pair kernel takes, and
+    past them)."""
+    print(f"covariance kernels d={d} L={L}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    shape = (d, 2, L ** d // 2)
+    J = 1.0 + 0.2 * torch.randn(shape, generator=gen, device="cuda")
+    g = torch.randn(shape, generator=gen, device="cuda", dtype=torch.float64)
+    centre = torch.full((1,), -0.3, dtype=torch.float64, device="cuda")
+    out = []
+    for kernel in ("pair", "lds"):
+        if kernel == "lds":
+            monkeypatch.setenv("SMC_CHAINS_KERNEL", "lds")
+        else:
+            monkeypatch.delenv("SMC_CHAINS_KERNEL", raising=False)
+        ch = smc_gpu.Chains(d, L, count, 6, J=J)
+        ch.sample(0.25, 2)
+        cov = torch.zeros(shape, dtype=torch.float64, device="cuda")
+        G = torch.zeros(2, dtype=torch.float64, device="cuda")
+        ch.covariance(0.25, sweeps, g, centre, cov, G)
+        out.append((ch.spins.clone(), cov, G))
+    (sa, ca, Ga), (sb, cb, Gb) = out
+    assert torch.equal(sa, sb)
+    most = float(g.abs().sum()) + 0.3          # of |G - centre|
+    eps, S = 2.0 ** -52, count * sweeps
+    err = eps * most * (d * L ** d + S) * S    # rounding of each G and of the sums over S samples
+    assert float((ca - cb).abs().max()) <= err and abs(float(Ga[0] - Gb[0])) <= err
+    assert abs(float(Ga[1] - Gb[1])) <= 2 * most * err
+
+
 def test_replay_refuses_no_sweeps(smc_gpu):
     ch = smc_gpu.Chains(2, 8, 2, 5)
     z = torch.zeros((2, 2, 32), dtype=torch.float64, device="cuda")
