@@ -430,8 +430,8 @@ int smc_chains_half_sweep(smc_chains* h, double beta, int colour);
 
 /* Kernel the handle's sweeps launch: "chains_pair" (at most 1024 site pairs
  * per colour, N <= 4096: one pair of sites per lane, state and couplings in
- * registers) or "chains_lds" (larger lattices, or SMC_CHAINS_KERNEL=lds in the
- * environment at init). */
+ * registers) or "chains_lds" (larger lattices, which run the same with two or
+ * three pairs per lane, or SMC_CHAINS_KERNEL=lds in the environment at init). */
 const char* smc_chains_kernel_name(const smc_chains* h);
 
 int smc_chains_get_sweep_index(const smc_chains* h, uint64_t* t);

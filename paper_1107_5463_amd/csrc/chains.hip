@@ -5,7 +5,8 @@
 // correlations themselves (fluctuation-dissipation):
 //   d <x_a> / d J_b = beta Cov(x_a, x_b).
 //
-// One workgroup runs one chain entirely in LDS: both colour planes, plus a
+// One workgroup runs one chain.  chains_pair_kernel and chains_multi_kernel keep
+// it in registers and LDS (below); chains_kernel, the general one, in LDS: both colour planes, plus a
 // per-bond accumulator (int32 sums of x_b for sampling, FP64 sums of
 // (G - c) x_b for the covariance pass).  Chain k uses replica replica0 + k in
 // the Philox counter, so chain k reproduces the single-lattice chain with FP32
@@ -247,7 +248,7 @@ __device__ __forceinline__ uint32_t swap_pair_lanes(uint32_t v) {
 // only_colour >= 0 and one sweep: that colour's half of sweep t0 alone).
 // The covariance replay of 3D lattices holds 96 registers of couplings, offsets,
 // weights and sums: workgroups of at most kPairCov3 lanes (L <= 12), above
-// which it runs chains_kernel (26 chains of L = 8, 80 sweeps: 272 us there, 101
+// which it runs chains_multi_kernel (against chains_kernel, 26 chains of L = 8, 80 sweeps: 272 us there, 101
 // here; 256 of L = 12, 100 sweeps: 510 / 169).
 constexpr uint32_t kPairCov3 = 512;
 
@@ -462,6 +463,261 @@ __global__ __launch_bounds__(D == 3 && MODE == 1 ? kPairCov3 : 1024u) void chain
       else
         part[(uint64_t)chain * nbonds + bond] = accd[b][m];
     }
+}
+
+// The pair kernel for lattices of more pairs than lanes (2D L = 68 .. 96, 3D L =
+// 14 .. 18): PPL pairs a lane, pairs q, q + T, ..  What a pair keeps in registers
+// has to leave room for PPL of it in the 168 of a 768-lane workgroup: the
+// neighbours' offsets are 16 bits, the covariance weights are read at the flush
+// and its sums wait in LDS (both once in eight sweeps).  The LDS kernel draws
+// every block twice, works out neighbours every sweep and adds to a sum in LDS a
+// bond and sweep (us of 100 sweeps, it / here: 2D L = 68, 100 chains 336 / 163,
+// covariance 544 / 309; L = 88 553 / 270, 908 / 704; 70 of 2D L = 96, 250 chains 452 /
+// 259, 766 / 584; 3D L = 16, 64 chains covariance 673 / 567).
+constexpr uint32_t kMultiLanes = 768;
+
+template <int D, int MODE, int PPL>
+__global__ __launch_bounds__(kMultiLanes) void chains_multi_kernel(const ChainsLaunch a,
+                                                                   int8_t* __restrict__ spins,
+                                                                   const uint32_t t0, const uint32_t n_sweeps,
+                                                                   const int only_colour,
+                                                                   int64_t* __restrict__ bond_sum,
+                                                                   const double* __restrict__ gvec,
+                                                                   const double* __restrict__ gcp,
+                                                                   double* __restrict__ part,
+                                                                   double* __restrict__ gpart) {
+  constexpr int B = 2 * D;  // bonds (neighbours) per site
+  extern __shared__ __align__(16) unsigned char smem[];
+  const double gc = (MODE == 1 && gcp) ? *gcp : 0.0;
+  const uint32_t NhU = (uint32_t)a.g.Nh, N = 2u * NhU, nbonds = (uint32_t)D * N;
+  const uint32_t pairs = NhU / 2, T = blockDim.x, tid = threadIdx.x;
+  const uint32_t chain = blockIdx.x, replica = a.key.replica + chain;
+  int8_t* gs = spins + (uint64_t)chain * N;
+  const int8_t* from = a.start ? a.start + (uint64_t)chain * N : gs;
+  double* red = reinterpret_cast<double*>(smem);
+  double* accd = red + kPairRed;
+  int8_t* lat = reinterpret_cast<int8_t*>(accd + (MODE == 1 ? nbonds : 0u));
+  const float bl2e = beta_log2e(a.beta);
+  for (uint32_t w = tid; w < N / 4; w += T)
+    reinterpret_cast<uint32_t*>(lat)[w] = reinterpret_cast<const uint32_t*>(from)[w];
+  if (MODE == 1)
+    for (uint32_t b = tid; b < nbonds; b += T) accd[b] = 0.0;
+  __syncthreads();
+
+  uint32_t off[PPL][2][2][B / 2];  // LDS byte offsets of the neighbours (other plane), two a register
+  float Jv[PPL][2][2][B];
+  int sv[PPL][2][2];
+  auto at = [&](int p, int c, int b, int m) -> uint32_t {
+    return (off[p][c][b][m >> 1] >> (16 * (m & 1))) & 0xFFFFu;
+  };
+#pragma unroll
+  for (int p = 0; p < PPL; ++p) {
+    const uint32_t q = tid + (uint32_t)p * T;
+#pragma unroll
+    for (uint32_t c = 0; c < 2; ++c)
+#pragma unroll
+      for (uint32_t b = 0; b < 2; ++b) {
+        const uint32_t j = q < pairs ? 2 * q + b : 0u;
+        uint32_t nb[6];
+        neighbours32<D>(j, c, a.divR, a.divL, nb);
+#pragma unroll
+        for (int mu = 0; mu < D; ++mu) {
+          const uint32_t pl = (1 - c) * NhU;
+          off[p][c][b][mu] = (pl + nb[2 * mu]) | ((pl + nb[2 * mu + 1]) << 16);
+          Jv[p][c][b][2 * mu] = a.J[(2 * mu + c) * NhU + j];
+          Jv[p][c][b][2 * mu + 1] = a.J[(2 * mu + 1 - c) * NhU + nb[2 * mu + 1]];
+        }
+        sv[p][c][b] = lat[c * NhU + j];
+      }
+  }
+  // colour-1 site b of pair p: m = 2 mu -> bond (mu, 1, j), m = 2 mu + 1 -> bond
+  // (mu, 0, -mu neighbour of j).  Worked out where it is used: hidden from the
+  // compiler, which would keep the addresses of all bonds in registers over the
+  // sweeps
+  auto bond_of = [&](int p, int b, int m) -> uint32_t {
+    const uint32_t mu = (uint32_t)m >> 1;
+    uint32_t w = (m & 1) ? off[p][1][b][m >> 1] : tid;
+    asm volatile("" : "+v"(w));
+    return (m & 1) ? 2 * mu * NhU + (w >> 16) : (2 * mu + 1) * NhU + 2 * (w + (uint32_t)p * T) + (uint32_t)b;
+  };
+  int32_t acc[PPL][2][B];
+#pragma unroll
+  for (int p = 0; p < PPL; ++p)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int m = 0; m < B; ++m) acc[p][b][m] = 0;
+
+  const uint32_t odd = tid & 1u;
+  constexpr uint32_t kSlot = D == 2 ? 8u : 16u, kPer = 32u / kSlot;  // bits of a sweep, sweeps a word
+  uint32_t xs[PPL][8 / kPer];
+  auto clear = [&] {
+#pragma unroll
+    for (int p = 0; p < PPL; ++p)
+#pragma unroll
+      for (uint32_t w = 0; w < 8u / kPer; ++w) xs[p][w] = 0u;
+  };
+  clear();
+  double Gsum = 0.0, G2sum = 0.0;  // thread s < 8: of the sweeps in slot s
+  auto flush = [&](uint32_t n) {   // as in the pair kernel
+    double v[8];
+#pragma unroll
+    for (uint32_t s = 0; s < 8u; ++s) v[s] = 0.0;
+#pragma unroll
+    for (int p = 0; p < PPL; ++p) {
+      const bool active = tid + (uint32_t)p * T < pairs;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        // a site's weights at a time (all of them in flight would spill)
+        __builtin_amdgcn_sched_barrier(0);
+        double g[B];
+#pragma unroll
+        for (int m = 0; m < B; ++m) g[m] = active ? gvec[bond_of(p, b, m)] : 0.0;
+#pragma unroll
+        for (int m = 0; m < B; ++m)
+#pragma unroll
+          for (uint32_t s = 0; s < 8u; ++s)
+            v[s] += ((xs[p][s / kPer] >> (kSlot * (s % kPer) + (uint32_t)(b * B + m))) & 1u) ? -g[m] : g[m];
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t lane = tid & 63u, wave = tid >> 6, nw = (T + 63) >> 6;
+#pragma unroll
+    for (uint32_t w = 0; w < 3u; ++w) {
+      const bool up = (lane >> w) & 1u;
+#pragma unroll
+      for (uint32_t i = 0; i < (4u >> w); ++i) {
+        const double keep = up ? v[2 * i + 1] : v[2 * i], send = up ? v[2 * i] : v[2 * i + 1];
+        v[i] = keep + __shfl_xor(send, 1 << w);
+      }
+    }
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) v[0] += __shfl_xor(v[0], o);
+    if (lane < 8u) red[8u + 16u * lane + wave] = v[0];
+    __syncthreads();
+    if (tid < n) {
+      double sg = 0.0;
+      for (uint32_t k = 0; k < nw; ++k) sg += red[8u + 16u * tid + k];
+      red[tid] = sg - gc;
+      Gsum += sg - gc;
+      G2sum += (sg - gc) * (sg - gc);
+    }
+    __syncthreads();
+    double G[8];
+#pragma unroll
+    for (uint32_t s = 0; s < 8u; ++s) G[s] = s < n ? red[s] : 0.0;
+#pragma unroll
+    for (int p = 0; p < PPL; ++p) {
+      if (tid + (uint32_t)p * T < pairs) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int m = 0; m < B; ++m) {
+            double* to = accd + bond_of(p, b, m);
+            double sum = *to;
+#pragma unroll
+            for (uint32_t s = 0; s < 8u; ++s)
+              sum += ((xs[p][s / kPer] >> (kSlot * (s % kPer) + (uint32_t)(b * B + m))) & 1u) ? -G[s] : G[s];
+            *to = sum;
+          }
+        }
+      }
+    }
+    clear();
+    // red is rewritten only after the next sweep's two barriers
+  };
+  for (uint32_t sw = 0; sw < n_sweeps; ++sw) {
+    const uint32_t t = t0 + sw;
+    uint32_t wd[PPL][2][2], xneg[PPL];
+#pragma unroll
+    for (int p = 0; p < PPL; ++p) {
+      // (T is even: the lanes of a block's two pairs are neighbours for every p)
+      const uint32_t q = tid + (uint32_t)p * T;
+      const Rand4 r = philox(q >> 1, t, replica, tag(odd, kContinuous), a.key.k0, a.key.k1);
+      const uint32_t got0 = swap_pair_lanes(odd ? r.w[0] : r.w[2]);
+      const uint32_t got1 = swap_pair_lanes(odd ? r.w[1] : r.w[3]);
+      wd[p][0][0] = odd ? got0 : r.w[0];
+      wd[p][0][1] = odd ? got1 : r.w[1];
+      wd[p][1][0] = odd ? r.w[2] : got0;
+      wd[p][1][1] = odd ? r.w[3] : got1;
+      xneg[p] = 0u;
+    }
+#pragma unroll
+    for (uint32_t c = 0; c < 2; ++c) {
+      if (MODE == 2 && only_colour >= 0 && c != (uint32_t)only_colour) continue;
+#pragma unroll
+      for (int p = 0; p < PPL; ++p) {
+        const uint32_t q = tid + (uint32_t)p * T;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          int nv[B];
+#pragma unroll
+          for (int m = 0; m < B; ++m) nv[m] = lat[at(p, (int)c, b, m)];
+          float h = signed_by(Jv[p][c][b][0], nv[0]);
+#pragma unroll
+          for (int m = 1; m < B; ++m) h += signed_by(Jv[p][c][b][m], nv[m]);
+          const int si = sv[p][c][b];
+          const float dE = 2.0f * signed_by(h, si);
+          const bool accept = metropolis_fp32(dE, u01f(wd[p][c][b]), bl2e);
+          const int sn = accept ? -si : si;
+          sv[p][c][b] = sn;
+          if (q < pairs && accept) lat[c * NhU + 2 * q + (uint32_t)b] = (int8_t)sn;
+          if (MODE != 2 && c == 1) {
+#pragma unroll
+            for (int m = 0; m < B; ++m) {
+              if (MODE == 0) acc[p][b][m] += sn ^ nv[m];
+              if (MODE == 1) xneg[p] |= (uint32_t)(sn != nv[m]) << (b * B + m);
+            }
+          }
+        }
+      }
+      __syncthreads();
+    }
+    if (MODE != 1) continue;
+    const uint32_t slot = sw & 7u;
+#pragma unroll
+    for (int p = 0; p < PPL; ++p)
+#pragma unroll
+      for (uint32_t w = 0; w < 8u / kPer; ++w)
+        if (slot / kPer == w) xs[p][w] |= xneg[p] << (kSlot * (slot % kPer));
+    if (slot == 7u || sw + 1u == n_sweeps) flush(slot + 1u);
+  }
+
+  if (MODE != 1 || !a.start)
+    for (uint32_t w = tid; w < N / 4; w += T)
+      reinterpret_cast<uint32_t*>(gs)[w] = reinterpret_cast<const uint32_t*>(lat)[w];
+  if (MODE == 1) {
+    __syncthreads();
+    if (tid < 8u) {
+      red[tid] = Gsum;
+      red[8u + tid] = G2sum;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      for (uint32_t s = 1; s < 8u; ++s) {
+        Gsum += red[s];
+        G2sum += red[8u + s];
+      }
+      gpart[2 * chain] = Gsum;
+      gpart[2 * chain + 1] = G2sum;
+    }
+    double* pc = part + (uint64_t)chain * nbonds;
+    for (uint32_t b = tid; b < nbonds; b += T) pc[b] = accd[b];
+  }
+  if (MODE == 0) {
+#pragma unroll
+    for (int p = 0; p < PPL; ++p) {
+      if (tid + (uint32_t)p * T < pairs) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int m = 0; m < B; ++m)
+            atomicAdd(reinterpret_cast<unsigned long long*>(bond_sum + bond_of(p, b, m)),
+                      (unsigned long long)((int64_t)n_sweeps + acc[p][b][m]));
+      }
+    }
+  }
 }
 
 // Sum the per-chain covariance partials into (add), or to, the caller's accumulators: 64
@@ -702,6 +958,30 @@ static hipError_t launch_chains(const ChainsLaunch& a, int mode, int8_t* spins, 
       if (mode == 0) SMC_CP(3, 0); else if (mode == 1) SMC_CP(3, 1); else SMC_CP(3, 2);
     }
 #undef SMC_CP
+    return hipGetLastError();
+  }
+  const uint32_t pairs = (uint32_t)(a.g.Nh / 2), ppl = (pairs + kMultiLanes - 1) / kMultiLanes;
+  if (a.multi_kernel && ppl <= (a.g.d == 2 ? 3u : 2u)) {
+    const dim3 lanes(((pairs + ppl - 1) / ppl + 63) / 64 * 64);
+    const size_t bytes = kPairRed * sizeof(double) + 2 * (size_t)a.g.Nh * (1 + (mode == 1 ? 8 * a.g.d : 0));
+#define SMC_CX(DD, MM, PP)                                                                           \
+  do {                                                                                               \
+    if (bytes > 65536) {                                                                             \
+      const hipError_t e = allow_dynamic_lds((const void*)chains_multi_kernel<DD, MM, PP>, bytes);   \
+      if (e != hipSuccess) return e;                                                                 \
+    }                                                                                                \
+    hipLaunchKernelGGL((chains_multi_kernel<DD, MM, PP>), grid, lanes, bytes, st, a, spins, t0, n_sweeps, \
+                       only_colour, bond_sum, g, gc, part, gpart);                                   \
+  } while (0)
+#define SMC_CXM(DD, PP) \
+  do { if (mode == 0) SMC_CX(DD, 0, PP); else if (mode == 1) SMC_CX(DD, 1, PP); else SMC_CX(DD, 2, PP); } while (0)
+    if (a.g.d == 2) {
+      if (ppl == 3) SMC_CXM(2, 3); else SMC_CXM(2, 2);
+    } else {
+      if (ppl == 2) SMC_CXM(3, 2); else SMC_CX(3, 1, 1);
+    }
+#undef SMC_CXM
+#undef SMC_CX
     return hipGetLastError();
   }
   const size_t ljl = chains_lds_bytes_jl(a.g, mode);

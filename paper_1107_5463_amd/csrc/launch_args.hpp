@@ -161,6 +161,7 @@ struct ChainsLaunch {
   const int8_t* start; // covariance replay from these spins, which stay as they are (sums
                        // overwritten), or null: from the chains' own, which move (sums added to)
   int pair_kernel;     // one pair of sites per lane, state in registers (N/4 <= 1024)
+  int multi_kernel;    // larger ones: two or three pairs per lane
 };
 
 }  // namespace smc

@@ -2262,6 +2262,7 @@ struct smc_chains {
   double* gpart;  // [n_chains][2]
   hipStream_t stream;
   uint64_t t;
+  int multi_kernel;    // more pairs: two or three per lane, or the LDS kernel (0)
   int pair_kernel;  // the register-resident pair kernel (SMC_CHAINS_KERNEL=lds forces the other)
 };
 
@@ -2299,6 +2300,7 @@ ChainsLaunch chains_args(const smc_chains* h, double beta) {
   a.divR = make_fastdiv((uint32_t)h->g.R);
   a.divL = make_fastdiv((uint32_t)h->g.L);
   a.pair_kernel = h->pair_kernel;
+  a.multi_kernel = h->multi_kernel;
   a.start = nullptr;
   return a;
 }
@@ -2373,8 +2375,9 @@ int smc_chains_init(smc_chains** out, int32_t d, int32_t L, int32_t n_chains, ui
   h->stream = (hipStream_t)stream;
   h->t = 0;
   h->pair_kernel = chains_pair_supported(h->g) ? 1 : 0;
+  h->multi_kernel = 1;
   if (const char* v = std::getenv("SMC_CHAINS_KERNEL"))
-    if (std::string(v) == "lds") h->pair_kernel = 0;
+    if (std::string(v) == "lds") h->pair_kernel = h->multi_kernel = 0;
   int rc = check(chains_allow_lds(h->g), "chains LDS attribute");
   const size_t N = chains_sites(d, L);
   for (int32_t k = 0; rc == SMC_OK && init != SMC_INIT_KEEP && k < n_chains; ++k) {

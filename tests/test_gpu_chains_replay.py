@@ -34,11 +34,12 @@ def test_replay_equals_covariance(smc_gpu, monkeypatch, d, L, count, sweeps, ker
 
 
 @pytest.mark.parametrize("d,L,count,sweeps", [(3, 4, 9, 1), (3, 6, 5, 8), (3, 8, 7, 19), (3, 12, 3, 9), (3, 14, 2, 5),
-                                              (2, 16, 6, 17)])
+                                              (3, 16, 2, 8), (3, 18, 3, 10), (2, 16, 6, 17), (2, 68, 3, 9),
+                                              (2, 80, 2, 16), (2, 96, 2, 7)])
 def test_covariance_pair_and_lds(smc_gpu, monkeypatch, d, L, count, sweeps):
-    """Both kernels' replays: the same chains; sums of the same terms in two
-    orders (3D: one wave, several, the most lanes the pair kernel takes, and
-    past them)."""
+    """Both kernels' samples and replays: the same chains; sums of the same
+    terms in two orders (3D: one wave, several, the most lanes the pair kernel
+    takes, and past them; both: two and three pairs a lane, all lanes full)."""
     print(f"covariance kernels d={d} L={L}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(4)
     shape = (d, 2, L ** d // 2)
@@ -52,13 +53,15 @@ def test_covariance_pair_and_lds(smc_gpu, monkeypatch, d, L, count, sweeps):
         else:
             monkeypatch.delenv("SMC_CHAINS_KERNEL", raising=False)
         ch = smc_gpu.Chains(d, L, count, 6, J=J)
-        ch.sample(0.25, 2)
+        bonds = ch.bond_zeros()
+        ch.sample(0.25, 2, bonds)
+        ch.half_sweep(0.25, 1)
         cov = torch.zeros(shape, dtype=torch.float64, device="cuda")
         G = torch.zeros(2, dtype=torch.float64, device="cuda")
         ch.covariance(0.25, sweeps, g, centre, cov, G)
-        out.append((ch.spins.clone(), cov, G))
-    (sa, ca, Ga), (sb, cb, Gb) = out
-    assert torch.equal(sa, sb)
+        out.append((ch.spins.clone(), cov, G, bonds))
+    (sa, ca, Ga, ba), (sb, cb, Gb, bb) = out
+    assert torch.equal(sa, sb) and torch.equal(ba, bb)
     most = float(g.abs().sum()) + 0.3          # of |G - centre|
     eps, S = 2.0 ** -52, count * sweeps
     err = eps * most * (d * L ** d + S) * S    # rounding of each G and of the sums over S samples
