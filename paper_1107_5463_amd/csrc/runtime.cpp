@@ -65,7 +65,7 @@ struct BrickPlan {
   double us;
 };
 
-// The plans of a handle's last eight call lengths (a plan takes 20 to 40 us to
+// The plans of a handle's last eight call lengths (a plan takes 1 to 40 us to
 // work out; calls of alternating lengths, or cut by renormalisations, reuse them).
 template <class P>
 struct PlanCache {
@@ -538,9 +538,10 @@ constexpr double kLaunch = 3.5, kFinish = 3.0, kStage = 4.4, kStep = 0.17, kWord
 constexpr uint32_t kCUs = 256;
 
 // The resident kernel with `launches` launches of at most `steps` half-sweeps
-// and `own` words a workgroup; false if it does not fit.
+// and `own` words a workgroup; false if it does not fit, or takes `limit` us
+// or more before any masks are formed.
 bool resident_shape(const smc_lattice* h, uint32_t S, uint32_t launches, uint32_t own, bool whole,
-                    bool drawn, SweepPlan& o) {
+                    bool drawn, double limit, SweepPlan& o) {
   const Geom& g = h->g;
   const uint32_t Wp = plane_words(g), tail = Wp * 32u - (uint32_t)g.Nh;
   const uint32_t steps = (S + launches - 1) / launches;
@@ -553,6 +554,12 @@ bool resident_shape(const smc_lattice* h, uint32_t S, uint32_t launches, uint32_
   const uint32_t room = 96u * 1024u / (4u * nc);
   const uint32_t chunk = std::min<uint32_t>({steps, 128u, std::max<uint32_t>(1u, room / (uint32_t)Wl)});
   if ((uint64_t)chunk * Wl > room) return false;
+  // a step drops rho words at either end
+  const double words = (double)(steps * Wl - rho * steps * ((uint64_t)steps + 1));
+  const double step = steps * kStep + words * (g.R % 32 ? kWordStepAny : kWordStep);
+  const uint32_t groups = (Wp + own - 1) / own;
+  const uint32_t rounds = (groups + kCUs - 1) / kCUs;
+  if (launches * (kStage + step) * (rounds == 1 ? 1.0 : 0.9 * rounds) >= limit) return false;
   // workgroup size: the draws of a chunk are rounds of `waves` waves, four
   // SIMDs wide; a round takes a wave's own latency at least
   const uint64_t M = (uint64_t)chunk * (Wl - 2 * rho) - rho * chunk * (chunk - 1);
@@ -568,19 +575,11 @@ bool resident_shape(const smc_lattice* h, uint32_t S, uint32_t launches, uint32_
   }
   const double chunks = (steps + chunk - 1) / chunk;
   draw *= chunks;
-  double step = 0, words = 0;
-  for (uint32_t k = 0; k < steps; ++k) {
-    const double n = (double)(Wl - 2 * rho * (k + 1));
-    step += kStep + n * (g.R % 32 ? kWordStepAny : kWordStep);
-    words += n;
-  }
   if (drawn) {
     draw = chunks * kRead + kWordRead * words * nc;
     o.threads = 64 * std::min(16u, std::max(need, (uint32_t)(Wl + 63) / 64));
   }
-  const uint32_t groups = (Wp + own - 1) / own;
   const double one = kStage + (h->p.J_kind == SMC_J_PM ? 0.5 : 0.0) + draw + step;
-  const uint32_t rounds = (groups + kCUs - 1) / kCUs;
   o.way = kWayResident;
   o.steps = S;
   o.drawn = drawn;
@@ -638,7 +637,7 @@ SweepPlan plan_sweeps(const smc_lattice* h, int64_t n_sweeps, bool measured) {
     const bool whole = h->forced_own >= Wp;
     const uint32_t So = h->forced_drawn ? Sd : S;
     const uint32_t launches = whole ? 1u : std::max(2u, (So + h->forced_steps - 1) / h->forced_steps);
-    if (So && resident_shape(h, So, launches, std::min(h->forced_own, Wp), whole, h->forced_drawn, o)) {
+    if (So && resident_shape(h, So, launches, std::min(h->forced_own, Wp), whole, h->forced_drawn, 1e30, o)) {
       if (whole) o.chunk = std::min(o.chunk, h->forced_steps);
       return o;
     }
@@ -657,12 +656,13 @@ SweepPlan plan_sweeps(const smc_lattice* h, int64_t n_sweeps, bool measured) {
     const uint32_t So = drawn ? Sd : S;
     if (So == 0) continue;
     const double calls = (double)S / So;
-    if (Wp <= 2048 && resident_shape(h, So, 1, Wp, true, drawn != 0, o) &&
+    if (Wp <= 2048 && resident_shape(h, So, 1, Wp, true, drawn != 0, best.us / calls, o) &&
         (o.us = calls * o.us + bonds) < best.us)
       best = o;
     for (uint32_t launches = 2; launches <= So; launches = launches < 8 ? launches + 1 : launches * 5 / 4) {
+      if (calls * (launches * kStage + So * kStep) >= best.us) break;
       for (uint32_t own = 16; own <= 2048; own = own * 3 / 2) {
-        if (!resident_shape(h, So, launches, own, false, drawn != 0, o)) continue;
+        if (!resident_shape(h, So, launches, own, false, drawn != 0, best.us / calls, o)) continue;
         o.us = calls * o.us + bonds + finish;
         if (o.us < best.us) best = o;
       }
@@ -842,13 +842,19 @@ bool brick_shape(const smc_lattice* h, uint32_t sweeps, const uint32_t nb[3], ui
 // sites are still right (fewer as the halo is used up), their issue slots; the
 // start takes a term a wave and, in 3D where bricks have short rows, their
 // bytes in parts of cache lines.
-// `limit`: larger times are not worked out (any larger one is returned).
+constexpr double kFit[3][9] = {
+    // start, step, step V, wave step V, wave V, wave, MB, MB of lines, MB of lines V
+    {1.80, 0.25, 0.080, 0.000, 0.39, 0.21, 0.000, 0.0100, 0.0220},
+    {1.80, 0.22, 0.190, 0.031, 0.28, 0.26, 0.008, 0.1350, 0.0000},
+    {1.88, 0.17, 0.310, 0.069, 0.45, 0.30, 0.043, 0.0760, 0.0000}};
+
+// vector spins with a coupling a bond are fitted least well: a margin
+double brick_margin(const smc_lattice* h) {
+  return h->p.n > 1 && h->p.J_kind != SMC_J_UNIFORM && h->g.d == 3 ? 1.25 : 1.0;
+}
+
+// The time of a launch.  `limit`: larger times are not worked out (any larger one is returned).
 double brick_us(const smc_lattice* h, const BrickLaunch& a, double limit) {
-  static const double kFit[3][9] = {
-      // start, step, step V, wave step V, wave V, wave, MB, MB of lines, MB of lines V
-      {1.80, 0.25, 0.080, 0.000, 0.39, 0.21, 0.000, 0.0100, 0.0220},
-      {1.80, 0.22, 0.190, 0.031, 0.28, 0.26, 0.008, 0.1350, 0.0000},
-      {1.88, 0.17, 0.310, 0.069, 0.45, 0.30, 0.043, 0.0760, 0.0000}};
   const double* f = kFit[h->p.n - 1];
   const uint32_t edge[3] = {(uint32_t)h->g.R, (uint32_t)h->g.L, h->g.d == 3 ? (uint32_t)h->g.L : 1u};
   const uint32_t groups = a.nb[0] * a.nb[1] * a.nb[2], per = (groups + kCUs - 1) / kCUs;
@@ -875,9 +881,8 @@ double brick_us(const smc_lattice* h, const BrickLaunch& a, double limit) {
                       (h->p.J_kind == SMC_J_FP32 ? 16 * d : h->p.J_kind == SMC_J_PM ? 4 * d : 0.0);
   const double mb = 1e-6 * groups * a.positions * site;
   const double lines = h->g.d == 3 ? mb * 32 / (own[0] + (a.nb[0] == 1 ? 0 : 2 * a.halo_x)) : mb;
-  // shapes of several workgroups a CU, and vector spins with a coupling a bond,
-  // are fitted least well: a margin
-  return (per > 1 ? 1.35 : 1.0) * (h->p.n > 1 && h->p.J_kind != SMC_J_UNIFORM && h->g.d == 3 ? 1.25 : 1.0) *
+  // (as are shapes of several workgroups a CU)
+  return (per > 1 ? 1.35 : 1.0) * brick_margin(h) *
          std::max(2.6, f[0] + K * (f[1] + f[2] * V) + f[3] * w * V + start * (f[4] * V + f[5]) +
                                 f[6] * mb + lines * (f[7] + f[8] * V));
 }
@@ -915,9 +920,25 @@ BrickPlan plan_bricks(const smc_lattice* h, int64_t n_sweeps) {
   static const uint32_t kCuts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64};
   const uint32_t vmax = h->p.n == 3 ? 2 : 4;
   const uint32_t L = (uint32_t)h->g.L, R = (uint32_t)h->g.R;
-  auto consider = [&](uint32_t launches, uint32_t per, const uint32_t nb[3]) {
+  // The least that `launches` launches can take with V positions a lane: `per`
+  // workgroups a CU, `waves` waves of a SIMD at the start, and at every step at
+  // least those of the lattice's own positions spread over the card.
+  const double* f = kFit[h->p.n - 1];
+  const double margin = 0.999 * brick_margin(h), spread = Nh / (256.0 * kCUs);
+  auto bound = [&](uint32_t launches, uint32_t sweeps, uint32_t V, uint32_t per, double waves) {
+    const double step = f[1] + f[2] * V + f[3] * std::max(0.25 * per * V, spread);
+    const double us = f[0] + 2.0 * sweeps * step + waves * (f[4] * V + f[5]);
+    return launches * (per > 1 ? 1.35 * margin : margin) * std::max(2.6, us);
+  };
+  auto consider = [&](uint32_t launches, uint32_t sweeps, const uint32_t nb[3], uint32_t positions,
+                      uint32_t Vs) {
+    const uint32_t groups = nb[0] * nb[1] * nb[2];
+    if (groups > kBricks) return;
+    const uint32_t per = (groups + kCUs - 1) / kCUs;
+    const double waves = per * positions / 256.0;
     for (uint32_t V = 1; V <= vmax; V *= 2) {
-      if (!brick_shape(h, per, nb, V, a)) continue;
+      if (!(Vs & V) || positions > 1024 * V || bound(launches, sweeps, V, per, waves / V) >= best.us) continue;
+      if (!brick_shape(h, sweeps, nb, V, a)) continue;
       const double us = launches * brick_us(h, a, best.us / launches);
       if (us < best.us) {
         best.us = us;
@@ -928,10 +949,9 @@ BrickPlan plan_bricks(const smc_lattice* h, int64_t n_sweeps) {
     }
   };
   const uint32_t one[3] = {1, 1, 1};
-  if (n_sweeps <= (1 << 20)) consider(1, (uint32_t)n_sweeps, one);
+  if (n_sweeps <= (1 << 20) && Nh <= 1024 * vmax) consider(1, (uint32_t)n_sweeps, one, (uint32_t)Nh, 7u);
   // extent of a brick with its halo, 0: none of that cut (a smaller one gives
-  // the same bricks, or the halo does not fit).  (A few hundred cuts are worked
-  // out, 20 to 40 us, once a handle and call length.)
+  // the same bricks, or the halo does not fit)
   auto extent = [&](uint32_t edge, size_t k, uint32_t halo) -> uint32_t {
     const uint32_t n = kCuts[k], own = (edge + n - 1) / n;
     if (n == 1) return edge;
@@ -946,22 +966,32 @@ BrickPlan plan_bricks(const smc_lattice* h, int64_t n_sweeps) {
     if (launches == last || launches < 2) continue;
     last = launches;
     const uint32_t per = (uint32_t)((n_sweeps + launches - 1) / launches);
+    // the lattice's own positions spread over the card, whatever the cut
+    uint32_t Vs = 0;
+    for (uint32_t V = 1; V <= vmax; V *= 2)
+      if (bound(launches, per, V, Nh > 1024.0 * kCUs * V ? 2u : 1u, std::max(0.25, spread / V)) < best.us) Vs |= V;
+    if (!Vs) continue;
+    uint32_t ext[2][kN];
+    for (size_t k = 0; k < kN; ++k) {
+      ext[0][k] = extent(R, k, per);
+      ext[1][k] = extent(L, k, 2 * per);
+    }
     for (size_t ix = 0; ix < kN; ++ix) {
-      const uint32_t ex = extent(R, ix, per);
+      const uint32_t ex = ext[0][ix];
       if (!ex) continue;
       for (size_t iy = 0; iy < kN; ++iy) {
-        const uint32_t ey = extent(L, iy, 2 * per);
+        const uint32_t ey = ext[1][iy];
         if (!ey || ex * ey > 1024 * vmax) continue;
         if (h->g.d == 2) {
           const uint32_t nb[3] = {kCuts[ix], kCuts[iy], 1};
-          consider(launches, per, nb);
+          consider(launches, per, nb, ex * ey, Vs);
           continue;
         }
         for (size_t iz = iy; iz < kN; ++iz) {
-          const uint32_t ez = extent(L, iz, 2 * per);
+          const uint32_t ez = ext[1][iz];
           if (!ez || ex * ey * ez > 1024 * vmax) continue;
           const uint32_t nb[3] = {kCuts[ix], kCuts[iy], kCuts[iz]};
-          consider(launches, per, nb);
+          consider(launches, per, nb, ex * ey * ez, Vs);
         }
       }
     }
