@@ -76,7 +76,7 @@ __global__ __launch_bounds__(1024) void brick_kernel(const BrickLaunch a) {
     ozm = lz == 0u ? (wz ? i + (Z - 1u) * H * W : i) : i - H * W;
     ozp = lz + 1u == Z ? (wz ? i - (Z - 1u) * H * W : i) : i + H * W;
   }
-  uint32_t e = in ? 0xFFFFu : 0u;
+  uint32_t e = in ? ~0u : 0u;  // (no cut face: right after every step of a call)
   if (in && !wx) e = min(e, 2u * min(lx + V, W - lx) - 1u);  // of its innermost site
   if (in && !wy) e = min(e, min(ly, H - 1u - ly));
   if (in && !wz) e = min(e, min(lz, Z - 1u - lz));
