@@ -252,6 +252,15 @@ int smc_autotune(smc_lattice* h, double beta, void* scratch, size_t scratch_byte
  * otherwise. */
 const char* smc_kernel_name(const smc_lattice* h, uint32_t* rows_per_band);
 
+/* Name of the kernel that does most of a call of n_sweeps (measured: with a
+ * record) from the handle's counter, and in launches (optional) how often the
+ * call launches it and the kernels of its other sweeps: the names above, or
+ * "ising_resident" (several half-sweeps a launch, the words in LDS; "ising_packed"
+ * for an int8 lattice: on a copy at one bit per site), "ising_bricks", "xy_bricks",
+ * "heisenberg_bricks" (several sweeps a launch of bricks held in LDS), "xy_march"
+ * (two sweeps a pass over memory).  "" for n_sweeps < 1. */
+const char* smc_sweeps_kernel(const smc_lattice* h, int64_t n_sweeps, int measured, uint64_t* launches);
+
 /* Free the handle (never the caller's buffers). */
 int smc_destroy(smc_lattice* h);
 

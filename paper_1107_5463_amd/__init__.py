@@ -43,7 +43,7 @@ EXPORTS = ["smc_spin_bytes", "smc_coupling_bytes", "smc_workspace_bytes", "smc_b
            "smc_measure",
            "smc_measure_async", "smc_measure_noalloc", "smc_bond_correlations", "smc_get_samples", "smc_set_samples",
            "smc_renormalize", "smc_validate", "smc_get_sweep_index", "smc_set_sweep_index",
-           "smc_kernel_name", "smc_autotune", "smc_destroy", "smc_last_error", "smc_version",
+           "smc_kernel_name", "smc_sweeps_kernel", "smc_autotune", "smc_destroy", "smc_last_error", "smc_version",
            "smc_batch_spin_bytes", "smc_batch_coupling_bytes", "smc_batch_workspace_bytes",
            "smc_batch_offsets", "smc_batch_init", "smc_batch_sweep", "smc_batch_sweep_series",
            "smc_batch_autotune", "smc_batch_lattice_packed", "smc_batch_set_schedule",
@@ -128,6 +128,8 @@ def load_library():
     lib.smc_autotune.argtypes = [vp, C.c_double, vp, sz, C.POINTER(C.c_uint32)]
     lib.smc_kernel_name.argtypes = [vp, C.POINTER(C.c_uint32)]
     lib.smc_kernel_name.restype = C.c_char_p
+    lib.smc_sweeps_kernel.argtypes = [vp, C.c_int64, C.c_int, C.POINTER(C.c_uint64)]
+    lib.smc_sweeps_kernel.restype = C.c_char_p
     lib.smc_destroy.argtypes = [vp]
     i32p = C.POINTER(C.c_int32)
     for f in ("smc_batch_spin_bytes", "smc_batch_coupling_bytes", "smc_batch_workspace_bytes"):
@@ -177,7 +179,8 @@ def load_library():
     lib.smc_version.restype = C.c_char_p
     for f in EXPORTS:
         if f not in ("smc_spin_bytes", "smc_coupling_bytes", "smc_workspace_bytes", "smc_bond_bytes",
-                     "smc_last_error", "smc_version", "smc_kernel_name", "smc_chains_kernel_name",
+                     "smc_last_error", "smc_version", "smc_kernel_name", "smc_sweeps_kernel",
+                     "smc_chains_kernel_name",
                      "smc_batch_spin_bytes",
                      "smc_batch_coupling_bytes", "smc_batch_workspace_bytes"):
             getattr(lib, f).restype = C.c_int
@@ -305,6 +308,14 @@ class Lattice:
         rows = C.c_uint32()
         name = self._lib().smc_kernel_name(self._h, C.byref(rows)).decode()
         return name, int(rows.value)
+
+    def sweeps_kernel(self, n_sweeps: int, measured: bool = False):
+        """(name, launches) of the kernel that a call of n_sweeps from the current
+        counter runs (smc_sweeps_kernel)."""
+        launches = C.c_uint64()
+        name = self._lib().smc_sweeps_kernel(self._h, int(n_sweeps), 1 if measured else 0,
+                                             C.byref(launches)).decode()
+        return name, int(launches.value)
 
     def autotune(self, beta: float) -> int:
         """Time the band heights of this lattice's kernel on a scratch copy of

@@ -671,6 +671,16 @@ SweepPlan plan_sweeps(const smc_lattice* h, int64_t n_sweeps, bool measured) {
   return best;
 }
 
+// Half-sweeps of a launch where S of them run together, and the launches.
+uint32_t resident_per(const SweepPlan& plan, uint32_t S) {
+  const uint32_t launches = plan.launches == 1 ? 1u : std::min(plan.launches, S);
+  return (S + launches - 1) / launches;
+}
+uint32_t resident_launches(const SweepPlan& plan, uint32_t S) {
+  const uint32_t per = resident_per(plan, S);
+  return (S + per - 1) / per;
+}
+
 int resident_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs,
                     const SweepPlan& plan) {
   const IsingLaunch ia = ising_args(h, beta);
@@ -704,8 +714,7 @@ int resident_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs
   for (int64_t done = 0; done < n_sweeps;) {
     const uint32_t S = (uint32_t)std::min<int64_t>(2 * (n_sweeps - done), plan.steps);
     const bool last_call = done + S / 2 >= n_sweeps;
-    const uint32_t launches = plan.launches == 1 ? 1u : std::min(plan.launches, S);
-    const uint32_t per = (S + launches - 1) / launches;
+    const uint32_t per = resident_per(plan, S);
     a.t0 = (uint32_t)h->t;
     if (plan.drawn) {
       a.drawn_stride = (uint64_t)S * a.Wp;
@@ -792,9 +801,11 @@ bool march_params(const smc_params* p) {
 }
 
 // n >= 2 sweeps in an even number of passes of two sweeps or one.
+int64_t march_passes(int64_t n) { return (n + 3) / 4 * 2; }
+
 int march_run(smc_lattice* h, double beta, int64_t n, void* dev_obs) {
   const ContLaunch a = cont_args(h, beta);
-  const int64_t passes = (n + 3) / 4 * 2;
+  const int64_t passes = march_passes(n);
   for (int64_t k = 0; k < passes; ++k) {
     const int sweeps = k < n - passes ? 2 : 1;
     const float* src = (const float*)(k % 2 ? (void*)h->march_work : h->spins);
@@ -1067,6 +1078,15 @@ int tiled_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs) {
   return SMC_OK;
 }
 
+// Sweeps between renormalisations (0: none), and those from counter t up to the
+// next, the sweep before it included, `left` at most.
+uint64_t renorm_interval(const smc_lattice* h) { return h->p.n > 1 ? (uint64_t)h->p.renorm_every : 0; }
+
+int64_t to_renorm(const smc_lattice* h, uint64_t t, int64_t left) {
+  const uint64_t every = renorm_interval(h);
+  return every ? (int64_t)std::min<uint64_t>((uint64_t)left, every - t % every) : left;
+}
+
 // `half`: one launch a half-sweep in any case (the band-height autotuner).
 int sweeps_impl(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, bool half = false) {
   if (h->p.tile > 0) return tiled_sweeps(h, beta, n_sweeps, dev_obs);
@@ -1082,10 +1102,8 @@ int sweeps_impl(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, bo
   int64_t planned = 0;  // sweeps before it run as planned
   for (int64_t k = 0; k < n_sweeps; ++k) {
     if ((h->brick_ok || h->march_rows) && !half && k >= planned) {
-      // up to the next renormalisation, the sweep before it included
-      const uint64_t every = h->p.n > 1 ? (uint64_t)h->p.renorm_every : 0;
-      int64_t m = n_sweeps - k;
-      if (every) m = (int64_t)std::min<uint64_t>((uint64_t)m, every - h->t % every);
+      const uint64_t every = renorm_interval(h);
+      const int64_t m = to_renorm(h, h->t, n_sweeps - k);
       const BrickPlan brick = h->bricks.get(m, [&] { return plan_bricks(h, m); });
       if (brick.launches || (h->march_rows && m >= 2)) {
         const bool end = k + m == n_sweeps, renorm = every && (h->t + (uint64_t)m) % every == 0;
@@ -1743,6 +1761,47 @@ const char* smc_kernel_name(const smc_lattice* h, uint32_t* rows_per_band) {
     case kVariantChunk: return "ising_chunk";
     default: return "ising_site";
   }
+}
+
+const char* smc_sweeps_kernel(const smc_lattice* h, int64_t n_sweeps, int measured, uint64_t* launches) {
+  if (launches) *launches = 0;
+  if (!h || n_sweeps < 1) return "";
+  uint64_t count = 0;
+  const char* name = smc_kernel_name(h, nullptr);
+  if (h->p.tile > 0) {
+    count = 2 * (uint64_t)n_sweeps;
+  } else if (h->use_fused) {
+    // an odd sweep runs in place by half-sweeps
+    count = (uint64_t)(n_sweeps / 2 * 2 + n_sweeps % 2 * 2);
+  } else if (h->multi_ok) {
+    const SweepPlan plan = plan_sweeps(h, n_sweeps, measured != 0);
+    count = 2 * (uint64_t)n_sweeps;
+    if (plan.way == kWayPackedCopy) name = "ising_packed";
+    if (plan.way == kWayResident) {
+      name = "ising_resident";
+      const uint64_t blocks = (uint64_t)n_sweeps / (plan.steps / 2);
+      const uint32_t rest = 2 * (uint32_t)((uint64_t)n_sweeps % (plan.steps / 2));
+      count = blocks * resident_launches(plan, plan.steps) + (rest ? resident_launches(plan, rest) : 0);
+    }
+  } else {
+    // stretches between renormalisations, each as the call would cut it; the
+    // name is that of the kernel of most sweeps
+    const char* const half = !h->cont_row_sweeps ? name : h->p.n == 2 ? "xy_site" : "heisenberg_site";
+    const char* const bricks = h->p.n == 1 ? "ising_bricks" : h->p.n == 2 ? "xy_bricks" : "heisenberg_bricks";
+    uint64_t by[3] = {0, 0, 0};  // sweeps by half-sweeps, bricks, passes
+    BrickPlan brick;
+    int64_t planned = 0;
+    for (int64_t k = 0, m; k < n_sweeps; k += m) {
+      m = to_renorm(h, h->t + (uint64_t)k, n_sweeps - k);
+      if (m != planned) brick = plan_bricks(h, planned = m);
+      const int way = brick.launches ? 1 : h->march_rows && m >= 2 ? 2 : 0;
+      by[way] += (uint64_t)m;
+      count += way == 1 ? brick.launches : way == 2 ? (uint64_t)march_passes(m) : 2 * (uint64_t)m;
+    }
+    name = by[1] >= by[0] && by[1] >= by[2] ? bricks : by[2] >= by[0] ? "xy_march" : half;
+  }
+  if (launches) *launches = count;
+  return name;
 }
 
 int smc_destroy(smc_lattice* h) {
