@@ -258,7 +258,8 @@ const char* smc_kernel_name(const smc_lattice* h, uint32_t* rows_per_band);
  * "ising_resident" (several half-sweeps a launch, the words in LDS; "ising_packed"
  * for an int8 lattice: on a copy at one bit per site), "ising_bricks", "xy_bricks",
  * "heisenberg_bricks" (several sweeps a launch of bricks held in LDS), "xy_march"
- * (two sweeps a pass over memory).  "" for n_sweeps < 1. */
+ * (two sweeps a pass over memory), "ising_tiles_ahead" (packed tiles whose
+ * decisions other waves form ahead).  "" for n_sweeps < 1. */
 const char* smc_sweeps_kernel(const smc_lattice* h, int64_t n_sweeps, int measured, uint64_t* launches);
 
 /* Free the handle (never the caller's buffers). */

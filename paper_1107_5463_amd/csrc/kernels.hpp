@@ -48,7 +48,7 @@ hipError_t launch_bond_words(const Geom& g, bool bytes, const void* J, uint32_t*
 
 // Tile passes with the masks of several hits formed ahead (tiles_ahead.hip).
 bool tile_ahead_supported(const Geom& g, uint32_t T);
-uint32_t tile_ahead_waves(const Geom& g, uint32_t T, bool heatbath);
+uint32_t tile_ahead_waves(const Geom& g, uint32_t T, bool heatbath, uint32_t hits);
 hipError_t launch_tile_ahead_pass(const IsingLaunch& a, bool heatbath, uint32_t T, uint32_t hits,
                                   int8_t* spins, uint32_t t, uint32_t tc, hipStream_t st, uint32_t waves);
 

@@ -1426,16 +1426,16 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
   h->tile_packed = true;
   h->tile_group = 0;
   const bool heatbath = (p->flags & SMC_FLAG_HEATBATH) != 0;
-  h->tile_ahead = p->tile > 0 ? tile_ahead_waves(h->g, (uint32_t)p->tile, heatbath) : 0u;
+  h->tile_ahead = p->tile > 0 ? tile_ahead_waves(h->g, (uint32_t)p->tile, heatbath, (uint32_t)p->hits) : 0u;
   if (const char* v = std::getenv("SMC_TILE_KERNEL")) {
     const std::string s(v);
     h->tile_packed = s != "byte";
     h->tile_group = s == "wave" ? 64u : s == "group" ? 256u : 0u;
     const unsigned long w = s.compare(0, 6, "ahead,") == 0 ? std::strtoul(s.c_str() + 6, nullptr, 10) : 0;
     if (w >= 2 && w <= 12 && tile_ahead_supported(h->g, (uint32_t)p->tile)) h->tile_ahead = (uint32_t)w;
-    if (s == "byte" || (heatbath && h->tile_group)) h->tile_ahead = 0u;
+    if (s == "byte" || h->tile_group) h->tile_ahead = 0u;
   }
-  if (heatbath && std::getenv("SMC_PACKED_TIES")) h->tile_ahead = 0u;
+  if (std::getenv("SMC_PACKED_TIES")) h->tile_ahead = 0u;
   if (const char* v = std::getenv("SMC_PACKED_TIES")) {
     const std::string s(v);
     if (s == "lane") h->packed_ties = 1;
@@ -1770,6 +1770,10 @@ const char* smc_sweeps_kernel(const smc_lattice* h, int64_t n_sweeps, int measur
   const char* name = smc_kernel_name(h, nullptr);
   if (h->p.tile > 0) {
     count = 2 * (uint64_t)n_sweeps;
+    const bool hb = (h->p.flags & SMC_FLAG_HEATBATH) != 0;
+    name = h->tile_ahead ? "ising_tiles_ahead"
+           : h->tile_packed && tile_packed_supported(h->g, (uint32_t)h->p.tile, hb) ? "ising_tiles_packed"
+                                                                                   : "ising_tiles";
   } else if (h->use_fused) {
     // an odd sweep runs in place by half-sweeps
     count = (uint64_t)(n_sweeps / 2 * 2 + n_sweeps % 2 * 2);

@@ -620,8 +620,8 @@ __global__ __launch_bounds__(BS) void tile_packed_kernel(const Geom g, const Rng
 }
 
 // ---------------------------------------------------------------------------
-// Bit-packed tiles of edge T = 16 or 32 (2D, heat bath in launches
-// that fill the chip; the others form their decisions ahead, tiles_ahead.hip): a tile
+// Bit-packed tiles of edge T = 16 or 32 (2D; launches that leave a SIMD few waves, and
+// Metropolis ones of many hits, form their decisions ahead, tiles_ahead.hip): a tile
 // row holds RB = T / 2 sites of a colour, so a word packs 32 / RB tile rows --
 // word i of a tile's colour holds rows NR i .. NR i + NR - 1 of the tile, site s
 // of row r in bit RB r + s (bit 1 = spin -1).  Per tile and colour, LDS holds
@@ -692,7 +692,7 @@ struct RowTile {
   }
 };
 
-template <uint32_t T, uint32_t BS>
+template <uint32_t T, bool FAST, bool HB, uint32_t BS>
 __global__ __launch_bounds__(BS) void tile_rows_kernel(const Geom g, const RngKey key,
                                                             const IsingTable table,
                                                             const uint32_t hits, const uint32_t t,
@@ -738,6 +738,8 @@ __global__ __launch_bounds__(BS) void tile_rows_kernel(const Geom g, const RngKe
   __syncthreads();
 
   const TabRegs tab = tab_regs(table);
+  FastTab ft;
+  if (FAST) ft = fast_tab<2>(tab);
   const uint32_t j0 = (Y0 + TL::NR * i) * R + x0;  // in-colour index of the word's first site
   __shared__ TileTies<BS> tt;
   for (uint32_t h = 0; h < hits; ++h) {
@@ -747,7 +749,7 @@ __global__ __launch_bounds__(BS) void tile_rows_kernel(const Geom g, const RngKe
       if (valid) {
         uint32_t* own = tw + c * TL::Words;
         const uint32_t* oth = tw + (1 - c) * TL::Words;
-        const uint32_t ct = oth[1 + i];
+        const uint32_t o = own[1 + i], ct = oth[1 + i];
         const uint32_t up = __builtin_amdgcn_alignbit(ct, oth[i], 32u - TL::RB);    // rows r - 1
         const uint32_t dn = __builtin_amdgcn_alignbit(oth[2 + i], ct, TL::RB);  // rows r + 1
         const uint32_t sh_next = ((ct >> 1) & ~TL::Last) | oth[TL::Right + i];   // site + 1 in its row
@@ -757,17 +759,20 @@ __global__ __launch_bounds__(BS) void tile_rows_kernel(const Geom g, const RngKe
         const uint32_t pm = P1[c];
         const uint32_t nxp = (ct & ~pm) | (sh_next & pm);
         const uint32_t nxm = (sh_prev & ~pm) | (ct & pm);
-        // the up neighbours
-        const uint32_t u[6] = {~nxp, ~nxm, ~dn, ~up, 0u, 0u};
+        // Metropolis: the unsatisfied bonds; heat bath: the up neighbours
+        const uint32_t u[6] = {HB ? ~nxp : o ^ nxp, HB ? ~nxm : o ^ nxm, HB ? ~dn : o ^ dn,
+                               HB ? ~up : o ^ up, 0u, 0u};
         count_planes<2>(u, k0, k1, k2);
         uint32_t P[8];
         TL::prefix(key, t, c, h, j0, R, P);
         uint32_t B[8];
         prefix_planes(P, B);
         // exact ties refused, resolved below
-        own[1 + i] = ~packed_compare<2>(tab, B, k0, k1, k2, ties);
+        const uint32_t flip = FAST ? packed_compare_fast<2>(ft, B, k0, k1, k2, ties)
+                                   : packed_compare<2>(tab, B, k0, k1, k2, ties);
+        own[1 + i] = HB ? ~flip : o ^ flip;
       }
-      tile_ties_group<BS, TL::RB, true>(tt, ties, k0, k1, k2, j0, R, lw,
+      tile_ties_group<BS, TL::RB, !FAST>(tt, ties, k0, k1, k2, j0, R, lw,
                                    gi * 2u * TL::Words + c * TL::Words + 1u + i, tab, key, t, c,
                                    h, tie_cap);
       __syncthreads();
@@ -956,12 +961,24 @@ hipError_t tile_allow_lds(int d, size_t bytes) {
   return hipSuccess;
 }
 
-// Below this many waves a SIMD a packed tile pass runs in workgroups of one
-// wave: the barriers and the one drawing wave of a 256-lane group then leave
+// Whether a packed tile pass of n waves runs in workgroups of one wave.  Below
+// four waves a SIMD the barriers and the one drawing wave of a 256-lane group leave
 // the SIMD idle (heat bath, us a sweep of k = 100, groups of 256 / of 64: 2D T =
-// 16 L = 4096 772 / 703, T = 64 657 / 581, 3D T = 16 L = 256 838 / 786); above it
-// the shared round of tie draws catches up (L = 8192: 2215 / 2224).
-constexpr uint32_t kTileWaves = 4;
+// 16 n = 2048 780 / 710, T = 64 658 / 582, 3D T = 16 839 / 788); above, the shared
+// round of tie draws catches up (T = 16 n = 8192 2218 / 2225).  With few hits the
+// group's coalesced staging counts for more, most of all in 3D, where its four
+// tiles lie side by side (k = 1: 3D T = 16 n = 2048 43 / 79, n = 4000 70 / 135; at n = 2916 k =
+// 16 212 / 227, k = 50 568 / 568; 2D T = 32 n = 2048 26 / 33, k = 12 97 / 97, n = 3200 k = 12 142 /
+// 148, k = 50 515 / 514; T = 64 n = 2048 35 / 40, k = 8 79 / 78, n = 3872 k = 12 149 / 154, k = 32 342 / 340;
+// T = 16 n = 1013 21 / 23, n = 3200 37 / 37, n = 3872 38 / 41, k = 8 123 / 123).
+static bool tile_one_wave(const Geom& g, uint32_t T, uint64_t n, uint32_t hits) {
+  uint32_t least;
+  if (g.d == 3) least = n < 1700 ? 3 : 50;
+  else if (T == 16) least = n < 1500 ? 4 : n < 3500 ? 1 : 8;
+  else if (T == 32) least = n < 2300 ? 12 : 50;
+  else least = n < 2300 ? 8 : 24;
+  return n < 4096 && hits >= least;
+}
 
 // One tile-colour pass (k hits) of the tiled schedule; `packed`: the bit-packed
 // kernel where it applies, in workgroups of `groups` lanes (64 or 256; 0: chosen here).
@@ -970,45 +987,47 @@ hipError_t launch_tile_pass(const IsingLaunch& a, bool heatbath, uint32_t T, uin
                             uint32_t groups) {
   const uint32_t nt = (uint32_t)a.g.L / T;
   const uint32_t tiles = (a.g.d == 3 ? nt * nt * nt : nt * nt) / 2;
-  // (the Metropolis rule of the other edges: launch_tile_ahead_pass)
-  if (packed && tile_packed_supported(a.g, T, heatbath) && (heatbath || T == 128 || (a.g.d == 3 && T == 32))) {
+  if (packed && tile_packed_supported(a.g, T, heatbath)) {
     // the fast decision when every class k >= d always accepts (J0 > 0)
     bool fast = true;
     for (int k = a.g.d; k <= 2 * a.g.d; ++k)
       if ((((k < 4 ? a.tab.al_lo : a.tab.al_hi) >> (8 * (k & 3))) & 0xFFu) != 0xFFu) fast = false;
     const uint32_t items = (a.g.d == 3 ? T : 1u) * T * T / 64u;  // lanes of a tile
-    // Workgroups of one wave where a tile fits one and the launch leaves a
-    // SIMD fewer than kTileWaves waves; else 256 lanes, whose ties share one
-    // round of draws.
     const bool one_wave = items <= 64u && groups != 256u &&
-                          (groups == 64u || (uint64_t)tiles * items < 64ull * 1024 * kTileWaves);
+                          (groups == 64u || tile_one_wave(a.g, T, (uint64_t)tiles * items / 64u, hits));
     const uint32_t bs = one_wave ? 64u : std::max(256u, items), G = bs / items;
     const dim3 grid((tiles + G - 1) / G), block(bs);
     // the workgroup's list of tied sites (packed_ties other than 0: each lane its own)
     const uint32_t cap = a.packed_ties == 0 ? tile_tie_cap(bs) : 0u;
 #define SMC_TP(K, ...) hipLaunchKernelGGL((K), grid, block, lds, st, a.g, a.key, a.tab, __VA_ARGS__, t, tc, tiles, cap, spins)
+// KERNEL(FAST, HB, BS) by rule and workgroup size
+#define SMC_TPB(KERNEL, BS, ...)                        \
+  do {                                                  \
+    if (heatbath) SMC_TP(KERNEL(false, true, BS), __VA_ARGS__);  \
+    else if (fast) SMC_TP(KERNEL(true, false, BS), __VA_ARGS__); \
+    else SMC_TP(KERNEL(false, false, BS), __VA_ARGS__); \
+  } while (0)
+#define SMC_TPW(KERNEL, ...) \
+  do { if (one_wave) SMC_TPB(KERNEL, 64, __VA_ARGS__); else SMC_TPB(KERNEL, 256, __VA_ARGS__); } while (0)
+#define SMC_R3(F, H, BS) (tile_rows3d_kernel<16, F, H, BS>)
+#define SMC_R3L(F, H, BS) (tile_rows3d_kernel<32, F, H, BS>)
+#define SMC_WIDE(F, H, BS) (tile_packed_kernel<F, H, BS>)
+#define SMC_R16(F, H, BS) (tile_rows_kernel<16, F, H, BS>)
+#define SMC_R32(F, H, BS) (tile_rows_kernel<32, F, H, BS>)
     const size_t lds = a.g.d == 2 && T >= 64 ? tile_packed_lds_bytes(T, G) : 0;
-    if (a.g.d == 3 && T == 32) {
-      if (heatbath) SMC_TP((tile_rows3d_kernel<32, false, true, 512>), hits);
-      else if (fast) SMC_TP((tile_rows3d_kernel<32, true, false, 512>), hits);
-      else SMC_TP((tile_rows3d_kernel<32, false, false, 512>), hits);
-    } else if (a.g.d == 3) {
-      if (one_wave) SMC_TP((tile_rows3d_kernel<16, false, true, 64>), hits);
-      else SMC_TP((tile_rows3d_kernel<16, false, true, 256>), hits);
-    } else if (T == 128) {
-      if (heatbath) SMC_TP((tile_packed_kernel<false, true, 256>), T, hits);
-      else if (fast) SMC_TP((tile_packed_kernel<true, false, 256>), T, hits);
-      else SMC_TP((tile_packed_kernel<false, false, 256>), T, hits);
-    } else if (T == 64) {
-      if (one_wave) SMC_TP((tile_packed_kernel<false, true, 64>), T, hits);
-      else SMC_TP((tile_packed_kernel<false, true, 256>), T, hits);
-    } else if (T == 32) {
-      if (one_wave) SMC_TP((tile_rows_kernel<32, 64>), hits);
-      else SMC_TP((tile_rows_kernel<32, 256>), hits);
-    } else {
-      if (one_wave) SMC_TP((tile_rows_kernel<16, 64>), hits);
-      else SMC_TP((tile_rows_kernel<16, 256>), hits);
-    }
+    if (a.g.d == 3 && T == 32) SMC_TPB(SMC_R3L, 512, hits);
+    else if (a.g.d == 3) SMC_TPW(SMC_R3, hits);
+    else if (T == 128) SMC_TPB(SMC_WIDE, 256, T, hits);
+    else if (T == 64) SMC_TPW(SMC_WIDE, T, hits);
+    else if (T == 32) SMC_TPW(SMC_R32, hits);
+    else SMC_TPW(SMC_R16, hits);
+#undef SMC_R3
+#undef SMC_R3L
+#undef SMC_WIDE
+#undef SMC_R16
+#undef SMC_R32
+#undef SMC_TPW
+#undef SMC_TPB
 #undef SMC_TP
     return hipGetLastError();
   }

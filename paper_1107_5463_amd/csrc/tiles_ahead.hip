@@ -344,21 +344,46 @@ bool tile_ahead_supported(const Geom& g, uint32_t T) {
          ((uint32_t)g.L / T) % 2 == 0;
 }
 
-// Waves of a workgroup, 0: the kernels of tiles.hip are faster.  More waves form
-// masks faster and hold more SIMD slots of one workgroup's passes idle; with 64
-// words a workgroup, n workgroups in a launch (us a sweep of k = 100 by waves 4 /
-// 8 / 12): Metropolis 2D T = 16 n = 128 125 / 86 / 81, n = 1152 324 / 305 / 317, n =
-// 2048 475 / 474 / 499, n = 8192 1668 / 1808 / 1937.  The heat bath has 2 d + 1
-// classes with a mask each, which is more work than the compare of each site's
-// own class in the pass (`in`): T = 16 n = 128 242 / 165 / 141, in 472; n = 512 314 /
-// 231 / 213, in 484; n = 1152 499 / 483 / 491, in 693; n = 2048 736 / 733 / 768, in
-// 705; 3D T = 16 n = 864 491 / 490 / 482, in 550; n = 2048 925 / 880 / 928, in 788.
-uint32_t tile_ahead_waves(const Geom& g, uint32_t T, bool heatbath) {
+// Waves of a workgroup, 0: the kernels of tiles.hip, which form the masks in the
+// passes, are faster.  More waves form masks faster and hold more SIMD slots of
+// one workgroup's passes idle, and with few hits have nothing to do; with 64 words
+// a workgroup, n workgroups in a launch (us a sweep of k = 100 by waves 4 / 8 / 12):
+// Metropolis 2D T = 16 n = 128 126 / 86 / 81, n = 1013 294 / 265 / 268, n = 2048 483 /
+// 471 / 502, n = 8192 1678 / 1816 / 1946; k = 4 n = 1013 26 / 30 / 33, n = 2048 37 / 40 / 47.
+// The heat bath has 2 d + 1 classes with a mask each, which is more work than the
+// compare of each site's own class in the pass (`in`): T = 16 n = 128 242 / 167 / 142,
+// in 477; n = 512 317 / 232 / 212, in 486; n = 1013 435 / 412 / 410, in 491; n = 2048
+// 739 / 736 / 773, in 710; 3D T = 16 n = 864 497 / 489 / 483, in 555; n = 2048 923 / 881 /
+// 928, in 788.
+// One wave of a workgroup stages and stores its tiles, where a 256-lane group in
+// the passes does by four waves, in 3D with four tiles a row: with few hits and a
+// full chip that is most of the time, and the masks ahead win from `least` hits on (us
+// a sweep, in the passes / ahead): Metropolis 2D T = 16 n = 2048 k = 1 26 / 30, k = 2 33 /
+// 31; n = 8192 k = 1 62 / 85, k = 3 89 / 93, k = 4 108 / 102; T = 32 n = 2048 k = 2 31 / 34, k =
+// 4 41 / 40; T = 64 n = 4608 k = 3 64 / 71, k = 4 73 / 68; 3D T = 16 n = 2048 k = 1 42 / 106, k =
+// 8 86 / 105, k = 12 112 / 107; n = 6912 k = 12 255 / 272, k = 16 322 / 316, k = 100 1746 / 1684;
+// above, at any k in the passes (n = 10976 k = 16 465 / 485, k = 100 2604 / 2625; n = 16384 1211 /
+// 1289 at k = 32, 3666 / 3852 at k = 100).
+uint32_t tile_ahead_waves(const Geom& g, uint32_t T, bool heatbath, uint32_t hits) {
   if (!tile_ahead_supported(g, T)) return 0u;
   const uint64_t words = (uint64_t)g.Nh / 32 / 2;  // of the tiles of one colour
   const uint64_t n = (words + 63) / 64;
-  if (heatbath) return n <= 896 ? 12u : n <= 1700 ? 8u : 0u;
-  return n <= 512 ? 12u : n <= 3072 ? 8u : 4u;
+  if (n <= 512) return 12u;
+  const uint32_t never = ~0u;
+  uint32_t least;
+  if (heatbath)
+    least = n > 1700 ? never : g.d == 3 ? (n <= 896 ? 2 : 6) : T == 64 && n <= 1200 ? 1 : 2;
+  else if (g.d == 3)
+    least = n <= 1400 ? 2 : n <= 6000 ? 12 : n <= 9000 ? 16 : never;
+  else if (T == 16)
+    least = n <= 768 ? 1 : n <= 3500 ? 2 : n <= 7000 ? 3 : 4;
+  else if (T == 32)
+    least = n <= 768 ? 1 : n <= 1500 ? 2 : n <= 7000 ? 4 : 6;
+  else
+    least = n <= 1500 ? 1 : n <= 2300 ? 2 : n <= 3500 ? 3 : 4;
+  if (hits < least) return 0u;
+  if (heatbath) return n > 896 && (g.d == 3 || hits >= 8) ? 8u : hits < (g.d == 3 ? 32u : 8u) ? 4u : 12u;
+  return n > 3072 || hits < (g.d == 3 && n <= 1400 ? 12u : 8u) ? 4u : 8u;
 }
 
 template <int D, uint32_t T>
