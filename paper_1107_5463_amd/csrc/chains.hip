@@ -83,7 +83,7 @@ __global__ __launch_bounds__(1024) void chains_kernel(const ChainsLaunch a, int8
   const uint32_t chain = blockIdx.x;
   const uint32_t replica = a.key.replica + chain;
   int8_t* gs = spins + (uint64_t)chain * N;
-  const int8_t* from = a.start ? a.start + (uint64_t)chain * N : gs;
+  const int8_t* from = MODE == 1 && a.start ? a.start + (uint64_t)chain * N : gs;
   // LDS: kRed doubles of reduction scratch, the accumulator (4 or 8 bytes per
   // bond), the couplings (JL), then both colour planes
   constexpr size_t kAcc = MODE == 1 ? 8 : 4;  // bytes per bond (chains_lds_bytes)
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(D == 3 && MODE == 1 ? kPairCov3 : 1024u) void chain
   const uint32_t q = threadIdx.x;
   const bool active = q < pairs;
   int8_t* gs = spins + (uint64_t)chain * N;
-  const int8_t* from = a.start ? a.start + (uint64_t)chain * N : gs;
+  const int8_t* from = MODE == 1 && a.start ? a.start + (uint64_t)chain * N : gs;
   double* red = reinterpret_cast<double*>(smem);
   int8_t* lat = reinterpret_cast<int8_t*>(smem + kPairRed * sizeof(double));
   const float bl2e = beta_log2e(a.beta);
@@ -493,7 +493,7 @@ __global__ __launch_bounds__(kMultiLanes) void chains_multi_kernel(const ChainsL
   const uint32_t pairs = NhU / 2, T = blockDim.x, tid = threadIdx.x;
   const uint32_t chain = blockIdx.x, replica = a.key.replica + chain;
   int8_t* gs = spins + (uint64_t)chain * N;
-  const int8_t* from = a.start ? a.start + (uint64_t)chain * N : gs;
+  const int8_t* from = MODE == 1 && a.start ? a.start + (uint64_t)chain * N : gs;
   double* red = reinterpret_cast<double*>(smem);
   double* accd = red + kPairRed;
   int8_t* lat = reinterpret_cast<int8_t*>(accd + (MODE == 1 ? nbonds : 0u));
