@@ -472,8 +472,8 @@ __global__ __launch_bounds__(D == 3 && MODE == 1 ? kPairCov3 : 1024u) void chain
 // and its sums wait in LDS (both once in eight sweeps).  The LDS kernel draws
 // every block twice, works out neighbours every sweep and adds to a sum in LDS a
 // bond and sweep (us of 100 sweeps, it / here: 2D L = 68, 100 chains 336 / 163,
-// covariance 544 / 309; L = 88 553 / 270, 908 / 704; 70 of 2D L = 96, 250 chains 452 /
-// 259, 766 / 584; 3D L = 16, 64 chains covariance 673 / 567).
+// covariance 544 / 309; L = 88 553 / 270, 908 / 704; 3D L = 16, 64 chains covariance 673 /
+// 567; 70 sweeps of 2D L = 96, 250 chains 452 / 259, 766 / 584).
 constexpr uint32_t kMultiLanes = 768;
 
 template <int D, int MODE, int PPL>
@@ -706,16 +706,24 @@ __global__ __launch_bounds__(kMultiLanes) void chains_multi_kernel(const ChainsL
     for (uint32_t b = tid; b < nbonds; b += T) pc[b] = accd[b];
   }
   if (MODE == 0) {
+    // through LDS (the spins are back), so that a wave's atomics fall on consecutive
+    // bonds: a lane's own lie 2 sites apart, which cost a call of one sweep more than
+    // the sweep (300 chains of 2D L = 96 127 us, now 65)
+    int32_t* acc_s = reinterpret_cast<int32_t*>(lat);
+    __syncthreads();
 #pragma unroll
     for (int p = 0; p < PPL; ++p) {
       if (tid + (uint32_t)p * T < pairs) {
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-          for (int m = 0; m < B; ++m)
-            atomicAdd(reinterpret_cast<unsigned long long*>(bond_sum + bond_of(p, b, m)),
-                      (unsigned long long)((int64_t)n_sweeps + acc[p][b][m]));
+          for (int m = 0; m < B; ++m) acc_s[bond_of(p, b, m)] = acc[p][b][m];
       }
+    }
+    __syncthreads();
+    for (uint32_t b = tid; b < nbonds; b += T) {
+      const int64_t v = (int64_t)n_sweeps + acc_s[b];
+      if (v != 0) atomicAdd(reinterpret_cast<unsigned long long*>(bond_sum + b), (unsigned long long)v);
     }
   }
 }
@@ -940,6 +948,25 @@ hipError_t chains_allow_lds(const Geom& g) {
   return hipSuccess;
 }
 
+// Whether the multi-pair kernel is faster than the LDS kernel (us, LDS / multi-pair, of
+// 4 and of 600 chains).  It sets a lane's couplings and addresses up once, which a
+// half-sweep does not repay (2D L = 80 5.9 / 6.9, 15 / 19), nor one sweep with three
+// pairs a lane and most waves partly filled (sampling 2D L = 80 10 / 12, 70 / 72; L = 96
+// 13 / 13, 98 / 85; two sweeps 15 / 14, 81 / 77).  Its covariance flush costs about as much
+// as a sweep of the other for each pair a lane holds, once in eight sweeps: two pairs 2D L =
+// 72 3 sweeps 24 / 24, 83 / 77, 4 sweeps 30 / 26; 3D L = 16 8 sweeps 60 / 56, 191 / 191; L = 18 4
+// sweeps 46 / 47, 156 / 174, 6 sweeps 65 / 56, 214 / 201; one pair 3D L = 14 1 sweep 13 / 18, 2
+// sweeps 19 / 18; three pairs 2D L = 80 40 sweeps 267 / 275, 817 / 838; L = 84 12 sweeps 98 / 100,
+// 16 sweeps 128 / 121; L = 96 4 sweeps 47 / 48, 158 / 183, 6 sweeps 66 / 59, 217 / 214.
+static bool chains_multi_faster(int d, int mode, uint32_t pairs, uint32_t ppl, uint32_t n_sweeps,
+                                int only_colour) {
+  if (only_colour >= 0) return false;
+  if (mode != 1) return n_sweeps > 1 || ppl < 3 || pairs >= 1900;
+  if (d == 3) return n_sweeps >= (ppl == 1 ? 2u : pairs <= 1024u ? 8u : 5u);
+  if (ppl == 2) return n_sweeps >= 4;
+  return pairs >= 1700 && n_sweeps >= (pairs < 1850 ? 14u : 6u);
+}
+
 // One launch of n_sweeps sweeps (mode 0: bond sums, 1: covariance partials,
 // 2: sweeps only, or one colour's half of sweep t0 with only_colour >= 0).
 static hipError_t launch_chains(const ChainsLaunch& a, int mode, int8_t* spins, uint32_t t0,
@@ -961,9 +988,12 @@ static hipError_t launch_chains(const ChainsLaunch& a, int mode, int8_t* spins, 
     return hipGetLastError();
   }
   const uint32_t pairs = (uint32_t)(a.g.Nh / 2), ppl = (pairs + kMultiLanes - 1) / kMultiLanes;
-  if (a.multi_kernel && ppl <= (a.g.d == 2 ? 3u : 2u)) {
+  if (a.multi_kernel && ppl <= (a.g.d == 2 ? 3u : 2u) &&
+      chains_multi_faster(a.g.d, mode, pairs, ppl, n_sweeps, only_colour)) {
     const dim3 lanes(((pairs + ppl - 1) / ppl + 63) / 64 * 64);
-    const size_t bytes = kPairRed * sizeof(double) + 2 * (size_t)a.g.Nh * (1 + (mode == 1 ? 8 * a.g.d : 0));
+    // sums: int32 a bond in the spins' place at the end, or double a bond beside them
+    const size_t bytes = kPairRed * sizeof(double) +
+                         2 * (size_t)a.g.Nh * (mode == 0 ? 4 * a.g.d : mode == 1 ? 1 + 8 * a.g.d : 1);
 #define SMC_CX(DD, MM, PP)                                                                           \
   do {                                                                                               \
     if (bytes > 65536) {                                                                             \
