@@ -17,7 +17,10 @@ __device__ __forceinline__ uint32_t gather7(uint32_t v) {
   return ((v & 0x80808080u) * 0x00204081u) >> 28;
 }
 
-// Signs of 32 int8 sites (the first nv of them exist) as a word.
+// Signs of 32 int8 sites (the first nv of them exist) as a word.  Sites that start
+// off a 16-byte line come by the aligned words that hold them, all in flight at
+// once (buffers start and end at multiples of four bytes): byte by byte, a batch of
+// 2D L = 62 took 26.5 us for one sweep, with them 12.
 __device__ __forceinline__ uint32_t load_signs(const int8_t* p, uint32_t nv) {
   uint32_t v = 0;
   if (nv == 32u && ((uintptr_t)p & 15u) == 0u) {
@@ -25,29 +28,33 @@ __device__ __forceinline__ uint32_t load_signs(const int8_t* p, uint32_t nv) {
     const uint32_t x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
     for (int k = 0; k < 8; ++k) v |= gather7(x[k]) << (4 * k);
-  } else if (((uintptr_t)p & 3u) == 0u && (nv & 3u) == 0u) {
-#pragma unroll 1
-    for (uint32_t k = 0; 4 * k < nv; ++k)
-      v |= gather7(reinterpret_cast<const uint32_t*>(p)[k]) << (4 * k);
-  } else {
-#pragma unroll 1
-    for (uint32_t k = 0; k < nv; ++k) v |= (p[k] < 0 ? 1u : 0u) << k;
+    return v;
   }
-  return v;
+  const uint32_t off = (uint32_t)((uintptr_t)p & 3u), n = (off + nv + 3u) >> 2;  // 1 .. 9 words
+  const uint32_t* q = reinterpret_cast<const uint32_t*>(p - off);
+  uint32_t x[9];
+#pragma unroll
+  for (uint32_t k = 0; k < 9u; ++k) x[k] = q[min(k, n - 1u)];  // (those past nv: masked below)
+#pragma unroll
+  for (uint32_t k = 0; k < 8u; ++k) v |= gather7(x[k]) << (4u * k);
+  v = __builtin_amdgcn_alignbit(gather7(x[8]), v, off);
+  return v & (~0u >> (32u - nv));
 }
 
 __device__ __forceinline__ void store_signs(int8_t* p, uint32_t v, uint32_t nv) {
-  auto four = [&](uint32_t k) -> uint32_t {  // sites 4k .. 4k + 3 as +-1 bytes
-    return kOnes | ((((((v >> (4 * k)) & 0xFu) * 0x00204081u) & kOnes)) * 0xFEu);
+  auto four = [&](uint32_t s) -> uint32_t {  // sites s .. s + 3 as +-1 bytes
+    return kOnes | (((((v >> s) & 0xFu) * 0x00204081u) & kOnes) * 0xFEu);
   };
   if (nv == 32u && ((uintptr_t)p & 15u) == 0u) {
-    reinterpret_cast<uint4*>(p)[0] = make_uint4(four(0), four(1), four(2), four(3));
-    reinterpret_cast<uint4*>(p)[1] = make_uint4(four(4), four(5), four(6), four(7));
-  } else if (((uintptr_t)p & 3u) == 0u && (nv & 3u) == 0u) {
-    for (uint32_t k = 0; 4 * k < nv; ++k) reinterpret_cast<uint32_t*>(p)[k] = four(k);
-  } else {
-    for (uint32_t k = 0; k < nv; ++k) p[k] = (v >> k) & 1u ? (int8_t)-1 : (int8_t)1;
+    reinterpret_cast<uint4*>(p)[0] = make_uint4(four(0), four(4), four(8), four(12));
+    reinterpret_cast<uint4*>(p)[1] = make_uint4(four(16), four(20), four(24), four(28));
+    return;
   }
+  auto one = [&](uint32_t s) { p[s] = (v >> s) & 1u ? (int8_t)-1 : (int8_t)1; };
+  uint32_t k = 0;
+  for (const uint32_t head = min(nv, (uint32_t)(0u - (uintptr_t)p) & 3u); k < head; ++k) one(k);
+  for (; k + 4u <= nv; k += 4u) *reinterpret_cast<uint32_t*>(p + k) = four(k);
+  for (; k < nv; ++k) one(k);
 }
 
 // Bit-sliced equality of the 3-bit count (k2 k1 k0) with a constant K.
