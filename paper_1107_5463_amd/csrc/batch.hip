@@ -24,6 +24,7 @@
 // reduces E and M of its state from LDS after every `every` sweeps (record m
 // of the call at obs[m * n_lattices + lattice]; with no sweeps, one record of
 // the current state).
+#include <algorithm>
 #include <type_traits>
 
 #include "chunk.hpp"
@@ -51,7 +52,7 @@ constexpr uint32_t kBatchTieSlots = 4;  // deferred ties per lane before a flush
 // kernel, so every lattice keeps the chain of its replica bit for bit.
 //
 // A lattice of at most 64 words a colour (2D L <= 64, 3D L <= 16) is one
-// wave's (WAVE): blockDim / 64 of them share a workgroup and none waits at a
+// wave's (WAVE): several share a workgroup (batch_split) and none waits at a
 // barrier.  With a workgroup each, three of its four waves idled and held
 // their registers: 2048 spin-glass samples of L = 8 .. 32, 100 sweeps recorded
 // every 10: 957 -> 738 us, of which 85 us were the couplings' bit-by-bit
@@ -61,6 +62,7 @@ constexpr uint32_t kBatchTieSlots = 4;  // deferred ties per lane before a flush
 // ---------------------------------------------------------------------------
 constexpr uint32_t kPackedBatchWordsPerLane = 2;
 constexpr uint32_t kWaveWords = 64;  // words a colour of a lattice that one wave takes
+constexpr uint32_t kTinyWords = 8;   // of a tiny one (batch_split)
 // LDS strides of a word's spin pair (colour 0, colour 1, unused) and of its
 // 4 d bond-sign words (+ one unused): an odd number of dwords, so that 32
 // lanes reading consecutive words touch 32 different banks.
@@ -188,6 +190,7 @@ __device__ __forceinline__ void batch_packed_lattice(unsigned char* lds, const B
   auto word_sites = [&](uint32_t w) -> uint32_t { return w + 1u == Wp ? 32u - tail : 32u; };
   // sign bits of a pair of int8 planes into the spin pairs
   auto stage = [&](const int8_t* planes) {
+#pragma unroll 1
     for (uint32_t i = q; i < 2u * Wp; i += T) {
       const uint32_t c = i & 1u, w = i >> 1;
       *reinterpret_cast<uint32_t*>(lds + SB + kPkSpin * (w + 1u) + 4u * c) =
@@ -404,15 +407,23 @@ __global__ __launch_bounds__(1024) void batch_kernel(const BatchDesc* __restrict
                                                     const int8_t* __restrict__ J,
                                                     const uint32_t t0, const uint32_t n_sweeps,
                                                     const uint32_t every, const uint32_t n_lattices,
-                                                    const uint32_t n_single,
+                                                    const BatchSplit split,
                                                     ObsOut* __restrict__ obs) {
   extern __shared__ uint32_t lat_words[];  // [2][Nh] spins of this lattice
   int8_t* const lat = reinterpret_cast<int8_t*>(lat_words);
-  // workgroups from n_single on: a lattice a wave
-  const bool by_wave = blockIdx.x >= n_single;
+  // workgroups from n_single on: a lattice a wave of the first `per` (no wave waits
+  // for another)
+  const bool by_wave = blockIdx.x >= split.n_single;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t at = by_wave ? n_single + (blockIdx.x - n_single) * (blockDim.x >> 6) + wave : blockIdx.x;
-  if (at >= n_lattices) return;  // a wave beyond the last lattice: the others wait for none
+  uint32_t at = blockIdx.x;
+  if (by_wave) {
+    const uint32_t b = blockIdx.x - split.n_single;
+    const bool full = b < split.g_full;
+    const uint32_t per = full ? split.per_full : split.per_tiny;
+    at = split.n_single + wave + (full ? b * per : split.g_full * split.per_full + (b - split.g_full) * per);
+    if (wave >= per) return;
+  }
+  if (at >= n_lattices) return;
   const uint32_t li = __builtin_amdgcn_readfirstlane(order[at]);
   const BatchDesc* dp = descs + li;
   const uint32_t L = __builtin_amdgcn_readfirstlane(dp->L);
@@ -896,12 +907,13 @@ bool batch_lattice_packed(int d, uint32_t L, uint32_t threads) {
 }
 
 size_t batch_lds_bytes(int d, bool pm, bool packed, const uint32_t* L, uint32_t n,
-                       uint32_t threads) {
+                       uint32_t threads, const BatchSplit& split) {
+  const uint32_t per = std::max(split.per_full, split.per_tiny);
   size_t bytes = 0;
   for (uint32_t r = 0; r < n; ++r) {
     size_t need;
     if (packed && batch_lattice_wave(d, L[r])) {
-      need = (size_t)(threads / 64) * batch_packed_lds_bytes(d, kWaveWords, pm);
+      need = (size_t)per * batch_packed_lds_bytes(d, kWaveWords, pm);
     } else if (packed && batch_packed_ok(d, L[r], threads)) {
       need = batch_packed_lds_bytes(d, batch_words(d, L[r]), pm);
     } else {
@@ -914,18 +926,41 @@ size_t batch_lds_bytes(int d, bool pm, bool packed, const uint32_t* L, uint32_t 
   return bytes;
 }
 
-uint32_t batch_groups(uint32_t n_lattices, uint32_t n_single, uint32_t threads) {
-  const uint32_t per = threads / 64u;
-  return n_single + (n_lattices - n_single + per - 1u) / per;
+bool batch_lattice_tiny(int d, uint32_t L) { return batch_words(d, L) <= kTinyWords; }
+
+// One-wave lattices of more than eight words run best four a workgroup at any count
+// (2D L = 32, 20 sweeps, 1 / 2 / 4 a workgroup of 256 lanes: 16 lattices 37 / 49 / 32 us,
+// 512 39 / 39 / 33; of 512 lanes 8 a workgroup 43 and 45), up to sixteen where 1024 lanes
+// would not all run at once.  Tiny ones slow each other down beside each other while
+// CUs are idle (3D L = 8: 16 lattices 35 / 48 / 57, 512 35 / 35 / 36): they fill the others'
+// last workgroup, and the rest of them get a workgroup each as long as all run at once (16 waves
+// a CU), or, in a batch of other lattices too, have a CU each (512 of 2D L = 8, 32: 95 us
+// one a workgroup, 78 by fours).
+BatchSplit batch_split(uint32_t n_single, uint32_t n_mid, uint32_t n_tiny, uint32_t threads) {
+  const uint32_t waves = threads / 64u, room = 4096u / waves;
+  const uint32_t most = n_single ? std::min(waves, 8u) : waves;
+  auto fit = [&](uint32_t n, uint32_t used, uint32_t groups) -> uint32_t {  // the least per workgroup
+    const uint32_t left = used < groups ? groups - used : 1u;
+    return (n + left - 1u) / left;
+  };
+  BatchSplit s;
+  s.n_single = n_single;
+  s.per_full = std::min(most, std::max(4u, fit(n_mid, n_single, room)));
+  s.g_full = (n_mid + s.per_full - 1u) / s.per_full;
+  const uint32_t used = n_single + s.g_full, rest = n_mid + n_tiny - std::min(n_mid + n_tiny, s.g_full * s.per_full);
+  s.per_tiny = used == 0 ? fit(rest, 0u, room) : std::min(std::max(4u, fit(rest, used, room)), fit(rest, used, 256u));
+  s.per_tiny = std::max(1u, std::min(most, s.per_tiny));
+  s.groups = used + (rest + s.per_tiny - 1u) / s.per_tiny;
+  return s;
 }
 
 hipError_t launch_batch(const BatchLaunch& a, int8_t* spins, const int8_t* J, uint32_t t0,
                         uint32_t n_sweeps, uint32_t every, void* dev_obs, hipStream_t st) {
-  const dim3 grid(batch_groups(a.n_lattices, a.n_single, a.threads)), block(a.threads);
+  const dim3 grid(a.split.groups), block(a.threads);
   const size_t lds = a.lds_bytes;
 #define SMC_BK(DD, PMM, MM)                                                                      \
   hipLaunchKernelGGL((batch_kernel<DD, PMM, MM>), grid, block, lds, st, a.descs, a.order, a.key, \
-                     spins, J, t0, n_sweeps, every, a.n_lattices, a.n_single, (ObsOut*)dev_obs)
+                     spins, J, t0, n_sweeps, every, a.n_lattices, a.split, (ObsOut*)dev_obs)
   const bool m = dev_obs != nullptr;
   if (a.d == 2) {
     if (a.pm) { if (m) SMC_BK(2, true, true); else SMC_BK(2, true, false); }

@@ -97,16 +97,16 @@ hipError_t batch_allow_lds(size_t bytes);
 // queues, or, on the packed path, its planes and bond signs at one bit per
 // site plus that path's tie queues.
 size_t batch_lds_bytes(int d, bool pm, bool packed, const uint32_t* L, uint32_t n,
-                       uint32_t threads);
+                       uint32_t threads, const BatchSplit& split);
 // Whether a lattice of edge L takes the packed (one bit per site) path.
 bool batch_lattice_packed(int d, uint32_t L, uint32_t threads);
-// Whether it is one wave's (at most 64 words a colour): such lattices come
-// last in the order, threads / 64 a workgroup.
+// Whether it is one wave's (at most 64 words a colour), and tiny (at most 8): such
+// lattices come last in the order, several a workgroup of `threads` (batch_split).
 bool batch_lattice_wave(int d, uint32_t L);
-// Workgroups of a launch: n_single lattices one each, the others by waves.
-uint32_t batch_groups(uint32_t n_lattices, uint32_t n_single, uint32_t threads);
+bool batch_lattice_tiny(int d, uint32_t L);
+BatchSplit batch_split(uint32_t n_single, uint32_t n_mid, uint32_t n_tiny, uint32_t threads);
 // The kernel a batch launch uses (for building graph nodes); its arguments are
-// (descs, order, key, spins, J, t0, n_sweeps, every, n_lattices, n_single, obs).
+// (descs, order, key, spins, J, t0, n_sweeps, every, n_lattices, split, obs).
 const void* batch_kernel_fn(int d, bool pm, bool measure);
 
 // Number of per-block partials the measurement writes (workspace sizing).

@@ -128,11 +128,17 @@ struct BatchDesc {
   double J0;
 };
 
+// Workgroups of a batch, in its order: n_single lattices one each, per_full (a wave
+// each) in each of the next g_full, per_tiny in the others.
+struct BatchSplit {
+  uint32_t n_single, g_full, per_full, per_tiny, groups;
+};
+
 struct BatchLaunch {
   int d;
   bool pm;                 // +-1 couplings (else uniform)
   uint32_t n_lattices;
-  uint32_t n_single;       // the first of the order: a workgroup each; the others a wave each
+  BatchSplit split;
   uint32_t threads;        // workgroup size
   size_t max_sites;        // the largest L^d
   size_t lds_bytes;        // dynamic LDS of a workgroup (batch_lds_bytes)

@@ -1848,8 +1848,9 @@ struct smc_batch {
   bool packed;               // lattices may take the packed path (SMC_BATCH_PACKED=0 disables)
   std::vector<int64_t> soff, joff;
   std::vector<BatchDesc> desc;
-  std::vector<uint32_t> orders;  // [largest first | as given], one-wave lattices last in either
-  uint32_t n_wave;               // how many of those
+  std::vector<uint32_t> orders;  // [largest first | as given], one-wave lattices last in either,
+                                 // of them the tiny ones
+  uint32_t n_wave, n_tiny;       // how many of those
   void* spins;
   void* J;
   hipStream_t stream;
@@ -1914,8 +1915,12 @@ size_t batch_ws_parts(int32_t d, int32_t n, const int32_t* L, size_t* desc_b, si
   return *desc_b + *order_b + *scratch_b;
 }
 
-// Lattices with a workgroup each (on the byte path every one has).
-uint32_t batch_single(const smc_batch* b) { return (uint32_t)b->n - (b->packed ? b->n_wave : 0u); }
+// (on the byte path every lattice has a workgroup)
+BatchSplit batch_split_of(const smc_batch* b, uint32_t threads) {
+  const uint32_t n = (uint32_t)b->n;
+  return b->packed ? batch_split(n - b->n_wave, b->n_wave - b->n_tiny, b->n_tiny, threads)
+                   : batch_split(n, 0, 0, threads);
+}
 
 int batch_launch(smc_batch* b, int8_t* spins, uint32_t t0, uint32_t n_sweeps, uint32_t every,
                  void* dev_obs, uint32_t threads, bool largest_first) {
@@ -1923,11 +1928,11 @@ int batch_launch(smc_batch* b, int8_t* spins, uint32_t t0, uint32_t n_sweeps, ui
   a.d = b->d;
   a.pm = b->J_kind == SMC_J_PM;
   a.n_lattices = (uint32_t)b->n;
-  a.n_single = batch_single(b);
+  a.split = batch_split_of(b, threads);
   a.threads = threads;
   a.max_sites = b->max_sites;
   a.lds_bytes = batch_lds_bytes(b->d, b->J_kind == SMC_J_PM, b->packed, b->Lu.data(), (uint32_t)b->n,
-                                threads);
+                                threads, a.split);
   a.descs = b->desc_dev;
   a.order = b->order_dev + (largest_first ? 0 : b->n);
   a.key = RngKey{(uint32_t)(b->seed & 0xffffffffu), (uint32_t)(b->seed >> 32), 0u};
@@ -1954,16 +1959,16 @@ int batch_graph_sweep(smc_batch* b, uint32_t n_sweeps, uint32_t every, void* dev
   uint32_t t0 = (uint32_t)b->t;
   void* obs = dev_obs;
   uint32_t nl = (uint32_t)b->n;
-  uint32_t ns = batch_single(b);
-  void* args[] = {&descs, &order, &key, &spins, &J, &t0, &n_sweeps, &every, &nl, &ns, &obs};
+  BatchSplit split = batch_split_of(b, b->threads);
+  void* args[] = {&descs, &order, &key, &spins, &J, &t0, &n_sweeps, &every, &nl, &split, &obs};
   hipKernelNodeParams kp;
   std::memset(&kp, 0, sizeof(kp));
   kp.func = const_cast<void*>(batch_kernel_fn(b->d, b->J_kind == SMC_J_PM, dev_obs != nullptr));
-  kp.gridDim = dim3(batch_groups(nl, ns, b->threads));
+  kp.gridDim = dim3(split.groups);
   kp.blockDim = dim3(b->threads);
   kp.sharedMemBytes =
       (unsigned)batch_lds_bytes(b->d, b->J_kind == SMC_J_PM, b->packed, b->Lu.data(), (uint32_t)b->n,
-                                b->threads);
+                                b->threads, split);
   kp.kernelParams = args;
   kp.extra = nullptr;
   const bool same = b->exec && b->graph_n == (int64_t)n_sweeps && b->graph_obs == dev_obs &&
@@ -2126,9 +2131,13 @@ int smc_batch_init(smc_batch** out, int32_t d, int32_t J_kind, uint64_t seed, do
   std::stable_sort(largest.begin(), largest.end(),
                    [&](uint32_t a, uint32_t c) { return b->desc[a].Nh > b->desc[c].Nh; });
   auto single = [&](uint32_t r) { return !batch_lattice_wave(d, b->desc[r].L); };
-  std::stable_partition(largest.begin(), largest.end(), single);
+  auto large = [&](uint32_t r) { return !batch_lattice_tiny(d, b->desc[r].L); };
   b->n_wave = (uint32_t)(n - std::count_if(idx.begin(), idx.end(), single));
-  std::stable_partition(idx.begin(), idx.end(), single);
+  b->n_tiny = (uint32_t)(n - std::count_if(idx.begin(), idx.end(), large));
+  for (auto* o : {&largest, &idx}) {
+    std::stable_partition(o->begin(), o->end(), large);
+    std::stable_partition(o->begin(), o->end(), single);
+  }
   b->orders = largest;
   b->orders.insert(b->orders.end(), idx.begin(), idx.end());
   // the largest workgroup (1024 lanes) with the largest lattice may pass the
@@ -2136,7 +2145,7 @@ int smc_batch_init(smc_batch** out, int32_t d, int32_t J_kind, uint64_t seed, do
   size_t lds_max = 0;
   for (uint32_t th = 64; th <= 1024; th *= 2)
     lds_max = std::max(lds_max, batch_lds_bytes(d, J_kind == SMC_J_PM, b->packed, b->Lu.data(),
-                                                (uint32_t)n, th));
+                                                (uint32_t)n, th, batch_split_of(b, th)));
   int rc = check(batch_allow_lds(lds_max), "batch LDS attribute");
   if (rc == SMC_OK)
     rc = check(hipMemcpyAsync(b->desc_dev, b->desc.data(), sizeof(BatchDesc) * n,
