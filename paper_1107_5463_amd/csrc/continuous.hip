@@ -450,7 +450,7 @@ static hipError_t launch_cont_stream(const ContLaunch& a, float* s, uint32_t t, 
 
 uint32_t cont_default_sites_per_lane(int n) { return n == 2 ? 4u : 2u; }
 
-// The streaming kernel below about a million sites a colour leaves a SIMD few
+// The streaming kernel below some hundred thousand sites a colour leaves a SIMD few
 // waves, each waiting on the loads that fill its ring: fewer sites a lane are
 // more waves.  us a half-sweep: XY, 4 / 2 a lane: 2D L = 1000 5.8 / 5.0, 3D
 // L = 64 5.7 / 4.6, L = 96 6.4 / 5.1, but 2D L = 2048 7.9 / 8.5, 3D L = 128
@@ -458,9 +458,17 @@ uint32_t cont_default_sites_per_lane(int n) { return n == 2 ? 4u : 2u; }
 // L = 128 9.4 / 8.3, L = 192 27.5 / 24.5, L = 256 52.9 / 50.3.  XY rows of an
 // odd number of pairs take 2 where 4 do not divide them (2D L = 1500, else one
 // site a lane: 11.9 / 7.4).
-uint32_t cont_sites_per_lane(const Geom& g, int n) {
+// With uniform or +-1 couplings 4 a lane are faster from 540000 sites a colour on in
+// 3D, where a few more waves do not make up for the rows between the lanes (ten
+// sweeps, 4 / 2 a lane: uniform L = 96 121 / 99, L = 104 128 / 131, L = 112 126 / 134, L = 120
+// 135 / 144; +-1 L = 96 191 / 158, L = 104 200 / 220, L = 112 198 / 215), and from 950000 in
+// 2D (uniform L = 1200 120 / 123, L = 1400 123 / 129, +-1 175 / 182; below, calls of sweeps run in
+// bricks); FP32 couplings, a 16-byte load a bond and lane, stay with 2 (L = 112 236 / 224,
+// 2D L = 1400 201 / 152).
+uint32_t cont_sites_per_lane(const Geom& g, int n, int J_kind) {
   if (n == 3) return 1u;
-  return g.Nh >= (1 << 20) && g.R % 4 == 0 ? 4u : 2u;
+  const int64_t least = J_kind == 2 ? 1 << 20 : g.d == 3 ? 540000 : 950000;
+  return g.Nh >= least && g.R % 4 == 0 ? 4u : 2u;
 }
 
 // Smaller lattices still are done in less than the time of a launch by the

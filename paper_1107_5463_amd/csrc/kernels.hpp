@@ -66,7 +66,7 @@ size_t brick_lds_bytes(int n, uint32_t positions);
 uint32_t cont_default_sites_per_lane(int n);
 // Sites per lane for a lattice, and whether its sweeps are faster by the
 // one-site kernel (rules with their figures in continuous.hip).
-uint32_t cont_sites_per_lane(const Geom& g, int n);
+uint32_t cont_sites_per_lane(const Geom& g, int n, int J_kind);
 bool cont_prefers_row(const Geom& g, int n);
 bool cont_sites_per_lane_ok(int n, uint32_t V);
 bool cont_stream_supported(const Geom& g, uint32_t V, uint32_t H);

@@ -1457,7 +1457,7 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
   h->cont_row_sweeps = false;
   if (p->n > 1) {
     const bool named = std::getenv("SMC_CONT_KERNEL") != nullptr;
-    h->cont_spl = named ? cont_default_sites_per_lane(p->n) : cont_sites_per_lane(h->g, p->n);
+    h->cont_spl = named ? cont_default_sites_per_lane(p->n) : cont_sites_per_lane(h->g, p->n, p->J_kind);
     if (const char* v = std::getenv("SMC_CONT_SPL")) {
       const long V = std::strtol(v, nullptr, 10);
       if (V > 0 && cont_sites_per_lane_ok(p->n, (uint32_t)V)) h->cont_spl = (uint32_t)V;
