@@ -98,9 +98,11 @@ __device__ __forceinline__ bool heis_update(float sv[3], const float h[3], const
   // precision for small caps, where 1 - c^2 would cancel.  The argument is at
   // least omc 2^-24 (a normal number), so the hardware square root (about one
   // ulp) needs no denormal scaling.
-  const float omca = u01f(w1) * omc;
-  const float ca = 1.0f - omca;
-  const float sa = __builtin_amdgcn_sqrtf(omca * (2.0f - omca));
+  // (the fused products are written out here too, as in xy_update)
+  const float u1 = u01f(w1);
+  const float omca = u1 * omc;
+  const float ca = fmaf(-u1, omc, 1.0f);
+  const float sa = __builtin_amdgcn_sqrtf(omca * fmaf(-u1, omc, 2.0f));
   // frame axis: smallest |s_k|, lowest k on ties
   const float a0 = fabsf(sv[0]), a1 = fabsf(sv[1]), a2 = fabsf(sv[2]);
   int k = 0;
@@ -109,13 +111,13 @@ __device__ __forceinline__ bool heis_update(float sv[3], const float h[3], const
   if (a2 < am) { k = 2; }
   const float sk = k == 0 ? sv[0] : (k == 1 ? sv[1] : sv[2]);
   float e1[3] = {-sk * sv[0], -sk * sv[1], -sk * sv[2]};
-  if (k == 0) e1[0] += 1.0f;
-  if (k == 1) e1[1] += 1.0f;
-  if (k == 2) e1[2] += 1.0f;
-  const float inv = rsqrtf(e1[0] * e1[0] + e1[1] * e1[1] + e1[2] * e1[2]);
+  if (k == 0) e1[0] = fmaf(-sk, sv[0], 1.0f);
+  if (k == 1) e1[1] = fmaf(-sk, sv[1], 1.0f);
+  if (k == 2) e1[2] = fmaf(-sk, sv[2], 1.0f);
+  const float inv = rsqrtf(fmaf(e1[2], e1[2], fmaf(e1[0], e1[0], e1[1] * e1[1])));
   e1[0] *= inv; e1[1] *= inv; e1[2] *= inv;
-  const float e2[3] = {sv[1] * e1[2] - sv[2] * e1[1], sv[2] * e1[0] - sv[0] * e1[2],
-                       sv[0] * e1[1] - sv[1] * e1[0]};
+  const float e2[3] = {fmaf(sv[1], e1[2], -(sv[2] * e1[1])), fmaf(sv[2], e1[0], -(sv[0] * e1[2])),
+                       fmaf(sv[0], e1[1], -(sv[1] * e1[0]))};
   // azimuth 2 pi u(w2)
   float sph, cph;
   if (FAST)
@@ -124,8 +126,8 @@ __device__ __forceinline__ bool heis_update(float sv[3], const float h[3], const
     sincos_turns(u01f(w2), &sph, &cph);
   float nv[3];
 #pragma unroll
-  for (int q = 0; q < 3; ++q) nv[q] = ca * sv[q] + sa * (cph * e1[q] + sph * e2[q]);
-  const float dE = -((nv[0] - sv[0]) * h[0] + (nv[1] - sv[1]) * h[1] + (nv[2] - sv[2]) * h[2]);
+  for (int q = 0; q < 3; ++q) nv[q] = fmaf(ca, sv[q], sa * fmaf(cph, e1[q], sph * e2[q]));
+  const float dE = -fmaf(nv[2] - sv[2], h[2], fmaf(nv[0] - sv[0], h[0], (nv[1] - sv[1]) * h[1]));
   const bool accept = cont_accept<FAST>(dE, w0, beta, bl2e);
   if (accept) {
     sv[0] = nv[0];

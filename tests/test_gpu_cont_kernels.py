@@ -26,3 +26,19 @@ def test_chosen_sites_a_lane(smc_gpu, monkeypatch, d, L, kind):
     got = _spins(smc_gpu, monkeypatch, {"SMC_BRICK": "0"}, d, 2, L, kind, (2,))
     ref = _spins(smc_gpu, monkeypatch, {"SMC_CONT_KERNEL": "row"}, d, 2, L, kind, (2,))
     assert torch.equal(got, ref)
+
+
+# every (dimension, components, kind of coupling), in the precise and the fast arithmetic
+@pytest.mark.parametrize("fast", [False, True])
+@pytest.mark.parametrize("d,n,kind", [(d, n, kind) for d in (2, 3) for n in (2, 3) for kind in (0, 1, 2)])
+def test_every_kernel_runs_the_same_chain(smc_gpu, monkeypatch, d, n, kind, fast):
+    print(f"cont kernels d={d} n={n} kind={kind} fast={fast}", flush=True)
+    L, calls = (48, (3, 9)) if d == 2 else (16, (3, 9))
+    ref = _spins(smc_gpu, monkeypatch, {"SMC_CONT_KERNEL": "row"}, d, n, L, kind, calls, fast_math=fast)
+    ways = [{"SMC_CONT_KERNEL": "stream", "SMC_CONT_SPL": str(v), "SMC_CONT_ROWS": str(h)}
+            for v in ((2, 4) if n == 2 else (1, 2)) for h in (4, 8)] + [{}]
+    if not fast:
+        # the whole lattice and bricks cut along y, with each number of positions a lane
+        ways += [{"SMC_BRICK": f"{m},1,{ny},1,{v}"} for m, ny in ((9, 1), (2, 2)) for v in ((1, 2, 4) if n == 2 else (1, 2))]
+    for env in ways:
+        assert torch.equal(_spins(smc_gpu, monkeypatch, env, d, n, L, kind, calls, fast_math=fast), ref), env
