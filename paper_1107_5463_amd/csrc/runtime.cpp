@@ -1245,9 +1245,13 @@ int smc_autotune(smc_lattice* h, double beta, void* scratch, size_t scratch_byte
     if (rows_out) *rows_out = 0;
     return SMC_OK;
   }
-  const std::string key = std::string(what) + ":d" + std::to_string(h->p.d) + ":n" +
-                          std::to_string(h->p.n) + ":L" + std::to_string(h->p.L) + ":J" +
-                          std::to_string(h->p.J_kind) + ":" + device_tag();
+  // (choices without a number of sites a lane were made with 4 of XY and 2 of
+  // Heisenberg: another number's best height is another)
+  const std::string base = std::string(what) + ":d" + std::to_string(h->p.d) + ":n" +
+                           std::to_string(h->p.n) + ":L" + std::to_string(h->p.L) + ":J" +
+                           std::to_string(h->p.J_kind) + ":" + device_tag();
+  const bool other = h->p.n > 1 && h->cont_spl != cont_default_sites_per_lane(h->p.n);
+  const std::string key = other ? base + ":v" + std::to_string(h->cont_spl) : base;
   std::string cached;
   if (cache_get(key, cached)) {
     const uint32_t v = (uint32_t)std::strtoul(cached.c_str(), nullptr, 10);
@@ -1256,6 +1260,11 @@ int smc_autotune(smc_lattice* h, double beta, void* scratch, size_t scratch_byte
       if (rows_out) *rows_out = v;
       return SMC_OK;
     }
+  }
+  if (!scratch && other && cache_get(base, cached)) {
+    // a caller that counts on a stored choice: there is none for these lanes
+    if (rows_out) *rows_out = *field;
+    return SMC_OK;
   }
   const size_t sb = spin_bytes(&h->p);
   if (!scratch || ((uintptr_t)scratch & 15) || scratch_bytes < sb)
@@ -2209,6 +2218,14 @@ static int batch_upload_desc(smc_batch* b) {
                               hipMemcpyHostToDevice, b->stream), "descriptor upload");
 }
 
+// Whether the batch holds lattices that once had the byte path only (2D, or an edge
+// that is no multiple of four): stored choices of a path were made between equals.
+static bool batch_path_new(const smc_batch* b) {
+  for (int32_t L : b->L)
+    if (b->d == 2 || L % 4 != 0) return true;
+  return false;
+}
+
 int smc_batch_autotune(smc_batch* b, int32_t* threads_out, int32_t* largest_first_out) {
   if (!b) return fail(SMC_EINVAL, "handle is NULL");
   // the cache key: shape of the batch (edges in order) and the device
@@ -2217,7 +2234,8 @@ int smc_batch_autotune(smc_batch* b, int32_t* threads_out, int32_t* largest_firs
   char hx[24];
   std::snprintf(hx, sizeof(hx), "%016llx", (unsigned long long)hsh);
   const std::string key = "batch:d" + std::to_string(b->d) + ":J" + std::to_string(b->J_kind) +
-                          ":n" + std::to_string(b->n) + ":L" + hx + ":" + device_tag();
+                          ":n" + std::to_string(b->n) + ":L" + hx + ":" + device_tag() +
+                          (batch_path_new(b) ? ":p2" : "");
   const bool packed_allowed = b->packed;
   std::string cached;
   if (cache_get(key, cached)) {
