@@ -793,11 +793,23 @@ size_t brick_bytes(const smc_params* p) {
 }
 
 // 2D XY lattices whose calls of several sweeps may run from one buffer to the
-// other (march.hip).
+// other (march.hip), and the rows of a band there: 0 where half-sweeps are faster, or a
+// half-sweep kernel is asked for by name; SMC_XY_MARCH names them (0: off).
 bool march_params(const smc_params* p) {
   return p->n == 2 && p->J_kind == SMC_J_UNIFORM && p->tile == 0 && xy_march_supported(make_geom(p)) &&
          n_sites(p) <= (1 << 28) &&
          !(p->flags & (SMC_FLAG_GENERIC_KERNEL | SMC_FLAG_FAST_MATH | SMC_FLAG_SCHEDULE_FUSED));
+}
+
+uint32_t march_band(const smc_params* p) {
+  if (!march_params(p)) return 0u;
+  if (const char* v = std::getenv("SMC_XY_MARCH")) {
+    const long rows = std::strtol(v, nullptr, 10);
+    return rows < 2 ? 0u : (uint32_t)std::min(rows, 65536l);
+  }
+  for (const char* v : {"SMC_CONT_KERNEL", "SMC_CONT_ROWS", "SMC_CONT_SPL"})
+    if (std::getenv(v)) return 0u;
+  return xy_march_rows(make_geom(p));
 }
 
 // n >= 2 sweeps in an even number of passes of two sweeps or one.
@@ -1367,7 +1379,7 @@ size_t smc_workspace_bytes(const smc_params* p) {
   if ((p->flags & SMC_FLAG_SCHEDULE_FUSED) && !is_packed(p)) b += round_up(spin_bytes(p), kAlign);
   b += multi_bytes(p);
   b += brick_bytes(p);
-  if (march_params(p)) b += round_up(spin_bytes(p), kAlign);
+  if (march_band(p)) b += round_up(spin_bytes(p), kAlign);
   return b;
 }
 
@@ -1497,15 +1509,7 @@ int smc_init_lattice(smc_lattice** out, const smc_params* p, void* spins, void* 
     if (got == 5 && v_ok && f[0] <= 1024 && std::max({f[1], f[2], f[3]}) <= 4096 && (p->d == 3 || f[3] == 1))
       for (int k = 0; k < 5; ++k) h->forced_brick[k] = f[k];
   }
-  h->march_rows = march_params(p) ? xy_march_rows(h->g) : 0u;
-  if (p->n > 1)
-    for (const char* v : {"SMC_CONT_KERNEL", "SMC_CONT_ROWS", "SMC_CONT_SPL"})
-      if (std::getenv(v)) h->march_rows = 0u;
-  if (const char* v = std::getenv("SMC_XY_MARCH"))
-    if (march_params(p)) {
-      const long rows = std::strtol(v, nullptr, 10);
-      h->march_rows = rows < 2 ? 0u : (uint32_t)std::min(rows, 65536l);
-    }
+  h->march_rows = march_band(p);
   h->use_fused = p->n == 1 && !is_packed(p) && p->tile == 0 && !(p->flags & SMC_FLAG_HEATBATH) &&
                  (p->flags & SMC_FLAG_SCHEDULE_FUSED) &&
                  !(p->flags & SMC_FLAG_GENERIC_KERNEL) &&
