@@ -710,12 +710,14 @@ int resident_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs
     a.bonds = h->work_bonds;
   }
   a.drawn = plan.drawn ? h->work_masks : nullptr;
+  // (h->t is the counter of the caller's buffer, also when a launch fails)
+  uint64_t t = h->t;
   uint32_t at = 0;  // buffer holding the state: 0 the caller's, 1 and 2 the packed copies
   for (int64_t done = 0; done < n_sweeps;) {
     const uint32_t S = (uint32_t)std::min<int64_t>(2 * (n_sweeps - done), plan.steps);
     const bool last_call = done + S / 2 >= n_sweeps;
     const uint32_t per = resident_per(plan, S);
-    a.t0 = (uint32_t)h->t;
+    a.t0 = (uint32_t)t;
     if (plan.drawn) {
       a.drawn_stride = (uint64_t)S * a.Wp;
       const int rc = check(launch_draws(a, hb, S, h->work_masks, h->stream), "draws launch");
@@ -739,15 +741,16 @@ int resident_sweeps(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs
       const uint32_t groups = (a.Wp + a.own - 1) / a.own;
       a.parts = meas && groups > 1 ? h->partials : nullptr;
       a.obs = meas && groups == 1 ? dev_obs : nullptr;
-      a.sweep = (int64_t)h->t + S / 2;
+      a.sweep = (int64_t)t + S / 2;
       int rc = check(launch_resident(a, hb, plan.threads, h->stream), "resident sweeps launch");
+      if (rc == SMC_OK && to == 0) h->t = t + S / 2;
       if (rc == SMC_OK && a.parts)
         rc = check(launch_finish(measure_args(h, a.sweep), h->partials, groups, dev_obs, h->stream),
                    "measurement finish launch");
       if (rc != SMC_OK) return rc;
       at = to;
     }
-    h->t += S / 2;
+    t += S / 2;
     done += S / 2;
   }
   return SMC_OK;
@@ -818,17 +821,19 @@ int64_t march_passes(int64_t n) { return (n + 3) / 4 * 2; }
 int march_run(smc_lattice* h, double beta, int64_t n, void* dev_obs) {
   const ContLaunch a = cont_args(h, beta);
   const int64_t passes = march_passes(n);
+  uint64_t t = h->t;  // (h->t: of the caller's buffer, written by every other pass)
   for (int64_t k = 0; k < passes; ++k) {
     const int sweeps = k < n - passes ? 2 : 1;
     const float* src = (const float*)(k % 2 ? (void*)h->march_work : h->spins);
     float* dst = (float*)(k % 2 ? h->spins : (void*)h->march_work);
     const bool meas = dev_obs && k + 1 == passes;
     int64_t nparts = 0;
-    int rc = check(launch_xy_march(a, sweeps, h->march_rows, src, dst, (uint32_t)h->t,
+    int rc = check(launch_xy_march(a, sweeps, h->march_rows, src, dst, (uint32_t)t,
                                    meas ? h->partials : nullptr, &nparts, h->stream),
                    "XY pass launch");
     if (rc != SMC_OK) return rc;
-    h->t += (uint64_t)sweeps;
+    t += (uint64_t)sweeps;
+    if (k % 2) h->t = t;
     if (meas)
       return check(launch_finish(measure_args(h, (int64_t)h->t), h->partials, nparts, dev_obs, h->stream),
                    "measurement finish launch");
@@ -1041,6 +1046,7 @@ int brick_run(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, cons
   a.param = h->p.n == 2 ? ca.delta : ca.one_minus_cos_cap;
   const uint32_t groups = plan.nb[0] * plan.nb[1] * plan.nb[2];
   int64_t done = 0;
+  uint64_t t = h->t;  // (h->t: of the caller's buffer, also when a launch fails)
   uint32_t at = 0;  // buffer holding the state: 0 the caller's, 1 and 2 the copies
   for (uint32_t l = 0; l < plan.launches; ++l) {
     const int64_t m = (n_sweeps - done + (plan.launches - l) - 1) / (plan.launches - l);
@@ -1051,18 +1057,19 @@ int brick_run(smc_lattice* h, double beta, int64_t n_sweeps, void* dev_obs, cons
     const uint32_t to = last || groups == 1 ? 0u : (at == 1 ? 2u : 1u);
     a.src = at == 0 ? h->spins : (void*)h->brick_work[at - 1];
     a.dst = to == 0 ? h->spins : (void*)h->brick_work[to - 1];
-    a.t0 = (uint32_t)h->t;
-    a.sweep = (int64_t)h->t + m;
+    a.t0 = (uint32_t)t;
+    a.sweep = (int64_t)t + m;
     const bool meas = last && dev_obs != nullptr;
     a.parts = meas && groups > 1 ? h->partials : nullptr;
     a.obs = meas && groups == 1 ? dev_obs : nullptr;
     int rc = check(launch_brick(a, h->stream), "brick sweeps launch");
+    if (rc == SMC_OK && to == 0) h->t = t + (uint64_t)m;
     if (rc == SMC_OK && a.parts)
       rc = check(launch_finish(measure_args(h, a.sweep), h->partials, groups, dev_obs, h->stream),
                  "measurement finish launch");
     if (rc != SMC_OK) return rc;
     at = to;
-    h->t += (uint64_t)m;
+    t += (uint64_t)m;
     done += m;
   }
   return SMC_OK;
