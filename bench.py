@@ -72,6 +72,8 @@ KERNEL_SOURCES = {
                      "reduce.hpp"],
     "ising_tiles": ["tiles.hip", "tiles_ahead.hip", "packed.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp"],
     "ising_tiles_packed": ["tiles.hip", "tiles_ahead.hip", "packed.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp"],
+    "ising_tiles_ahead": ["tiles.hip", "tiles_ahead.hip", "packed.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp"],
+    "ising_resident": ["resident.hip", "packed.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp", "reduce.hpp"],
     "xy_stream": ["continuous.hip", "spin_update.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp"],
     "xy_march": ["march.hip", "spin_update.hpp", "chunk.hpp", "device.hpp", "launch_args.hpp"],
     "heisenberg_stream": ["continuous.hip", "spin_update.hpp", "chunk.hpp", "device.hpp",
@@ -240,24 +242,31 @@ def without_env(name):
     return os.environ.pop(name, None)
 
 
-def kernel_model(kname, n, N, sweeps, tile, hits, per_call=0):
-    """(launches, algorithmic HBM bytes per launch, schedule) of the dominant kernel."""
+def kernel_model(kname, n, N, launches, word_spins=False, tile=0, hits=1):
+    """(algorithmic HBM bytes per launch, schedule) of the kernel that does most
+    of a call of sweeps, which launches it `launches` times."""
     if kname == "xy_march":
-        # a call of S sweeps: an even number of passes of two sweeps or one, each
-        # reading and writing both planes once
-        passes = (per_call + 3) // 4 * 2
-        return sweeps // per_call * passes, 2.0 * N * n * 4, "two sweeps a pass, ping-pong buffers, FP32 components"
-    if kname in ("ising_tiles", "ising_tiles_packed"):
+        # each pass reads and writes both planes once
+        return 2.0 * N * n * 4, "two sweeps a pass, ping-pong buffers, FP32 components"
+    if kname in ("ising_tiles", "ising_tiles_packed", "ising_tiles_ahead"):
         # one launch per tile colour: its half of both planes read and written once
-        return 2 * sweeps, 1.0 * N, f"tiled k-hit, T={tile}, k={hits}"
+        return 1.0 * N, f"tiled k-hit, T={tile}, k={hits}"
     if kname == "ising_packed":
-        return 2 * sweeps, 1.5 * N / 8, "two-pass colour-split, in place, one bit per site"
+        return 1.5 * N / 8, ("two-pass colour-split, in place, one bit per site"
+                             + ("" if word_spins else ", on a copy made by each call"))
+    if kname == "ising_resident":
+        # each launch reads and writes both planes' words; int8 spins come in by
+        # the first and go out by the last
+        ends = 0.0 if word_spins else 2.0 * (N - N / 8)
+        return 2.0 * N / 8 + ends / launches, "several half-sweeps a launch, words in LDS"
     if kname == "ising_fused":
-        return sweeps, 2.0 * N, "fused one-pass, ping-pong buffers"
+        return 2.0 * N, "fused one-pass, ping-pong buffers"
+    if kname in ("ising_bricks", "xy_bricks", "heisenberg_bricks"):
+        return 2.0 * N * (1 if n == 1 else 4 * n), "several sweeps a launch, bricks in LDS"
     if n == 1:
-        return 2 * sweeps, 1.5 * N, "two-pass colour-split, in place"
+        return 1.5 * N, "two-pass colour-split, in place"
     # own colour read + written and other colour read, n FP32 components
-    return 2 * sweeps, 1.5 * N * n * 4, "two-pass colour-split, in place, FP32 components"
+    return 1.5 * N * n * 4, "two-pass colour-split, in place, FP32 components"
 
 
 def hbm_roofline(kname, workload, bytes_per_launch, kernel_ms):
@@ -345,18 +354,17 @@ def run_lattice(args, wl, torch, smc):
     sweeps = K * S
     hits = args.hits if (n == 1 and args.tile) else 1
     attempts = N * sweeps * hits
-    kname, band_rows = lat.kernel()
-    if kname == "xy_stream" and d == 2 and L >= 2600 and S >= 2 and "SMC_XY_MARCH" not in os.environ:
-        kname = "xy_march"  # calls of several sweeps of a large 2D XY lattice
-    launches, bytes_per_launch, schedule = kernel_model(kname, n, N, sweeps, args.tile, args.hits, S)
-    if n == 1 and args.heatbath and not args.tile and S >= 2:
-        kname, schedule = "ising_resident", "several half-sweeps a launch, words in LDS"
+    band_rows = lat.kernel()[1]
+    kname, per_call = lat.sweeps_kernel(S, measured=True)
+    launches = K * per_call
+    bytes_per_launch, schedule = kernel_model(kname, n, N, per_call, packed, args.tile, args.hits)
     # the step time also holds the measurement finish (and renormalisation)
     # kernels: a conservative average of the dominant kernel
     kernel_ms = total_ms / launches
-    if kname in ("ising_packed", "ising_tiles", "ising_tiles_packed", "ising_resident", "xy_march"):
+    if kname in ("ising_packed", "ising_tiles", "ising_tiles_packed", "ising_tiles_ahead", "ising_resident",
+                 "xy_march"):
         variant = None
-        if kname in ("ising_tiles", "ising_tiles_packed"):
+        if args.tile:
             variant = f"T={args.tile} k={args.hits} {'heat bath' if args.heatbath else 'Metropolis'}"
         roof = valu_roofline(kname, args.workload, kernel_ms, bytes_per_launch,
                              attempts / launches, variant)
@@ -410,8 +418,9 @@ def run_lattice(args, wl, torch, smc):
             if not args.no_autotune:
                 lat8.autotune(beta)
             ms8, _, obs8 = timed_steps(lat8, beta, K, W, S, torch)
-            k8, rows8 = lat8.kernel()
-            l8, b8, sch8 = kernel_model(k8, n, N, sweeps, 0, 1)
+            rows8 = lat8.kernel()[1]
+            k8, l8 = lat8.sweeps_kernel(S, measured=True)
+            b8, sch8 = kernel_model(k8, n, N, l8)
             result[key] = {
                 "value": round(attempts / (ms8 * 1e6), 2),
                 "unit": "attempts/ns",
@@ -420,12 +429,12 @@ def run_lattice(args, wl, torch, smc):
                                          and obs8.M_int == obs.M_int),
             }
             if key == "int8_two_pass":
-                roof8 = hbm_roofline(k8, args.workload, b8, ms8 / l8)
+                roof8 = hbm_roofline(k8, args.workload, b8, ms8 / (K * l8))
                 roof8["copy_ceiling_GBps"] = copy_ceiling(torch, lat8.device,
                                                           lat8.spins.numel() * lat8.spins.element_size())
                 result[key].update(schedule=sch8, rows_per_band=rows8, roofline=roof8)
             else:
-                result[key]["schedule"] = "each call on a copy at one bit per site, two-pass"
+                result[key].update(kernel=k8, schedule=sch8)
             if resident is None:
                 os.environ.pop("SMC_RESIDENT", None)
             else:
