@@ -29,9 +29,11 @@
  *          reduction partials, an observable slot, for the fused schedule the
  *          second spin buffer and, for plain sweeps of Ising spins with
  *          uniform or +-1 couplings, two copies at one bit per site (and the
- *          bonds' signs) that calls of several sweeps may work on, or, for
- *          continuous spins and FP32 couplings up to 2^21 sites, two copies
- *          of the spins for such calls (one, for larger 2D XY lattices).
+ *          bonds' signs, and up to 8 MiB of accept masks) that calls of several
+ *          sweeps may work on, or two copies of the spins for such calls: for
+ *          Ising spins with FP32 couplings up to 2^21 sites, for continuous
+ *          spins up to 7 * 2^18 (2D XY lattices of more: one copy, if their
+ *          calls run two sweeps a pass).
  * Random numbers.  Philox4x32-10 (Salmon et al., SC'11), key = seed, counter
  *   = (block, sweep t, replica, colour | purpose << 1); the same (seed,
  *   replica) gives the same chain whatever the launch geometry or schedule.
@@ -232,6 +234,8 @@ int smc_set_samples(smc_lattice* h, int64_t samples);
  * kernel, shape and device is taken without timing (scratch may then be
  * NULL), and new choices are added to it.  rows_out (optional) receives the
  * chosen height, 0 if the handle's kernel has no bands.  Synchronises.
+ * It is the kernel of half-sweeps (smc_kernel_name) that is timed: a call of
+ * sweeps that takes another (smc_sweeps_kernel) keeps that one's own cut.
  */
 int smc_autotune(smc_lattice* h, double beta, void* scratch, size_t scratch_bytes,
                  uint32_t* rows_out);

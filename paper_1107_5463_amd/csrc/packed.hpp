@@ -20,7 +20,7 @@ __device__ __forceinline__ uint32_t gather7(uint32_t v) {
 // Signs of 32 int8 sites (the first nv of them exist) as a word.  Sites that start
 // off a 16-byte line come by the aligned words that hold them, all in flight at
 // once (buffers start and end at multiples of four bytes): byte by byte, a batch of
-// 2D L = 62 took 26.5 us for one sweep, with them 12.
+// 2D L = 62 took 26.5 us for one sweep, with them 10.
 __device__ __forceinline__ uint32_t load_signs(const int8_t* p, uint32_t nv) {
   uint32_t v = 0;
   if (nv == 32u && ((uintptr_t)p & 15u) == 0u) {

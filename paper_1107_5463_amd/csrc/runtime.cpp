@@ -65,7 +65,7 @@ struct BrickPlan {
   double us;
 };
 
-// The plans of a handle's last eight call lengths (a plan takes 1 to 40 us to
+// The plans of a handle's last eight call lengths (one by bricks takes 11 to 43 us to
 // work out; calls of alternating lengths, or cut by renormalisations, reuse them).
 template <class P>
 struct PlanCache {
