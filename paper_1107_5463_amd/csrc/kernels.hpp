@@ -106,7 +106,7 @@ bool batch_lattice_wave(int d, uint32_t L);
 bool batch_lattice_tiny(int d, uint32_t L);
 BatchSplit batch_split(uint32_t n_single, uint32_t n_mid, uint32_t n_tiny, uint32_t threads);
 // The kernel a batch launch uses (for building graph nodes); its arguments are
-// (descs, order, key, spins, J, t0, n_sweeps, every, n_lattices, split, obs).
+// (descs, order, key, spins, J, t0, n_sweeps, every, n_lattices, obs, split).
 const void* batch_kernel_fn(int d, bool pm, bool measure);
 
 // Number of per-block partials the measurement writes (workspace sizing).

@@ -1980,7 +1980,7 @@ int batch_graph_sweep(smc_batch* b, uint32_t n_sweeps, uint32_t every, void* dev
   void* obs = dev_obs;
   uint32_t nl = (uint32_t)b->n;
   BatchSplit split = batch_split_of(b, b->threads);
-  void* args[] = {&descs, &order, &key, &spins, &J, &t0, &n_sweeps, &every, &nl, &split, &obs};
+  void* args[] = {&descs, &order, &key, &spins, &J, &t0, &n_sweeps, &every, &nl, &obs, &split};
   hipKernelNodeParams kp;
   std::memset(&kp, 0, sizeof(kp));
   kp.func = const_cast<void*>(batch_kernel_fn(b->d, b->J_kind == SMC_J_PM, dev_obs != nullptr));
